@@ -331,7 +331,8 @@ const char* lba_strerror(int code);
 /* Which kernel a call would run, without running it (host only; needs no GPU).
  * The numeric result never depends on this choice; it is exposed for benchmarking reports. */
 typedef struct {
-    int32_t kernel;        /* 0: scaled-domain FP32-carrier kernel, 1: general kernel            */
+    int32_t kernel;        /* 0: scaled-domain kernel (FP32 carrier, or two chains per register on
+                              FP16 carriers where every step is exact on them), 1: general kernel */
     int32_t prod_mode;     /* kernel 0: 0 Q_prod is the identity, 1 flush only, 2 flush + clamp,
                               3 / 4 truncated mantissa (+ clamp), 5 / 6 nearest-even mantissa (+ clamp) */
     int32_t round;         /* rounding of Q_acc as executed                                       */
@@ -340,7 +341,8 @@ typedef struct {
     int32_t grid_x, grid_y;           /* workgroups launched                                      */
     int32_t valu_per_mac_x100;        /* kernel 0: full-rate VALU issue slots per MAC of the inner
                                          loop without the accumulator clamp, times 100 (a half-rate
-                                         instruction counts as 2 slots); kernel 1: the budget of a plain
+                                         instruction counts as 2 slots; FP16 carriers: half of the
+                                         packed step, and at least 200); kernel 1: the budget of a plain
                                          FMAq step (10 floor, 12 nearest-even, 4 more with event bits), which
                                          is less than its loop issues */
     int32_t tail_blocks;              /* tail_blocks + mid_blocks > 0: mixed grid: grid_x counts, in this order,

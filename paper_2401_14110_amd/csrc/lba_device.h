@@ -895,10 +895,29 @@ __device__ __forceinline__ void store_event_words(uint32_t* of_plane, uint32_t* 
     }
 }
 
+// The same tile on packed FP16 carriers (lba_half.h): LX lanes along n.
+template <int TM, int TN, int LX, int PM, int ORDER, int AMODE>
+__device__ __forceinline__ void half_body(const KParams& p, uint32_t* __restrict__ smem, int m0, int n0);
+
+// One workgroup's tile on the carrier the planner chose (p.h_on, uniform): both carriers take the same grids, so a
+// kernel holds both.  The 32 x 16 tile (2 x 1 outputs per lane) has its pairs along n on packed carriers: 1 x 2.
+template <int TM, int TN, int BK, int PM, int RND, int ORDER, int AMODE>
+__device__ __forceinline__ void forward_body(const KParams& p, float* smem, int m0, int n0) {
+    if constexpr (RND == LBA_ROUND_FLOOR && (PM == PM_IDENT || PM == PM_FLUSH || PM == PM_TRUNC)) {
+        if (p.h_on) {
+            uint32_t* words = reinterpret_cast<uint32_t*>(smem);
+            if constexpr (TN == 1) half_body<1, 2, 8, PM, ORDER, AMODE>(p, words, m0, n0);
+            else                   half_body<TM, TN, 16, PM, ORDER, AMODE>(p, words, m0, n0);
+            return;
+        }
+    }
+    fast_body<TM, TN, BK, PM, RND, ORDER, AMODE>(p, smem, m0, n0);
+}
+
 template <int TM, int TN, int BK, int PM, int RND, int ORDER, int AMODE = 0>
 __global__ void __launch_bounds__(256, LBA_FAST_MIN_WAVES) lba_fast_kernel(const KParams p) {
     __shared__ __attribute__((aligned(16))) float smem[2 * fast_stage_depth(TM, TN, BK) * 16 * (TM + TN)];
-    fast_body<TM, TN, BK, PM, RND, ORDER, AMODE>(p, smem, blockIdx.x * 16 * TM, blockIdx.y * 16 * TN);
+    forward_body<TM, TN, BK, PM, RND, ORDER, AMODE>(p, smem, blockIdx.x * 16 * TM, blockIdx.y * 16 * TN);
 }
 
 // Mixed grid for launches that would leave the last round of 64 x 64 workgroups half empty, or a CU with an odd
@@ -916,16 +935,16 @@ template <int BK, int PM, int RND, int ORDER, int AMODE>
 __device__ __forceinline__ void fast_mixed_body(const KParams& p, float* smem, const int b) {
     if (b < p.mix_main) {                                      // uniform
         const int by = b / p.mix_gx_main, bx = b - by * p.mix_gx_main;
-        fast_body<4, 4, BK, PM, RND, ORDER, AMODE>(p, smem, bx * 64, by * 64);
+        forward_body<4, 4, BK, PM, RND, ORDER, AMODE>(p, smem, bx * 64, by * 64);
     } else if (b < p.mix_main + p.mix_half) {
         const int t = b - p.mix_main;
         const int by = t / p.mix_gx_half, bx = t - by * p.mix_gx_half;
-        fast_body<3, 4, BK, PM, RND, ORDER, AMODE>(p, smem, p.mix_m_main + bx * 48, by * 64);
+        forward_body<3, 4, BK, PM, RND, ORDER, AMODE>(p, smem, p.mix_m_main + bx * 48, by * 64);
     } else {
         const int t = b - p.mix_main - p.mix_half;
         const int by = t / p.mix_gx_tail, bx = t - by * p.mix_gx_tail;
-        if (p.mix_tail16) fast_body<2, 1, BK, PM, RND, ORDER, AMODE>(p, smem, p.mix_m_half + bx * 32, by * 16);   // uniform
-        else              fast_body<2, 2, BK, PM, RND, ORDER, AMODE>(p, smem, p.mix_m_half + bx * 32, by * 32);
+        if (p.mix_tail16) forward_body<2, 1, BK, PM, RND, ORDER, AMODE>(p, smem, p.mix_m_half + bx * 32, by * 16);   // uniform
+        else              forward_body<2, 2, BK, PM, RND, ORDER, AMODE>(p, smem, p.mix_m_half + bx * 32, by * 32);
     }
 }
 
@@ -1903,4 +1922,7 @@ __global__ void __launch_bounds__(256) lba_gen_kernel(const KParams p) {
 }
 
 }  // namespace lba
+
+#include "lba_half.h"
+
 #endif

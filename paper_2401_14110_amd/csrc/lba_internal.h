@@ -61,6 +61,12 @@ struct KParams {
     uint8_t* map_dx;
     uint8_t* map_dw;
     int32_t map_rbx, map_sbx, map_rbw, map_sbw;
+    // packed FP16 carriers (lba_half.h; h_on = 1): two copies of an FP16 value or of a 16-bit mask per word
+    int32_t h_on;
+    uint32_t h_kc, h_rof, h_mask_a, h_mask_p;
+    uint32_t h_scale_a, h_scale_b;          // a decoded code's image times this is the operand in the tile's domain
+    uint32_t h_keep_a, h_keep_b;            // the image's bits: code in the word's high byte >> h_shift, & h_keep
+    int32_t h_shift_a, h_shift_b;
     int32_t prod_round;      // GEN: product mantissa narrower than a product of two operands
     int32_t prod_rne;        // GEN: its rounding
     float diff_eps;          // DIFF plane (written through of_mask): the threshold eps2, exact

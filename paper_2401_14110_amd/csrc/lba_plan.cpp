@@ -1,7 +1,8 @@
 // lba_plan.cpp -- argument validation and kernel selection for the LBA GEMM (host only, no HIP).
 //
 // The quantizer Q_{M,E,b} is the one of arXiv 2401.14110 Sec. 2.3; FMAq = Q_acc(Q_prod(x w) + s)
-// is Sec. 3.  Two kernels implement one FMAq step, both on an FP32 carrier:
+// is Sec. 3.  Two kernels implement one FMAq step on an FP32 carrier (the first also, where every step is exact
+// there, on packed FP16 carriers: half_carrier() and lba_half.h):
 //
 // FAST  works in a scaled domain where the accumulator's R_UF sits at 2^-126, the smallest FP32
 //       normal, with FP32 denormals flushed: the hardware flush of the add IS Q_acc's underflow.
@@ -149,6 +150,50 @@ static bool rne_odd_ok(const lba_qfmt& qp, const lba_qfmt& qa, bool flush, bool 
     if (nouf_a) return true;
     const int bpe = flush ? qp.bias : -in.min_lsb;
     return bpe - qa.bias < 24;
+}
+
+// Packed FP16 carriers (lba_half.h): fills in kp.h_* and returns true when every step of the chain is exact on them.
+// c_p / c_a: the exponents that put Q_prod's effective R_UF (2^-bpe) and Q_acc's (2^-bae) at 2^-14.  Conditions, in the
+// order of the code: R_OF of Q_acc a normal FP16 number; a product that Q_prod does not truncate at most 11 bits wide
+// (PM_IDENT: the multiply-add takes it unrounded); the largest product below FP16's largest number; kc and both scaled
+// operands, down to their subnormal units, FP16 numbers.
+static bool half_carrier(const lba_qfmt& qp, const lba_qfmt& qa, const InSpec& in, int prod_mode, int bpe, int bae, KParams* kp) {
+    if (in.ea > 4 || in.eb > 4 || qa.man_bits > 10) return false;
+    const int c_a = bae - 14, c_p = prod_mode == PM_IDENT ? c_a : bpe - 14;
+    const int top = (1 << qa.exp_bits) - qa.bias - 1 + c_a;    // top exponent of Q_acc in the tile's domain
+    if (top < -14 || top > 14) return false;
+    if (prod_mode == PM_FLUSH && in.sig_bits > 11) return false;
+    if (prod_mode == PM_TRUNC && qp.man_bits > 10) return false;
+    if (prod_mode != PM_IDENT && std::ldexp(in.max_prod, c_p) > 65504.0) return false;
+    if (c_a - c_p < -24 || c_a - c_p > 15) return false;
+    // a code's image is value * 2^(canonical bias - 15); operand x is scaled by 2^e_x, e_a + e_b = c_p, from its unit
+    // (1 - bias - M) to its top exponent; A's image is taken as it is where that is possible
+    const int E[2] = {in.ea, in.eb}, Mb[2] = {in.ma, in.mb};
+    int lo[2], hi[2], img[2];
+    for (int i = 0; i < 2; ++i) {
+        const int bias = (1 << (E[i] - 1)) - 1;
+        img[i] = bias - 15;
+        lo[i] = -24 - (1 - bias - Mb[i]);
+        hi[i] = 15 - ((1 << E[i]) - 1 - bias);
+    }
+    const int e_min = std::max(lo[0], c_p - hi[1]), e_max = std::min(hi[0], c_p - lo[1]);
+    if (e_min > e_max) return false;
+    const int e_a = std::min(std::max(img[0], e_min), e_max), e_b = c_p - e_a;
+    if (std::abs(e_a - img[0]) > 14 || std::abs(e_b - img[1]) > 14) return false;
+    const auto twice = [](uint32_t h) { return h | (h << 16); };
+    const auto pow2 = [&](int e) { return twice(e >= -14 ? (uint32_t)(e + 15) << 10 : 1u << (e + 24)); };
+    kp->h_kc = pow2(c_a - c_p);
+    kp->h_rof = twice(((uint32_t)(top + 15) << 10) | ((0x3FFu << (10 - qa.man_bits)) & 0x3FFu));
+    kp->h_mask_a = twice((0xFFFFu << (10 - qa.man_bits)) & 0xFFFFu);
+    kp->h_mask_p = qp.man_bits >= 10 ? 0xFFFFFFFFu : twice((0xFFFFu << (10 - qp.man_bits)) & 0xFFFFu);
+    kp->h_scale_a = pow2(e_a - img[0]);
+    kp->h_scale_b = pow2(e_b - img[1]);
+    kp->h_shift_a = in.ma - 2;                                 // mantissa bits from the top of the low byte to FP16's bit 10
+    kp->h_shift_b = in.mb - 2;
+    kp->h_keep_a = twice(0x8000u | (0x7Fu << (10 - in.ma)));
+    kp->h_keep_b = twice(0x8000u | (0x7Fu << (10 - in.mb)));
+    kp->h_on = 1;
+    return true;
 }
 
 #ifndef LBA_FAST_BK
@@ -376,6 +421,12 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
         }
         if (events == 2)                                         // mul, fma, and, mul, max, min, mul, sub, cmp; med3, addc at half rate; nearest-even: bfe, add3
             p.valu_per_mac_x100 = 1300 + (p.prod_mode == PM_FLUSH_CLAMP ? 200 : 0) + (qa.round == LBA_ROUND_RNE ? 400 : 0);
+        // packed FP16 carriers (forward call, floor, underflow kept): v_pk_mul, [v_and,] v_pk_fma at half rate for two
+        // chains, one v_and for both; never priced below the two slots of the FP32 multiply-add and mask
+        const bool half = !events && !rne_odd && qa.round == LBA_ROUND_FLOOR && !nouf_a &&
+                          (p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH || p.prod_mode == PM_TRUNC) &&
+                          half_carrier(qp, qa, in, p.prod_mode, bpe, bae, &kp);
+        if (half) p.valu_per_mac_x100 = p.prod_mode == PM_IDENT ? 200 : (p.prod_mode == PM_FLUSH ? 250 : 300);
         if (order == LBA_ORDER_CHUNK16)                          // add, and [, bfe, add3], zero per 16 steps
             p.valu_per_mac_x100 += (events == 2 ? 1300 : events ? 900 : (qa.round == LBA_ROUND_RNE ? 700 : 300)) / 16;
     } else {
@@ -434,7 +485,7 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
         kp.rof_grow1 = g1f;
         // (floor only: under nearest-even the growth allowance eats most of the margin, and the sweep of 4096^3 formats
         // measured no gain there)
-        kp.dyn_bound = (p.amode != 1 && !p.rne_odd && qa.round == LBA_ROUND_FLOOR && kp.fast_thresh4 <= 0.0f) ? 1 : 0;
+        kp.dyn_bound = ((p.amode != 1 || kp.h_on) && !p.rne_odd && qa.round == LBA_ROUND_FLOOR && kp.fast_thresh4 <= 0.0f) ? 1 : 0;
     }
     const int64_t bm = 16 * p.tm, bn = 16 * p.tn;
     p.grid_x = (int)((M + bm - 1) / bm);

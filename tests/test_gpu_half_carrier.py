@@ -1,0 +1,80 @@
+"""The forward tile on packed FP16 carriers (csrc/lba_half.h): every result is the oracle's, bit for bit, at the edges of
+the rule that admits a format (both sides of every line), of the tiles and of the k remainders."""
+import itertools
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2401_14110_amd import binding as lb
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def bits(x):
+    return np.ascontiguousarray(x).view(np.uint32)
+
+
+def codes(rng, shape, lo=0, hi=15, E=4):
+    """Random codes whose exponent field lies in [lo, hi] (of a format with E exponent bits), zeros among them."""
+    m = 7 - E
+    c = rng.integers(0, 256, size=shape, dtype=np.uint8)
+    e = np.clip((c >> m) & ((1 << E) - 1), lo, min(hi, (1 << E) - 1)).astype(np.uint8)
+    c = ((c & 0x80) | (e << m) | (c & ((1 << m) - 1))).astype(np.uint8)
+    return np.where(rng.random(shape) < 0.2, np.uint8(0), c)
+
+
+def product(A, B, qp, qa, order, fa=None, fb=None):
+    dA, dB = torch.from_numpy(A).to(DEV), torch.from_numpy(B).to(DEV)
+    C = lb.gemm(dA, dB, qp, qa, order=order) if fa is None else lb.gemm_in(dA, dB, fa, fb, qp, qa, order=order)
+    torch.cuda.synchronize()
+    return C.cpu().numpy()
+
+
+def slots(M, N, K, qp, qa):
+    return lb.lba_plan_query(M, N, K, qp, qa, 0)["valu_per_mac_x100"]
+
+
+@pytest.mark.parametrize("qae,qam", [(4, 1), (4, 7), (4, 10), (4, 11), (3, 4), (2, 3), (5, 7)])
+def test_every_side_of_the_admission_rule(ref, qae, qam):
+    # product domains from "the largest product is just too large" to "a scaled unit would fall below FP16's", and the
+    # accumulator's domain moving past the product's on both sides (kc from 2^-25 to 2^16); M = 11 and E = 5 stay on FP32
+    rng = np.random.default_rng(11)
+    A, B = codes(rng, (48, 83)), codes(rng, (36, 83))
+    packed = set()
+    for bp, ba in itertools.product((13, 12, 11, 4, -1, -9, -14, -16, -17, -18), (16, 11, 7, -2, -9, -15, -17, -24)):
+        qp, qa = (6, 7, bp, 0), (qae, qam, ba, 0)
+        packed.add(slots(48, 36, 83, qp, qa) == 250)
+        for order in (0, 1):
+            got = product(A, B, qp, qa, order)
+            want = ref.gemm(A, B, ref.QFmt(*qp), ref.QFmt(*qa), order=order)
+            assert np.array_equal(bits(got), bits(want)), (qp, qa, order)
+    assert packed == ({False} if qam > 10 or qae > 4 else {True, False})
+
+
+@pytest.mark.parametrize("K", [1, 2, 15, 16, 17, 31, 32, 33, 63, 64, 65, 96, 97, 129, 200])
+def test_k_remainders_and_ragged_tiles(ref, K):
+    # quiet operands (clamp-free tiles) and loud ones (every sum saturates), rows and columns off the tiles of every region
+    rng = np.random.default_rng(K)
+    qp, qa = (5, 7, -1, 0), (4, 7, -9, 0)
+    for (M, N), (lo, hi) in itertools.product([(33, 18), (65, 130), (300, 257)], [(0, 9), (3, 15)]):
+        assert slots(M, N, K, qp, qa) == 250
+        A, B = codes(rng, (M, K), lo, hi), codes(rng, (N, K), lo, hi)
+        for order in (0, 1):
+            got = product(A, B, qp, qa, order)
+            assert np.array_equal(bits(got), bits(ref.gemm(A, B, ref.QFmt(*qp), ref.QFmt(*qa), order=order))), (M, N, K, lo, order)
+
+
+@pytest.mark.parametrize("fa,fb", [((3, 4, 3), (3, 4, 3)), ((2, 5, 1), (3, 4, 5)), ((4, 3, 9), (2, 5, -2)), ((2, 5, 1), (2, 5, 1)), ((5, 2, 15), (3, 4, 3))])
+def test_operand_formats(ref, fa, fb):
+    # products of up to 12 bits, truncated by Q_prod (10 bits of mantissa at most on packed carriers) or kept; E = 5
+    # operands stay on FP32
+    rng = np.random.default_rng(5)
+    for (M, N, K), qpm in itertools.product([(70, 50, 96), (33, 20, 147)], (4, 7, 10, 12)):
+        A, B = codes(rng, (M, K), E=fa[0]), codes(rng, (N, K), E=fb[0])
+        for bp, ba, order in itertools.product((0, 6, 12), (2, 7, 10), (0, 1)):
+            qp, qa = (6, qpm, bp, 0), (4, 7, ba, 0)
+            got = product(A, B, qp, qa, order, fa, fb)
+            want = ref.gemm_in(A, B, ref.InFmt(*fa), ref.InFmt(*fb), ref.QFmt(*qp), ref.QFmt(*qa), order=order)
+            assert np.array_equal(bits(got), bits(want)), (M, N, K, qp, qa, order)
