@@ -217,9 +217,8 @@ size_t lba_mask_words_level2(int64_t M, int64_t N, int64_t K);
  *   LBA_STE_COEF_PLANE    c is read from of_mask as it is (a plane written by lba_ste_plane).
  * Arithmetic: FP32 products and FP32 sums.  The order of the summation is unspecified (the sum may be
  * split across workgroups and combined with atomic adds), so results are reproducible up to FP32
- * rounding: |error| <= (terms + 1) * 2^-24 * sum of |terms| to first order.  The identity and the
- * recursive estimator run on the matrix cores when G (and last_of) are 16-byte aligned and N % 4 == 0
- * (recursive: K <= 12288): g is split exactly into three bfloat16
+ * rounding: |error| <= (terms + 1) * 2^-24 * sum of |terms| to first order.  The identity estimator runs on the
+ * matrix cores, the recursive one when G and last_of are 16-byte aligned, N % 4 == 0 and K <= 12288: g is split exactly into three bfloat16
  * pieces whose products with the FP8 values are exact; gradient values below about 2^-100 may lose
  * pieces to the flush of subnormal numbers there.
  */
@@ -261,7 +260,7 @@ int lba_grad(const float* G, const uint8_t* A, const uint8_t* B,
 
 /* lba_grad with a workspace (Sec. 4, App. D: the immediate estimator is the plain backward product wherever no
  * step of a region overflowed).  Same arguments, results and error bound as lba_grad; with ste =
- * LBA_STE_IMMEDIATE_OF or LBA_STE_COEF_PLANE (and G 16-byte aligned, N % 4 == 0) the work is split by bricks of
+ * LBA_STE_IMMEDIATE_OF or LBA_STE_COEF_PLANE (and the plane 16-byte aligned) the work is split by bricks of
  * 128 rows x 32 summed indices x 256 k: one pass over the plane marks, in the workspace, the bricks that hold a
  * blocked coefficient; all other bricks are dense products and run on the matrix cores, the marked ones in the
  * kernel that applies the plane bit by bit.  Where the accumulator format fits the data (few or no overflows)

@@ -472,8 +472,12 @@ __global__ void __launch_bounds__(256) lba_grad_kernel(const float* __restrict__
 // (dX: rows m, s = n; dW: rows n, s = m); its byte becomes non-zero if some coefficient in it is 0 (flip = all ones: the
 // plane holds OF bits, a set bit blocks; flip = 0: it holds coefficients, a clear bit among the K valid ones blocks).
 // The maps are zeroed beforehand.  One workgroup per group of rows of the [words * M][N] matrix of plane words.
+// RAGGED: N % 4 != 0: a group may hold the end of one row and the start of the next, and the last one fewer than four
+// words; the groups are still read whole, and each word of a marked group finds its own brick.
 struct BrickDims {
-    int64_t quads;             // words * M * N / 4: 16-byte groups of plane words (N % 4 == 0: a group lies in one row)
+    int64_t quads;             // 16-byte groups of plane words: words * M * N / 4 (N % 4 == 0: a group lies in one row), or
+                               // that rounded up (RAGGED)
+    int64_t total;             // words * M * N
     int32_t M, N, K, qpr;      // qpr = N / 4
     int32_t rbx, sbx, rbw, sbw;
     uint32_t flip;
@@ -481,15 +485,26 @@ struct BrickDims {
 
 constexpr int kBrickQuadsPerWg = 4096;                         // 64 KB of the plane per workgroup
 
+template <bool RAGGED>
 __global__ void __launch_bounds__(256) lba_brick_map_kernel(const uint32_t* __restrict__ plane, uint8_t* __restrict__ map_dx,
                                                             uint8_t* __restrict__ map_dw, const BrickDims d) {
     const int words = (d.K + 31) >> 5;
     // the workgroup's first group: row (w, m) of the [words * M][N] matrix and position in it, computed once
     const int64_t q0 = (int64_t)blockIdx.x * kBrickQuadsPerWg;
-    const int64_t row0 = q0 / d.qpr;
-    const int rem0 = (int)(q0 - row0 * d.qpr);
+    const int64_t row0 = RAGGED ? 0 : q0 / d.qpr;
+    const int rem0 = RAGGED ? 0 : (int)(q0 - row0 * d.qpr);
     const int w0 = (int)(row0 / d.M);
     const int m0 = (int)(row0 - (int64_t)w0 * d.M);
+    auto mark = [&](int w, int m, int n, uint32_t raw) {
+        const int valid = d.K - 32 * w;
+        const uint32_t vmask = (w == words - 1 && valid < 32) ? ((1u << valid) - 1u) : 0xFFFFFFFFu;
+        if (raw & vmask) {
+            uint8_t* bx = map_dx + ((int64_t)(w >> 3) * d.rbx + (m >> 7)) * d.sbx + (n >> 5);
+            uint8_t* bw = map_dw + ((int64_t)(w >> 3) * d.rbw + (n >> 7)) * d.sbw + (m >> 5);
+            if (!*bx) *bx = 1;                                 // racing stores write the same value
+            if (!*bw) *bw = 1;
+        }
+    };
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     const u32x4* __restrict__ src = reinterpret_cast<const u32x4*>(plane) + q0;
     constexpr int BATCH = 8;                                   // loads in flight per lane: the pass is bound by memory
@@ -498,7 +513,19 @@ __global__ void __launch_bounds__(256) lba_brick_map_kernel(const uint32_t* __re
 #pragma unroll
         for (int j = 0; j < BATCH; ++j) {
             const int l = (i0 + j) * 256 + (int)threadIdx.x;
-            xs[j] = (q0 + l < d.quads) ? __builtin_nontemporal_load(src + l) : u32x4{d.flip, d.flip, d.flip, d.flip};
+            const int64_t left = RAGGED ? d.total - 4 * (q0 + l) : 4;            // words from this group on
+            u32x4 x = {d.flip, d.flip, d.flip, d.flip};
+            if (q0 + l < d.quads) {
+                if (!RAGGED || left >= 4) {
+                    x = __builtin_nontemporal_load(src + l);
+                } else {
+                    const uint32_t* tail = plane + 4 * (q0 + l);
+                    x.x = tail[0];                             // (left >= 1: the last group is not empty)
+                    if (left > 1) x.y = tail[1];
+                    if (left > 2) x.z = tail[2];
+                }
+            }
+            xs[j] = x;
         }
 #pragma unroll
         for (int j = 0; j < BATCH; ++j) {
@@ -506,18 +533,21 @@ __global__ void __launch_bounds__(256) lba_brick_map_kernel(const uint32_t* __re
             const uint32_t raw = (x.x ^ d.flip) | (x.y ^ d.flip) | (x.z ^ d.flip) | (x.w ^ d.flip);
             if (raw == 0u) continue;                           // the usual case: nothing blocked in these 128 steps
             const int l = (i0 + j) * 256 + (int)threadIdx.x;
-            const int t = rem0 + l;
-            const int dr = t / d.qpr;
-            const int n = (t - dr * d.qpr) * 4;
-            int w = w0, m = m0 + dr;
-            while (m >= d.M) { m -= d.M; ++w; }
-            const int valid = d.K - 32 * w;
-            const uint32_t vmask = (w == words - 1 && valid < 32) ? ((1u << valid) - 1u) : 0xFFFFFFFFu;
-            if (raw & vmask) {                                 // the four words share every brick index (n / 32, n / 128)
-                uint8_t* bx = map_dx + ((int64_t)(w >> 3) * d.rbx + (m >> 7)) * d.sbx + (n >> 5);
-                uint8_t* bw = map_dw + ((int64_t)(w >> 3) * d.rbw + (n >> 7)) * d.sbw + (m >> 5);
-                if (!*bx) *bx = 1;                             // racing stores write the same value
-                if (!*bw) *bw = 1;
+            if (RAGGED) {
+                const uint32_t e[4] = {x.x ^ d.flip, x.y ^ d.flip, x.z ^ d.flip, x.w ^ d.flip};
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (e[u] == 0u) continue;
+                    const int64_t i = 4 * (q0 + l) + u, row = i / d.N;
+                    const int w = (int)(row / d.M);
+                    mark(w, (int)(row - (int64_t)w * d.M), (int)(i - row * d.N), e[u]);
+                }
+            } else {
+                const int t = rem0 + l;
+                const int dr = t / d.qpr;
+                int w = w0, m = m0 + dr;
+                while (m >= d.M) { m -= d.M; ++w; }
+                mark(w, m, (t - dr * d.qpr) * 4, raw);         // the four words share every brick index (n / 32, n / 128)
             }
         }
     }
@@ -684,14 +714,17 @@ int brick_maps_scan(const uint32_t* plane, void* workspace, int64_t M, int64_t N
     uint8_t* map_dx = (uint8_t*)workspace;
     uint8_t* map_dw = map_dx + bx;
     BrickDims bd;
-    bd.quads = ((K + 31) / 32) * M * (N / 4);
+    const bool ragged = (N % 4) != 0;
+    bd.total = ((K + 31) / 32) * M * N;
+    bd.quads = (bd.total + 3) / 4;
     bd.M = (int32_t)M; bd.N = (int32_t)N; bd.K = (int32_t)K; bd.qpr = (int32_t)(N / 4);
     bd.rbx = (int32_t)((M + 127) / 128); bd.sbx = (int32_t)((N + 31) / 32);
     bd.rbw = (int32_t)((N + 127) / 128); bd.sbw = (int32_t)((M + 31) / 32);
     bd.flip = flip;
     const int64_t wgs = (bd.quads + kBrickQuadsPerWg - 1) / kBrickQuadsPerWg;
     if (wgs > 2147483647LL) return LBA_ERR_SHAPE;
-    hipLaunchKernelGGL(lba_brick_map_kernel, dim3((unsigned)wgs), dim3(256), 0, st, plane, map_dx, map_dw, bd);
+    if (ragged) hipLaunchKernelGGL(lba_brick_map_kernel<true>, dim3((unsigned)wgs), dim3(256), 0, st, plane, map_dx, map_dw, bd);
+    else        hipLaunchKernelGGL(lba_brick_map_kernel<false>, dim3((unsigned)wgs), dim3(256), 0, st, plane, map_dx, map_dw, bd);
     return hipGetLastError() == hipSuccess ? LBA_OK : LBA_ERR_LAUNCH;
 }
 

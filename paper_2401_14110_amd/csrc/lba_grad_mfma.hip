@@ -85,14 +85,18 @@ __device__ __forceinline__ void decode4(uint32_t w, float (&v)[4]) {
 }
 
 // S_CONTIG: G(r, s) = G[r * ld + s] (dX); else G(r, s) = G[s * ld + r] (dW).  MASKED: L (same layout as G)
-// holds last-overflow indices and g' = [L < k0] g.
-template <bool S_CONTIG, bool MASKED, int DTK, bool BYTES = false>
+// holds last-overflow indices and g' = [L < k0] g.  GVEC: G is 16-byte aligned and N % 4 == 0, so that a patch row is one
+// 16-byte load that lies inside the matrix or outside; otherwise its four values are loaded one by one (3985 x 770 x 771:
+// dX 71 us, dW 93 us, bound by the chain load -> split -> LDS -> barrier like the others; the vector kernel took such
+// shapes before, 2.0 and 2.5 ms).
+template <bool S_CONTIG, bool MASKED, int DTK, bool BYTES = false, bool GVEC = true>
 __global__ void __launch_bounds__(256, 2) lba_grad_dense_kernel(const float* __restrict__ G, const uint8_t* __restrict__ V,
                                                                 const int32_t* __restrict__ L,
                                                                 float* __restrict__ out, const DenseDims d,
                                                                 const uint8_t* __restrict__ bricks) {
     constexpr int DNBJ = DTK / 64;                             // MFMA column blocks per wave (two waves side by side)
     static_assert(!BYTES || DTK == 128, "unaligned rows of codes: the narrow tile only");
+    static_assert(GVEC || !MASKED, "last-overflow indices are read in groups of four");
     __shared__ __attribute__((aligned(16))) uint16_t sA[3][DTR * DPITCH];
     __shared__ __attribute__((aligned(16))) uint16_t sB[DTK * DPITCH];
 
@@ -120,7 +124,17 @@ __global__ void __launch_bounds__(256, 2) lba_grad_dense_kernel(const float* __r
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             float4 g = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (S_CONTIG) {                                    // q: row within the patch; the float4 runs along s (S % 4 == 0 and
+            if (!GVEC) {                                       // the loads are unconditional, from addresses inside the matrix
+                float e[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int r = r0 + 4 * a_pr + (S_CONTIG ? q : u), s = sb + 4 * a_ps + (S_CONTIG ? u : q);
+                    const int rc = min(r, d.R - 1), sc = min(s, s_end - 1);
+                    const float x = G[S_CONTIG ? (int64_t)rc * d.ld_g + sc : (int64_t)sc * d.ld_g + rc];
+                    e[u] = (r < d.R && s < s_end) ? x : 0.0f;
+                }
+                g = make_float4(e[0], e[1], e[2], e[3]);
+            } else if (S_CONTIG) {                                    // q: row within the patch; the float4 runs along s (S % 4 == 0 and
                                                                // s_chunk % 32 == 0: it is inside the range or outside, never across)
                 const int r = r0 + 4 * a_pr + q, s = sb + 4 * a_ps;
                 if (r < d.R && s < s_end) {
@@ -372,14 +386,13 @@ __global__ void lba_grad_dense_zero_kernel(float* x, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += step) x[i] = 0.0f;
 }
 
-// Can the matrix-core path take this product?  16-byte rows of G (and of last_of) in both directions; with last_of
-// also a row of K sums within 48 KB of LDS.  (Codes are read in 4-byte groups: one load when their rows are aligned,
+// Can the matrix-core path take this product?  With last_of only 16-byte rows of G and of last_of in both directions and
+// a row of K sums within 48 KB of LDS; otherwise any N and any alignment of G (GVEC).  (Codes are read in 4-byte groups: one load when their rows are aligned,
 // else the two aligned words around the group.)
 bool grad_dense_ok(const float* G, const uint8_t* V, const int32_t* last_of, int64_t M, int64_t N, int64_t K) {
     (void)V;
-    if (((uintptr_t)G % 16) != 0 || (N % 4) != 0 || (K + 127) / 128 > 65535)
-        return false;
-    if (last_of && (((uintptr_t)last_of % 16) != 0 || K > 12288)) return false;
+    if ((K + 127) / 128 > 65535) return false;
+    if (last_of && (((uintptr_t)G % 16) != 0 || (N % 4) != 0 || ((uintptr_t)last_of % 16) != 0 || K > 12288)) return false;
     return true;
 }
 
@@ -451,11 +464,13 @@ int run_grad_dense(bool dx, const float* G, const uint8_t* V, const int32_t* las
         if (hipGetLastError() != hipSuccess) return LBA_ERR_LAUNCH;
     }
     const dim3 grid((unsigned)gx, (unsigned)gy, (unsigned)split);
-#define LBA_DENSE(SC, MK) do { if (wide)          hipLaunchKernelGGL((lba_grad_dense_kernel<SC, MK, 256>), grid, dim3(256), 0, st, G, V, last_of, target, d, bricks); \
-                               else if (d.v_vec) hipLaunchKernelGGL((lba_grad_dense_kernel<SC, MK, 128>), grid, dim3(256), 0, st, G, V, last_of, target, d, bricks); \
-                               else              hipLaunchKernelGGL((lba_grad_dense_kernel<SC, MK, 128, true>), grid, dim3(256), 0, st, G, V, last_of, target, d, bricks); } while (0)
-    if (!last_of) { if (dx) LBA_DENSE(true, false); else LBA_DENSE(false, false); }
-    else          { if (dx) LBA_DENSE(true, true);  else LBA_DENSE(false, true); }
+    const bool gvec = ((uintptr_t)G % 16) == 0 && (N % 4) == 0;
+#define LBA_DENSE(SC, MK, GV) do { if (wide)          hipLaunchKernelGGL((lba_grad_dense_kernel<SC, MK, 256, false, GV>), grid, dim3(256), 0, st, G, V, last_of, target, d, bricks); \
+                                   else if (d.v_vec) hipLaunchKernelGGL((lba_grad_dense_kernel<SC, MK, 128, false, GV>), grid, dim3(256), 0, st, G, V, last_of, target, d, bricks); \
+                                   else              hipLaunchKernelGGL((lba_grad_dense_kernel<SC, MK, 128, true, GV>), grid, dim3(256), 0, st, G, V, last_of, target, d, bricks); } while (0)
+    if (last_of)   { if (dx) LBA_DENSE(true, true, true);   else LBA_DENSE(false, true, true); }
+    else if (gvec) { if (dx) LBA_DENSE(true, false, true);  else LBA_DENSE(false, false, true); }
+    else           { if (dx) LBA_DENSE(true, false, false); else LBA_DENSE(false, false, false); }
 #undef LBA_DENSE
     if (hipGetLastError() != hipSuccess) return LBA_ERR_LAUNCH;
     if (d.atomic == 2) {                                       // the slices, added in order, become the output

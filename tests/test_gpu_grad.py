@@ -497,3 +497,31 @@ def test_split_sums_combined_in_the_workspace(ref, gref):
                         assert (np.abs(dW - wW) <= 2 * (M + 1) * 2.0 ** -24 * aW + 1e-30).all(), (M, N, K, ste, "dW")
     assert lb.lba_grad_workspace_bytes_fast(0, 8, 8) == 0 and lb.lba_grad_workspace_bytes_fast(1 << 31, 8, 8) == 0
     assert lb.lba_grad_workspace_bytes_fast(4096, 4096, 4096) == lb.lba_grad_workspace_bytes(4096, 4096, 4096)
+
+
+@pytest.mark.parametrize("M,N,K", [(300, 201, 600), (131, 70, 257), (64, 515, 640), (1500, 63, 147), (129, 1, 300), (1, 130, 72),
+                                   (33, 3, 31), (257, 37, 1028)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_any_width_and_alignment_on_the_matrix_cores(ref, gref, M, N, K, offset):
+    # N % 4 != 0 and G off a 16-byte boundary: the identity estimator and the clean bricks of a plane whose rows are not
+    # whole 16-byte groups (plane sizes of 0 to 3 words beyond the last group); clean and marked bricks side by side.
+    # Sums of eighths below 2^24 units: exact in any order.
+    rng = np.random.default_rng(M * 1000 + N)
+    qp, qa = (4, 7, 12, 0), (4, 7, 10, 0)
+    A = codes(rng, (M, K), 2, 5); B = codes(rng, (N, K), 2, 5)
+    A[:, K - K // 3:] = codes(rng, (M, K // 3), 6, 10); B[N // 2:, K - K // 3:] = codes(rng, (N - N // 2, K // 3), 6, 10)
+    tA, tB = torch.from_numpy(A).to(DEV), torch.from_numpy(B).to(DEV)
+    _, of, _ = lb.gemm_bwd(tA, tB, qp, qa, want_c=False)
+    G = (rng.integers(-8, 9, (M, N)) / 4.0).astype(np.float32)
+    flat = torch.zeros(M * N + 4, dtype=torch.float32, device=DEV)
+    tG = flat[offset:offset + M * N].view(M, N)
+    tG.copy_(torch.from_numpy(G))
+    ws = torch.full((max(256, lb.lba_grad_workspace_bytes_fast(M, N, K)),), 0x5A, dtype=torch.uint8, device=DEV)
+    coef = lb.ste_plane(of, K, lb.STE_RECURSIVE_OF)
+    for ste, plane, est in ((lb.STE_IDENTITY, None, 0), (lb.STE_IMMEDIATE_OF, of, 1), (lb.STE_COEF_PLANE, coef, 2)):
+        wX, wW = gref.grad(G, A, B, ref.QFmt(*qp), ref.QFmt(*qa), est)
+        for w in (ws, ws[:max(256, lb.lba_grad_workspace_bytes(M, N, K))], None):
+            dX, dW = lb.grad(tG, tA, tB, ste, of_plane=plane, workspace=w)
+            torch.cuda.synchronize()
+            assert np.array_equal(dX.cpu().numpy(), wX.astype(np.float32)), (ste, w is None, "dX")
+            assert np.array_equal(dW.cpu().numpy(), wW.astype(np.float32)), (ste, w is None, "dW")
