@@ -600,6 +600,8 @@ def conv_kernel_name(name):
             return conv + name[len(plain):]
     if (name.startswith("lba_fast_kernel<") or name.startswith("lba_fast_bwd_kernel<")) and name.endswith(", 0>"):
         return name[:-4] + ", 2>"
+    if name.startswith("lba_half_bwd") and name.endswith(", 0>"):
+        return name[:-4] + ", 2>"
     return name
 
 

@@ -49,6 +49,15 @@ __device__ __forceinline__ void set_flush_f32()     { asm volatile("s_setreg_imm
 // FP16 denormals on (MODE[7:6] = 3): the staging decodes 8-bit codes through an exact FP16 image
 __device__ __forceinline__ void set_denorm_f16()    { asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 6, 2), 3\n\ts_nop 1" ::: "memory"); }
 
+// Vectors that need not be aligned to their size: gfx950 takes 8- and 16-byte global accesses at any address (the rows of a
+// width that is not a multiple of 4, or of a depth that is not a multiple of 16).  Four-byte stores instead cost most where
+// they are non-temporal, as the plane words are: partial lines go to memory one by one.
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x2_any __attribute__((ext_vector_type(2), aligned(4)));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(4)));
+typedef uint32_t u32x4_bytes __attribute__((ext_vector_type(4), aligned(1)));
+
 __device__ __forceinline__ float med3(float x, float lo, float hi) { return __builtin_amdgcn_fmed3f(x, lo, hi); }
 
 // ---------------------------------------------------------------------------------------------
@@ -284,8 +293,8 @@ struct Stage {
 
 // Fetch this lane's 16-byte pieces of one operand tile into registers (zero outside the matrix).
 // ld_align == 16: every piece is 16-byte aligned and wholly inside its row (K % 16 == 0).
-// Otherwise: five 4-byte-aligned loads cover the piece at any byte offset and are funnel-shifted
-// into place.  Each load address is clamped to the aligned word holding the last valid byte, so
+// Otherwise one unaligned 16-byte load, and for the pieces that would read beyond the matrix (the end of its last row) five
+// 4-byte-aligned loads that cover the piece at any byte offset and are funnel-shifted into place.  Each load address is clamped to the aligned word holding the last valid byte, so
 // every word read contains at least one byte of the matrix (it cannot cross into another page).
 template <int ROWS, int BK>
 __device__ __forceinline__ void fetch_tile(const uint8_t* __restrict__ G, int rows, int K, int r0, int k0,
@@ -302,6 +311,17 @@ __device__ __forceinline__ void fetch_tile(const uint8_t* __restrict__ G, int ro
                 const uint8_t* src = G + (int64_t)r * K + k;
                 if (ld_align == 16) {
                     v = *reinterpret_cast<const uint4*>(src);
+                } else if (src + 16 <= G + (int64_t)rows * K) {             // 16 bytes of the matrix, the next row's among them
+                    const u32x4_bytes x = *reinterpret_cast<const u32x4_bytes*>(src);
+                    uint32_t w[4] = {x.x, x.y, x.z, x.w};
+                    if (k + 16 > K) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const int nb = K - k - 4 * j;                   // valid bytes in this word
+                            w[j] &= nb >= 4 ? 0xFFFFFFFFu : (nb <= 0 ? 0u : ((1u << (8 * nb)) - 1u));
+                        }
+                    }
+                    v = make_uint4(w[0], w[1], w[2], w[3]);
                 } else {
                     const int nvalid = (K - k) < 16 ? (K - k) : 16;         // bytes of this piece inside the row
                     const uintptr_t a0 = reinterpret_cast<uintptr_t>(src);
@@ -836,9 +856,9 @@ __device__ __forceinline__ void fast_body(const KParams& p, float* __restrict__ 
         }
         float* dst = pC + (int64_t)m * p.N + n;
         if (TN == 4 && p.c_vec && n + 3 < p.N) {
-            *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[TN - 2], v[TN - 1]);
+            *reinterpret_cast<f32x4_any*>(dst) = f32x4_any{v[0], v[1], v[TN - 2], v[TN - 1]};
         } else if (TN == 2 && p.c_vec && n + 1 < p.N) {
-            *reinterpret_cast<float2*>(dst) = make_float2(v[0], v[1]);
+            *reinterpret_cast<f32x2_any*>(dst) = f32x2_any{v[0], v[1]};
         } else {
 #pragma unroll
             for (int j = 0; j < TN; ++j)
@@ -871,15 +891,13 @@ __device__ __forceinline__ void store_event_words(uint32_t* of_plane, uint32_t* 
             }
             // written once and not read again by this call: non-temporal stores, so that the plane (one word per 32
             // MACs, more bytes than A, B and C together) does not push the operand tiles out of L2
-            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-            if (p.c_vec && n + TN - 1 < p.N) {                 // N % 4 == 0 and aligned planes: 16- or 8-byte stores
+            if (p.c_vec && n + TN - 1 < p.N) {                 // 16- or 8-byte stores
                 if (TN == 4) {
-                    if (of_plane) __builtin_nontemporal_store(u32x4{o[0], o[1], o[TN - 2], o[TN - 1]}, reinterpret_cast<u32x4*>(of_plane + off));
-                    if (uf_plane) __builtin_nontemporal_store(u32x4{u[0], u[1], u[TN - 2], u[TN - 1]}, reinterpret_cast<u32x4*>(uf_plane + off));
+                    if (of_plane) __builtin_nontemporal_store(u32x4_any{o[0], o[1], o[TN - 2], o[TN - 1]}, reinterpret_cast<u32x4_any*>(of_plane + off));
+                    if (uf_plane) __builtin_nontemporal_store(u32x4_any{u[0], u[1], u[TN - 2], u[TN - 1]}, reinterpret_cast<u32x4_any*>(uf_plane + off));
                 } else {
-                    if (of_plane) __builtin_nontemporal_store(u32x2{o[0], o[1]}, reinterpret_cast<u32x2*>(of_plane + off));
-                    if (uf_plane) __builtin_nontemporal_store(u32x2{u[0], u[1]}, reinterpret_cast<u32x2*>(uf_plane + off));
+                    if (of_plane) __builtin_nontemporal_store(u32x2_any{o[0], o[1]}, reinterpret_cast<u32x2_any*>(of_plane + off));
+                    if (uf_plane) __builtin_nontemporal_store(u32x2_any{u[0], u[1]}, reinterpret_cast<u32x2_any*>(uf_plane + off));
                 }
             } else {
 #pragma unroll
@@ -1307,6 +1325,24 @@ __device__ __forceinline__ void bwd_tile(float (&acc)[TM][TN], float (&top)[TM][
     }
 }
 
+// any: non-zero on the lanes that have an overflow in plane word t (see mark_bricks)
+template <int TM, int TN>
+__device__ __forceinline__ void mark_bricks_of_wave(uint32_t any, int m0, int n0, int t, int tx, int ty, const KParams& p) {
+    (void)tx;
+    const uint64_t dirty = __builtin_amdgcn_ballot_w64(any != 0u);
+    if (dirty == 0) return;                                    // uniform; the usual case
+    if ((threadIdx.x & 63) == 0) {                             // this lane's first row is the wave's (tx = 0)
+        const int64_t kb = t >> 3;
+        const int m = m0 + ty * TM;
+        uint8_t* bw = p.map_dw + (kb * p.map_rbw + (n0 >> 7)) * p.map_sbw + (m >> 5);
+        if (!*bw) *bw = 1;                                     // racing stores write the same value
+        uint8_t* bx = p.map_dx + (kb * p.map_rbx + (m >> 7)) * p.map_sbx + (n0 >> 5);
+        const uint64_t low = TN == 4 ? 0x00FF00FF00FF00FFull : ~0ull;   // lanes whose columns lie in the first group
+        if ((dirty & low) && !*bx) *bx = 1;
+        if (TN == 4 && (dirty & ~low) && !bx[1]) bx[1] = 1;
+    }
+}
+
 // Brick maps of the overflow plane as a by-product of the recompute (the gradient side's split of the immediate
 // estimator): a brick is 128 rows x 32 s x 256 k of a gradient product (dX: rows m, s = n; dW: rows n, s = m) and its
 // byte is set when one of its steps overflows.  Called after a k-tile that was not provably quiet, before its words
@@ -1323,18 +1359,7 @@ __device__ __forceinline__ void mark_bricks(const uint32_t (&wof)[TM][TN], int m
         for (int j = 0; j < TN; ++j)
             if (m0 + ty * TM + i < p.M && n0 + tx * TN + j < p.N) any |= wof[i][j];
     if (valid < 32) any &= ~((1u << (32 - valid)) - 1u);       // steps at and beyond K
-    const uint64_t dirty = __builtin_amdgcn_ballot_w64(any != 0u);
-    if (dirty == 0) return;                                    // uniform; the usual case
-    if ((threadIdx.x & 63) == 0) {                             // this lane's first row is the wave's (tx = 0)
-        const int64_t kb = t >> 3;
-        const int m = m0 + ty * TM;
-        uint8_t* bw = p.map_dw + (kb * p.map_rbw + (n0 >> 7)) * p.map_sbw + (m >> 5);
-        if (!*bw) *bw = 1;                                     // racing stores write the same value
-        uint8_t* bx = p.map_dx + (kb * p.map_rbx + (m >> 7)) * p.map_sbx + (n0 >> 5);
-        const uint64_t low = TN == 4 ? 0x00FF00FF00FF00FFull : ~0ull;   // lanes whose columns lie in the first group
-        if ((dirty & low) && !*bx) *bx = 1;
-        if (TN == 4 && (dirty & ~low) && !bx[1]) bx[1] = 1;
-    }
+    mark_bricks_of_wave<TM, TN>(any, m0, n0, t, tx, ty, p);
 }
 
 template <int TM, int TN, int PM, int RND, int ORDER, int UF, int AMODE>
@@ -1466,8 +1491,8 @@ __device__ __forceinline__ void fast_bwd_body(const KParams& p, float* smem, con
             }
             float* dst = pC + (int64_t)m * p.N + n;
             if (p.c_vec && n + TN - 1 < p.N) {
-                if (TN == 4) *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[TN - 2], v[TN - 1]);
-                else         *reinterpret_cast<float2*>(dst) = make_float2(v[0], v[1]);
+                if (TN == 4) *reinterpret_cast<f32x4_any*>(dst) = f32x4_any{v[0], v[1], v[TN - 2], v[TN - 1]};
+                else         *reinterpret_cast<f32x2_any*>(dst) = f32x2_any{v[0], v[1]};
             } else {
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
@@ -1655,8 +1680,8 @@ __device__ __forceinline__ void fast_diff_body(const KParams& p, float* smem, co
             }
             float* dst = pC + (int64_t)m * p.N + n;
             if (p.c_vec && n + TN - 1 < p.N) {
-                if (TN == 4) *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[TN - 2], v[TN - 1]);
-                else         *reinterpret_cast<float2*>(dst) = make_float2(v[0], v[1]);
+                if (TN == 4) *reinterpret_cast<f32x4_any*>(dst) = f32x4_any{v[0], v[1], v[TN - 2], v[TN - 1]};
+                else         *reinterpret_cast<f32x2_any*>(dst) = f32x2_any{v[0], v[1]};
             } else {
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
@@ -1911,7 +1936,7 @@ __global__ void __launch_bounds__(256) lba_gen_kernel(const KParams p) {
             }
             float* dst = pC + (int64_t)m * p.N + n;
             if (p.c_vec && n + 3 < p.N) {
-                *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+                *reinterpret_cast<f32x4_any*>(dst) = f32x4_any{v[0], v[1], v[2], v[3]};
             } else {
 #pragma unroll
                 for (int j = 0; j < 4; ++j)

@@ -235,6 +235,48 @@ __device__ __forceinline__ void half_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[TM][T
     }
 }
 
+// Decodes and stores the pieces of one k-tile.  dyn: also leaves the largest squared norm of a piece of A (low half) and of
+// B, to 8 bits, rounded up, per wave.
+template <int BM, int BN>
+__device__ __forceinline__ void half_stage(const KParams& p, uint32_t* __restrict__ Ad, uint32_t* __restrict__ Bd, const uint4& ra, const uint4& rb,
+                                           int tid, int tidb, bool dyn, uint32_t* __restrict__ norm) {
+    uint32_t wa[8], wb[8];
+    decode_half(ra, p.h_shift_a, p.h_keep_a, p.h_scale_a, wa);
+    store_half_a<BM>(Ad, tid, wa);
+    decode_half(rb, p.h_shift_b, p.h_keep_b, p.h_scale_b, wb);
+    store_half_b<BN>(Bd, tidb, wb);
+    if (dyn) {
+        const uint32_t na = __float_as_uint(piece_norm2(wa)), nb = __float_as_uint(piece_norm2(wb));
+        uint32_t m = ((na + 0xFFFFu) >> 16) | ((nb + 0xFFFFu) & 0xFFFF0000u);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) m = pk_max_u16(m, (uint32_t)__shfl_xor((int)m, o, 64));
+        if ((tid & 63) == 0) norm[tid >> 6] = m;
+    }
+}
+
+// The bound that follows the data costs a reduction per staged tile: only where the fixed one leaves less than half of the
+// range (R_OF below 64 of the largest products).
+__device__ __forceinline__ bool half_follows_data(const KParams& p) { return p.dyn_bound != 0 && 2.0f * p.fast_thresh < p.rof_a; }
+
+// For how many of the next tiles of 32 steps (0 to 4) no sum of the wave can reach R_OF; mf: this lane's largest |S|.
+struct HalfBound {
+    float rof, thresh, grow, kcf;
+    // the planner's bound is in the FP32 tile's domain (R_UF at 2^-126); 2^112 moves it to R_UF at 2^-14.  grow: 32 of the
+    // largest products there are (thresh is rounded down; the factor covers the roundings here)
+    __device__ __forceinline__ explicit HalfBound(const KParams& p)
+        : rof(p.rof_a * 0x1p112f), thresh(p.fast_thresh * 0x1p112f), grow(1.0001f * (rof - thresh)), kcf((float)as_h2(p.h_kc).x) {}
+    // norms: half_stage's, for the current tile, or null
+    __device__ __forceinline__ int safe(float mf, const uint32_t* norms) const {
+        if (__all(mf < thresh)) return 1 + __all(mf < thresh - grow) + __all(mf < thresh - 2.0f * grow) + __all(mf < thresh - 3.0f * grow);
+        if (!norms) return 0;
+        // Cauchy-Schwarz: 16 products of a row's piece and a column's piece add at most the product of their norms; 32 steps
+        // are two pieces.  (The factor covers the roundings of the norms and of this line.)
+        const uint32_t m = pk_max_u16(pk_max_u16(norms[0], norms[1]), pk_max_u16(norms[2], norms[3]));
+        const float n2 = __uint_as_float(m << 16) * __uint_as_float(m & 0xFFFF0000u);
+        return __all(mf < rof - 2.0f * 1.001f * __builtin_sqrtf(n2) * kcf) ? 1 : 0;
+    }
+};
+
 // The work of one workgroup: the BM x BN tile of C at (m0, n0).  smem: two stages.  Structure, clamp-free tiles and their
 // bounds as in fast_body; AMODE as there (1 and 0 differ in the fetch of im2col rows only: every code format decodes alike).
 template <int TM, int TN, int LX, int PM, int ORDER, int AMODE>
@@ -256,7 +298,6 @@ __device__ __forceinline__ void half_body(const KParams& p, uint32_t* __restrict
 
     HalfConst c;
     c.kc = as_h2(p.h_kc); c.rof = as_h2(p.h_rof); c.nrof = as_h2(p.h_rof ^ 0x80008000u); c.mask = p.h_mask_a; c.maskp = p.h_mask_p;
-    uint32_t sc_a = p.h_scale_a, sc_b = p.h_scale_b;
     asm volatile("" : "+v"(c.kc), "+v"(c.rof), "+v"(c.nrof), "+v"(c.mask), "+v"(c.maskp));
 
     h2 acc[TM][TN / 2], top[TM][TN / 2];
@@ -268,9 +309,7 @@ __device__ __forceinline__ void half_body(const KParams& p, uint32_t* __restrict
     uint4 ra[1], rb[1];
     const int ntiles = (p.K + HBK - 1) / HBK;
     __shared__ uint32_t half_norm[2][4];                       // per stage and wave: largest squared norm of a piece of A (low half), of B
-    // The bound that follows the data costs a reduction per staged tile: only where the fixed one leaves less than half of
-    // the range (R_OF below 64 of the largest products).
-    const bool dyn = p.dyn_bound != 0 && 2.0f * p.fast_thresh < p.rof_a;
+    const bool dyn = half_follows_data(p);
     ConvLane cl;
     if (AMODE == 2) cl = conv_lane<BM, HBK>(pA, p, m0, tid);
     auto fetch = [&](int k0) {
@@ -279,29 +318,12 @@ __device__ __forceinline__ void half_body(const KParams& p, uint32_t* __restrict
         else                 fetch_tile<BM, HBK>(pA, p.M, p.K, m0, k0, p.ld_align, tid, ra);
         fetch_tile<BN, HBK>(pB, p.N, p.K, n0, k0, p.ld_align, tidb, rb);
     };
-    auto stage = [&](int st) {
-        uint32_t* Ad = smem + st * T::STAGE;
-        uint32_t wa[8], wb[8];
-        decode_half(ra[0], p.h_shift_a, p.h_keep_a, sc_a, wa);
-        store_half_a<BM>(Ad, tid, wa);
-        decode_half(rb[0], p.h_shift_b, p.h_keep_b, sc_b, wb);
-        store_half_b<BN>(Ad + T::A_WORDS, tidb, wb);
-        if (dyn) {                                             // both norms to 8 bits, rounded up, in one word
-            const uint32_t na = __float_as_uint(piece_norm2(wa)), nb = __float_as_uint(piece_norm2(wb));
-            uint32_t m = ((na + 0xFFFFu) >> 16) | ((nb + 0xFFFFu) & 0xFFFF0000u);
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) m = pk_max_u16(m, (uint32_t)__shfl_xor((int)m, o, 64));
-            if ((tid & 63) == 0) half_norm[st][tid >> 6] = m;
-        }
-    };
+    auto stage = [&](int st) { half_stage<BM, BN>(p, smem + st * T::STAGE, smem + st * T::STAGE + T::A_WORDS, ra[0], rb[0], tid, tidb, dyn, half_norm[st]); };
     fetch(0);
     stage(0);
     __syncthreads();
 
-    // the planner's bound is in the FP32 tile's domain (R_UF at 2^-126); 2^112 moves it to R_UF at 2^-14.  grow: 32 of the
-    // largest products there are (thresh is rounded down; the factor covers the roundings here)
-    const float rof = p.rof_a * 0x1p112f, thresh = p.fast_thresh * 0x1p112f, grow = 1.0001f * (rof - thresh);
-    const float kcf = (float)c.kc.x;
+    const HalfBound bound(p);
     int safe_tiles = 0;
     for (int t = 0; t < ntiles; ++t) {
         const uint32_t* As0 = smem + (t & 1) * T::STAGE;
@@ -319,17 +341,7 @@ __device__ __forceinline__ void half_body(const KParams& p, uint32_t* __restrict
 #pragma unroll
                     for (int j = 0; j < TN / 2; ++j)
                         mx = pk_max_u16(mx, as_u32(ORDER == LBA_ORDER_CHUNK16 ? top[i][j] : acc[i][j]) & 0x7FFF7FFFu);
-                const float mf = max_half(mx);
-                // n tiles are safe while every |S| of the wave is below R_OF minus n times what a tile can add
-                if (__all(mf < thresh)) safe_tiles = 1 + __all(mf < thresh - grow) + __all(mf < thresh - 2.0f * grow) + __all(mf < thresh - 3.0f * grow);
-                else if (dyn) {
-                    // Cauchy-Schwarz: 16 products of a row's piece and a column's piece add at most the product of their
-                    // norms; 32 steps are two pieces.  (The factor covers the roundings of the norms and of this line.)
-                    const uint32_t* hn = half_norm[t & 1];
-                    const uint32_t m = pk_max_u16(pk_max_u16(hn[0], hn[1]), pk_max_u16(hn[2], hn[3]));
-                    const float n2 = __uint_as_float(m << 16) * __uint_as_float(m & 0xFFFF0000u);
-                    if (__all(mf < rof - 2.0f * 1.001f * __builtin_sqrtf(n2) * kcf)) safe_tiles = 1;
-                }
+                safe_tiles = bound.safe(max_half(mx), dyn ? half_norm[t & 1] : nullptr);
             }
             if (safe_tiles > 0) {
                 --safe_tiles;
@@ -357,9 +369,9 @@ __device__ __forceinline__ void half_body(const KParams& p, uint32_t* __restrict
         }
         float* dst = pC + (int64_t)m * p.N + n;
         if (TN == 4 && p.c_vec && n + 3 < p.N) {
-            *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[TN - 2], v[TN - 1]);
+            *reinterpret_cast<f32x4_any*>(dst) = f32x4_any{v[0], v[1], v[TN - 2], v[TN - 1]};
         } else if (TN == 2 && p.c_vec && n + 1 < p.N) {
-            *reinterpret_cast<float2*>(dst) = make_float2(v[0], v[1]);
+            *reinterpret_cast<f32x2_any*>(dst) = f32x2_any{v[0], v[1]};
         } else {
 #pragma unroll
             for (int j = 0; j < TN; ++j)

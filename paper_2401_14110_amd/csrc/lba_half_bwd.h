@@ -1,0 +1,405 @@
+// lba_half_bwd.h -- the recompute call (forward chain + event planes) on the packed FP16 carriers of lba_half.h: floor
+// rounding, Q_prod can flush, both orders.  Two chains per register; the event bits are collected two chains per register
+// too, without the lane masks and carry-in adds of the FP32 kernel.
+//
+//   OF_k  <=>  |t| >= R_OF: the truncated sum's magnitude bits plus (0x8000 - bits of R_OF) carry into bit 15.
+//   UF_k  <=>  the product was flushed with both operands non-zero, or 0 < |t| < R_UF.  The multiply runs with results flushed
+//         (q = 0: flushed, or an operand is zero), the multiply-add with denormal results kept and denormal inputs read as
+//         zero: t is a denormal number exactly when it underflows, and the next step reads it as the zero the quantizer
+//         asks for.  A non-zero sum never rounds to zero there: with S != 0 it is a multiple of 2^-24 (S of M + 1 <= 11 bits
+//         at 2^-14 or above, a product of at most 10 bits cancelling it), with S = 0 it is the product, at least 2^-14 * kc
+//         (the planner admits kc >= 2^-10).  2|q| and 2|t| - 2 (a zero sum wraps to the top) are below 0x7FE exactly for
+//         the two events, so one minimum and one add put "no event" into bit 15.  Steps with a zero operand are cleared
+//         afterwards, a word at a time, from per-row masks of non-zero codes left by the staging.
+//   Bit 15 of both halves enters a shift register from the top: after 16 steps bit j of each half is step j.
+// A k-tile in which no sum can reach R_OF (HalfBound) has no overflow test, and no underflow plane asked for it is the
+// forward tile.
+//
+// What bounds it: VALU issue, nine instructions for two chains with the underflow plane and a quiet tile (7 of them at half
+// rate: 17.8 cycles per chain and step by the issue-rate probe).  The FP32 kernel (compares to 64-bit masks, scalar logic, one
+// carry-in add per chain and plane) takes 27.  Measured against it, both planes of 4096 x 768 x 3072: 1703 -> 1418 us (23
+// cycles; 2.4 GB of planes leave at 1.7 TB/s); the overflow plane alone of 12544 x 256 x 2304: 533 -> 440 us.  Reading
+// operands a step ahead, or two waves per SIMD instead of three for the underflow plane, changed nothing.
+#ifndef LBA_HALF_BWD_H_
+#define LBA_HALF_BWD_H_
+
+#include "lba_device.h"
+
+namespace lba {
+
+// FP16: denormal inputs read as zero, denormal results kept / both flushed (no memory clobber: everything that depends on
+// the mode between two writes is volatile assembly itself)
+__device__ __forceinline__ void half_keep_out()  { asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 6, 2), 2\n\ts_nop 1"); }
+__device__ __forceinline__ void half_flush_out() { asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 6, 2), 1\n\ts_nop 1"); }
+__device__ __forceinline__ void half_flush_all() { asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 6, 2), 0\n\ts_nop 1" ::: "memory"); }
+
+__device__ __forceinline__ uint32_t pk_add_u16(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, a) + __builtin_bit_cast(u16x2, b)));
+}
+__device__ __forceinline__ uint32_t pk_add_u16_sat(uint32_t a, uint32_t b) {   // saturates at 0xFFFF
+    uint32_t r;
+    asm("v_pk_add_u16 %0, %1, %2 clamp" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+// shift register of two chains: bit 15 of y's halves enters from the top
+__device__ __forceinline__ uint32_t pk_shift_in(uint32_t w, uint32_t y, uint32_t bit15) {
+    uint32_t r;
+    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "v"(bit15), "v"(y), "v"(w >> 1));
+    return r;
+}
+
+struct HalfBwdConst {
+    h2 kc, rof, nrof;
+    uint32_t mask, maskp;
+    uint32_t absmask;          // the accumulator's mask without the sign
+    uint32_t of_bias;          // 0x8000 - bits of R_OF
+    uint32_t two, minus2, uf_bias;   // 2, -2, 0x8000 - 0x7FE
+    uint32_t bit15;            // 0x80008000
+};
+
+// 16-bit mask of a piece's non-zero codes, code 0 in bit 0
+__device__ __forceinline__ uint32_t nonzero_codes(const uint4& v) {
+    const uint32_t q[4] = {v.x, v.y, v.z, v.w};
+    uint32_t b[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) b[i] = (((q[i] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) >> 7) & 0x01010101u;   // 1 per non-zero byte
+    const uint32_t lo = __builtin_amdgcn_udot4(b[1], 0x80402010u, __builtin_amdgcn_udot4(b[0], 0x08040201u, 0u, false), false);
+    const uint32_t hi = __builtin_amdgcn_udot4(b[3], 0x80402010u, __builtin_amdgcn_udot4(b[2], 0x08040201u, 0u, false), false);
+    return lo | (hi << 8);
+}
+
+// 32 steps with event bits: word [i][j] of chain (i, j) gets step k in bit k (of: 1 = overflow; uf: 1 = underflow or a zero
+// operand, cleared by the caller).  of2 / uf2: the two chunks' bits enter the second-level words at bits pos, pos + 1.
+template <int PM, int ORDER, bool UF, bool QUIET, int TM, int TN, int BMP, int BNP>
+__device__ __forceinline__ void half_bwd_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[TM][TN / 2], uint32_t (&of)[TM][TN], uint32_t (&uf)[TM][TN],
+                                              uint32_t (&of2)[TM][TN], uint32_t (&uf2)[TM][TN], int pos, const uint32_t* As,
+                                              const uint32_t* Bs, int tx, int ty, const HalfBwdConst& c) {
+    constexpr int NJ = TN / 2;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        uint32_t wo[TM][NJ], wu[TM][NJ];
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) { wo[i][j] = 0u; wu[i][j] = 0u; }
+        uint32_t an[TM], bn[2][NJ];                            // the next pair of steps' operands, read one pair ahead
+#pragma unroll 2
+        for (int s = 0; s < 8; ++s) {
+            uint32_t a[TM], b[2][NJ];
+            read_half_a<TM, BMP>(As, 8 * h + s, ty, a);
+            read_half_b<TN, BNP>(Bs, 16 * h + 2 * s, tx, b[0]);
+            read_half_b<TN, BNP>(Bs, 16 * h + 2 * s + 1, tx, b[1]);
+            
+            uint32_t q[2][TM][NJ];
+            // both steps' products under one mode: below Q_prod's R_UF they are flushed
+            if (UF) half_flush_out();
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    asm volatile("v_pk_mul_f16 %0, %1, %2 op_sel_hi:[0,1]" : "=v"(q[0][i][j]) : "v"(a[i]), "v"(b[0][j]));
+                    asm volatile("v_pk_mul_f16 %0, %1, %2 op_sel:[1,0]" : "=v"(q[1][i][j]) : "v"(a[i]), "v"(b[1][j]));
+                }
+            if (UF) half_keep_out();
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (PM == PM_TRUNC) {
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < NJ; ++j) q[u][i][j] &= c.maskp;
+                }
+                uint32_t t[TM][NJ];
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) asm volatile("v_pk_fma_f16 %0, %1, %2, %3" : "=v"(t[i][j]) : "v"(q[u][i][j]), "v"(c.kc), "v"(acc[i][j]));
+                // phase by phase over the lane's chains, as the forward tile
+#define LBA_EACH for (int i = 0; i < TM; ++i) _Pragma("unroll") for (int j = 0; j < NJ; ++j)
+                __builtin_amdgcn_sched_barrier(0);
+                _Pragma("unroll") LBA_EACH acc[i][j] = as_h2(t[i][j] & c.mask);
+                __builtin_amdgcn_sched_barrier(0);
+                if (!QUIET) {
+                    _Pragma("unroll") LBA_EACH asm("v_pk_min_f16 %0, %0, %1" : "+v"(acc[i][j]) : "v"(c.rof));
+                    _Pragma("unroll") LBA_EACH asm("v_pk_max_f16 %0, %0, %1" : "+v"(acc[i][j]) : "v"(c.nrof));
+                    __builtin_amdgcn_sched_barrier(0);
+                    uint32_t y[TM][NJ];
+                    _Pragma("unroll") LBA_EACH y[i][j] = pk_add_u16(t[i][j] & c.absmask, c.of_bias);
+                    __builtin_amdgcn_sched_barrier(0);
+                    _Pragma("unroll") LBA_EACH wo[i][j] = pk_shift_in(wo[i][j], y[i][j], c.bit15);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (UF) {
+                    _Pragma("unroll") LBA_EACH asm("v_pk_mad_u16 %0, %0, %1, %2" : "+v"(t[i][j]) : "v"(c.two), "v"(c.minus2));
+                    _Pragma("unroll") LBA_EACH q[u][i][j] = pk_add_u16(q[u][i][j], q[u][i][j]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    _Pragma("unroll") LBA_EACH t[i][j] = pk_min_u16(q[u][i][j], t[i][j]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    _Pragma("unroll") LBA_EACH t[i][j] = pk_add_u16_sat(t[i][j], c.uf_bias);
+                    __builtin_amdgcn_sched_barrier(0);
+                    _Pragma("unroll") LBA_EACH wu[i][j] = pk_shift_in(wu[i][j], t[i][j], c.bit15);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#undef LBA_EACH
+            }
+        }
+        if (ORDER == LBA_ORDER_CHUNK16) {                      // the mode is the multiply-add's (UF) or the forward call's
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    uint32_t t;
+                    asm volatile("v_pk_add_f16 %0, %1, %2" : "=v"(t) : "v"(top[i][j]), "v"(acc[i][j]));
+                    top[i][j] = as_h2(t & c.mask);
+                    acc[i][j] = as_h2(0u);
+                    if (!QUIET) {
+                        asm("v_pk_min_f16 %0, %0, %1" : "+v"(top[i][j]) : "v"(c.rof));
+                        asm("v_pk_max_f16 %0, %0, %1" : "+v"(top[i][j]) : "v"(c.nrof));
+                        const uint32_t y = pk_add_u16(t & c.absmask, c.of_bias);
+                        of2[i][2 * j] |= ((y >> 15) & 1u) << (pos + h);
+                        of2[i][2 * j + 1] |= (y >> 31) << (pos + h);
+                    }
+                    if (UF) {                                  // 0 < |t| < R_UF
+                        uint32_t t2;
+                        asm("v_pk_mad_u16 %0, %1, %2, %3" : "=v"(t2) : "v"(t), "v"(c.two), "v"(c.minus2));
+                        const uint32_t y = ~pk_add_u16_sat(t2, c.uf_bias);
+                        uf2[i][2 * j] |= ((y >> 15) & 1u) << (pos + h);
+                        uf2[i][2 * j + 1] |= (y >> 31) << (pos + h);
+                    }
+                }
+        }
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                if (h == 0) {
+                    of[i][2 * j] = wo[i][j]; uf[i][2 * j] = wu[i][j];      // both halves' first 16 steps, sorted below
+                } else {
+                    const uint32_t o = of[i][2 * j], x = uf[i][2 * j];
+                    of[i][2 * j]     = __builtin_amdgcn_perm(wo[i][j], o, 0x05040100u);
+                    of[i][2 * j + 1] = __builtin_amdgcn_perm(wo[i][j], o, 0x07060302u);
+                    if (UF) {                                  // bits say "no event": inverted
+                        uf[i][2 * j]     = ~__builtin_amdgcn_perm(wu[i][j], x, 0x05040100u);
+                        uf[i][2 * j + 1] = ~__builtin_amdgcn_perm(wu[i][j], x, 0x07060302u);
+                    }
+                }
+            }
+    }
+}
+
+// Stores a lane's words (one per chain, first step in bit 0) as word `word` of a plane; non-temporal, see store_event_words.
+template <int TM, int TN>
+__device__ __forceinline__ void store_half_words(uint32_t* __restrict__ plane, int word, const uint32_t (&w)[TM][TN], int m0, int n0,
+                                                 int tx, int ty, const KParams& p) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int m = m0 + ty * TM + i, n = n0 + tx * TN;
+        if (m >= p.M) continue;
+        uint32_t* dst = plane + ((int64_t)word * p.M + m) * p.N + n;
+        if (TN == 4 && p.c_vec && n + 3 < p.N) {
+            __builtin_nontemporal_store(u32x4_any{w[i][0], w[i][1], w[i][TN - 2], w[i][TN - 1]}, reinterpret_cast<u32x4_any*>(dst));
+        } else if (TN == 2 && p.c_vec && n + 1 < p.N) {
+            __builtin_nontemporal_store(u32x2_any{w[i][0], w[i][1]}, reinterpret_cast<u32x2_any*>(dst));
+        } else {
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                if (n + j < p.N) __builtin_nontemporal_store(w[i][j], dst + j);
+        }
+    }
+}
+
+// mark_bricks (lba_device.h) for words whose first step is bit 0 and whose steps beyond K are cleared; word w.
+template <int TM, int TN>
+__device__ __forceinline__ void mark_bricks_lsb(const uint32_t (&of)[TM][TN], int m0, int n0, int w, int tx, int ty, const KParams& p) {
+    uint32_t any = 0u;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+            if (m0 + ty * TM + i < p.M && n0 + tx * TN + j < p.N) any |= of[i][j];
+    mark_bricks_of_wave<TM, TN>(any, m0, n0, w, tx, ty, p);
+}
+
+template <int TM, int TN, int PM, int ORDER, bool UF, int AMODE>
+__device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __restrict__ smem, int m0, int n0) {
+    using T = HalfTile<TM, TN, 16>;
+    constexpr int BM = T::BM, BN = T::BN, NJ = TN / 2;
+    const int tid = threadIdx.x;
+    const int tx = tid & 15, ty = tid >> 4;
+    const int tidb = tid - Stage<BN, HBK>::kTailShift;
+
+    set_flush_f32();
+    set_round_zero_f16();
+    set_flush_out_f16();
+
+    HalfConst fc;
+    fc.kc = as_h2(p.h_kc); fc.rof = as_h2(p.h_rof); fc.nrof = as_h2(p.h_rof ^ 0x80008000u); fc.mask = p.h_mask_a; fc.maskp = p.h_mask_p;
+    HalfBwdConst c;
+    c.kc = fc.kc; c.rof = fc.rof; c.nrof = fc.nrof; c.mask = fc.mask; c.maskp = fc.maskp;
+    c.absmask = p.h_mask_a & 0x7FFF7FFFu;
+    c.of_bias = pk_add_u16(0x80008000u, pk_add_u16(~p.h_rof, 0x00010001u));
+    c.two = 0x00020002u; c.minus2 = 0xFFFEFFFEu; c.uf_bias = 0x78027802u; c.bit15 = 0x80008000u;
+    asm volatile("" : "+v"(c.kc), "+v"(c.rof), "+v"(c.nrof), "+v"(c.mask), "+v"(c.maskp), "+v"(c.absmask), "+v"(c.of_bias), "+v"(c.two), "+v"(c.minus2), "+v"(c.uf_bias), "+v"(c.bit15));
+    fc.kc = c.kc; fc.rof = c.rof; fc.nrof = c.nrof; fc.mask = c.mask; fc.maskp = c.maskp;
+
+    h2 acc[TM][NJ], top[TM][NJ];
+    uint32_t of2[TM][TN], uf2[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) { acc[i][j] = as_h2(0u); top[i][j] = as_h2(0u); }
+#pragma unroll
+        for (int j = 0; j < TN; ++j) { of2[i][j] = 0u; uf2[i][j] = 0u; }
+    }
+
+    uint4 ra[1], rb[1];
+    const int ntiles = (p.K + HBK - 1) / HBK;
+    __shared__ uint32_t half_norm[2][4];
+    // non-zero codes: 64 bits per row of A and per column of B and stage, 16 per piece
+    __shared__ __attribute__((aligned(8))) uint16_t nza[2][BM][4], nzb[2][BN][4];
+    const bool dyn = half_follows_data(p);
+    ConvLane cl;
+    if (AMODE == 2) cl = conv_lane<BM, HBK>(p.A, p, m0, tid);
+    auto fetch = [&](int k0) {
+        if (AMODE == 2) fetch_tile_conv_lane<BM, HBK>(cl, p, k0, ra);
+        else            fetch_tile<BM, HBK>(p.A, p.M, p.K, m0, k0, p.ld_align, tid, ra);
+        fetch_tile<BN, HBK>(p.B, p.N, p.K, n0, k0, p.ld_align, tidb, rb);
+    };
+    auto stage = [&](int st) {
+        half_stage<BM, BN>(p, smem + st * T::STAGE, smem + st * T::STAGE + T::A_WORDS, ra[0], rb[0], tid, tidb, dyn, half_norm[st]);
+        if (UF) {
+            if (tid < Stage<BM, HBK>::kChunks) nza[st][tid % BM][tid / BM] = (uint16_t)nonzero_codes(ra[0]);
+            if (tidb >= 0 && tidb < Stage<BN, HBK>::kChunks) nzb[st][tidb % BN][tidb / BN] = (uint16_t)nonzero_codes(rb[0]);
+        }
+    };
+    fetch(0);
+    stage(0);
+    __syncthreads();
+
+    const HalfBound bound(p);
+    const int words = (p.K + 31) >> 5;
+    int safe_tiles = 0;
+    for (int t = 0; t < ntiles; ++t) {
+        const uint32_t* As0 = smem + (t & 1) * T::STAGE;
+        const uint32_t* Bs0 = As0 + T::A_WORDS;
+        const bool more = (t + 1) < ntiles;
+        if (more) fetch((t + 1) * HBK);
+        const int parts = p.K - t * HBK > 32 ? 2 : 1;
+        for (int part = 0; part < parts; ++part) {
+            const uint32_t* As = As0 + part * 16 * T::BMP;
+            const uint32_t* Bs = Bs0 + part * 32 * T::BNP;
+            const int w = 2 * t + part;                        // plane word of this part's steps
+            if (safe_tiles == 0) {
+                uint32_t mx = 0u;
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j)
+                        mx = pk_max_u16(mx, as_u32(ORDER == LBA_ORDER_CHUNK16 ? top[i][j] : acc[i][j]) & 0x7FFF7FFFu);
+                safe_tiles = bound.safe(max_half(mx), dyn ? half_norm[t & 1] : nullptr);
+            }
+            uint32_t of[TM][TN], uf[TM][TN];
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) { of[i][j] = 0u; uf[i][j] = 0u; }
+            const int pos = 2 * (w & 15);
+            const bool quiet = safe_tiles > 0;
+            if (quiet) {
+                --safe_tiles;
+                if (UF) half_bwd_tile<PM, ORDER, UF, true, TM, TN, T::BMP, T::BNP>(acc, top, of, uf, of2, uf2, pos, As, Bs, tx, ty, c);
+                else    half_tile<PM, ORDER, false, TM, TN, T::BMP, T::BNP>(acc, top, As, Bs, tx, ty, fc);
+            } else {
+                half_bwd_tile<PM, ORDER, UF, false, TM, TN, T::BMP, T::BNP>(acc, top, of, uf, of2, uf2, pos, As, Bs, tx, ty, c);
+                const int valid = p.K - 32 * w;                // a saturated sum stays at R_OF beyond K
+                if (valid < 32) {
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j) of[i][j] &= (1u << valid) - 1u;
+                }
+                if (ORDER == LBA_ORDER_SEQ && p.map_dx) mark_bricks_lsb<TM, TN>(of, m0, n0, w, tx, ty, p);
+            }
+            if (p.of_mask) store_half_words<TM, TN>(p.of_mask, w, of, m0, n0, tx, ty, p);
+            if (UF && p.uf_mask) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i) {
+                    const uint32_t na = *reinterpret_cast<const uint32_t*>(&nza[t & 1][ty * TM + i][2 * part]);
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) uf[i][j] &= na & *reinterpret_cast<const uint32_t*>(&nzb[t & 1][tx * TN + j][2 * part]);
+                }
+                store_half_words<TM, TN>(p.uf_mask, w, uf, m0, n0, tx, ty, p);
+            }
+            if (ORDER == LBA_ORDER_CHUNK16 && ((w & 15) == 15 || w == words - 1)) {
+                // two chunks per word: a second-level word is complete after 16 of them
+                const int left = ((p.K + 15) >> 4) - 32 * (w >> 4);
+                const uint32_t vmask = left >= 32 ? 0xFFFFFFFFu : (1u << left) - 1u;
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) { of2[i][j] &= vmask; uf2[i][j] &= vmask; }
+                if (p.of_mask2) store_half_words<TM, TN>(p.of_mask2, w >> 4, of2, m0, n0, tx, ty, p);
+                if (UF && p.uf_mask2) store_half_words<TM, TN>(p.uf_mask2, w >> 4, uf2, m0, n0, tx, ty, p);
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) { of2[i][j] = 0u; uf2[i][j] = 0u; }
+            }
+        }
+        if (more) stage((t + 1) & 1);
+        __syncthreads();
+    }
+    if (!p.C) return;
+    half_flush_all();                                          // a denormal sum reads as zero
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int m = m0 + ty * TM + i, n = n0 + tx * TN;
+        if (m >= p.M) continue;
+        float v[TN];
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const uint32_t w = as_u32(ORDER == LBA_ORDER_CHUNK16 ? top[i][j / 2] : acc[i][j / 2]);
+            float s;
+            asm volatile("v_cvt_f32_f16 %0, %1" : "=v"(s) : "v"(j & 1 ? w >> 16 : w));
+            v[j] = __builtin_ldexpf(s, p.out_exp - 112) + 0.0f;
+        }
+        float* dst = p.C + (int64_t)m * p.N + n;
+        if (TN == 4 && p.c_vec && n + 3 < p.N) {
+            *reinterpret_cast<f32x4_any*>(dst) = f32x4_any{v[0], v[1], v[TN - 2], v[TN - 1]};
+        } else if (TN == 2 && p.c_vec && n + 1 < p.N) {
+            *reinterpret_cast<f32x2_any*>(dst) = f32x2_any{v[0], v[1]};
+        } else {
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                if (n + j < p.N) dst[j] = v[j];
+        }
+    }
+}
+
+// The grids of lba_fast_bwd_kernel and lba_fast_bwd_mixed_kernel.  AMODE 0: a row-major matrix of any code format with E <= 4,
+// 2: im2col rows of an NHWC tensor.
+template <int PM, int ORDER, bool UF, int AMODE>
+__global__ void __launch_bounds__(256, ORDER == LBA_ORDER_CHUNK16 && UF ? 2 : UF || ORDER == LBA_ORDER_CHUNK16 ? 3 : 4) lba_half_bwd_kernel(const KParams p) {
+    __shared__ __attribute__((aligned(16))) uint32_t smem[2 * HalfTile<4, 4, 16>::STAGE];
+    half_bwd_body<4, 4, PM, ORDER, UF, AMODE>(p, smem, blockIdx.x * 64, blockIdx.y * 64);
+}
+
+template <int PM, bool UF, int AMODE>
+__global__ void __launch_bounds__(256, UF ? 3 : 4) lba_half_bwd_mixed_kernel(const KParams p) {
+    __shared__ __attribute__((aligned(16))) uint32_t smem[2 * HalfTile<4, 4, 16>::STAGE];
+    const int b = blockIdx.x;
+    if (b < p.mix_main) {                                      // uniform
+        const int by = b / p.mix_gx_main, bx = b - by * p.mix_gx_main;
+        half_bwd_body<4, 4, PM, LBA_ORDER_SEQ, UF, AMODE>(p, smem, bx * 64, by * 64);
+    } else {
+        const int t = b - p.mix_main;
+        const int by = t / p.mix_gx_tail, bx = t - by * p.mix_gx_tail;
+        half_bwd_body<2, 2, PM, LBA_ORDER_SEQ, UF, AMODE>(p, smem, p.mix_m_main + bx * 32, by * 32);
+    }
+}
+
+}  // namespace lba
+#endif

@@ -27,7 +27,7 @@ struct KParams {
     int32_t batch;           // grid z; member z reads A + z*stride_a, B + z*stride_b, writes C + z*stride_c
     int64_t stride_a, stride_b, stride_c;   // in elements (bytes for A and B, floats for C)
     int32_t ld_align;        // 16: every row start of A and B is 16-byte aligned; 1: any alignment
-    int32_t c_vec;           // 1 if rows of C (and of the planes) can take 16-byte stores
+    int32_t c_vec;           // 1 if C and the planes start on a 4-byte boundary (stores of several elements)
     // operand decode: value(code) * 2^exp_a / 2^exp_b, folded into the lookup tables
     int32_t exp_a, exp_b;
     int32_t out_exp;         // C = S * 2^out_exp

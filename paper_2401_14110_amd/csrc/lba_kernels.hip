@@ -18,6 +18,7 @@ __global__ void lba_fill_zero_kernel(float* C, int64_t n) {
 static hipError_t launch_plan(const Plan& pl, hipStream_t st) {
     if (pl.kernel == KERNEL_FAST && pl.kpar > 0) return launch_kpar(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.events == 2) return launch_fast_diff(pl, st);
+    if (pl.kernel == KERNEL_FAST && pl.events && pl.kp.h_on) return launch_half_bwd(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.events) return launch_fast_bwd(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.rne_odd) return launch_fast_odd(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.amode == 2) return launch_fast_conv(pl, st);
@@ -49,6 +50,10 @@ static void plan_kernel_name(const Plan& pl, bool uf, char* buf, size_t n) {
         snprintf(buf, n, "lba_kpar_kernel<%d, 4, %d, %d, %d>", pl.kpar == 3 ? 2 : 4, pl.kpar == 1 ? 1 : 4, pm, rnd);
     } else if (pl.events == 2) {
         snprintf(buf, n, pl.mix_tail > 0 ? "lba_fast_diff_mixed_kernel<%d, %d, %d>" : "lba_fast_diff_kernel<%d, %d, %d>", pm, pl.round, ord);
+    } else if (pl.events && pl.kp.h_on) {
+        const int am = pl.amode == 2 ? 2 : 0;
+        if (pl.mix_tail > 0) snprintf(buf, n, "lba_half_bwd_mixed_kernel<%d, %s, %d>", pm, uf ? "true" : "false", am);
+        else                 snprintf(buf, n, "lba_half_bwd_kernel<%d, %d, %s, %d>", pm, ord, uf ? "true" : "false", am);
     } else if (pl.events) {
         if (pl.amode == 2 && pl.mix_tail > 0) snprintf(buf, n, "lba_fast_bwd_conv_mixed_kernel<%d, 0, %s>", pm, b);
         else if (pl.amode == 2)   snprintf(buf, n, "lba_fast_bwd_kernel<%d, 0, 0, %s, 2>", pm, b);
@@ -123,11 +128,8 @@ static int run(const uint8_t* A, const uint8_t* B, float* C, uint32_t* of_mask, 
     }
     kp.ld_align = (la < lb ? la : lb);
     if ((stride_a % 16) != 0 || (stride_b % 16) != 0) kp.ld_align = 1;
-    const bool c_ok = (!C || ((uintptr_t)C % 16) == 0) && (stride_c % 4) == 0;
-    const bool o_ok = !of_mask || ((uintptr_t)of_mask % 16) == 0;
-    const bool u_ok = !uf_mask || ((uintptr_t)uf_mask % 16) == 0;
-    const bool l2_ok = ((uintptr_t)of_mask2 % 16) == 0 && ((uintptr_t)uf_mask2 % 16) == 0;
-    kp.c_vec = ((N % 4) == 0 && c_ok && o_ok && u_ok && l2_ok) ? 1 : 0;
+    // whole 4-byte elements at every address: outputs leave in groups of up to four, at any alignment of the rows
+    kp.c_vec = (((uintptr_t)C | (uintptr_t)of_mask | (uintptr_t)uf_mask | (uintptr_t)of_mask2 | (uintptr_t)uf_mask2) % 4) == 0 ? 1 : 0;
     return launch_plan(pl, st) == hipSuccess ? LBA_OK : LBA_ERR_LAUNCH;
 }
 

@@ -196,6 +196,12 @@ static bool half_carrier(const lba_qfmt& qp, const lba_qfmt& qa, const InSpec& i
     return true;
 }
 
+// With an underflow plane also: a sum below R_UF is a non-zero denormal number (lba_half_bwd.h): products of at most 10 bits,
+// and a product alone, at least 2^-14 * kc, not below 2^-24.
+static bool half_underflow_ok(const lba_qfmt& qp, const InSpec& in, int bpe, int bae) {
+    return std::min(in.sig_bits, qp.man_bits + 1) <= 10 && bae - bpe >= -10;
+}
+
 #ifndef LBA_FAST_BK
 #define LBA_FAST_BK 32
 #endif
@@ -423,10 +429,12 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
             p.valu_per_mac_x100 = 1300 + (p.prod_mode == PM_FLUSH_CLAMP ? 200 : 0) + (qa.round == LBA_ROUND_RNE ? 400 : 0);
         // packed FP16 carriers (forward call, floor, underflow kept): v_pk_mul, [v_and,] v_pk_fma at half rate for two
         // chains, one v_and for both; never priced below the two slots of the FP32 multiply-add and mask
-        const bool half = !events && !rne_odd && qa.round == LBA_ROUND_FLOOR && !nouf_a &&
+        // (the recompute call is priced at the FP32 kernel's step on either carrier)
+        const bool half = events != 2 && !rne_odd && qa.round == LBA_ROUND_FLOOR && !nouf_a &&
                           (p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH || p.prod_mode == PM_TRUNC) &&
+                          (!p.events || p.of_only || half_underflow_ok(qp, in, bpe, bae)) &&
                           half_carrier(qp, qa, in, p.prod_mode, bpe, bae, &kp);
-        if (half) p.valu_per_mac_x100 = p.prod_mode == PM_IDENT ? 200 : (p.prod_mode == PM_FLUSH ? 250 : 300);
+        if (half && !events) p.valu_per_mac_x100 = p.prod_mode == PM_IDENT ? 200 : (p.prod_mode == PM_FLUSH ? 250 : 300);
         if (order == LBA_ORDER_CHUNK16)                          // add, and [, bfe, add3], zero per 16 steps
             p.valu_per_mac_x100 += (events == 2 ? 1300 : events ? 900 : (qa.round == LBA_ROUND_RNE ? 700 : 300)) / 16;
     } else {

@@ -78,3 +78,54 @@ def test_operand_formats(ref, fa, fb):
             got = product(A, B, qp, qa, order, fa, fb)
             want = ref.gemm_in(A, B, ref.InFmt(*fa), ref.InFmt(*fb), ref.QFmt(*qp), ref.QFmt(*qa), order=order)
             assert np.array_equal(bits(got), bits(want)), (M, N, K, qp, qa, order)
+
+
+def planes(A, B, qp, qa, order):
+    dA, dB = torch.from_numpy(A).to(DEV), torch.from_numpy(B).to(DEV)
+    got = lb.gemm_bwd_chunked(dA, dB, qp, qa) if order else lb.gemm_bwd(dA, dB, qp, qa)
+    torch.cuda.synchronize()
+    return [t.cpu().numpy() for t in got]
+
+
+@pytest.mark.parametrize("ba,bp", [(7, 17), (7, 18), (7, 15), (-9, -1), (10, 12), (4, 11), (-2, -17), (3, 1)])
+def test_event_planes_on_both_sides_of_the_underflow_rule(ref, ba, bp):
+    # kc = 2^-10 (a product alone is FP16's smallest denormal number) and 2^-11 (beyond: FP32), accumulators of 2 to 11 bits,
+    # operands full of subnormal codes and zeros, cancelling pairs next to R_UF
+    rng = np.random.default_rng([ba + 100, bp + 100])
+    for M, N, K in [(33, 18, 70), (70, 66, 97)]:
+        A, B = codes(rng, (M, K), 0, 15), codes(rng, (N, K), 0, 15)
+        A[:, 1::4] = A[:, 0::4][:, :A[:, 1::4].shape[1]] ^ 0x80      # x w, then almost -x w
+        B[:, 1::4] = np.clip(B[:, 0::4][:, :B[:, 1::4].shape[1]].astype(np.int32) + rng.integers(-1, 2, B[:, 1::4].shape), 0, 255).astype(np.uint8)
+        for qam, order in itertools.product((1, 7, 10), (0, 1)):
+            qp, qa = (6, 7, bp, 0), (4, qam, ba, 0)
+            got = planes(A, B, qp, qa, order)
+            want = ref.gemm_bwd(A, B, ref.QFmt(*qp), ref.QFmt(*qa), order=order, level2=True) if order else \
+                ref.gemm_bwd(A, B, ref.QFmt(*qp), ref.QFmt(*qa))
+            assert np.array_equal(bits(got[0]), bits(want[0])), (M, N, K, qp, qa, order)
+            for i in range(1, len(want)):
+                assert np.array_equal(got[i].view(np.uint32), want[i]), (M, N, K, qp, qa, order, "plane %d" % i)
+
+
+@pytest.mark.parametrize("K", [1, 15, 16, 17, 32, 33, 63, 65, 96, 129, 512, 530])
+def test_event_planes_of_ragged_shapes(ref, K):
+    # words at every remainder of k and of the second level, rows of the planes at every alignment, loud and quiet tiles, each
+    # plane alone; saturated sums stay at R_OF beyond K and set no bit there
+    rng = np.random.default_rng(K)
+    qp, qa = (5, 7, -1, 0), (4, 7, -9, 0)
+    for (M, N), (lo, hi) in itertools.product([(33, 17), (65, 66), (20, 131)], [(0, 9), (3, 15)]):
+        A, B = codes(rng, (M, K), lo, hi), codes(rng, (N, K), lo, hi)
+        name = lb.lba_plan_kernel_name(M, N, K, qp, qa, 0, 1)
+        assert name.startswith("lba_half_bwd"), name
+        for order in (0, 1):
+            want = ref.gemm_bwd(A, B, ref.QFmt(*qp), ref.QFmt(*qa), order=order, level2=True) if order else \
+                ref.gemm_bwd(A, B, ref.QFmt(*qp), ref.QFmt(*qa))
+            got = planes(A, B, qp, qa, order)
+            for i in range(len(want)):
+                assert np.array_equal(bits(got[i]), bits(want[i])), (M, N, K, lo, order, i)
+        dA, dB = torch.from_numpy(A).to(DEV), torch.from_numpy(B).to(DEV)
+        _, of, _ = lb.gemm_bwd(dA, dB, qp, qa, want_c=False, want_uf=False)
+        uf = torch.full((-(-K // 32), M, N), -1, dtype=torch.int32, device=DEV)
+        assert lb.lba_gemm_bwd(dA.data_ptr(), dB.data_ptr(), None, None, uf.data_ptr(), M, N, K, qp, qa) == lb.OK
+        torch.cuda.synchronize()
+        w = ref.gemm_bwd(A, B, ref.QFmt(*qp), ref.QFmt(*qa))
+        assert np.array_equal(bits(of.cpu().numpy()), bits(w[1])) and np.array_equal(bits(uf.cpu().numpy()), bits(w[2]))
