@@ -600,8 +600,10 @@ def conv_kernel_name(name):
             return conv + name[len(plain):]
     if (name.startswith("lba_fast_kernel<") or name.startswith("lba_fast_bwd_kernel<")) and name.endswith(", 0>"):
         return name[:-4] + ", 2>"
-    if name.startswith("lba_half_bwd") and name.endswith(", 0>"):
+    if name.startswith("lba_half_") and name.endswith(", 0>"):
         return name[:-4] + ", 2>"
+    if name.startswith("lba_half_") and not name.startswith("lba_half_bwd") and name.endswith(", 3>"):
+        return name[:-4] + ", 4>"                  # K % 16 != 0: rows of any alignment, im2col rows of any channel count
     return name
 
 

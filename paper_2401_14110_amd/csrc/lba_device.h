@@ -57,6 +57,7 @@ typedef float f32x2_any __attribute__((ext_vector_type(2), aligned(4)));
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(4)));
 typedef uint32_t u32x4_bytes __attribute__((ext_vector_type(4), aligned(1)));
+typedef uint32_t u32x2_bytes __attribute__((ext_vector_type(2), aligned(1)));
 
 __device__ __forceinline__ float med3(float x, float lo, float hi) { return __builtin_amdgcn_fmed3f(x, lo, hi); }
 
@@ -293,8 +294,8 @@ struct Stage {
 
 // Fetch this lane's 16-byte pieces of one operand tile into registers (zero outside the matrix).
 // ld_align == 16: every piece is 16-byte aligned and wholly inside its row (K % 16 == 0).
-// Otherwise one unaligned 16-byte load, and for the pieces that would read beyond the matrix (the end of its last row) five
-// 4-byte-aligned loads that cover the piece at any byte offset and are funnel-shifted into place.  Each load address is clamped to the aligned word holding the last valid byte, so
+// Otherwise: five 4-byte-aligned loads cover the piece at any byte offset and are funnel-shifted
+// into place.  (One unaligned 16-byte load instead, as lba_piece.h does, took 1 % off every aligned shape of these kernels.)  Each load address is clamped to the aligned word holding the last valid byte, so
 // every word read contains at least one byte of the matrix (it cannot cross into another page).
 template <int ROWS, int BK>
 __device__ __forceinline__ void fetch_tile(const uint8_t* __restrict__ G, int rows, int K, int r0, int k0,
@@ -311,17 +312,6 @@ __device__ __forceinline__ void fetch_tile(const uint8_t* __restrict__ G, int ro
                 const uint8_t* src = G + (int64_t)r * K + k;
                 if (ld_align == 16) {
                     v = *reinterpret_cast<const uint4*>(src);
-                } else if (src + 16 <= G + (int64_t)rows * K) {             // 16 bytes of the matrix, the next row's among them
-                    const u32x4_bytes x = *reinterpret_cast<const u32x4_bytes*>(src);
-                    uint32_t w[4] = {x.x, x.y, x.z, x.w};
-                    if (k + 16 > K) {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            const int nb = K - k - 4 * j;                   // valid bytes in this word
-                            w[j] &= nb >= 4 ? 0xFFFFFFFFu : (nb <= 0 ? 0u : ((1u << (8 * nb)) - 1u));
-                        }
-                    }
-                    v = make_uint4(w[0], w[1], w[2], w[3]);
                 } else {
                     const int nvalid = (K - k) < 16 ? (K - k) : 16;         // bytes of this piece inside the row
                     const uintptr_t a0 = reinterpret_cast<uintptr_t>(src);
@@ -917,25 +907,20 @@ __device__ __forceinline__ void store_event_words(uint32_t* of_plane, uint32_t* 
 template <int TM, int TN, int LX, int PM, int ORDER, int AMODE>
 __device__ __forceinline__ void half_body(const KParams& p, uint32_t* __restrict__ smem, int m0, int n0);
 
-// One workgroup's tile on the carrier the planner chose (p.h_on, uniform): both carriers take the same grids, so a
-// kernel holds both.  The 32 x 16 tile (2 x 1 outputs per lane) has its pairs along n on packed carriers: 1 x 2.
-template <int TM, int TN, int BK, int PM, int RND, int ORDER, int AMODE>
-__device__ __forceinline__ void forward_body(const KParams& p, float* smem, int m0, int n0) {
-    if constexpr (RND == LBA_ROUND_FLOOR && (PM == PM_IDENT || PM == PM_FLUSH || PM == PM_TRUNC)) {
+// Plain grids of other operand formats (AMODE 1) host both carriers and the planner's choice is uniform (p.h_on).  Every other
+// call on packed carriers has kernels of its own (lba_half.hip, lba_half_conv.hip): an FP32 body beside the other one ran
+// 1.5 % slower.
+template <int TM, int TN, int BK, int PM, int RND, int ORDER, int AMODE = 0>
+__global__ void __launch_bounds__(256, LBA_FAST_MIN_WAVES) lba_fast_kernel(const KParams p) {
+    __shared__ __attribute__((aligned(16))) float smem[2 * fast_stage_depth(TM, TN, BK) * 16 * (TM + TN)];
+    const int m0 = blockIdx.x * 16 * TM, n0 = blockIdx.y * 16 * TN;
+    if constexpr (AMODE == 1 && RND == LBA_ROUND_FLOOR && (PM == PM_IDENT || PM == PM_FLUSH || PM == PM_TRUNC)) {
         if (p.h_on) {
-            uint32_t* words = reinterpret_cast<uint32_t*>(smem);
-            if constexpr (TN == 1) half_body<1, 2, 8, PM, ORDER, AMODE>(p, words, m0, n0);
-            else                   half_body<TM, TN, 16, PM, ORDER, AMODE>(p, words, m0, n0);
+            half_body<TM, TN, 16, PM, ORDER, AMODE>(p, reinterpret_cast<uint32_t*>(smem), m0, n0);
             return;
         }
     }
     fast_body<TM, TN, BK, PM, RND, ORDER, AMODE>(p, smem, m0, n0);
-}
-
-template <int TM, int TN, int BK, int PM, int RND, int ORDER, int AMODE = 0>
-__global__ void __launch_bounds__(256, LBA_FAST_MIN_WAVES) lba_fast_kernel(const KParams p) {
-    __shared__ __attribute__((aligned(16))) float smem[2 * fast_stage_depth(TM, TN, BK) * 16 * (TM + TN)];
-    forward_body<TM, TN, BK, PM, RND, ORDER, AMODE>(p, smem, blockIdx.x * 16 * TM, blockIdx.y * 16 * TN);
 }
 
 // Mixed grid for launches that would leave the last round of 64 x 64 workgroups half empty, or a CU with an odd
@@ -953,16 +938,16 @@ template <int BK, int PM, int RND, int ORDER, int AMODE>
 __device__ __forceinline__ void fast_mixed_body(const KParams& p, float* smem, const int b) {
     if (b < p.mix_main) {                                      // uniform
         const int by = b / p.mix_gx_main, bx = b - by * p.mix_gx_main;
-        forward_body<4, 4, BK, PM, RND, ORDER, AMODE>(p, smem, bx * 64, by * 64);
+        fast_body<4, 4, BK, PM, RND, ORDER, AMODE>(p, smem, bx * 64, by * 64);
     } else if (b < p.mix_main + p.mix_half) {
         const int t = b - p.mix_main;
         const int by = t / p.mix_gx_half, bx = t - by * p.mix_gx_half;
-        forward_body<3, 4, BK, PM, RND, ORDER, AMODE>(p, smem, p.mix_m_main + bx * 48, by * 64);
+        fast_body<3, 4, BK, PM, RND, ORDER, AMODE>(p, smem, p.mix_m_main + bx * 48, by * 64);
     } else {
         const int t = b - p.mix_main - p.mix_half;
         const int by = t / p.mix_gx_tail, bx = t - by * p.mix_gx_tail;
-        if (p.mix_tail16) forward_body<2, 1, BK, PM, RND, ORDER, AMODE>(p, smem, p.mix_m_half + bx * 32, by * 16);   // uniform
-        else              forward_body<2, 2, BK, PM, RND, ORDER, AMODE>(p, smem, p.mix_m_half + bx * 32, by * 32);
+        if (p.mix_tail16) fast_body<2, 1, BK, PM, RND, ORDER, AMODE>(p, smem, p.mix_m_half + bx * 32, by * 16);   // uniform
+        else              fast_body<2, 2, BK, PM, RND, ORDER, AMODE>(p, smem, p.mix_m_half + bx * 32, by * 32);
     }
 }
 

@@ -18,12 +18,14 @@
 // one wave).  It also reads a quarter of the LDS bytes per step, and 64 steps take the LDS of 32: with stages of 32 steps
 // every shape measured 3-8 % slower, with 5 to 8 waves per SIMD instead of 4 none faster, and an 8 x 4 lane block slower
 // on every layer of ResNet-50.  Measured against the FP32 tile on the same grids: 8192 x 4096 x 1152 1819 -> 1573 us
-// (6.4 cycles per chain and step), the ResNet-50 sweep 14.06 -> 11.88 ms, the 64 x 1000 x 2048 classifier 61 -> 47 us.
+// (6.4 cycles per chain and step), the ResNet-50 sweep 14.05 -> 11.97 ms, its 7 x 7 x 3 first convolution at batch 37 337 ->
+// 255 us, the 64 x 1000 x 2048 classifier 61 -> 45 us, 3136 x 512 x 4608 of M4E3 codes 593 -> 522 us.
 
 #ifndef LBA_HALF_H_
 #define LBA_HALF_H_
 
 #include "lba_device.h"
+#include "lba_piece.h"
 
 namespace lba {
 
@@ -121,21 +123,19 @@ __device__ __forceinline__ void store_half_b(uint32_t* __restrict__ dst, int tid
     }
 }
 
-// One step of all chains of the lane.  HI: the step is the odd k of its pair of steps.
-template <int PM, bool CLAMP, bool HI, int TM, int TN>
-__device__ __forceinline__ void half_step(h2 (&acc)[TM][TN / 2], const uint32_t (&a)[TM], const uint32_t (&b)[TN / 2], const HalfConst& c) {
-    h2 q[TM][TN / 2];
+// A step's products (PM_IDENT: none).  HI: the step is the odd k of its pair of steps.
+template <int PM, bool HI, int TM, int TN>
+__device__ __forceinline__ void half_products(h2 (&q)[TM][TN / 2], const uint32_t (&a)[TM], const uint32_t (&b)[TN / 2], const HalfConst& c) {
+    if (PM != PM_IDENT) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        const h2 w = as_h2(a[i]);
-        const h2 ab = HI ? __builtin_shufflevector(w, w, 1, 1) : __builtin_shufflevector(w, w, 0, 0);
+        for (int i = 0; i < TM; ++i) {
+            const h2 w = as_h2(a[i]);
+            const h2 ab = HI ? __builtin_shufflevector(w, w, 1, 1) : __builtin_shufflevector(w, w, 0, 0);
 #pragma unroll
-        for (int j = 0; j < TN / 2; ++j) {
-            if (PM == PM_IDENT) acc[i][j] = __builtin_elementwise_fma(ab, as_h2(b[j]), acc[i][j]);
-            else                q[i][j] = ab * as_h2(b[j]);    // exact; flushed below Q_prod's R_UF
+            for (int j = 0; j < TN / 2; ++j) q[i][j] = ab * as_h2(b[j]);   // exact; flushed below Q_prod's R_UF
         }
+        __builtin_amdgcn_sched_barrier(0);
     }
-    __builtin_amdgcn_sched_barrier(0);
     if (PM == PM_TRUNC) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -143,13 +143,26 @@ __device__ __forceinline__ void half_step(h2 (&acc)[TM][TN / 2], const uint32_t 
             for (int j = 0; j < TN / 2; ++j) q[i][j] = as_h2(as_u32(q[i][j]) & c.maskp);
         __builtin_amdgcn_sched_barrier(0);
     }
-    if (PM != PM_IDENT) {
+}
+
+// The sums of a step: one rounding of the exact sum toward zero.
+template <int PM, bool HI, int TM, int TN>
+__device__ __forceinline__ void half_sums(h2 (&acc)[TM][TN / 2], const h2 (&q)[TM][TN / 2], const uint32_t (&a)[TM], const uint32_t (&b)[TN / 2],
+                                          const HalfConst& c) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i) {
+        const h2 w = as_h2(a[i]);
+        const h2 ab = HI ? __builtin_shufflevector(w, w, 1, 1) : __builtin_shufflevector(w, w, 0, 0);
 #pragma unroll
-            for (int j = 0; j < TN / 2; ++j) acc[i][j] = __builtin_elementwise_fma(q[i][j], c.kc, acc[i][j]);
-        __builtin_amdgcn_sched_barrier(0);
+        for (int j = 0; j < TN / 2; ++j)
+            acc[i][j] = PM == PM_IDENT ? __builtin_elementwise_fma(ab, as_h2(b[j]), acc[i][j]) : __builtin_elementwise_fma(q[i][j], c.kc, acc[i][j]);
     }
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// ... and their rounding to M + 1 bits
+template <bool CLAMP, int TM, int TN>
+__device__ __forceinline__ void half_round(h2 (&acc)[TM][TN / 2], const HalfConst& c) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -210,27 +223,39 @@ __device__ __forceinline__ void read_half_b(const uint32_t* Bs, int k, int tx, u
     }
 }
 
-// 32 steps (16 pairs) from LDS, fully unrolled; operands are read AHEAD pairs of steps before their use.
+// 32 steps (16 pairs) from LDS, fully unrolled; operands are read AHEAD pairs of steps before their use.  A lane block of one
+// or two pairs of chains takes the next step's products between a step's sums and their rounding: nothing else separates the
+// dependent instructions there (the compiler puts a wait between a packed instruction and one that reads it at once).
 template <int PM, int ORDER, bool CLAMP, int TM, int TN, int BMP, int BNP>
 __device__ __forceinline__ void half_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[TM][TN / 2], const uint32_t* As, const uint32_t* Bs,
                                           int tx, int ty, const HalfConst& c) {
-    constexpr int AHEAD = TM * TN >= 12 ? 1 : (TM * TN >= 8 ? 2 : 4), SLOTS = AHEAD + 1;
+    constexpr int AHEAD = TM * TN >= 12 ? 1 : (TM * TN >= 8 ? 2 : 4), SLOTS = AHEAD + 2;
+    constexpr bool EARLY = TM * TN <= 4;
     uint32_t a[SLOTS][TM], b0[SLOTS][TN / 2], b1[SLOTS][TN / 2];
+    h2 q[2][TM][TN / 2];
 #pragma unroll
     for (int s = 0; s < AHEAD; ++s) {
         read_half_a<TM, BMP>(As, s, ty, a[s]);
         read_half_b<TN, BNP>(Bs, 2 * s, tx, b0[s]);
         read_half_b<TN, BNP>(Bs, 2 * s + 1, tx, b1[s]);
     }
+    if (EARLY) half_products<PM, false, TM, TN>(q[0], a[0], b0[0], c);
 #pragma unroll
     for (int s = 0; s < 16; ++s) {
+        const int x = s % SLOTS;
         if (s + AHEAD < 16) {
             read_half_a<TM, BMP>(As, s + AHEAD, ty, a[(s + AHEAD) % SLOTS]);
             read_half_b<TN, BNP>(Bs, 2 * (s + AHEAD), tx, b0[(s + AHEAD) % SLOTS]);
             read_half_b<TN, BNP>(Bs, 2 * (s + AHEAD) + 1, tx, b1[(s + AHEAD) % SLOTS]);
         }
-        half_step<PM, CLAMP, false, TM, TN>(acc, a[s % SLOTS], b0[s % SLOTS], c);
-        half_step<PM, CLAMP, true, TM, TN>(acc, a[s % SLOTS], b1[s % SLOTS], c);
+        if (!EARLY) half_products<PM, false, TM, TN>(q[0], a[x], b0[x], c);
+        half_sums<PM, false, TM, TN>(acc, q[0], a[x], b0[x], c);
+        if (EARLY) half_products<PM, true, TM, TN>(q[1], a[x], b1[x], c);
+        half_round<CLAMP, TM, TN>(acc, c);
+        if (!EARLY) half_products<PM, true, TM, TN>(q[1], a[x], b1[x], c);
+        half_sums<PM, true, TM, TN>(acc, q[1], a[x], b1[x], c);
+        if (EARLY && s < 15) half_products<PM, false, TM, TN>(q[0], a[(s + 1) % SLOTS], b0[(s + 1) % SLOTS], c);
+        half_round<CLAMP, TM, TN>(acc, c);
         if (ORDER == LBA_ORDER_CHUNK16 && ((s + 1) & 7) == 0) half_level2<CLAMP, TM, TN>(top, acc, c);
     }
 }
@@ -277,8 +302,12 @@ struct HalfBound {
     }
 };
 
+// k-tiles whose pieces are in flight at a time: one for the large lane blocks (two measured the same); four for the small ones,
+// whose tile takes less time than a load (64 x 1000 x 2048: 47 -> 45 us).
+__host__ __device__ constexpr int half_depth(int TM, int TN) { return TM * TN <= 4 ? 4 : 1; }
+
 // The work of one workgroup: the BM x BN tile of C at (m0, n0).  smem: two stages.  Structure, clamp-free tiles and their
-// bounds as in fast_body; AMODE as there (1 and 0 differ in the fetch of im2col rows only: every code format decodes alike).
+// bounds as in fast_body; AMODE as there, and 3, 4 below (every code format decodes alike).
 template <int TM, int TN, int LX, int PM, int ORDER, int AMODE>
 __device__ __forceinline__ void half_body(const KParams& p, uint32_t* __restrict__ smem, int m0, int n0) {
     using T = HalfTile<TM, TN, LX>;
@@ -306,52 +335,89 @@ __device__ __forceinline__ void half_body(const KParams& p, uint32_t* __restrict
 #pragma unroll
         for (int j = 0; j < TN / 2; ++j) { acc[i][j] = as_h2(0u); top[i][j] = as_h2(0u); }
 
-    uint4 ra[1], rb[1];
     const int ntiles = (p.K + HBK - 1) / HBK;
     __shared__ uint32_t half_norm[2][4];                       // per stage and wave: largest squared norm of a piece of A (low half), of B
     const bool dyn = half_follows_data(p);
-    ConvLane cl;
-    if (AMODE == 2) cl = conv_lane<BM, HBK>(pA, p, m0, tid);
-    auto fetch = [&](int k0) {
-        if (AMODE == 2)      fetch_tile_conv_lane<BM, HBK>(cl, p, k0, ra);
-        else if (AMODE == 1) fetch_tile_a<BM, HBK>(pA, p, m0, k0, tid, ra);
-        else                 fetch_tile<BM, HBK>(pA, p.M, p.K, m0, k0, p.ld_align, tid, ra);
-        fetch_tile<BN, HBK>(pB, p.N, p.K, n0, k0, p.ld_align, tidb, rb);
+    // How the pieces come.  Aligned rows and im2col rows of whole 16-channel taps (AMODE 0, 2): one aligned load, zeroed at once
+    // outside the operand.  Any other rows (AMODE 3, 4) and the small lane blocks: lba_piece.h, uncorrected loads that stay in
+    // flight (C = 3 under a 7 x 7 filter: two loads a piece instead of sixteen, 279 -> 255 us).  Either kind of code in the other's kernel, behind a uniform branch, cost the aligned shapes 1 to 4 %.
+    constexpr bool SMALL = TM * TN <= 4, PIECES = SMALL || AMODE >= 3;
+    const bool conv = AMODE == 2 || AMODE == 4 || (AMODE == 1 && p.conv);    // uniform
+    const RowPieces<BM> sa(pA, conv ? 1 : p.M, p.K, conv ? 0 : m0, tid);
+    const RowPieces<BN> sb(pB, p.N, p.K, n0, tidb);
+    ConvPieces sc = {};
+    ConvLane cl = {};
+    if (PIECES && conv) sc = ConvPieces::make<BM>(pA, p, m0, tid);
+    if (!PIECES && AMODE == 2) cl = conv_lane<BM, HBK>(pA, p, m0, tid);
+    // pieces in flight: DEPTH tiles of them (1: asked for at the start of the tile before)
+    constexpr int DEPTH = half_depth(TM, TN);
+    uint4 ra[DEPTH], rc[DEPTH], rb[DEPTH];
+    auto fetch = [&](int t, int d) {
+        const int k0 = t * HBK;
+        if (PIECES) {
+            if (conv) sc.load(p, k0, ra[d], rc[d]);
+            else      ra[d] = sa.load(k0);
+            rb[d] = sb.load(k0);
+        } else if (AMODE == 1) {
+            uint4 va[1], vb[1];
+            fetch_tile_a<BM, HBK>(pA, p, m0, k0, tid, va);
+            fetch_tile<BN, HBK>(pB, p.N, p.K, n0, k0, p.ld_align, tidb, vb);
+            ra[d] = va[0]; rb[d] = vb[0];
+        } else {
+            ra[d] = AMODE == 2 ? fetch_taps(cl, p, k0) : fetch_aligned<BM>(pA, p.M, p.K, m0, k0, tid);
+            rb[d] = fetch_aligned<BN>(pB, p.N, p.K, n0, k0, tidb);
+        }
     };
-    auto stage = [&](int st) { half_stage<BM, BN>(p, smem + st * T::STAGE, smem + st * T::STAGE + T::A_WORDS, ra[0], rb[0], tid, tidb, dyn, half_norm[st]); };
-    fetch(0);
-    stage(0);
+    auto stage = [&](int t, int d) {
+        const uint4 va = !PIECES ? ra[d] : (conv ? sc.codes(p, ra[d], rc[d], t * HBK) : sa.codes(ra[d], t * HBK));
+        const uint4 vb = PIECES ? sb.codes(rb[d], t * HBK) : rb[d];
+        const int st = t & 1;
+        half_stage<BM, BN>(p, smem + st * T::STAGE, smem + st * T::STAGE + T::A_WORDS, va, vb, tid, tidb, dyn, half_norm[st]);
+    };
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) fetch(d, d);               // (a tile beyond K reads codes inside the operands that nothing uses)
+    stage(0, 0);
+    if (DEPTH > 1) fetch(DEPTH, 0);
     __syncthreads();
 
     const HalfBound bound(p);
     int safe_tiles = 0;
-    for (int t = 0; t < ntiles; ++t) {
-        const uint32_t* As0 = smem + (t & 1) * T::STAGE;
-        const uint32_t* Bs0 = As0 + T::A_WORDS;
-        const bool more = (t + 1) < ntiles;
-        if (more) fetch((t + 1) * HBK);
-        const int parts = p.K - t * HBK > 32 ? 2 : 1;          // steps beyond K are products of zeros: skipped 32 at a time
-        for (int part = 0; part < parts; ++part) {
-            const uint32_t* As = As0 + part * 16 * T::BMP;
-            const uint32_t* Bs = Bs0 + part * 32 * T::BNP;
-            if (safe_tiles == 0) {
-                uint32_t mx = 0u;
+    for (int t0 = 0; t0 < ntiles; t0 += DEPTH) {
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
+        for (int d = 0; d < DEPTH; ++d) {
+            const int t = t0 + d;
+            if (t >= ntiles) break;
+            const uint32_t* As0 = smem + (t & 1) * T::STAGE;
+            const uint32_t* Bs0 = As0 + T::A_WORDS;
+            const bool more = (t + 1) < ntiles;
+            if (DEPTH == 1 && (PIECES || more)) fetch(t + 1, 0);
+            const int parts = p.K - t * HBK > 32 ? 2 : 1;      // steps beyond K are products of zeros: skipped 32 at a time
+            for (int part = 0; part < parts; ++part) {
+                const uint32_t* As = As0 + part * 16 * T::BMP;
+                const uint32_t* Bs = Bs0 + part * 32 * T::BNP;
+                if (safe_tiles == 0) {
+                    uint32_t mx = 0u;
 #pragma unroll
-                    for (int j = 0; j < TN / 2; ++j)
-                        mx = pk_max_u16(mx, as_u32(ORDER == LBA_ORDER_CHUNK16 ? top[i][j] : acc[i][j]) & 0x7FFF7FFFu);
-                safe_tiles = bound.safe(max_half(mx), dyn ? half_norm[t & 1] : nullptr);
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN / 2; ++j)
+                            mx = pk_max_u16(mx, as_u32(ORDER == LBA_ORDER_CHUNK16 ? top[i][j] : acc[i][j]) & 0x7FFF7FFFu);
+                    safe_tiles = bound.safe(max_half(mx), dyn ? half_norm[t & 1] : nullptr);
+                }
+                if (safe_tiles > 0) {
+                    --safe_tiles;
+                    half_tile<PM, ORDER, false, TM, TN, T::BMP, T::BNP>(acc, top, As, Bs, tx, ty, c);
+                } else {
+                    half_tile<PM, ORDER, true, TM, TN, T::BMP, T::BNP>(acc, top, As, Bs, tx, ty, c);
+                }
             }
-            if (safe_tiles > 0) {
-                --safe_tiles;
-                half_tile<PM, ORDER, false, TM, TN, T::BMP, T::BNP>(acc, top, As, Bs, tx, ty, c);
-            } else {
-                half_tile<PM, ORDER, true, TM, TN, T::BMP, T::BNP>(acc, top, As, Bs, tx, ty, c);
+            if (more) {
+                constexpr int next = (DEPTH > 1) ? 1 : 0;
+                stage(t + 1, (d + next) % DEPTH);
+                if (DEPTH > 1) fetch(t + 1 + DEPTH, (d + next) % DEPTH);
             }
+            __syncthreads();
         }
-        if (more) stage((t + 1) & 1);
-        __syncthreads();
     }
 
     // C = S * 2^out_exp, zero written as +0
@@ -377,6 +443,33 @@ __device__ __forceinline__ void half_body(const KParams& p, uint32_t* __restrict
             for (int j = 0; j < TN; ++j)
                 if (n + j < p.N) dst[j] = v[j];
         }
+    }
+}
+
+// The grids of lba_fast_kernel and lba_fast_mixed_kernel (the same tiles, numbered the same) on packed carriers.
+// AMODE 0: row-major, 16-byte rows; 3: row-major, any K and alignment; 2: im2col rows, C % 16 == 0 and 16-byte rows; 4: any other.
+template <int TM, int TN, int PM, int ORDER, int AMODE>
+__global__ void __launch_bounds__(256, LBA_FAST_MIN_WAVES) lba_half_kernel(const KParams p) {
+    __shared__ __attribute__((aligned(16))) uint32_t smem[2 * HalfTile<TM, TN, 16>::STAGE];
+    half_body<TM, TN, 16, PM, ORDER, AMODE>(p, smem, blockIdx.x * 16 * TM, blockIdx.y * 16 * TN);
+}
+
+template <int PM, int ORDER, int AMODE>
+__global__ void __launch_bounds__(256, LBA_FAST_MIN_WAVES) lba_half_mixed_kernel(const KParams p) {
+    __shared__ __attribute__((aligned(16))) uint32_t smem[2 * HalfTile<4, 4, 16>::STAGE];
+    const int b = blockIdx.x;
+    if (b < p.mix_main) {                                      // uniform
+        const int by = b / p.mix_gx_main, bx = b - by * p.mix_gx_main;
+        half_body<4, 4, 16, PM, ORDER, AMODE>(p, smem, bx * 64, by * 64);
+    } else if (b < p.mix_main + p.mix_half) {
+        const int t = b - p.mix_main;
+        const int by = t / p.mix_gx_half, bx = t - by * p.mix_gx_half;
+        half_body<3, 4, 16, PM, ORDER, AMODE>(p, smem, p.mix_m_main + bx * 48, by * 64);
+    } else {
+        const int t = b - p.mix_main - p.mix_half;
+        const int by = t / p.mix_gx_tail, bx = t - by * p.mix_gx_tail;
+        if (p.mix_tail16) half_body<1, 2, 8, PM, ORDER, AMODE>(p, smem, p.mix_m_half + bx * 32, by * 16);   // uniform
+        else              half_body<2, 2, 16, PM, ORDER, AMODE>(p, smem, p.mix_m_half + bx * 32, by * 32);
     }
 }
 

@@ -1,0 +1,33 @@
+// lba_half.hip -- instantiations of the forward kernels on packed FP16 carriers (lba_half.h) for row-major matrices.
+#include "lba_device.h"
+#include "lba_launch.h"
+
+namespace lba {
+
+template <int PM, int ORDER, int AMODE>
+static hipError_t launch_one(const Plan& pl, hipStream_t st) {
+    const dim3 grid(pl.grid_x, pl.grid_y, pl.kp.batch), block(256);
+    if (pl.mix_tail > 0)                    hipLaunchKernelGGL((lba_half_mixed_kernel<PM, ORDER, AMODE>), grid, block, 0, st, pl.kp);
+    else if (pl.tm == 4 && pl.tn == 4)      hipLaunchKernelGGL((lba_half_kernel<4, 4, PM, ORDER, AMODE>), grid, block, 0, st, pl.kp);
+    else if (pl.tm == 2 && pl.tn == 4)      hipLaunchKernelGGL((lba_half_kernel<2, 4, PM, ORDER, AMODE>), grid, block, 0, st, pl.kp);
+    else if (pl.tm == 2 && pl.tn == 2)      hipLaunchKernelGGL((lba_half_kernel<2, 2, PM, ORDER, AMODE>), grid, block, 0, st, pl.kp);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+template <int ORDER, int AMODE>
+static hipError_t launch_order(const Plan& pl, hipStream_t st) {
+    if (pl.prod_mode == PM_IDENT) return launch_one<PM_IDENT, ORDER, AMODE>(pl, st);
+    if (pl.prod_mode == PM_FLUSH) return launch_one<PM_FLUSH, ORDER, AMODE>(pl, st);
+    if (pl.prod_mode == PM_TRUNC) return launch_one<PM_TRUNC, ORDER, AMODE>(pl, st);
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_half(const Plan& pl, hipStream_t st) {
+    if (pl.events || pl.round != LBA_ROUND_FLOOR || pl.kp.conv || !pl.kp.h_on) return hipErrorInvalidValue;
+    if (pl.kp.ld_align == 16)
+        return pl.order == LBA_ORDER_CHUNK16 ? launch_order<LBA_ORDER_CHUNK16, 0>(pl, st) : launch_order<LBA_ORDER_SEQ, 0>(pl, st);
+    return pl.order == LBA_ORDER_CHUNK16 ? launch_order<LBA_ORDER_CHUNK16, 3>(pl, st) : launch_order<LBA_ORDER_SEQ, 3>(pl, st);
+}
+
+}  // namespace lba

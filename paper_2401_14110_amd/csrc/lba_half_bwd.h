@@ -255,24 +255,29 @@ __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __rest
         for (int j = 0; j < TN; ++j) { of2[i][j] = 0u; uf2[i][j] = 0u; }
     }
 
-    uint4 ra[1], rb[1];
     const int ntiles = (p.K + HBK - 1) / HBK;
     __shared__ uint32_t half_norm[2][4];
     // non-zero codes: 64 bits per row of A and per column of B and stage, 16 per piece
     __shared__ __attribute__((aligned(8))) uint16_t nza[2][BM][4], nzb[2][BN][4];
     const bool dyn = half_follows_data(p);
-    ConvLane cl;
-    if (AMODE == 2) cl = conv_lane<BM, HBK>(p.A, p, m0, tid);
-    auto fetch = [&](int k0) {
-        if (AMODE == 2) fetch_tile_conv_lane<BM, HBK>(cl, p, k0, ra);
-        else            fetch_tile<BM, HBK>(p.A, p.M, p.K, m0, k0, p.ld_align, tid, ra);
-        fetch_tile<BN, HBK>(p.B, p.N, p.K, n0, k0, p.ld_align, tidb, rb);
+    const RowPieces<BM> sa(p.A, AMODE == 2 ? 1 : p.M, p.K, AMODE == 2 ? 0 : m0, tid);
+    const RowPieces<BN> sb(p.B, p.N, p.K, n0, tidb);
+    ConvPieces sc = {};
+    if (AMODE == 2) sc = ConvPieces::make<BM>(p.A, p, m0, tid);
+    uint4 ra, rc, rb;
+    auto fetch = [&](int t) {
+        if (AMODE == 2) sc.load(p, t * HBK, ra, rc);
+        else            ra = sa.load(t * HBK);
+        rb = sb.load(t * HBK);
     };
-    auto stage = [&](int st) {
-        half_stage<BM, BN>(p, smem + st * T::STAGE, smem + st * T::STAGE + T::A_WORDS, ra[0], rb[0], tid, tidb, dyn, half_norm[st]);
+    auto stage = [&](int t) {
+        const uint4 va = AMODE == 2 ? sc.codes(p, ra, rc, t * HBK) : sa.codes(ra, t * HBK);
+        const uint4 vb = sb.codes(rb, t * HBK);
+        const int st = t & 1;
+        half_stage<BM, BN>(p, smem + st * T::STAGE, smem + st * T::STAGE + T::A_WORDS, va, vb, tid, tidb, dyn, half_norm[st]);
         if (UF) {
-            if (tid < Stage<BM, HBK>::kChunks) nza[st][tid % BM][tid / BM] = (uint16_t)nonzero_codes(ra[0]);
-            if (tidb >= 0 && tidb < Stage<BN, HBK>::kChunks) nzb[st][tidb % BN][tidb / BN] = (uint16_t)nonzero_codes(rb[0]);
+            if (tid < Stage<BM, HBK>::kChunks) nza[st][tid % BM][tid / BM] = (uint16_t)nonzero_codes(va);
+            if (tidb >= 0 && tidb < Stage<BN, HBK>::kChunks) nzb[st][tidb % BN][tidb / BN] = (uint16_t)nonzero_codes(vb);
         }
     };
     fetch(0);
@@ -286,7 +291,7 @@ __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __rest
         const uint32_t* As0 = smem + (t & 1) * T::STAGE;
         const uint32_t* Bs0 = As0 + T::A_WORDS;
         const bool more = (t + 1) < ntiles;
-        if (more) fetch((t + 1) * HBK);
+        fetch(t + 1);
         const int parts = p.K - t * HBK > 32 ? 2 : 1;
         for (int part = 0; part < parts; ++part) {
             const uint32_t* As = As0 + part * 16 * T::BMP;
@@ -349,7 +354,7 @@ __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __rest
                     for (int j = 0; j < TN; ++j) { of2[i][j] = 0u; uf2[i][j] = 0u; }
             }
         }
-        if (more) stage((t + 1) & 1);
+        if (more) stage(t + 1);
         __syncthreads();
     }
     if (!p.C) return;

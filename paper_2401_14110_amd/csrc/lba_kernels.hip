@@ -20,6 +20,7 @@ static hipError_t launch_plan(const Plan& pl, hipStream_t st) {
     if (pl.kernel == KERNEL_FAST && pl.events == 2) return launch_fast_diff(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.events && pl.kp.h_on) return launch_half_bwd(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.events) return launch_fast_bwd(pl, st);
+    if (pl.kernel == KERNEL_FAST && pl.kp.h_on && (pl.amode != 1 || pl.mix_tail > 0)) return pl.kp.conv ? launch_half_conv(pl, st) : launch_half(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.rne_odd) return launch_fast_odd(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.amode == 2) return launch_fast_conv(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.amode == 1 && pl.mix_tail > 0)
@@ -61,6 +62,10 @@ static void plan_kernel_name(const Plan& pl, bool uf, char* buf, size_t n) {
         else if (pl.amode)        snprintf(buf, n, "lba_fast_bwd_kernel<%d, 0, 0, %s, 1>", pm, b);
         else if (pl.mix_tail > 0) snprintf(buf, n, "lba_fast_bwd_mixed_kernel<%d, %d, %s>", pm, pl.round, b);
         else                      snprintf(buf, n, "lba_fast_bwd_kernel<%d, %d, %d, %s, 0>", pm, pl.round, ord, b);
+    } else if (pl.kp.h_on && (pl.amode != 1 || pl.mix_tail > 0)) {
+        const int am = (pl.amode == 2 ? 2 : 0) + (pl.kp.K % 16 == 0 ? 0 : (pl.amode == 2 ? 2 : 3));      // (operands on a 16-byte boundary)
+        if (pl.mix_tail > 0) snprintf(buf, n, "lba_half_mixed_kernel<%d, %d, %d>", pm, ord, am);
+        else                 snprintf(buf, n, "lba_half_kernel<%d, %d, %d, %d, %d>", pl.tm, pl.tn, pm, ord, am);
     } else if (pl.rne_odd) {
         snprintf(buf, n, "lba_fast_kernel<4, 4, %d, %d, 3, %d, 0>", pl.bk, pm, ord);
     } else {
@@ -121,6 +126,7 @@ static int run(const uint8_t* A, const uint8_t* B, float* C, uint32_t* of_mask, 
         kp.conv = 1;
         kp.cv_h = conv->h; kp.cv_w = conv->w; kp.cv_c = conv->c; kp.cv_kw = conv->kw;
         kp.cv_stride = conv->stride; kp.cv_pad = conv->pad; kp.cv_oh = conv_oh; kp.cv_ow = conv_ow;
+        if ((int64_t)conv->n * conv->h * conv->w * conv->c < 16) kp.h_on = 0;   // packed carriers fetch 16 bytes at a time
         kp.cv_vec = ((conv->c % 16) == 0 && ((uintptr_t)A % 16) == 0) ? 1 : 0;
         kp.cv_magic_c = (((uint64_t)1 << 40) + (uint64_t)conv->c - 1) / (uint64_t)conv->c;
         kp.cv_magic_kw = (((uint64_t)1 << 40) + (uint64_t)conv->kw - 1) / (uint64_t)conv->kw;

@@ -129,3 +129,59 @@ def test_event_planes_of_ragged_shapes(ref, K):
         torch.cuda.synchronize()
         w = ref.gemm_bwd(A, B, ref.QFmt(*qp), ref.QFmt(*qa))
         assert np.array_equal(bits(of.cpu().numpy()), bits(w[1])) and np.array_equal(bits(uf.cpu().numpy()), bits(w[2]))
+
+
+def at(a, off):
+    """A device copy of a that starts off bytes past a 16-byte boundary."""
+    buf = torch.zeros(a.size + 32, dtype=torch.uint8, device=DEV)
+    t = buf[off:off + a.size].view(a.shape)
+    t.copy_(torch.from_numpy(a))
+    return t
+
+
+@pytest.mark.parametrize("n,h,w,c,cout,kh,kw,stride,pad", [
+    (2, 9, 8, 5, 17, 3, 3, 1, 1),            # a filter row of 15 codes: byte by byte
+    (2, 9, 8, 16, 17, 3, 1, 1, 1),           # one tap to a filter row, aligned
+    (2, 9, 8, 17, 18, 3, 1, 2, 2),           # a filter row one code longer than a piece
+    (3, 11, 7, 3, 66, 7, 7, 2, 3),           # two filter rows to a piece, cut off at both edges of the image
+    (1, 6, 5, 9, 130, 2, 2, 1, 4),           # padding wider than the image's reach: pieces wholly outside, before and after it
+    (1, 4, 4, 1, 3, 3, 3, 1, 0),             # a tensor of exactly 16 bytes
+    (1, 3, 5, 1, 3, 3, 3, 1, 1),             # one byte short of that
+    (4, 40, 40, 6, 300, 3, 3, 1, 1),         # the large lane blocks
+])
+def test_pieces_of_im2col_rows(ref, n, h, w, c, cout, kh, kw, stride, pad):
+    rng = np.random.default_rng([n, c, kw])
+    qp, qa = (5, 7, -1, 0), (4, 7, -9, 0)
+    X, W = codes(rng, (n, h, w, c)), codes(rng, (cout, kh, kw, c))
+    B = W.reshape(cout, kh * kw * c)
+    for (ox, ow), order in itertools.product([(0, 0), (1, 0), (0, 3), (13, 8)], (0, 1)):
+        got = lb.conv2d(at(X, ox), at(W, ow), qp, qa, stride=stride, pad=pad, order=order)
+        torch.cuda.synchronize()
+        want = ref.gemm(ref.im2col_nhwc(X, kh, kw, stride, pad), B, ref.QFmt(*qp), ref.QFmt(*qa), order=order)
+        assert np.array_equal(bits(got.cpu().numpy().reshape(want.shape)), bits(want)), (ox, ow, order)
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 1, 15), (1, 1, 16), (3, 5, 3), (1, 40, 16), (16, 1, 1), (33, 31, 48), (64, 64, 257),
+                                   (1000, 700, 64), (1000, 700, 83)])
+def test_pieces_of_rows_at_any_alignment(ref, M, N, K):
+    # operands under 16 bytes stay on FP32; aligned and unaligned forms of the small and of the large lane blocks
+    rng = np.random.default_rng([M, K])
+    qp, qa = (5, 7, -1, 0), (4, 7, -9, 0)
+    A, B = codes(rng, (M, K)), codes(rng, (N, K))
+    assert (slots(M, N, K, qp, qa) == 250) == (M * K >= 16 and N * K >= 16)
+    for (oa, ob), order in itertools.product([(0, 0), (1, 0), (0, 15), (4, 8)], (0, 1)):
+        got = lb.gemm(at(A, oa), at(B, ob), qp, qa, order=order)
+        torch.cuda.synchronize()
+        assert np.array_equal(bits(got.cpu().numpy()), bits(ref.gemm(A, B, ref.QFmt(*qp), ref.QFmt(*qa), order=order))), (oa, ob, order)
+
+
+def test_rounded_products_of_im2col_rows(ref):
+    # products that Q_prod truncates, on a mixed grid and on a plain one, aligned and not
+    rng = np.random.default_rng(77)
+    qp, qa = (5, 4, -1, 0), (4, 7, -9, 0)
+    for n, h, w, c, cout in [(4, 40, 40, 16, 40), (4, 40, 40, 6, 40), (2, 9, 8, 16, 17), (33, 56, 56, 3, 64)]:
+        X, W = codes(rng, (n, h, w, c)), codes(rng, (cout, 3, 3, c))
+        got = lb.conv2d(at(X, 0), at(W, 0), qp, qa, stride=1, pad=1)
+        torch.cuda.synchronize()
+        want = ref.gemm(ref.im2col_nhwc(X, 3, 3, 1, 1), W.reshape(cout, 9 * c), ref.QFmt(*qp), ref.QFmt(*qa))
+        assert np.array_equal(bits(got.cpu().numpy().reshape(want.shape)), bits(want)), (n, h, w, c, cout)
