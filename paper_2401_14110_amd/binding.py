@@ -124,7 +124,13 @@ def lib(path=None):
 
 def qfmt(f):
     """(E, M, b, round) tuple or lba_qfmt -> lba_qfmt."""
-    return f if isinstance(f, lba_qfmt) else lba_qfmt(*[int(v) for v in f])
+    if isinstance(f, lba_qfmt):
+        return f
+    f = tuple(f)
+    try:
+        return lba_qfmt(*f)
+    except TypeError:                              # fields that are numbers without being integers
+        return lba_qfmt(*[int(v) for v in f])
 
 
 def lba_strerror(code):
@@ -141,7 +147,9 @@ def _check(rc):
 
 def _stream(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the current device's current stream, without the Stream object torch.cuda.current_stream() builds around it (2.9 us
+        # of the 10 us that a 64 x 64 call took on the host; 0.3 us)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
 
