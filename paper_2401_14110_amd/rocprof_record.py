@@ -6,7 +6,7 @@ taken from separate rocprofv3 runs of the same command and stored in profiles/ro
 by the workload and by the kernel's name, so that bench.py can attach the figures only to the kernel they were
 measured on.  One record needs, all from the same build:
 
-    cd /tmp && export TMPDIR=/tmp                       # on the GPU machine, repository root = $R
+    cd /tmp && export TMPDIR=/tmp                       # repository root = $R
     python3 $R/bench.py <flags> --steps 5 --warmup 1 --no-cpu-baseline --dump-kernels $R/out/kernels.json
     rocprofv3 --kernel-trace --stats --output-format csv -d $R/out/prof_kt -- python3 $R/bench.py <flags> --steps 5 --warmup 1 --no-cpu-baseline
     rocprofv3 --pmc SQ_INSTS_VALU SQ_INSTS_SALU SQ_INSTS_LDS SQ_WAVES SQ_BUSY_CYCLES SQ_ACTIVE_INST_VALU SQ_WAIT_INST_LDS \\
