@@ -340,7 +340,8 @@ __device__ __forceinline__ void half_body(const KParams& p, uint32_t* __restrict
     const bool dyn = half_follows_data(p);
     // How the pieces come.  Aligned rows and im2col rows of whole 16-channel taps (AMODE 0, 2): one aligned load, zeroed at once
     // outside the operand.  Any other rows (AMODE 3, 4) and the small lane blocks: lba_piece.h, uncorrected loads that stay in
-    // flight (C = 3 under a 7 x 7 filter: two loads a piece instead of sixteen, 279 -> 255 us).  Either kind of code in the other's kernel, behind a uniform branch, cost the aligned shapes 1 to 4 %.
+    // flight (C = 3 under a 7 x 7 filter: two loads a piece instead of sixteen, 279 -> 255 us).  Either kind of
+    // code in the other's kernel, behind a uniform branch, cost the aligned shapes 1 to 4 %.
     constexpr bool SMALL = TM * TN <= 4, PIECES = SMALL || AMODE >= 3;
     const bool conv = AMODE == 2 || AMODE == 4 || (AMODE == 1 && p.conv);    // uniform
     const RowPieces<BM> sa(pA, conv ? 1 : p.M, p.K, conv ? 0 : m0, tid);
