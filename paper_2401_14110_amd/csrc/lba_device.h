@@ -28,6 +28,7 @@
 #include <stdint.h>
 
 #include "lba_internal.h"
+#include "lba_piece_index.h"
 
 namespace lba {
 
@@ -345,8 +346,6 @@ __device__ __forceinline__ void fetch_tile(const uint8_t* __restrict__ G, int ro
 // (n, oh, ow); byte k of the row is X[n, oh*stride - pad + kh, ow*stride - pad + kw, c] with
 // k = (kh * KW + kw) * C + c, or code 0 (the value +0) outside the image.  With C % 16 == 0 a 16-byte
 // piece lies inside one tap and is one aligned load; otherwise its bytes are gathered one by one.
-__device__ __forceinline__ uint32_t div_magic(uint32_t x, uint64_t magic) { return (uint32_t)(((uint64_t)x * magic) >> 40); }
-
 template <int ROWS, int BK>
 __device__ __forceinline__ void fetch_tile_conv(const uint8_t* __restrict__ X, const KParams& p, int r0, int k0,
                                                 int tid, uint4 (&regs)[Stage<ROWS, BK>::kPerLane]) {

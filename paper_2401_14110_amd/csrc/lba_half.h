@@ -55,9 +55,8 @@ struct HalfConst {
 };
 
 // Geometry of one workgroup tile: LX lanes along n, 256 / LX along m, TM x TN outputs per lane (TN even: the pairs are
-// neighbours along n).  A k-tile in LDS is HBK = 64 steps deep: A as words (k, k + 1) of one row, [k / 2][row], so that one
+// neighbours along n).  A k-tile in LDS is HBK (64) steps deep: A as words (k, k + 1) of one row, [k / 2][row], so that one
 // read serves two steps (the step's half is picked by the instruction); B as words (n, n + 1) of one k, [k][n / 2].
-enum { HBK = 64 };
 template <int TM, int TN, int LX>
 struct HalfTile {
     static constexpr int BM = 256 / LX * TM, BN = LX * TN;
@@ -354,11 +353,11 @@ __device__ __forceinline__ void half_body(const KParams& p, uint32_t* __restrict
     constexpr int DEPTH = half_depth(TM, TN);
     uint4 ra[DEPTH], rc[DEPTH], rb[DEPTH];
     auto fetch = [&](int t, int d) {
-        const int k0 = t * HBK;
+        const int k0 = tile_start(t, ntiles);
         if (PIECES) {
-            if (conv) sc.load(p, k0, ra[d], rc[d]);
-            else      ra[d] = sa.load(k0);
-            rb[d] = sb.load(k0);
+            if (conv) load_piece(sc, p, k0, ra[d], rc[d]);
+            else      ra[d] = load_piece(sa, k0);
+            rb[d] = load_piece(sb, k0);
         } else if (AMODE == 1) {
             uint4 va[1], vb[1];
             fetch_tile_a<BM, HBK>(pA, p, m0, k0, tid, va);

@@ -266,9 +266,10 @@ __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __rest
     if (AMODE == 2) sc = ConvPieces::make<BM>(p.A, p, m0, tid);
     uint4 ra, rc, rb;
     auto fetch = [&](int t) {
-        if (AMODE == 2) sc.load(p, t * HBK, ra, rc);
-        else            ra = sa.load(t * HBK);
-        rb = sb.load(t * HBK);
+        const int k0 = tile_start(t, ntiles);
+        if (AMODE == 2) load_piece(sc, p, k0, ra, rc);
+        else            ra = load_piece(sa, k0);
+        rb = load_piece(sb, k0);
     };
     auto stage = [&](int t) {
         const uint4 va = AMODE == 2 ? sc.codes(p, ra, rc, t * HBK) : sa.codes(ra, t * HBK);

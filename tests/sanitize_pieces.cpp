@@ -1,0 +1,93 @@
+// Host build of the piece arithmetic of the packed FP16 tiles (csrc/lba_piece_index.h) under the address and
+// undefined-behaviour sanitizers: every address stays inside its operand and every piece holds the codes that the definition
+// (64-bit indices, one byte at a time) gives.  Operands of 2 GiB and more are reserved address space of which only the rows
+// under test are ever written.  tests/test_sanitizers_cpu.py compiles and runs it, one check at a time; nothing touches a GPU.
+#include <sys/mman.h>
+
+#include <cstdint>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+
+#include <vector>
+
+#include "lba_piece_index.h"
+
+static int failures = 0;
+#define CHECK(cond, ...) do { if (!(cond) && ++failures < 20) { std::printf("FAIL %s:%d: ", __FILE__, __LINE__); std::printf(__VA_ARGS__); std::printf("\n"); } } while (0)
+
+static uint64_t rng_state = 0x9E3779B97F4A7C15ull;
+static uint32_t rnd32() {                                      // xorshift64*
+    rng_state ^= rng_state >> 12; rng_state ^= rng_state << 25; rng_state ^= rng_state >> 27;
+    return (uint32_t)((rng_state * 0x2545F4914F6CDD1Dull) >> 32);
+}
+static int below(int n) { return (int)(rnd32() % (uint32_t)n); }
+
+struct Words { uint32_t x, y, z, w; };
+static Words load(const uint8_t* a) { Words v; std::memcpy(&v, a, 16); return v; }
+
+struct Operand {                                               // zero bytes until written; an access outside it faults
+    uint8_t* base; size_t bytes, span;
+    explicit Operand(size_t n) : bytes(n), span((n + 4095) / 4096 * 4096) {
+        base = (uint8_t*)mmap(nullptr, span + 8192, PROT_NONE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+        if (base == MAP_FAILED || mprotect(base + 4096, span, PROT_READ | PROT_WRITE) != 0) { std::perror("mmap"); std::exit(3); }
+        base += 4096;
+    }
+    ~Operand() { munmap(base - 4096, span + 8192); }
+    Operand(const Operand&) = delete;
+    void fill(size_t at, size_t n) { for (size_t i = at; i < at + n && i < bytes; ++i) base[i] = (uint8_t)(1 + below(255)); }
+};
+
+static const int kRows = 64;
+
+// every piece of one row over the tiles [t0, t1): the matrix [rows][K] at op.base + off
+static void check_row(const Operand& op, size_t off, int rows, int K, int r, int t0, int t1) {
+    const uint8_t* G = op.base + off;
+    const int ntiles = (int)(((int64_t)K + 63) / 64);
+    for (int q = 0; q < 4; ++q) {
+        const lba::RowPieces<kRows> s(G, rows, K, r / kRows * kRows, r % kRows + kRows * q);
+        for (int t = t0; t < t1; ++t) {
+            const int k0 = lba::tile_start(t, ntiles);
+            const uint8_t* a = s.address(k0);
+            const bool in = a >= G && a + 16 <= G + (int64_t)rows * K;
+            CHECK(in, "rows %d K %d row %d tile %d of %d piece %d: loads at %lld", rows, K, r, t, ntiles, q, (long long)(a - G));
+            if (!in || t >= ntiles) continue;                  // (a tile past the last one is fetched and dropped)
+            const Words got = s.codes(load(a), k0);
+            uint8_t want[16] = {};
+            for (int j = 0; j < 16; ++j) {
+                const int64_t k = (int64_t)t * 64 + 16 * q + j;
+                if (r < rows && k < K) want[j] = G[(int64_t)r * K + k];
+            }
+            CHECK(std::memcmp(&got, want, 16) == 0, "rows %d K %d row %d tile %d piece %d: wrong codes", rows, K, r, t, q);
+        }
+    }
+}
+
+// rows at every distance from the operand's end, up to 4.5 GB
+static void far_rows() {
+    const int shapes[][2] = {{16000000, 147}, {33554435, 136}, {6, 3}, {1, 17}, {70, 64}, {300, 83}, {2, 1000}, {40000000, 113}};
+    for (const auto& sh : shapes) {
+        const int rows = sh[0], K = sh[1], ntiles = (K + 63) / 64;
+        for (int off : {0, 5}) {
+            Operand op((size_t)rows * K + off);
+            std::vector<int> rs = {0, 1, 63, 64, rows / 2, rows - 2, rows - 1, rows};
+            for (int64_t d : {1LL << 30, 1LL << 31, 3LL << 30, 1LL << 32})
+                for (int e = -2; e <= 2; ++e) rs.push_back((int)(((int64_t)rows * K - d) / K + e));
+            for (int i = 0; i < 60; ++i) rs.push_back(below(rows));
+            for (int r : rs) {
+                if (r < 0 || r > rows) continue;               // r == rows: a lane beyond the matrix
+                op.fill((size_t)r * K + off, (size_t)K + 16);
+                check_row(op, (size_t)off, rows, K, r, 0, ntiles + 2);
+            }
+        }
+    }
+}
+
+int main(int argc, char** argv) {
+    if (argc != 2) { std::printf("usage: %s <check>\n", argv[0]); return 2; }
+    if (!std::strcmp(argv[1], "far_rows")) far_rows();
+    else { std::printf("no such check\n"); return 2; }
+    if (failures) { std::printf("%d failures\n", failures); return 1; }
+    std::printf("pieces ok\n");
+    return 0;
+}

@@ -87,6 +87,38 @@ def test_operand_beyond_4_gib_and_its_planes(ref):
         del gots
 
 
+def test_operand_beyond_4_gib_on_packed_carriers(ref):
+    # the same operand with a Q_prod that cannot saturate: floor on packed FP16 carriers, forward and planes, both orders.
+    # The last piece of a row is cut by K (136 = 8 * 16 + 8); rows at every multiple of 2^30 bytes from the operand's end
+    M, N, K = 2 ** 25 + 3, 2, 136
+    qp, qa = (5, 7, 12, 0), (4, 7, 7, 0)
+    rng = np.random.default_rng(2039)
+    A = periodic_rows(rng, M, K, 3, 11)
+    Bh = codes(rng, (N, K), 3, 11)
+    B = torch.from_numpy(Bh).to(DEV)
+    rows = {0, 1, 63, 64, M - 1, M - 2, M - 65, PERIOD - 1, PERIOD, PERIOD + 1}
+    for off in (2 ** 30, 2 ** 31, 3 * 2 ** 30, 2 ** 32):
+        rows |= {off // K + d for d in (-1, 0, 1, 2)} | {(M * K - off) // K + d for d in (-1, 0, 1, 2)}
+    rows |= set(int(r) for r in rng.integers(0, M, 300))
+    rows = np.array(sorted(rows))
+    idx = torch.from_numpy(rows).to(DEV)
+    Ah = A.index_select(0, idx).cpu().numpy()
+    for order in (0, 1):
+        assert lb.lba_plan_kernel_name(M, N, K, qp, qa, order, 0).startswith("lba_half"), order
+        assert lb.lba_plan_kernel_name(M, N, K, qp, qa, order, 1).startswith("lba_half_bwd"), order
+        wants = ref.gemm_bwd(Ah, Bh, ref.QFmt(*qp), ref.QFmt(*qa), order=order, level2=bool(order))
+        C = lb.gemm(A, B, qp, qa, order=order)
+        torch.cuda.synchronize()
+        assert np.array_equal(bits(C.index_select(0, idx).cpu().numpy()), bits(wants[0])), (order, "C")
+        del C
+        gots = lb.gemm_bwd_chunked(A, B, qp, qa) if order else lb.gemm_bwd(A, B, qp, qa)
+        torch.cuda.synchronize()
+        assert np.array_equal(bits(gots[0].index_select(0, idx).cpu().numpy()), bits(wants[0])), (order, "C of the recompute call")
+        for i in range(1, len(wants)):
+            assert np.array_equal(gots[i].index_select(1, idx).cpu().numpy().view(np.uint32), wants[i]), (order, i)
+        del gots
+
+
 def test_chains_longer_than_2_to_24(ref):
     # K = 2^24 + 7 (odd: unaligned rows), 3 x 5 outputs: complete comparison, both roundings and orders; the
     # recompute call at K = 2^22 + 5 with complete planes

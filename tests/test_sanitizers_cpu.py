@@ -6,6 +6,8 @@ sweeps the planner over the format space and the shape limits.  CPU only: nothin
 import os
 import subprocess
 
+import pytest
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 GOLD = os.path.join(ROOT, "tests", "golden")
 
@@ -38,3 +40,19 @@ def test_oracle_and_planner_under_asan_and_ubsan(tmp_path):
     run = subprocess.run([exe, str(rpath), os.path.join(GOLD, "chain_p1b.txt")], capture_output=True, text=True, env=env)
     assert run.returncode == 0, (run.returncode, run.stdout[-3000:], run.stderr[-3000:])
     assert "sanitize driver ok" in run.stdout
+
+
+@pytest.fixture(scope="module")
+def pieces(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("pieces") / "sanitize_pieces")
+    subprocess.run([_clang(), "-std=c++17", "-O1", "-g", "-fno-omit-frame-pointer",
+                    "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                    "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2401_14110_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "sanitize_pieces.cpp"), "-o", exe], check=True)
+    return exe
+
+
+@pytest.mark.parametrize("check", ["far_rows"])
+def test_pieces_of_the_packed_tiles(pieces, check):
+    run = subprocess.run([pieces, check], capture_output=True, text=True, env=dict(os.environ, UBSAN_OPTIONS="print_stacktrace=1"))
+    assert run.returncode == 0 and "pieces ok" in run.stdout, (run.returncode, run.stdout[-3000:], run.stderr[-3000:])
