@@ -303,7 +303,7 @@ struct HalfBound {
 
 // k-tiles whose pieces are in flight at a time: one for the large lane blocks (two measured the same); four for the small ones,
 // whose tile takes less time than a load (64 x 1000 x 2048: 47 -> 45 us).
-__host__ __device__ constexpr int half_depth(int TM, int TN) { return TM * TN <= 4 ? 4 : 1; }
+__host__ __device__ constexpr int half_depth(int TM, int TN) { return TM * TN <= 4 ? kTilesAhead : 1; }
 
 // The work of one workgroup: the BM x BN tile of C at (m0, n0).  smem: two stages.  Structure, clamp-free tiles and their
 // bounds as in fast_body; AMODE as there, and 3, 4 below (every code format decodes alike).
@@ -353,7 +353,7 @@ __device__ __forceinline__ void half_body(const KParams& p, uint32_t* __restrict
     constexpr int DEPTH = half_depth(TM, TN);
     uint4 ra[DEPTH], rc[DEPTH], rb[DEPTH];
     auto fetch = [&](int t, int d) {
-        const int k0 = tile_start(t, ntiles);
+        const int k0 = tile_start(t);
         if (PIECES) {
             if (conv) load_piece(sc, p, k0, ra[d], rc[d]);
             else      ra[d] = load_piece(sa, k0);

@@ -266,7 +266,7 @@ __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __rest
     if (AMODE == 2) sc = ConvPieces::make<BM>(p.A, p, m0, tid);
     uint4 ra, rc, rb;
     auto fetch = [&](int t) {
-        const int k0 = tile_start(t, ntiles);
+        const int k0 = tile_start(t);
         if (AMODE == 2) load_piece(sc, p, k0, ra, rc);
         else            ra = load_piece(sa, k0);
         rb = load_piece(sb, k0);

@@ -43,6 +43,7 @@
 #include <algorithm>
 
 #include "lba_internal.h"
+#include "lba_piece_index.h"
 
 namespace lba {
 
@@ -430,8 +431,9 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
         // packed FP16 carriers (forward call, floor, underflow kept): v_pk_mul, [v_and,] v_pk_fma at half rate for two
         // chains, one v_and for both; never priced below the two slots of the FP32 multiply-add and mask
         // (the recompute call is priced at the FP32 kernel's step on either carrier)
-        // (pieces are loads of 16 bytes from inside an operand: at least 16 of them; im2col rows: checked by the caller)
-        const bool half = N * K >= 16 && (conv || M * K >= 16) && events != 2 && !rne_odd && qa.round == LBA_ROUND_FLOOR && !nouf_a &&
+        // (pieces are loads of 16 bytes from inside an operand: at least 16 of them; im2col rows: checked by the caller;
+        // fetched ahead of the chain: K not at the end of its range)
+        const bool half = N * K >= 16 && K <= kPieceMaxK && (conv || M * K >= 16) && events != 2 && !rne_odd && qa.round == LBA_ROUND_FLOOR && !nouf_a &&
                           (p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH || p.prod_mode == PM_TRUNC) &&
                           (!p.events || p.of_only || half_underflow_ok(qp, in, bpe, bae)) &&
                           half_carrier(qp, qa, in, p.prod_mode, bpe, bae, &kp);

@@ -47,12 +47,11 @@ static void check_row(const Operand& op, size_t off, int rows, int K, int r, int
     for (int q = 0; q < 4; ++q) {
         const lba::RowPieces<kRows> s(G, rows, K, r / kRows * kRows, r % kRows + kRows * q);
         for (int t = t0; t < t1; ++t) {
-            const int k0 = lba::tile_start(t, ntiles);
-            const uint8_t* a = s.address(k0);
+            const uint8_t* a = s.address(lba::tile_start(t));
             const bool in = a >= G && a + 16 <= G + (int64_t)rows * K;
             CHECK(in, "rows %d K %d row %d tile %d of %d piece %d: loads at %lld", rows, K, r, t, ntiles, q, (long long)(a - G));
             if (!in || t >= ntiles) continue;                  // (a tile past the last one is fetched and dropped)
-            const Words got = s.codes(load(a), k0);
+            const Words got = s.codes(load(a), t * 64);
             uint8_t want[16] = {};
             for (int j = 0; j < 16; ++j) {
                 const int64_t k = (int64_t)t * 64 + 16 * q + j;
@@ -83,9 +82,32 @@ static void far_rows() {
     }
 }
 
+// chains up to the longest, K = 2^31 - 64, that the planner gives to the packed tiles: the last tiles and the ones fetched ahead
+// beyond them (the small lane blocks keep four tiles in flight: up to tile ntiles + 3).  M = N = 1 runs on those blocks.
+static void long_chains() {
+    int packed = 0, plain = 0;
+    for (int d : {0, 1, 15, 16, 63, 64, 65, 127, 128, 190, 255, 256, 257, 300, 1000})
+        for (int rows : {1, 2}) {
+            const int K = 2147483584 - d, ntiles = (int)(((int64_t)K + 63) / 64);
+            lba::Plan pl;
+            const lba_qfmt qp = {5, 7, 12, 0}, qa = {4, 7, 7, 0};
+            CHECK(lba::make_plan(rows, rows, K, qp, qa, LBA_ORDER_SEQ, 0, &pl) == LBA_OK && pl.kernel == lba::KERNEL_FAST, "plan of K = %d", K);
+            ++(pl.kp.h_on ? packed : plain);
+            if (!pl.kp.h_on) continue;
+            Operand op((size_t)rows * K);
+            for (int r = 0; r <= rows; ++r) {
+                if (r < rows) { op.fill((size_t)r * K, 300); op.fill((size_t)(r + 1) * K - 300, 300); }
+                check_row(op, 0, rows, K, r, 0, 6);
+                check_row(op, 0, rows, K, r, ntiles - 3, ntiles + 4);
+            }
+        }
+    CHECK(packed == 8 && plain == 22, "%d plans on packed carriers, %d not", packed, plain);
+}
+
 int main(int argc, char** argv) {
     if (argc != 2) { std::printf("usage: %s <check>\n", argv[0]); return 2; }
     if (!std::strcmp(argv[1], "far_rows")) far_rows();
+    else if (!std::strcmp(argv[1], "long_chains")) long_chains();
     else { std::printf("no such check\n"); return 2; }
     if (failures) { std::printf("%d failures\n", failures); return 1; }
     std::printf("pieces ok\n");

@@ -48,11 +48,12 @@ def pieces(tmp_path_factory):
     subprocess.run([_clang(), "-std=c++17", "-O1", "-g", "-fno-omit-frame-pointer",
                     "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
                     "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2401_14110_amd", "csrc"),
+                    os.path.join(ROOT, "paper_2401_14110_amd", "csrc", "lba_plan.cpp"),
                     os.path.join(ROOT, "tests", "sanitize_pieces.cpp"), "-o", exe], check=True)
     return exe
 
 
-@pytest.mark.parametrize("check", ["far_rows"])
+@pytest.mark.parametrize("check", ["far_rows", "long_chains"])
 def test_pieces_of_the_packed_tiles(pieces, check):
     run = subprocess.run([pieces, check], capture_output=True, text=True, env=dict(os.environ, UBSAN_OPTIONS="print_stacktrace=1"))
     assert run.returncode == 0 and "pieces ok" in run.stdout, (run.returncode, run.stdout[-3000:], run.stderr[-3000:])
