@@ -107,11 +107,15 @@ struct RowPieces {
 // when KW * C >= 16: two unaligned loads (the first convolution of a ResNet, C = 3: sixteen byte loads before).
 struct ConvPieces {
     const uint8_t* X;
-    const uint8_t* img;        // X + n * H * W * C
-    const uint8_t* last;       // the last address from which 16 bytes lie inside the tensor (which holds at least 16)
+    int64_t img;               // n * H * W * C
+    int64_t last;              // the last offset from which 16 bytes lie inside the tensor (which holds at least 16)
     int ih0, iw0, kq;
+    int lo, hi;                // of a filter row's KW * C codes, those inside the image's columns: [lo, hi)
     bool ok, spans;
 
+    // Columns are compared as columns: the padding is not limited, so iw0 * C (or W - iw0) can pass 2^31.  ih0 and iw0 are taken
+    // modulo 2^32 (unsigned arithmetic): one that wraps lies 2^31 or more beyond the image, wraps to a negative number and stays
+    // outside.
     template <int ROWS>
     static LBA_HOST_DEVICE ConvPieces make(const uint8_t* X, const KParams& p, int r0, int c) {
         ConvPieces s;
@@ -122,11 +126,15 @@ struct ConvPieces {
         const int oh = t % p.cv_oh, n = t / p.cv_oh;
         const int64_t image = (int64_t)p.cv_h * p.cv_w * p.cv_c, total = image * (p.M / (p.cv_oh * p.cv_ow));
         s.X = X;
-        s.img = X + n * image;
-        s.last = X + (total - 16);
-        s.ih0 = oh * p.cv_stride - p.cv_pad;
-        s.iw0 = ow * p.cv_stride - p.cv_pad;
+        s.img = n * image;
+        s.last = total - 16;
+        s.ih0 = (int)((uint32_t)oh * (uint32_t)p.cv_stride - (uint32_t)p.cv_pad);
+        s.iw0 = (int)((uint32_t)ow * (uint32_t)p.cv_stride - (uint32_t)p.cv_pad);
         s.kq = c >= 0 ? c / ROWS * 16 : 0;
+        const int left = s.iw0 >= 0 ? 0 : (s.iw0 > -p.cv_kw ? -s.iw0 : p.cv_kw);              // taps left of the image
+        const int right = s.iw0 <= p.cv_w - p.cv_kw ? p.cv_kw : (s.iw0 < p.cv_w ? p.cv_w - s.iw0 : 0);   // taps not right of it
+        s.lo = left * p.cv_c;
+        s.hi = right * p.cv_c;
         s.spans = p.cv_kw * p.cv_c >= 16;                      // uniform
         return s;
     }
@@ -136,22 +144,22 @@ struct ConvPieces {
         const int kh = (int)div_magic((uint32_t)tap, p.cv_magic_kw);
         return {kh, k - kh * p.cv_kw * p.cv_c};
     }
-    // bytes of the filter row's run that lie inside the image: [lo, hi)
-    LBA_HOST_DEVICE bool inside(const KParams& p, int kh, int& lo, int& hi) const {
-        lo = iw0 < 0 ? -iw0 * p.cv_c : 0;
-        hi = (p.cv_kw < p.cv_w - iw0 ? p.cv_kw : p.cv_w - iw0) * p.cv_c;
-        return ok && (unsigned)(ih0 + kh) < (unsigned)p.cv_h;
+    LBA_HOST_DEVICE bool inside(const KParams& p, int kh) const { return ok && (uint32_t)ih0 + (uint32_t)kh < (uint32_t)p.cv_h; }
+    // offset of code r of filter row kh (meaningful, and free of wraps, for a row inside the image)
+    LBA_HOST_DEVICE int64_t offset(const KParams& p, int kh, int r) const {
+        const uint64_t ih = (uint64_t)(int64_t)(int)((uint32_t)ih0 + (uint32_t)kh);
+        return img + (int64_t)((ih * (uint64_t)p.cv_w + (uint64_t)(int64_t)iw0) * (uint64_t)p.cv_c + (uint64_t)r);
     }
-    LBA_HOST_DEVICE const uint8_t* address(const KParams& p, int kh, int r) const {
-        return img + ((int64_t)(ih0 + kh) * p.cv_w + iw0) * p.cv_c + r;
-    }
-    LBA_HOST_DEVICE const uint8_t* clamped(const uint8_t* a) const { return a < X ? X : (a > last ? last : a); }
+    LBA_HOST_DEVICE int64_t clamped(int64_t a) const { return a < 0 ? 0 : (a > last ? last : a); }
+    // how many bytes before a its clamped load started (< 0: after it): at most 15 where any of the piece's codes are inside the
+    // image, and anything from -16 to 15 (the difference's low five bits) where none are and nothing is kept
+    LBA_HOST_DEVICE int early(int64_t a) const { return (int32_t)((uint32_t)(uint64_t)(a - clamped(a)) << 27) >> 27; }
     // where the two loads of the tile at k0 start: at its first code, and at the next filter row
     LBA_HOST_DEVICE const uint8_t* first(const KParams& p, int k0) const {
         const At a = at(p, k0 + kq);
-        return clamped(address(p, a.kh, a.r));
+        return X + clamped(offset(p, a.kh, a.r));
     }
-    LBA_HOST_DEVICE const uint8_t* second(const KParams& p, int k0) const { return clamped(address(p, at(p, k0 + kq).kh + 1, 0)); }
+    LBA_HOST_DEVICE const uint8_t* second(const KParams& p, int k0) const { return X + clamped(offset(p, at(p, k0 + kq).kh + 1, 0)); }
 
     // the codes of the tile at k0 in what first(k0) and second(k0) hold (v is not read where p.cv_vec)
     template <class V>
@@ -159,8 +167,7 @@ struct ConvPieces {
         if (p.cv_vec) {                                        // uniform: one tap
             const int k = k0 + kq;
             const At a = at(p, k);
-            const int iw = iw0 + (int)div_magic((uint32_t)a.r, p.cv_magic_c);
-            const bool in = ok && k < p.K && (unsigned)(ih0 + a.kh) < (unsigned)p.cv_h && (unsigned)iw < (unsigned)p.cv_w;
+            const bool in = k < p.K && inside(p, a.kh) && a.r >= lo && a.r < hi;
             return in ? u : as_words<V>({0, 0});
         }
         if (!spans) {                                          // uniform: a few channels under a narrow filter, byte by byte
@@ -169,9 +176,8 @@ struct ConvPieces {
             for (int j = 0; j < 16; ++j) {
                 const int k = k0 + kq + j;
                 const At e = at(p, k);
-                int lo, hi;
-                if (k < p.K && inside(p, e.kh, lo, hi) && e.r >= lo && e.r < hi)
-                    (j < 8 ? b.lo : b.hi) |= (uint64_t)*address(p, e.kh, e.r) << (8 * (j & 7));
+                if (k < p.K && inside(p, e.kh) && e.r >= lo && e.r < hi)
+                    (j < 8 ? b.lo : b.hi) |= (uint64_t)X[offset(p, e.kh, e.r)] << (8 * (j & 7));
             }
             return as_words<V>(b);
         }
@@ -179,14 +185,11 @@ struct ConvPieces {
         const At a = at(p, k);
         const int left = p.cv_kw * p.cv_c - a.r, n1 = n < left ? n : left;   // of them in the first filter row
         Bytes16 x = {0, 0}, y = {0, 0};
-        int lo, hi;
-        if (n > 0 && inside(p, a.kh, lo, hi)) {
-            const uint8_t* q = address(p, a.kh, a.r);
-            x = keep_bytes(shift_bytes(as_bytes(u), (int)(q - clamped(q))), lo - a.r, n1 < hi - a.r ? n1 : hi - a.r);
+        if (n > 0 && inside(p, a.kh)) {
+            x = keep_bytes(shift_bytes(as_bytes(u), early(offset(p, a.kh, a.r))), lo - a.r, n1 < hi - a.r ? n1 : hi - a.r);
         }
-        if (n > n1 && inside(p, a.kh + 1, lo, hi)) {
-            const uint8_t* q = address(p, a.kh + 1, 0);
-            y = shift_bytes(keep_bytes(shift_bytes(as_bytes(v), (int)(q - clamped(q))), lo, n - n1 < hi ? n - n1 : hi), -n1);
+        if (n > n1 && inside(p, a.kh + 1)) {
+            y = shift_bytes(keep_bytes(shift_bytes(as_bytes(v), early(offset(p, a.kh + 1, 0))), lo, n - n1 < hi ? n - n1 : hi), -n1);
         }
         return as_words<V>({x.lo | y.lo, x.hi | y.hi});
     }

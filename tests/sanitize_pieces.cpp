@@ -104,10 +104,83 @@ static void long_chains() {
     CHECK(packed == 8 && plain == 22, "%d plans on packed carriers, %d not", packed, plain);
 }
 
+// im2col rows of an NHWC tensor: every piece of every row of the tile rows at r0
+static void check_conv(const Operand& op, size_t off, int n, int h, int w, int c, int kh, int kw, int stride, int pad) {
+    const uint8_t* X = op.base + off;
+    const int64_t oh = ((int64_t)h + 2 * (int64_t)pad - kh) / stride + 1, ow = ((int64_t)w + 2 * (int64_t)pad - kw) / stride + 1;
+    const int64_t total = (int64_t)n * h * w * c;
+    lba::KParams p = {};
+    p.M = (int32_t)(n * oh * ow); p.K = kh * kw * c;
+    p.conv = 1; p.cv_h = h; p.cv_w = w; p.cv_c = c; p.cv_kw = kw; p.cv_stride = stride; p.cv_pad = pad; p.cv_oh = (int32_t)oh; p.cv_ow = (int32_t)ow;
+    p.cv_vec = (c % 16 == 0 && (uintptr_t)X % 16 == 0) ? 1 : 0;
+    p.cv_magic_c = (((uint64_t)1 << 40) + (uint64_t)c - 1) / (uint64_t)c;
+    p.cv_magic_kw = (((uint64_t)1 << 40) + (uint64_t)kw - 1) / (uint64_t)kw;
+    const int ntiles = (p.K + 63) / 64;
+    for (int r = 0; r <= p.M; ++r) {
+        if (r > 300 && r < p.M - 100) continue;
+        for (int q = 0; q < 4; ++q) {
+            const lba::ConvPieces s = lba::ConvPieces::make<kRows>(X, p, r / kRows * kRows, r % kRows + kRows * q);
+            for (int t = 0; t < ntiles + 4; ++t) {
+                if (t > 40 && t < ntiles - 3) continue;
+                const int k0 = lba::tile_start(t);
+                const uint8_t* a = s.first(p, k0);
+                const uint8_t* b = p.cv_vec ? a : s.second(p, k0);
+                const bool in = a >= X && a + 16 <= X + total && b >= X && b + 16 <= X + total;
+                CHECK(in, "%dx%dx%dx%d kw %d stride %d pad %d row %d tile %d: loads at %lld and %lld", n, h, w, c, kw, stride, pad, r, t,
+                      (long long)(a - X), (long long)(b - X));
+                if (!in || t >= ntiles) continue;
+                const Words got = s.codes(p, load(a), load(b), k0);
+                uint8_t want[16] = {};
+                for (int j = 0; j < 16; ++j) {
+                    const int64_t k = (int64_t)t * 64 + 16 * q + j, tap = k / c;
+                    if (r >= p.M || k >= p.K) continue;
+                    const int64_t ih = r / ow % oh * stride - pad + tap / kw, iw = r % ow * stride - pad + tap % kw;
+                    if (ih >= 0 && ih < h && iw >= 0 && iw < w) want[j] = X[((r / (oh * ow) * h + ih) * w + iw) * c + k % c];
+                }
+                CHECK(std::memcmp(&got, want, 16) == 0, "%dx%dx%dx%d kw %d stride %d pad %d row %d tile %d piece %d: wrong codes", n, h, w, c,
+                      kw, stride, pad, r, t, q);
+            }
+        }
+    }
+}
+
+// padding far beyond the image: distances in codes of 2^31 and more, output rows up to w + pad codes to the right of it
+static void wide_padding() {
+    for (int c : {1, 3, 5, 17, 1000, 16368, 16383})
+        for (int kw : {1, 2, 3, 7})
+            for (int64_t pad : {(1LL << 31) / c - 1, (1LL << 31) / c + 1, (1LL << 32) / c - 2, (1LL << 32) / c + 3, (1LL << 31) - 1}) {
+                if (pad > 2147483647LL) continue;
+                Operand op((size_t)2 * 3 * 4 * c + 32);
+                op.fill(0, (size_t)2 * 3 * 4 * c + 32);
+                for (int64_t stride : {pad, pad / 2 + 1, pad - 1})
+                    for (int off : {0, 1}) check_conv(op, (size_t)off, 2, 3, 4, c, 2, kw, (int)stride, (int)pad);
+            }
+    Operand row((size_t)2147483647);                           // the widest image
+    row.fill(0, 64);
+    row.fill(2147483647u - 64, 64);
+    for (int kw : {1, 3, 16, 20})
+        for (int pad : {0, 1, 2147483647})
+            for (int stride : {2147483647, 2147483646, 1 << 30}) check_conv(row, 0, 1, 1, 2147483647, 1, 1, kw, stride, pad);
+}
+
+// ordinary convolutions, some thousand
+static void convolutions() {
+    for (int i = 0; i < 3000; ++i) {
+        const int n = 1 + below(3), h = 1 + below(12), w = 1 + below(12), kh = 1 + below(5), kw = 1 + below(8);
+        const int c = (const int[]){1, 2, 3, 4, 5, 8, 15, 16, 17, 32, 48}[below(11)], pad = below(6), stride = 1 + below(3), off = below(2) * below(16);
+        if (h + 2 * pad < kh || w + 2 * pad < kw || n * h * w * c < 16) continue;
+        Operand op((size_t)n * h * w * c + off);
+        op.fill(0, op.bytes);
+        check_conv(op, (size_t)off, n, h, w, c, kh, kw, stride, pad);
+    }
+}
+
 int main(int argc, char** argv) {
     if (argc != 2) { std::printf("usage: %s <check>\n", argv[0]); return 2; }
     if (!std::strcmp(argv[1], "far_rows")) far_rows();
     else if (!std::strcmp(argv[1], "long_chains")) long_chains();
+    else if (!std::strcmp(argv[1], "convolutions")) convolutions();
+    else if (!std::strcmp(argv[1], "wide_padding")) wide_padding();
     else { std::printf("no such check\n"); return 2; }
     if (failures) { std::printf("%d failures\n", failures); return 1; }
     std::printf("pieces ok\n");
