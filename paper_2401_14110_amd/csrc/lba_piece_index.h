@@ -64,8 +64,10 @@ LBA_HOST_DEVICE int tile_start(int t) { return t * HBK; }
 template <int ROWS>
 struct RowPieces {
     const uint8_t* row;        // the lane's row (a row of the matrix in any case)
-    const uint8_t* last;       // the last address from which 16 bytes lie inside the matrix (which holds at least 16)
     int K, kq;
+    int room;                  // the last k from which 16 bytes lie inside the matrix (which holds at least 16): -15 or more, and
+                               // taken as 2^31 - 1 where it is larger
+    int end;                   // of K and room the smaller
     bool ok, whole;            // the row exists; K % 16 == 0 (uniform): every piece is inside its row or beyond it
 
     LBA_HOST_DEVICE RowPieces(const uint8_t* G, int rows, int K_, int r0, int c) {
@@ -74,14 +76,15 @@ struct RowPieces {
         K = K_;
         kq = c >= 0 ? c / ROWS * 16 : 0;
         row = G + (int64_t)(ok ? r : 0) * K;
-        last = G + ((int64_t)rows * K - 16);
+        const int64_t left = (int64_t)(rows - (ok ? r : 0)) * K - 16;
+        room = left < 0x7FFFFFFF ? (int)left : 0x7FFFFFFF;
+        end = K < room ? K : room;
         whole = (K & 15) == 0;
     }
     // where the 16 bytes of the tile at k0 are loaded from
     LBA_HOST_DEVICE const uint8_t* address(int k0) const {
         const int k = k0 + kq;
-        const uint8_t* p = row + (k < K ? k : K);
-        return p < last ? p : last;
+        return row + (k < end ? k : end);
     }
     // the codes of the tile at k0 in what address(k0) holds: zero beyond the row and outside the matrix
     template <class V>
@@ -92,10 +95,9 @@ struct RowPieces {
             return v;
         }
         if (n < 16) {
-            const uint8_t* p = row + (k0 + kq);
+            const int back = k0 + kq - room;                   // > 0: the load started that many bytes early (15 at most)
             Bytes16 b = as_bytes(v);
-            if (n > 0 && p > last) b = shift_bytes(b, (int)(p - last));   // the load started at most 15 bytes early (before
-                                                               // the last rows the difference is as large as the operand)
+            if (n > 0 && back > 0) b = shift_bytes(b, back);
             v = as_words<V>(keep_bytes(b, 0, n));
         }
         return v;
