@@ -219,8 +219,9 @@ size_t lba_mask_words_level2(int64_t M, int64_t N, int64_t K);
  * split across workgroups and combined with atomic adds), so results are reproducible up to FP32
  * rounding: |error| <= (terms + 1) * 2^-24 * sum of |terms| to first order.  The identity estimator runs on the
  * matrix cores, the recursive one when G and last_of are 16-byte aligned, N % 4 == 0 and K <= 12288: g is split exactly into three bfloat16
- * pieces whose products with the FP8 values are exact; gradient values below about 2^-100 may lose
- * pieces to the flush of subnormal numbers there.
+ * pieces whose products with the FP8 values are exact.  Where G is 16-byte aligned and N % 4 == 0, gradient values below
+ * about 2^-100 may lose pieces to the flush of subnormal numbers there and an infinite one gives NaN; any other G is
+ * summed as FP32 multiply-adds would, infinities and normal numbers down to 2^-126 included.
  */
 enum { LBA_STE_IDENTITY = 0, LBA_STE_IMMEDIATE_OF = 1, LBA_STE_RECURSIVE_OF = 2,
        LBA_STE_COEF_PLANE = 3 };   /* lba_grad only: of_mask holds the coefficients themselves (lba_ste_plane) */

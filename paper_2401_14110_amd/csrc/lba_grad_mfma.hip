@@ -8,8 +8,10 @@
 // (g = hi + mid + lo, 8 significant bits each: truncate, subtract, truncate, subtract; every step is exact),
 // an E4M3 value is a bfloat16 number as it is, so the three bfloat16 products hi*v, mid*v, lo*v are exact
 // and their FP32 accumulation in v_mfma_f32_32x32x16_bf16 is the FP32 sum of products the interface
-// promises (order of summation unspecified; pieces or products below the FP32 normal range, i.e. gradients
-// under about 2^-100, may be flushed).  Three MFMA passes at the bfloat16 rate are about five times
+// promises (order of summation unspecified).  Values that do not split exactly, infinities and those under 2^-94 whose
+// pieces or products may fall below the FP32 normal range and be flushed, are left out of the tile and added in FP32
+// where the vector kernel used to serve the call (a width that is no multiple of 4, G off 16 bytes: add_unsplit); with
+// aligned G they lose their low pieces, and an infinity gives NaN.  Three MFMA passes at the bfloat16 rate are about five times
 // the FP32 rate of the vector units or of the FP32 MFMA.
 //
 // The recursive estimator under the sequential order (App. D: c = [k > last overflow index L(r, s)]) is the same
@@ -84,11 +86,86 @@ __device__ __forceinline__ void decode4(uint32_t w, float (&v)[4]) {
     }
 }
 
+// Does g split with nothing lost?  True of zeros and of 2^-94 <= |g| < infinity: no piece and no product of a piece is below
+// the FP32 normal range then (the last piece's lowest bit is 2^-23 of the value, a code's 2^-9 of one).
+constexpr uint32_t kSplitLeast = (127 - 94) << 23, kSplitInf = 0x7F800000u;
+__device__ __forceinline__ bool splits(float g) {
+    const uint32_t u = __float_as_uint(g) & 0x7FFFFFFFu;
+    return u == 0u || (u >= kSplitLeast && u < kSplitInf);
+}
+// The same of a whole patch, from its bfloat16 heads two at a time: four instructions for two words.  (A value with a head of 0
+// is an FP32 denormal number, which counts as zero.)
+struct SplitRange {
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
+    u16x2 low = {0xFFFF, 0xFFFF};      // smallest head - 1; 0xFFFF for zeros
+    i16x2 high = {-1, -1};             // largest head - 1; -1 for zeros
+    __device__ __forceinline__ void add(uint32_t heads) {
+        const u16x2 h = __builtin_bit_cast(u16x2, heads & 0x7FFF7FFFu) + u16x2{0xFFFF, 0xFFFF};
+        low = __builtin_elementwise_min(low, h);
+        high = __builtin_elementwise_max(high, __builtin_bit_cast(i16x2, h));
+    }
+    __device__ __forceinline__ bool outside() const {
+        constexpr uint16_t least = kSplitLeast >> 16;
+        constexpr int16_t inf = kSplitInf >> 16;
+        return low[0] < least - 1 || low[1] < least - 1 || high[0] >= inf - 1 || high[1] >= inf - 1;
+    }
+};
+
+// The terms of one workgroup's tile and range of s whose g do not split (infinities, NaN, values under 2^-94), which the tile
+// left out: added to the output in FP32.  A wave takes one row after the other, finds its such values 64 s at a time and adds
+// them with its lanes along k, as the vector kernel of lba_grad.hip would.  For the few values it is meant for: one infinity in
+// 3985 x 770 x 771 takes dX from 68 to 117 us and dW from 95 to 171, G wholly under 2^-94 takes them to 1.9 and 2.8 ms (the vector
+// kernel: 0.87 and 0.75 ms).  Testing for such values costs the others 2 to 4 %; the FP32 matrix instruction for a step that
+// holds one, in this loop, took registers up to spilling and cost 1.1 % of the whole training step instead of 0.6 %.
+template <bool S_CONTIG, int DTK>
+__device__ __forceinline__ void add_unsplit(const float* __restrict__ G, const uint8_t* __restrict__ V, float* out, const DenseDims& d,
+                                         const uint8_t* __restrict__ brick_row, int r0, int k0, int s_begin, int s_end) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int r = r0 + wave; r < min(r0 + DTR, d.R); r += 4) {
+        float sum[DTK / 64];
+#pragma unroll
+        for (int i = 0; i < DTK / 64; ++i) sum[i] = 0.0f;
+        uint64_t any = 0;
+        for (int s0 = s_begin; s0 < s_end; s0 += 64) {
+            const int s = s0 + lane;
+            float g = 0.0f;
+            if (s < s_end && !(brick_row && brick_row[s >> 5])) g = G[S_CONTIG ? (int64_t)r * d.ld_g + s : (int64_t)s * d.ld_g + r];
+            uint64_t todo = __builtin_amdgcn_ballot_w64(!splits(g));
+            any |= todo;
+            while (todo) {                                     // uniform over the wave: eight of them, their codes in flight together
+                float gs[8];
+                const uint8_t* rows[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const int j = todo ? __builtin_ctzll(todo) : 0;
+                    gs[q] = todo ? __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(g), j)) : 0.0f;
+                    rows[q] = V + (int64_t)(s0 + j) * d.K;
+                    todo &= todo - 1;
+                }
+#pragma unroll
+                for (int i = 0; i < DTK / 64; ++i) {
+                    const int k = k0 + 64 * i + lane;
+                    uint32_t code[8];
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) code[q] = k < d.K ? rows[q][k] : 0u;
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) sum[i] = __builtin_fmaf(gs[q], dense_decode_e4m3(code[q]), sum[i]);
+                }
+            }
+        }
+        if (any)                                               // uniform over the wave
+#pragma unroll
+            for (int i = 0; i < DTK / 64; ++i)
+                if (k0 + 64 * i + lane < d.K) unsafeAtomicAdd(out + (int64_t)r * d.K + k0 + 64 * i + lane, sum[i]);
+    }
+}
+
 // S_CONTIG: G(r, s) = G[r * ld + s] (dX); else G(r, s) = G[s * ld + r] (dW).  MASKED: L (same layout as G)
 // holds last-overflow indices and g' = [L < k0] g.  GVEC: G is 16-byte aligned and N % 4 == 0, so that a patch row is one
-// 16-byte load that lies inside the matrix or outside; otherwise its four values are loaded one by one (3985 x 770 x 771:
-// dX 71 us, dW 93 us, bound by the chain load -> split -> LDS -> barrier like the others; the vector kernel took such
-// shapes before, 2.0 and 2.5 ms).
+// 16-byte load that lies inside the matrix or outside; otherwise its four values are loaded one by one (identity, 3985 x 770 x
+// 771: dX 68 us, dW 95 us, bound by the chain load -> split -> LDS -> barrier like the others; the vector kernel took such
+// shapes before, 873 and 747 us).
 template <bool S_CONTIG, bool MASKED, int DTK, bool BYTES = false, bool GVEC = true>
 __global__ void __launch_bounds__(256, 2) lba_grad_dense_kernel(const float* __restrict__ G, const uint8_t* __restrict__ V,
                                                                 const int32_t* __restrict__ L,
@@ -182,6 +259,7 @@ __global__ void __launch_bounds__(256, 2) lba_grad_dense_kernel(const float* __r
     // Immediate estimator: a brick (128 rows x 32 s x 256 k) in which some coefficient is 0 is left to the vector
     // kernel, which applies the coefficients bit by bit; this kernel adds the bricks whose coefficients are all 1.
     const uint8_t* __restrict__ brick_row = bricks ? bricks + ((int64_t)(k0 >> 8) * d.brick_rb + (r0 >> 7)) * d.brick_sb : nullptr;
+    bool unsplit = false;                                      // uniform over the wave: some g of its patches did not split
     fetch(s_begin);
     for (int sb = s_begin; sb < s_end; sb += DBS) {
         if (brick_row && brick_row[sb >> 5]) {                 // uniform over the workgroup
@@ -204,13 +282,34 @@ __global__ void __launch_bounds__(256, 2) lba_grad_dense_kernel(const float* __r
                     if (S_CONTIG) g[q][e] = x[e]; else g[e][q] = x[e];
                 }
             }
+            uint32_t heads[4][2];                              // the first pieces, two to a word
+            auto take_heads = [&] {
+#pragma unroll
+                for (int a = 0; a < 4; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) heads[a][b] = pack_hi(__float_as_uint(g[a][2 * b]), __float_as_uint(g[a][2 * b + 1]));
+            };
+            take_heads();
+            if (!GVEC) {                                       // what does not split is added at the end
+                SplitRange range;
+#pragma unroll
+                for (int a = 0; a < 4; ++a) { range.add(heads[a][0]); range.add(heads[a][1]); }
+                if (__builtin_amdgcn_ballot_w64(range.outside())) {            // uniform over the wave; rare
+                    unsplit = true;
+#pragma unroll
+                    for (int a = 0; a < 4; ++a)
+#pragma unroll
+                        for (int b = 0; b < 4; ++b) g[a][b] = splits(g[a][b]) ? g[a][b] : 0.0f;
+                    take_heads();
+                }
+            }
 #pragma unroll
             for (int a = 0; a < 4; ++a) {
                 uint32_t h[4], m[4], l[4];
 #pragma unroll
                 for (int b = 0; b < 4; ++b) split3(g[a][b], h[b], m[b], l[b]);
                 const int off = (4 * a_pr + a) * DPITCH + 4 * a_ps;
-                *reinterpret_cast<uint2*>(&sA[0][off]) = make_uint2(pack_hi(h[0], h[1]), pack_hi(h[2], h[3]));
+                *reinterpret_cast<uint2*>(&sA[0][off]) = make_uint2(heads[a][0], heads[a][1]);
                 *reinterpret_cast<uint2*>(&sA[1][off]) = make_uint2(pack_hi(m[0], m[1]), pack_hi(m[2], m[3]));
                 *reinterpret_cast<uint2*>(&sA[2][off]) = make_uint2(pack_hi(l[0], l[1]), pack_hi(l[2], l[3]));
             }
@@ -273,6 +372,16 @@ __global__ void __launch_bounds__(256, 2) lba_grad_dense_kernel(const float* __r
                 }
             }
         }
+    if (!GVEC) {
+        uint32_t* flags = reinterpret_cast<uint32_t*>(&sB[0]); // (the last step's barrier is behind every wave)
+        if (lane == 0) flags[wave] = unsplit ? 1u : 0u;
+        __syncthreads();
+        if (flags[0] | flags[1] | flags[2] | flags[3]) {       // uniform over the workgroup; rare
+            __threadfence();                                   // every wave's stores above come before the additions
+            __syncthreads();
+            add_unsplit<S_CONTIG, DTK>(G, V, out, d, brick_row, r0, k0, s_begin, s_end);
+        }
+    }
 }
 
 // The sliver of the recursive estimator that the masked dense product leaves out: for every pair (r, s) with

@@ -525,3 +525,49 @@ def test_any_width_and_alignment_on_the_matrix_cores(ref, gref, M, N, K, offset)
             torch.cuda.synchronize()
             assert np.array_equal(dX.cpu().numpy(), wX.astype(np.float32)), (ste, w is None, "dX")
             assert np.array_equal(dW.cpu().numpy(), wW.astype(np.float32)), (ste, w is None, "dW")
+
+
+@pytest.mark.parametrize("M,N,K", [(40, 37, 70), (300, 201, 600), (131, 70, 257), (37, 515, 260)])
+@pytest.mark.parametrize("what", ["tiny", "mixed", "infinite"])
+def test_any_width_keeps_the_range_of_fp32(ref, gref, M, N, K, what):
+    # Widths that are no multiple of 4 split g into bfloat16 pieces too; a step whose g do not split exactly (infinities, NaN,
+    # values whose pieces would fall below FP32's normal range) runs in FP32.  tiny: all of G around 2^-118, whose last two
+    # pieces are denormal numbers; mixed: some of them zero or of ordinary size; infinite: a few infinities and one NaN among
+    # ordinary values, which reach their own row of dX and column of dW and nothing else.
+    # Bound: 2 (terms + 1) 2^-24 sum|terms| as elsewhere in this file, and 2^-126 a term for results flushed as denormal.
+    rng = np.random.default_rng([M, N, len(what)])
+    qp, qa = (4, 7, 12, 0), (4, 7, 10, 0)
+    A = codes(rng, (M, K), 2, 5); B = codes(rng, (N, K), 2, 5)
+    A[:, K - K // 3:] = codes(rng, (M, K // 3), 6, 10); B[N // 2:, K - K // 3:] = codes(rng, (N - N // 2, K // 3), 6, 10)
+    tA, tB = torch.from_numpy(A).to(DEV), torch.from_numpy(B).to(DEV)
+    _, of, _ = lb.gemm_bwd(tA, tB, qp, qa, want_c=False)
+    coef = lb.ste_plane(of, K, lb.STE_RECURSIVE_OF)
+    G = rng.standard_normal((M, N)).astype(np.float32)
+    G = np.where(np.abs(G) < 2.0 ** -8, np.float32(2.0 ** -8), G)     # (times 2^-118: the smallest normal number)
+    if what == "tiny":
+        G *= np.float32(2.0 ** -118)
+    elif what == "mixed":
+        G[rng.random((M, N)) < 0.3] = 0.0
+        G[:, N // 2:] *= np.float32(2.0 ** -112)
+        G[: M // 2, : N // 2] *= np.float32(2.0 ** -98)
+    else:
+        for v in (np.inf, -np.inf, np.inf, np.nan):
+            G[rng.integers(M // 2), rng.integers(N // 2)] = v
+    tG = torch.from_numpy(G).to(DEV)
+    ws = torch.full((max(256, lb.lba_grad_workspace_bytes_fast(M, N, K)),), 0x5A, dtype=torch.uint8, device=DEV)
+    finite = np.where(np.isfinite(G), G, 0.0)
+    for ste, plane, est in ((lb.STE_IDENTITY, None, 0), (lb.STE_IMMEDIATE_OF, of, 1), (lb.STE_COEF_PLANE, coef, 2)):
+        c = gref.coefficients(A, B, ref.QFmt(*qp), ref.QFmt(*qa), est)
+        tab = gref.decode_table()
+        gc = np.where(c, G.astype(np.float64)[:, :, None], 0.0)
+        with np.errstate(invalid="ignore"):
+            wX, wW = (gc * tab[B][None]).sum(1), (gc * tab[A][:, None]).sum(0)
+        aX, aW = gref.grad_abs(finite, A, B, ref.QFmt(*qp), ref.QFmt(*qa), est, c=c)
+        for w in (ws, ws[:max(256, lb.lba_grad_workspace_bytes(M, N, K))], None):
+            dX, dW = lb.grad(tG, tA, tB, ste, of_plane=plane, workspace=w)
+            torch.cuda.synchronize()
+            for got, want, scale, terms in ((dX.cpu().numpy(), wX, aX, N), (dW.cpu().numpy(), wW, aW, M)):
+                ok = np.isfinite(want)
+                assert ok.all() == (what != "infinite")
+                assert np.array_equal(got[~ok], want[~ok].astype(np.float32), equal_nan=True), (ste, w is None)
+                assert (np.abs(got[ok] - want[ok]) <= 2 * (terms + 1) * 2.0 ** -24 * scale[ok] + terms * 2.0 ** -126).all(), (ste, w is None)
