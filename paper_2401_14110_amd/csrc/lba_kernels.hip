@@ -180,7 +180,7 @@ int lba_gemm_bwd_ws(const uint8_t* A, const uint8_t* B, float* C, uint32_t* of_m
     if (!A || !B) return LBA_ERR_NULL;
     hipStream_t st = (hipStream_t)hip_stream;
     // the scaled-domain recompute kernel marks the bricks itself; after the general kernel one pass over the plane
-    // does (or, where that pass cannot read the plane in 16-byte groups, every brick is marked)
+    // does (or, for a plane off a 16-byte boundary, which that pass does not read, every brick is marked)
     const bool fused = pl.kernel == lba::KERNEL_FAST;
     if (fused) {
         rc = lba::brick_maps_fill(workspace, M, N, K, false, st);
@@ -189,7 +189,7 @@ int lba_gemm_bwd_ws(const uint8_t* A, const uint8_t* B, float* C, uint32_t* of_m
     rc = lba::run(A, B, C, of_mask, uf_mask, M, N, K, qprod, qacc, LBA_ORDER_SEQ, events, hip_stream,
                   1, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, 0, 0, 0.0f, fused ? workspace : nullptr);
     if (rc != LBA_OK || fused) return rc;
-    if ((N % 4) == 0 && ((uintptr_t)of_mask % 16) == 0) return lba::brick_maps_scan(of_mask, workspace, M, N, K, 0u, st);
+    if (((uintptr_t)of_mask % 16) == 0) return lba::brick_maps_scan(of_mask, workspace, M, N, K, 0u, st);
     return lba::brick_maps_fill(workspace, M, N, K, true, st);
 }
 

@@ -398,9 +398,8 @@ def brick_maps_of(ofn, M, N, K):
 def test_recompute_call_leaves_the_brick_maps(ref, gref):
     # lba_gemm_bwd_ws + lba_grad_premapped: same C and planes as lba_gemm_bwd; the maps in the workspace are those of
     # the plane (computed here from the plane itself), whichever kernel wrote it: the scaled-domain kernel that marks
-    # bricks as it goes (floor and nearest-even, both planes or the overflow plane alone, plain and mixed grids), the
-    # general kernel followed by the pass over the plane, and the all-marked maps where that pass cannot run
-    # (N % 4 != 0).  Then the gradients from those maps against the oracle.
+    # bricks as it goes (floor and nearest-even, both planes or the overflow plane alone, plain and mixed grids), or the
+    # general kernel followed by the pass over the plane (any width).  Then the gradients from those maps against the oracle.
     rng = np.random.default_rng(4242)
     QPb, QAb = (4, 7, 12), (4, 7, 10)                                        # R_OF = 63.75
     GEN_P, GEN_A = (5, 3, 12), (4, 7, 10)                                    # Q_prod rounds the mantissa: general kernel with planes
@@ -432,15 +431,12 @@ def test_recompute_call_leaves_the_brick_maps(ref, gref):
             got = ws[:need].cpu().numpy()
             want = brick_maps_of(of1.cpu().numpy(), M, N, K)
             assert want.size == need
-            if plan["kernel"] == 1 and N % 4 != 0:
-                assert (got == 1).all(), (M, N, K, "all marked")
-                seen.add("all-marked")
-            else:
-                assert np.array_equal(got != 0, want != 0), (M, N, K, qp, rnd, plan["kernel"], int((got != 0).sum()), int(want.sum()))
-                seen.add(("general" if plan["kernel"] == 1 else "fused") + ("+mixed" if plan["tail_blocks"] + plan["mid_blocks"] > 0 else ""))
-                kb = (K + 255) // 256
-                bricks = kb * (((M + 127) // 128) * ((N + 31) // 32) + ((N + 127) // 128) * ((M + 31) // 32))
-                seen.add("clean" if not want.any() else ("dirty" if int(want.sum()) == bricks else "partly"))
+            assert np.array_equal(got != 0, want != 0), (M, N, K, qp, rnd, plan["kernel"], int((got != 0).sum()), int(want.sum()))
+            seen.add(("general" if plan["kernel"] == 1 else "fused") + ("+mixed" if plan["tail_blocks"] + plan["mid_blocks"] > 0 else "") +
+                     ("+ragged" if N % 4 != 0 else ""))
+            kb = (K + 255) // 256
+            bricks = kb * (((M + 127) // 128) * ((N + 31) // 32) + ((N + 127) // 128) * ((M + 31) // 32))
+            seen.add("clean" if not want.any() else ("dirty" if int(want.sum()) == bricks else "partly"))
             if qp is GEN_P and (M, N, K) != (300, 200, 600):
                 continue                                                     # gradients: once per shape, and once on the general kernel's plane
             G = rng.standard_normal((M, N)).astype(np.float32)
@@ -452,7 +448,37 @@ def test_recompute_call_leaves_the_brick_maps(ref, gref):
             aX, aW = gref.grad_abs(G, A, B, ref.QFmt(*qpf), ref.QFmt(*qaf), 1)
             assert (np.abs(dX - wX) <= 2 * (N + 1) * 2.0 ** -24 * aX + 1e-30).all(), (M, N, K, loud, "dX")
             assert (np.abs(dW - wW) <= 2 * (M + 1) * 2.0 ** -24 * aW + 1e-30).all(), (M, N, K, loud, "dW")
-    assert {"fused", "fused+mixed", "general", "all-marked", "clean", "dirty", "partly"} <= seen, seen
+    assert {"fused", "fused+mixed", "general", "general+ragged", "fused+ragged", "clean", "dirty", "partly"} <= seen, seen
+
+
+@pytest.mark.parametrize("M,N,K", [(70, 66, 100), (130, 64, 300)])
+def test_a_plane_off_a_16_byte_boundary_marks_every_brick(ref, gref, M, N, K):
+    # the general kernel's plane where the pass over it does not run: every brick is marked, and the gradients are the oracle's
+    rng = np.random.default_rng(M)
+    qp, qa = (5, 3, 12, 0), (4, 7, 10, 1)                                    # a rounded product and a nearest-even sum: the general kernel
+    A = codes(rng, (M, K), 4, 9); B = codes(rng, (N, K), 4, 9)
+    tA, tB = torch.from_numpy(A).to(DEV), torch.from_numpy(B).to(DEV)
+    assert lb.lba_plan_query(M, N, K, qp, qa, 0, 3)["kernel"] == 1
+    words = lb.lba_mask_words(M, N, K)
+    of = torch.empty(words + 4, dtype=torch.int32, device=DEV)[1:1 + words]
+    assert of.data_ptr() % 16 == 4
+    need = lb.lba_grad_workspace_bytes(M, N, K)
+    ws = torch.full((need,), 0x5A, dtype=torch.uint8, device=DEV)
+    assert lb.lba_gemm_bwd_ws(tA.data_ptr(), tB.data_ptr(), None, of.data_ptr(), None, M, N, K, qp, qa, ws.data_ptr(), need) == lb.OK
+    torch.cuda.synchronize()
+    assert bool((ws == 1).all())
+    _, wof, _ = ref.gemm_bwd(A, B, ref.QFmt(*qp), ref.QFmt(*qa))
+    assert wof.any() and np.array_equal(of.cpu().numpy().view(np.uint32).reshape(wof.shape), wof)
+    G = (rng.integers(-8, 9, (M, N)) / 4.0).astype(np.float32)
+    tG = torch.from_numpy(G).to(DEV)
+    dX, dW = torch.empty(M, K, device=DEV), torch.empty(N, K, device=DEV)
+    assert lb.lba_grad_premapped(tG.data_ptr(), tA.data_ptr(), tB.data_ptr(), of.data_ptr(), dX.data_ptr(), dW.data_ptr(), M, N, K,
+                                 ws.data_ptr(), need) == lb.OK
+    torch.cuda.synchronize()
+    wX, wW = gref.grad(G, A, B, ref.QFmt(*qp), ref.QFmt(*qa), 1)
+    aX, aW = gref.grad_abs(G, A, B, ref.QFmt(*qp), ref.QFmt(*qa), 1)
+    assert (np.abs(dX.cpu().numpy() - wX) <= 2 * (N + 1) * 2.0 ** -24 * aX + 1e-30).all()
+    assert (np.abs(dW.cpu().numpy() - wW) <= 2 * (M + 1) * 2.0 ** -24 * aW + 1e-30).all()
 
 
 def test_split_sums_combined_in_the_workspace(ref, gref):
