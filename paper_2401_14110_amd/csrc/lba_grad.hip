@@ -491,8 +491,8 @@ __global__ void __launch_bounds__(256) lba_brick_map_kernel(const uint32_t* __re
     const int words = (d.K + 31) >> 5;
     // the workgroup's first group: row (w, m) of the [words * M][N] matrix and position in it, computed once
     const int64_t q0 = (int64_t)blockIdx.x * kBrickQuadsPerWg;
-    const int64_t row0 = RAGGED ? 0 : q0 / d.qpr;
-    const int rem0 = RAGGED ? 0 : (int)(q0 - row0 * d.qpr);
+    const int64_t row0 = RAGGED ? 4 * q0 / d.N : q0 / d.qpr;   // position: in groups, or (RAGGED) in words
+    const int rem0 = (int)(RAGGED ? 4 * q0 - row0 * d.N : q0 - row0 * d.qpr);
     const int w0 = (int)(row0 / d.M);
     const int m0 = (int)(row0 - (int64_t)w0 * d.M);
     auto mark = [&](int w, int m, int n, uint32_t raw) {
@@ -538,9 +538,9 @@ __global__ void __launch_bounds__(256) lba_brick_map_kernel(const uint32_t* __re
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     if (e[u] == 0u) continue;
-                    const int64_t i = 4 * (q0 + l) + u, row = i / d.N;
-                    const int w = (int)(row / d.M);
-                    mark(w, (int)(row - (int64_t)w * d.M), (int)(i - row * d.N), e[u]);
+                    const uint32_t t = (uint32_t)rem0 + 4u * (uint32_t)l + (uint32_t)u, dr = t / (uint32_t)d.N;
+                    const uint32_t m = (uint32_t)m0 + dr, dw = m / (uint32_t)d.M;
+                    mark(w0 + (int)dw, (int)(m - dw * (uint32_t)d.M), (int)(t - dr * (uint32_t)d.N), e[u]);
                 }
             } else {
                 const int t = rem0 + l;
@@ -671,13 +671,14 @@ static int run_grad_side(bool dx, const float* G, const uint8_t* V, const uint32
     const int64_t gx = (gp.R + 63) / 64, gy = (K + 63) / 64;      // row blocks on x (no 65535 limit there)
     int split = 1;
     plan_grad_split(gx * gy, gp.S, &split, &gp.s_chunk);
+    const uintptr_t al = (uintptr_t)G | (uintptr_t)plane | (uintptr_t)last_of;
+    gp.vec_ok = ((al % 16) == 0 && (N % 4) == 0) ? 1 : 0;
     if (bricks) {                                              // slices of s on brick boundaries
-        gp.s_chunk = (gp.s_chunk + 31) / 32 * 32;
+        // (rows that are read value by value run longest, one s after the other: no slice longer than without bricks)
+        gp.s_chunk = gp.vec_ok ? (gp.s_chunk + 31) / 32 * 32 : (gp.s_chunk < 64 ? 32 : gp.s_chunk / 32 * 32);
         split = (int)((gp.S + gp.s_chunk - 1) / gp.s_chunk);
     }
     gp.atomic = (split > 1 || bricks) ? 1 : 0;
-    const uintptr_t al = (uintptr_t)G | (uintptr_t)plane | (uintptr_t)last_of;
-    gp.vec_ok = ((al % 16) == 0 && (N % 4) == 0) ? 1 : 0;
     gp.v16 = (((uintptr_t)V % 16) == 0 && (K % 16) == 0) ? 1 : 0;
     if (gp.atomic && !bricks) {
         const int64_t n = (int64_t)gp.R * K;
