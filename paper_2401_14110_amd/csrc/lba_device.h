@@ -902,24 +902,10 @@ __device__ __forceinline__ void store_event_words(uint32_t* of_plane, uint32_t* 
     }
 }
 
-// The same tile on packed FP16 carriers (lba_half.h): LX lanes along n.
-template <int TM, int TN, int LX, int PM, int ORDER, int AMODE>
-__device__ __forceinline__ void half_body(const KParams& p, uint32_t* __restrict__ smem, int m0, int n0);
-
-// Plain grids of other operand formats (AMODE 1) host both carriers and the planner's choice is uniform (p.h_on).  Every other
-// call on packed carriers has kernels of its own (lba_half.hip, lba_half_conv.hip): an FP32 body beside the other one ran
-// 1.5 % slower.
 template <int TM, int TN, int BK, int PM, int RND, int ORDER, int AMODE = 0>
 __global__ void __launch_bounds__(256, LBA_FAST_MIN_WAVES) lba_fast_kernel(const KParams p) {
     __shared__ __attribute__((aligned(16))) float smem[2 * fast_stage_depth(TM, TN, BK) * 16 * (TM + TN)];
-    const int m0 = blockIdx.x * 16 * TM, n0 = blockIdx.y * 16 * TN;
-    if constexpr (AMODE == 1 && RND == LBA_ROUND_FLOOR && (PM == PM_IDENT || PM == PM_FLUSH || PM == PM_TRUNC)) {
-        if (p.h_on) {
-            half_body<TM, TN, 16, PM, ORDER, AMODE>(p, reinterpret_cast<uint32_t*>(smem), m0, n0);
-            return;
-        }
-    }
-    fast_body<TM, TN, BK, PM, RND, ORDER, AMODE>(p, smem, m0, n0);
+    fast_body<TM, TN, BK, PM, RND, ORDER, AMODE>(p, smem, blockIdx.x * 16 * TM, blockIdx.y * 16 * TN);
 }
 
 // Mixed grid for launches that would leave the last round of 64 x 64 workgroups half empty, or a CU with an odd
@@ -1931,7 +1917,5 @@ __global__ void __launch_bounds__(256) lba_gen_kernel(const KParams p) {
 }
 
 }  // namespace lba
-
-#include "lba_half.h"
 
 #endif

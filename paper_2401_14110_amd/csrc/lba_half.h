@@ -342,7 +342,8 @@ __device__ __forceinline__ void half_body(const KParams& p, uint32_t* __restrict
     // flight (C = 3 under a 7 x 7 filter: two loads a piece instead of sixteen, 279 -> 255 us).  Either kind of
     // code in the other's kernel, behind a uniform branch, cost the aligned shapes 1 to 4 %.
     constexpr bool SMALL = TM * TN <= 4, PIECES = SMALL || AMODE >= 3;
-    const bool conv = AMODE == 2 || AMODE == 4 || (AMODE == 1 && p.conv);    // uniform
+    static_assert(AMODE == 0 || AMODE == 2 || AMODE == 3 || AMODE == 4, "other operand formats decode alike: no AMODE of their own");
+    constexpr bool conv = AMODE == 2 || AMODE == 4;
     const RowPieces<BM> sa(pA, conv ? 1 : p.M, p.K, conv ? 0 : m0, tid);
     const RowPieces<BN> sb(pB, p.N, p.K, n0, tidb);
     ConvPieces sc = {};
@@ -358,11 +359,6 @@ __device__ __forceinline__ void half_body(const KParams& p, uint32_t* __restrict
             if (conv) load_piece(sc, p, k0, ra[d], rc[d]);
             else      ra[d] = load_piece(sa, k0);
             rb[d] = load_piece(sb, k0);
-        } else if (AMODE == 1) {
-            uint4 va[1], vb[1];
-            fetch_tile_a<BM, HBK>(pA, p, m0, k0, tid, va);
-            fetch_tile<BN, HBK>(pB, p.N, p.K, n0, k0, p.ld_align, tidb, vb);
-            ra[d] = va[0]; rb[d] = vb[0];
         } else {
             ra[d] = AMODE == 2 ? fetch_taps(cl, p, k0) : fetch_aligned<BM>(pA, p.M, p.K, m0, k0, tid);
             rb[d] = fetch_aligned<BN>(pB, p.N, p.K, n0, k0, tidb);

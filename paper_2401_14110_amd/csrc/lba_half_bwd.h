@@ -23,7 +23,7 @@
 #ifndef LBA_HALF_BWD_H_
 #define LBA_HALF_BWD_H_
 
-#include "lba_device.h"
+#include "lba_half.h"
 
 namespace lba {
 

@@ -1,5 +1,5 @@
 // lba_half_conv.hip -- instantiations of the forward kernels on packed FP16 carriers (lba_half.h) for im2col rows of an NHWC tensor.
-#include "lba_device.h"
+#include "lba_half.h"
 #include "lba_launch.h"
 
 namespace lba {
@@ -19,8 +19,11 @@ template <int ORDER, int AMODE>
 static hipError_t launch_order(const Plan& pl, hipStream_t st) {
     if (pl.prod_mode == PM_IDENT) return launch_one<PM_IDENT, ORDER, AMODE>(pl, st);
     if (pl.prod_mode == PM_FLUSH) return launch_one<PM_FLUSH, ORDER, AMODE>(pl, st);
-    if (pl.prod_mode == PM_TRUNC && pl.mix_tail > 0) {            // (plain grids: lba_fast_kernel, AMODE 1)
-        hipLaunchKernelGGL((lba_half_mixed_kernel<PM_TRUNC, ORDER, AMODE>), dim3(pl.grid_x, pl.grid_y, pl.kp.batch), dim3(256), 0, st, pl.kp);
+    if (pl.prod_mode == PM_TRUNC) {                            // amode 1: mixed grids and the 4 x 4 lane block
+        const dim3 grid(pl.grid_x, pl.grid_y, pl.kp.batch), block(256);
+        if (pl.mix_tail > 0)               hipLaunchKernelGGL((lba_half_mixed_kernel<PM_TRUNC, ORDER, AMODE>), grid, block, 0, st, pl.kp);
+        else if (pl.tm == 4 && pl.tn == 4) hipLaunchKernelGGL((lba_half_kernel<4, 4, PM_TRUNC, ORDER, AMODE>), grid, block, 0, st, pl.kp);
+        else return hipErrorInvalidValue;
         return hipGetLastError();
     }
     return hipErrorInvalidValue;

@@ -20,7 +20,7 @@ static hipError_t launch_plan(const Plan& pl, hipStream_t st) {
     if (pl.kernel == KERNEL_FAST && pl.events == 2) return launch_fast_diff(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.events && pl.kp.h_on) return launch_half_bwd(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.events) return launch_fast_bwd(pl, st);
-    if (pl.kernel == KERNEL_FAST && pl.kp.h_on && (pl.amode != 1 || pl.mix_tail > 0)) return pl.kp.conv ? launch_half_conv(pl, st) : launch_half(pl, st);
+    if (pl.kernel == KERNEL_FAST && pl.kp.h_on) return pl.kp.conv ? launch_half_conv(pl, st) : launch_half(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.rne_odd) return launch_fast_odd(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.amode == 2) return launch_fast_conv(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.amode == 1 && pl.mix_tail > 0)
@@ -62,7 +62,7 @@ static void plan_kernel_name(const Plan& pl, bool uf, char* buf, size_t n) {
         else if (pl.amode)        snprintf(buf, n, "lba_fast_bwd_kernel<%d, 0, 0, %s, 1>", pm, b);
         else if (pl.mix_tail > 0) snprintf(buf, n, "lba_fast_bwd_mixed_kernel<%d, %d, %s>", pm, pl.round, b);
         else                      snprintf(buf, n, "lba_fast_bwd_kernel<%d, %d, %d, %s, 0>", pm, pl.round, ord, b);
-    } else if (pl.kp.h_on && (pl.amode != 1 || pl.mix_tail > 0)) {
+    } else if (pl.kp.h_on) {
         const int am = (pl.amode == 2 ? 2 : 0) + (pl.kp.K % 16 == 0 ? 0 : (pl.amode == 2 ? 2 : 3));      // (operands on a 16-byte boundary)
         if (pl.mix_tail > 0) snprintf(buf, n, "lba_half_mixed_kernel<%d, %d, %d>", pm, ord, am);
         else                 snprintf(buf, n, "lba_half_kernel<%d, %d, %d, %d, %d>", pl.tm, pl.tn, pm, ord, am);

@@ -304,3 +304,17 @@ def test_workspace_sizes_of_the_gradient_calls():
     assert extra > 0 and extra % (512 * 128 * 4) == 0          # whole slices of dW [512, 128]; dX [50176, 128] fills the chip uncut
     for bad in [(0, 8, 8), (8, 0, 8), (8, 8, 0), (-1, 8, 8), (1 << 31, 8, 8), (1 << 20, 1 << 11, 64)]:
         assert lb.lba_grad_workspace_bytes_fast(*bad) == 0 and lb.lba_grad_workspace_bytes(*bad) == 0
+
+
+def test_one_carrier_to_a_kernel():
+    # a call whose chains fit packed FP16 carriers has a kernel of its own on every grid, whatever its operand formats; the FP32
+    # kernels of other operand formats hold no second body
+    name = lb.lba_plan_kernel_name_in
+    m4e3, e5m2 = (3, 4, 3), (5, 2, 15)
+    for M, N, mixed in [(8192, 4096, False), (2048, 1024, False), (64, 1000, True), (3136, 512, True)]:
+        for K, order in ((512, 0), (512, 1), (147, 0), (147, 1)):
+            got = name(M, N, K, m4e3, m4e3, (5, 7, 1, 0), (4, 7, 2, 0), order)
+            assert got.startswith("lba_half_mixed_kernel<3" if mixed else "lba_half_kernel<4, 4, 3"), (M, N, K, got)
+            assert got.endswith(", 0>" if K % 16 == 0 else ", 3>"), got
+            assert name(M, N, K, m4e3, m4e3, (5, 7, 6, 0), (5, 10, 15, 0), order).startswith("lba_fast"), "a wide accumulator"
+            assert name(M, N, K, e5m2, m4e3, (5, 7, 6, 0), (4, 7, 7, 0), order).startswith("lba_fast"), "E = 5"

@@ -80,6 +80,25 @@ def test_operand_formats(ref, fa, fb):
             assert np.array_equal(bits(got), bits(want)), (M, N, K, qp, qa, order)
 
 
+@pytest.mark.parametrize("K", [96, 147])
+def test_operand_formats_on_plain_grids(ref, K):
+    # 64 x 64 workgroups throughout (512 of them): products kept, flushed and truncated; sampled rows, the tiles' edges among them
+    rng = np.random.default_rng(K)
+    M, N = 2048, 1024
+    rows = np.array(sorted({0, 1, 63, 64, M - 1} | set(int(r) for r in rng.integers(0, M, 40))))
+    for fa, fb in [((3, 4, 3), (3, 4, 3)), ((2, 5, 1), (3, 4, 5)), ((4, 3, 7), (3, 4, 3))]:
+        A, B = codes(rng, (M, K), E=fa[0]), codes(rng, (N, K), E=fb[0])
+        dA, dB = torch.from_numpy(A).to(DEV), torch.from_numpy(B).to(DEV)
+        for (bp, qpm), order in itertools.product([(1, 4), (1, 7), (16, 12), (1, 12)], (0, 1)):
+            qp, qa = (6, qpm, bp, 0), (4, 7, 2, 0)
+            name = lb.lba_plan_kernel_name_in(M, N, K, fa, fb, qp, qa, order)
+            assert name.startswith("lba_half_kernel<4, 4"), name
+            C = lb.gemm_in(dA, dB, fa, fb, qp, qa, order=order)
+            torch.cuda.synchronize()
+            want = ref.gemm_in(A[rows], B, ref.InFmt(*fa), ref.InFmt(*fb), ref.QFmt(*qp), ref.QFmt(*qa), order=order)
+            assert np.array_equal(bits(C.cpu().numpy()[rows]), bits(want)), (fa, fb, qp, order, name)
+
+
 def planes(A, B, qp, qa, order):
     dA, dB = torch.from_numpy(A).to(DEV), torch.from_numpy(B).to(DEV)
     got = lb.gemm_bwd_chunked(dA, dB, qp, qa) if order else lb.gemm_bwd(dA, dB, qp, qa)
@@ -176,7 +195,7 @@ def test_pieces_of_rows_at_any_alignment(ref, M, N, K):
 
 
 def test_rounded_products_of_im2col_rows(ref):
-    # products that Q_prod truncates, on a mixed grid and on a plain one, aligned and not
+    # products that Q_prod truncates, on mixed grids and on a plain one (33 x 56 x 56 rows), aligned and not
     rng = np.random.default_rng(77)
     qp, qa = (5, 4, -1, 0), (4, 7, -9, 0)
     for n, h, w, c, cout in [(4, 40, 40, 16, 40), (4, 40, 40, 6, 40), (2, 9, 8, 16, 17), (33, 56, 56, 3, 64)]:
