@@ -188,6 +188,10 @@ def run(args):
                 l["plan"] = dict(l["plan"], valu_per_mac_x100=fwd["valu_per_mac_x100"])
             if args.implicit:
                 l["kname"] = conv_kernel_name(l["kname"])
+        if args.bwd and args.diff is None and not args.of_only and l["kname"].startswith("lba_half_bwd"):
+            # both planes on packed FP16 carriers: 8 slots of the packed step (9 instructions for two chains, 7 at half rate; half
+            # a slot more for truncated products); the library's own price is the FP32 kernel's
+            l["plan"] = dict(l["plan"], valu_per_mac_x100=850 if l["plan"]["prod_mode"] == 3 else 800)
         l["C"] = Cbuf[: l["M"] * l["N"]].view(l["M"], l["N"])
         l["macs"] = l["M"] * l["N"] * l["K"]
     if args.grad:

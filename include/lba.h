@@ -342,7 +342,9 @@ typedef struct {
     int32_t valu_per_mac_x100;        /* kernel 0: full-rate VALU issue slots per MAC of the inner
                                          loop without the accumulator clamp, times 100 (a half-rate
                                          instruction counts as 2 slots; FP16 carriers: half of the
-                                         packed step, and at least 200); kernel 1: the budget of a plain
+                                         packed step, and at least 200, except for the recompute call
+                                         with an underflow plane, which keeps the FP32 kernel's price);
+                                         kernel 1: the budget of a plain
                                          FMAq step (10 floor, 12 nearest-even, 4 more with event bits), which
                                          is less than its loop issues */
     int32_t tail_blocks;              /* tail_blocks + mid_blocks > 0: mixed grid: grid_x counts, in this order,

@@ -6,6 +6,7 @@
 
 #include "lba_internal.h"
 #include "lba_launch.h"
+#include "lba_piece_index.h"
 
 namespace lba {
 
@@ -346,7 +347,7 @@ static int plan_query(int64_t M, int64_t N, int64_t K, lba_qfmt qprod, lba_qfmt 
     int rc = lba::make_plan(M, N, K, qprod, qacc, order, with_masks, &pl, 1, in);
     if (rc != LBA_OK) return rc;
     out->kernel = pl.kernel; out->prod_mode = pl.prod_mode; out->round = pl.round;
-    out->tile_m = 16 * pl.tm; out->tile_n = 16 * pl.tn; out->tile_k = pl.bk;
+    out->tile_m = 16 * pl.tm; out->tile_n = 16 * pl.tn; out->tile_k = pl.kp.h_on ? lba::HBK : pl.bk;
     if (pl.kpar > 0) {                                         // outputs per workgroup and depth of a k-tile (chunks in flight x 16)
         out->tile_m = pl.kpar == 1 ? 32 : 8;
         out->tile_n = pl.kpar == 1 ? 32 : 16;

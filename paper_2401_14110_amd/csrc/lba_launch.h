@@ -27,7 +27,7 @@ hipError_t launch_fast_bwd(const Plan& pl, hipStream_t st);
 hipError_t launch_fast_bwd_rne(const Plan& pl, hipStream_t st);
 hipError_t launch_fast_bwd_conv(const Plan& pl, hipStream_t st);   // plans with amode == 2
 hipError_t launch_fast_bwd_in_mixed(const Plan& pl, hipStream_t st);   // plans with amode == 1 on a mixed grid
-// forward, packed FP16 carriers (kp.h_on) of E4M3 codes: plans with amode == 0, amode == 2
+// forward, packed FP16 carriers (kp.h_on) of any code format with E <= 4: row-major matrices, im2col rows
 hipError_t launch_half(const Plan& pl, hipStream_t st);
 hipError_t launch_half_conv(const Plan& pl, hipStream_t st);
 hipError_t launch_half_bwd(const Plan& pl, hipStream_t st);        // plans with events == 1 on packed FP16 carriers (kp.h_on)

@@ -390,6 +390,7 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
     // the DIFF plane's scaled-domain kernel: E4M3 operands, Q_prod without mantissa rounding
     if (events == 2 && (prod_round || nouf_a || conv || in.ea != 4 || in.eb != 4)) fast = false;
 
+    int kpar_slots_x100 = 0;
     if (fast) {
         p.kernel = KERNEL_FAST;
         p.prod_mode = !prod_round ? (clamp ? PM_FLUSH_CLAMP : (flush ? PM_FLUSH : PM_IDENT))
@@ -430,16 +431,20 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
             p.valu_per_mac_x100 = 1300 + (p.prod_mode == PM_FLUSH_CLAMP ? 200 : 0) + (qa.round == LBA_ROUND_RNE ? 400 : 0);
         // packed FP16 carriers (forward call, floor, underflow kept): v_pk_mul, [v_and,] v_pk_fma at half rate for two
         // chains, one v_and for both; never priced below the two slots of the FP32 multiply-add and mask
-        // (the recompute call is priced at the FP32 kernel's step on either carrier)
+        // The recompute call for the overflow plane alone: the same, its tiles that cannot overflow are the forward call's.  With an
+        // underflow plane it keeps the FP32 kernel's price, above the 8 slots of the packed step (lba_half_bwd.h): a budget.
         // (pieces are loads of 16 bytes from inside an operand: at least 16 of them; im2col rows: checked by the caller;
         // fetched ahead of the chain: K not at the end of its range)
         const bool half = N * K >= 16 && K <= kPieceMaxK && (conv || M * K >= 16) && events != 2 && !rne_odd && qa.round == LBA_ROUND_FLOOR && !nouf_a &&
                           (p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH || p.prod_mode == PM_TRUNC) &&
                           (!p.events || p.of_only || half_underflow_ok(qp, in, bpe, bae)) &&
                           half_carrier(qp, qa, in, p.prod_mode, bpe, bae, &kp);
-        if (half && !events) p.valu_per_mac_x100 = p.prod_mode == PM_IDENT ? 200 : (p.prod_mode == PM_FLUSH ? 250 : 300);
-        if (order == LBA_ORDER_CHUNK16)                          // add, and [, bfe, add3], zero per 16 steps
-            p.valu_per_mac_x100 += (events == 2 ? 1300 : events ? 900 : (qa.round == LBA_ROUND_RNE ? 700 : 300)) / 16;
+        const int fp32_slots_x100 = p.valu_per_mac_x100;
+        if (half && (!p.events || p.of_only)) p.valu_per_mac_x100 = p.prod_mode == PM_IDENT ? 200 : (p.prod_mode == PM_FLUSH ? 250 : 300);
+        const int level2_x100 = order != LBA_ORDER_CHUNK16 ? 0   // add, and [, bfe, add3], zero per 16 steps
+                                : (events == 2 ? 1300 : events ? 900 : (qa.round == LBA_ROUND_RNE ? 700 : 300)) / 16;
+        p.valu_per_mac_x100 += level2_x100;
+        kpar_slots_x100 = fp32_slots_x100 + level2_x100;         // lba_kpar_kernel runs the FP32 step
     } else {
         p.kernel = KERNEL_GEN;
         p.prod_mode = PM_FLUSH_CLAMP;
@@ -516,6 +521,8 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
             p.tm = p.kpar == 3 ? 2 : 4; p.tn = 4;
             p.grid_x = (int)((M + tm - 1) / tm);
             p.grid_y = (int)((N + tn - 1) / tn);
+            kp.h_on = 0;
+            p.valu_per_mac_x100 = kpar_slots_x100;
         }
     }
     if (p.kpar == 0) plan_mixed_grid(M, N, batch, &p);

@@ -318,3 +318,17 @@ def test_one_carrier_to_a_kernel():
             assert got.endswith(", 0>" if K % 16 == 0 else ", 3>"), got
             assert name(M, N, K, m4e3, m4e3, (5, 7, 6, 0), (5, 10, 15, 0), order).startswith("lba_fast"), "a wide accumulator"
             assert name(M, N, K, e5m2, m4e3, (5, 7, 6, 0), (4, 7, 7, 0), order).startswith("lba_fast"), "E = 5"
+
+
+def test_the_price_is_that_of_the_kernel_that_runs():
+    # packed FP16 carriers: 2.5 slots (k-tiles of 64), also for the overflow plane alone; the K-parallel kernel of small grids in
+    # chunks and the recompute call with an underflow plane run or are priced at the FP32 step
+    q, name = lb.lba_plan_query, lb.lba_plan_kernel_name
+    qp, qa = (5, 7, 12, 0), (4, 7, 7, 0)
+    for order, masks, kernel, price, depth in [(0, 0, "lba_half", 250, 64), (1, 0, "lba_kpar", 318, 256), (0, 3, "lba_half_bwd", 250, 64),
+                                               (0, 1, "lba_half_bwd", 900, 64), (1, 1, "lba_half_bwd", 956, 64)]:
+        plan = q(256, 256, 4096, qp, qa, order, masks)
+        assert name(256, 256, 4096, qp, qa, order, masks).startswith(kernel)
+        assert (plan["valu_per_mac_x100"], plan["tile_k"]) == (price, depth), (order, masks, plan)
+    assert q(8192, 4096, 4096, qp, qa, 1)["valu_per_mac_x100"] == 268 and q(8192, 4096, 4096, qp, qa, 1)["tile_k"] == 64
+    assert q(256, 256, 4096, (5, 7, 15, 0), qa, 1)["valu_per_mac_x100"] == 518 and q(256, 256, 4096, (5, 7, 15, 0), qa)["tile_k"] == 32
