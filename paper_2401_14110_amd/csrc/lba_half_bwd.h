@@ -85,14 +85,12 @@ __device__ __forceinline__ void half_bwd_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[T
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < NJ; ++j) { wo[i][j] = 0u; wu[i][j] = 0u; }
-        uint32_t an[TM], bn[2][NJ];                            // the next pair of steps' operands, read one pair ahead
 #pragma unroll 2
         for (int s = 0; s < 8; ++s) {
             uint32_t a[TM], b[2][NJ];
             read_half_a<TM, BMP>(As, 8 * h + s, ty, a);
             read_half_b<TN, BNP>(Bs, 16 * h + 2 * s, tx, b[0]);
             read_half_b<TN, BNP>(Bs, 16 * h + 2 * s + 1, tx, b[1]);
-            
             uint32_t q[2][TM][NJ];
             // both steps' products under one mode: below Q_prod's R_UF they are flushed
             if (UF) half_flush_out();

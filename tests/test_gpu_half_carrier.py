@@ -55,15 +55,35 @@ def test_every_side_of_the_admission_rule(ref, qae, qam):
 
 @pytest.mark.parametrize("K", [1, 2, 15, 16, 17, 31, 32, 33, 63, 64, 65, 96, 97, 129, 200])
 def test_k_remainders_and_ragged_tiles(ref, K):
-    # quiet operands (clamp-free tiles) and loud ones (every sum saturates), rows and columns off the tiles of every region
+    # quiet operands (clamp-free tiles) and loud ones (every sum saturates), rows and columns off the tiles of every region (the
+    # chunked order's grids are too small for the packed tile here: lba_kpar_kernel from K = 17 on; the next test has larger ones)
     rng = np.random.default_rng(K)
     qp, qa = (5, 7, -1, 0), (4, 7, -9, 0)
     for (M, N), (lo, hi) in itertools.product([(33, 18), (65, 130), (300, 257)], [(0, 9), (3, 15)]):
         assert slots(M, N, K, qp, qa) == 250
+        assert lb.lba_plan_kernel_name(M, N, K, qp, qa, 0).startswith("lba_half")
+        assert lb.lba_plan_kernel_name(M, N, K, qp, qa, 1).startswith("lba_kpar" if K > 16 else "lba_half")
         A, B = codes(rng, (M, K), lo, hi), codes(rng, (N, K), lo, hi)
         for order in (0, 1):
             got = product(A, B, qp, qa, order)
             assert np.array_equal(bits(got), bits(ref.gemm(A, B, ref.QFmt(*qp), ref.QFmt(*qa), order=order))), (M, N, K, lo, order)
+
+
+@pytest.mark.parametrize("K", [1, 15, 17, 32, 33, 63, 65, 97, 129, 200])
+@pytest.mark.parametrize("M,N,kernel", [(1040, 530, "lba_half_kernel<2, 4,"), (8200, 530, "lba_half_kernel<4, 4,"),
+                                        (9000, 66, "lba_half_mixed_kernel"), (20000, 66, "lba_half_mixed_kernel"), (33000, 66, "lba_half_mixed_kernel")])
+def test_k_remainders_of_the_chunked_packed_tile(ref, M, N, kernel, K):
+    # chunks of 16 on grids of 512 workgroups of 32 x 32 and more: every lane block, and mixed grids with 48-row and 32 x 32 tails;
+    # sampled rows of every region, short last chunks, quiet and loud operands
+    rng = np.random.default_rng([M, K])
+    qp, qa = (5, 7, -1, 0), (4, 7, -9, 0)
+    name = lb.lba_plan_kernel_name(M, N, K, qp, qa, 1)
+    assert name.startswith(kernel), name
+    rows = np.array(sorted({0, 1, 63, 64, M // 2, M - 49, M - 33, M - 2, M - 1} | set(int(r) for r in rng.integers(0, M, 60))))
+    for lo, hi in [(0, 9), (3, 15)]:
+        A, B = codes(rng, (M, K), lo, hi), codes(rng, (N, K), lo, hi)
+        got = product(A, B, qp, qa, 1)[rows]
+        assert np.array_equal(bits(got), bits(ref.gemm(A[rows], B, ref.QFmt(*qp), ref.QFmt(*qa), order=1))), (lo, name)
 
 
 @pytest.mark.parametrize("fa,fb", [((3, 4, 3), (3, 4, 3)), ((2, 5, 1), (3, 4, 5)), ((4, 3, 9), (2, 5, -2)), ((2, 5, 1), (2, 5, 1)), ((5, 2, 15), (3, 4, 3))])
@@ -106,10 +126,17 @@ def planes(A, B, qp, qa, order):
     return [t.cpu().numpy() for t in got]
 
 
-@pytest.mark.parametrize("ba,bp", [(7, 17), (7, 18), (7, 15), (-9, -1), (10, 12), (4, 11), (-2, -17), (3, 1)])
-def test_event_planes_on_both_sides_of_the_underflow_rule(ref, ba, bp):
-    # kc = 2^-10 (a product alone is FP16's smallest denormal number) and 2^-11 (beyond: FP32), accumulators of 2 to 11 bits,
-    # operands full of subnormal codes and zeros, cancelling pairs next to R_UF
+@pytest.mark.parametrize("ba,bp,kernel,of_alone", [
+    (2, 12, "lba_half_bwd", "lba_half_bwd"),       # kc = 2^-10: a product alone is FP16's smallest denormal number
+    (1, 12, "lba_fast_bwd", "lba_half_bwd"),       # kc = 2^-11: FP32, but for the overflow plane alone
+    (-9, 1, "lba_half_bwd", "lba_half_bwd"), (-10, 1, "lba_fast_bwd", "lba_half_bwd"),
+    (-9, -1, "lba_half_bwd", "lba_half_bwd"), (10, 12, "lba_half_bwd", "lba_half_bwd"), (4, 11, "lba_half_bwd", "lba_half_bwd"),
+    (3, 1, "lba_half_bwd", "lba_half_bwd"),
+    (7, 15, "lba_fast_bwd", "lba_fast_bwd"), (7, 17, "lba_fast_bwd", "lba_fast_bwd"), (-2, -17, "lba_fast_bwd", "lba_fast_bwd"),   # products beyond FP16
+    (7, 18, "lba_gen", "lba_gen"),                 # Q_prod cannot flush: the general kernel
+])
+def test_event_planes_on_both_sides_of_the_underflow_rule(ref, ba, bp, kernel, of_alone):
+    # accumulators of 2 to 11 bits, operands full of subnormal codes and zeros, cancelling pairs next to R_UF
     rng = np.random.default_rng([ba + 100, bp + 100])
     for M, N, K in [(33, 18, 70), (70, 66, 97)]:
         A, B = codes(rng, (M, K), 0, 15), codes(rng, (N, K), 0, 15)
@@ -117,12 +144,18 @@ def test_event_planes_on_both_sides_of_the_underflow_rule(ref, ba, bp):
         B[:, 1::4] = np.clip(B[:, 0::4][:, :B[:, 1::4].shape[1]].astype(np.int32) + rng.integers(-1, 2, B[:, 1::4].shape), 0, 255).astype(np.uint8)
         for qam, order in itertools.product((1, 7, 10), (0, 1)):
             qp, qa = (6, 7, bp, 0), (4, qam, ba, 0)
+            assert lb.lba_plan_kernel_name(M, N, K, qp, qa, order, 1).startswith(kernel), order
+            assert order or lb.lba_plan_kernel_name(M, N, K, qp, qa, order, 3).startswith(of_alone)
             got = planes(A, B, qp, qa, order)
             want = ref.gemm_bwd(A, B, ref.QFmt(*qp), ref.QFmt(*qa), order=order, level2=True) if order else \
                 ref.gemm_bwd(A, B, ref.QFmt(*qp), ref.QFmt(*qa))
             assert np.array_equal(bits(got[0]), bits(want[0])), (M, N, K, qp, qa, order)
             for i in range(1, len(want)):
                 assert np.array_equal(got[i].view(np.uint32), want[i]), (M, N, K, qp, qa, order, "plane %d" % i)
+            dA, dB = torch.from_numpy(A).to(DEV), torch.from_numpy(B).to(DEV)
+            of = lb.gemm_bwd_chunked(dA, dB, qp, qa, want_c=False, want_uf=False)[1] if order else lb.gemm_bwd(dA, dB, qp, qa, want_c=False, want_uf=False)[1]
+            torch.cuda.synchronize()
+            assert np.array_equal(of.cpu().numpy().view(np.uint32), want[1]), (M, N, K, qp, qa, order, "overflow plane alone")
 
 
 @pytest.mark.parametrize("K", [1, 15, 16, 17, 32, 33, 63, 65, 96, 129, 512, 530])
@@ -133,9 +166,9 @@ def test_event_planes_of_ragged_shapes(ref, K):
     qp, qa = (5, 7, -1, 0), (4, 7, -9, 0)
     for (M, N), (lo, hi) in itertools.product([(33, 17), (65, 66), (20, 131)], [(0, 9), (3, 15)]):
         A, B = codes(rng, (M, K), lo, hi), codes(rng, (N, K), lo, hi)
-        name = lb.lba_plan_kernel_name(M, N, K, qp, qa, 0, 1)
-        assert name.startswith("lba_half_bwd"), name
         for order in (0, 1):
+            name = lb.lba_plan_kernel_name(M, N, K, qp, qa, order, 1)
+            assert name.startswith("lba_half_bwd"), name
             want = ref.gemm_bwd(A, B, ref.QFmt(*qp), ref.QFmt(*qa), order=order, level2=True) if order else \
                 ref.gemm_bwd(A, B, ref.QFmt(*qp), ref.QFmt(*qa))
             got = planes(A, B, qp, qa, order)
@@ -159,7 +192,8 @@ def at(a, off):
 
 
 @pytest.mark.parametrize("n,h,w,c,cout,kh,kw,stride,pad", [
-    (2, 9, 8, 5, 17, 3, 3, 1, 1),            # a filter row of 15 codes: byte by byte
+    (2, 9, 8, 5, 17, 3, 3, 1, 1),            # a filter row of 15 codes: byte by byte, on the smallest grids only
+    (33, 28, 28, 5, 40, 3, 3, 1, 1),         # ... and on FP32 on any other
     (2, 9, 8, 16, 17, 3, 1, 1, 1),           # one tap to a filter row, aligned
     (2, 9, 8, 17, 18, 3, 1, 2, 2),           # a filter row one code longer than a piece
     (3, 11, 7, 3, 66, 7, 7, 2, 3),           # two filter rows to a piece, cut off at both edges of the image
