@@ -13,13 +13,13 @@
 // accumulator format fits, not a reduced precision.
 //
 // What bounds it: VALU issue.  The FP32 step of a chain is mul, fma, and at one wave64 instruction per 2.3 to 2.8 cycles
-// with several waves per SIMD (6.96 cycles per chain in the issue-rate probe, 13.9 with one wave); the packed step of two
-// chains is v_pk_mul, v_pk_fma (4.3 cycles each, whatever the number of waves) and one v_and (6.1 per chain, 7.8 with
+// with several waves per SIMD (6.8 cycles per chain in the issue-rate probe, 12.9 with one wave); the packed step of two
+// chains is v_pk_mul, v_pk_fma (4.3 cycles each, whatever the number of waves) and one v_and (6.1 per chain, 7.5 with
 // one wave).  It also reads a quarter of the LDS bytes per step, and 64 steps take the LDS of 32: with stages of 32 steps
 // every shape measured 3-8 % slower, with 5 to 8 waves per SIMD instead of 4 none faster, and an 8 x 4 lane block slower
 // on every layer of ResNet-50.  Measured against the FP32 tile on the same grids: 8192 x 4096 x 1152 1819 -> 1573 us
-// (6.4 cycles per chain and step), the ResNet-50 sweep 14.05 -> 11.97 ms, its 7 x 7 x 3 first convolution at batch 37 337 ->
-// 255 us, the 64 x 1000 x 2048 classifier 61 -> 45 us, 3136 x 512 x 4608 of M4E3 codes 593 -> 522 us.
+// (6.4 cycles per chain and step), the ResNet-50 sweep 14.05 -> 11.92 ms, its 7 x 7 x 3 first convolution at batch 37 337 ->
+// 250 us, the 64 x 1000 x 2048 classifier 61 -> 44 us, 3136 x 512 x 4608 of M4E3 codes 593 -> 520 us.
 
 #ifndef LBA_HALF_H_
 #define LBA_HALF_H_
@@ -339,7 +339,7 @@ __device__ __forceinline__ void half_body(const KParams& p, uint32_t* __restrict
     const bool dyn = half_follows_data(p);
     // How the pieces come.  Aligned rows and im2col rows of whole 16-channel taps (AMODE 0, 2): one aligned load, zeroed at once
     // outside the operand.  Any other rows (AMODE 3, 4) and the small lane blocks: lba_piece.h, uncorrected loads that stay in
-    // flight (C = 3 under a 7 x 7 filter: two loads a piece instead of sixteen, 279 -> 255 us).  Either kind of
+    // flight (C = 3 under a 7 x 7 filter: two loads a piece instead of sixteen, 279 -> 250 us).  Either kind of
     // code in the other's kernel, behind a uniform branch, cost the aligned shapes 1 to 4 %.
     constexpr bool SMALL = TM * TN <= 4, PIECES = SMALL || AMODE >= 3;
     static_assert(AMODE == 0 || AMODE == 2 || AMODE == 3 || AMODE == 4, "other operand formats decode alike: no AMODE of their own");

@@ -16,8 +16,8 @@
 // forward tile.
 //
 // What bounds it: VALU issue, nine instructions for two chains with the underflow plane and a quiet tile (7 of them at half
-// rate: 17.8 cycles per chain and step by the issue-rate probe).  The FP32 kernel (compares to 64-bit masks, scalar logic, one
-// carry-in add per chain and plane) takes 27.  Measured against it, both planes of 4096 x 768 x 3072: 1703 -> 1418 us (23
+// rate: 18.4 cycles per chain and step by the issue-rate probe).  The FP32 kernel (compares to 64-bit masks, scalar logic, one
+// carry-in add per chain and plane) takes 27.  Measured against it, both planes of 4096 x 768 x 3072: 1703 -> 1396 us (22.7
 // cycles; 2.4 GB of planes leave at 1.7 TB/s); the overflow plane alone of 12544 x 256 x 2304: 533 -> 440 us.  Reading
 // operands a step ahead, or two waves per SIMD instead of three for the underflow plane, changed nothing.
 #ifndef LBA_HALF_BWD_H_
