@@ -93,7 +93,7 @@ __device__ __forceinline__ bool splits(float g) {
     const uint32_t u = __float_as_uint(g) & 0x7FFFFFFFu;
     return u == 0u || (u >= kSplitLeast && u < kSplitInf);
 }
-// The same of a whole patch, from its bfloat16 heads two at a time: four instructions for two words.  (A value with a head of 0
+// The same of a whole patch, from its bfloat16 heads, two to a word: four instructions a word.  (A value with a head of 0
 // is an FP32 denormal number, which counts as zero.)
 struct SplitRange {
     typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
