@@ -16,10 +16,8 @@
 // with several waves per SIMD (6.8 cycles per chain in the issue-rate probe, 12.9 with one wave); the packed step of two
 // chains is v_pk_mul, v_pk_fma (4.3 cycles each, whatever the number of waves) and one v_and (6.1 per chain, 7.5 with
 // one wave).  It also reads a quarter of the LDS bytes per step, and 64 steps take the LDS of 32: with stages of 32 steps
-// every shape measured 3-8 % slower, with 5 to 8 waves per SIMD instead of 4 none faster, and an 8 x 4 lane block slower
-// on every layer of ResNet-50.  Measured against the FP32 tile on the same grids: 8192 x 4096 x 1152 1819 -> 1573 us
-// (6.4 cycles per chain and step), the ResNet-50 sweep 14.05 -> 11.92 ms, its 7 x 7 x 3 first convolution at batch 37 337 ->
-// 250 us, the 64 x 1000 x 2048 classifier 61 -> 44 us, 3136 x 512 x 4608 of M4E3 codes 593 -> 520 us.
+// every shape measured 3-8 % slower, with 5 to 8 waves per SIMD instead of 4 none faster.  The forward call's tile is lba_rows.h;
+// the 4 x 4 lane block here serves the recompute call (lba_half_bwd.h).
 
 #ifndef LBA_HALF_H_
 #define LBA_HALF_H_
@@ -122,8 +120,12 @@ __device__ __forceinline__ void store_half_b(uint32_t* __restrict__ dst, int tid
     }
 }
 
+// Priority of a wave's packed instructions over its masks (lba_rows.h: why).
+template <bool ON> __device__ __forceinline__ void issue_first() { if (ON) __builtin_amdgcn_s_setprio(1); }
+template <bool ON> __device__ __forceinline__ void issue_last() { if (ON) __builtin_amdgcn_s_setprio(0); }
+
 // A step's products (PM_IDENT: none).  HI: the step is the odd k of its pair of steps.
-template <int PM, bool HI, int TM, int TN>
+template <int PM, bool HI, int TM, int TN, bool PRIO = (TM * TN > 4)>
 __device__ __forceinline__ void half_products(h2 (&q)[TM][TN / 2], const uint32_t (&a)[TM], const uint32_t (&b)[TN / 2], const HalfConst& c) {
     if (PM != PM_IDENT) {
 #pragma unroll
@@ -136,11 +138,13 @@ __device__ __forceinline__ void half_products(h2 (&q)[TM][TN / 2], const uint32_
         __builtin_amdgcn_sched_barrier(0);
     }
     if (PM == PM_TRUNC) {
+        issue_last<PRIO>();
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN / 2; ++j) q[i][j] = as_h2(as_u32(q[i][j]) & c.maskp);
         __builtin_amdgcn_sched_barrier(0);
+        issue_first<PRIO>();
     }
 }
 
@@ -160,14 +164,16 @@ __device__ __forceinline__ void half_sums(h2 (&acc)[TM][TN / 2], const h2 (&q)[T
 }
 
 // ... and their rounding to M + 1 bits
-template <bool CLAMP, int TM, int TN>
+template <bool CLAMP, int TM, int TN, bool PRIO = (TM * TN > 4)>
 __device__ __forceinline__ void half_round(h2 (&acc)[TM][TN / 2], const HalfConst& c) {
+    issue_last<PRIO>();
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN / 2; ++j) acc[i][j] = as_h2(as_u32(acc[i][j]) & c.mask);
+    __builtin_amdgcn_sched_barrier(0);
+    issue_first<PRIO>();
     if (CLAMP) {
-        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -278,196 +284,44 @@ __device__ __forceinline__ void half_stage(const KParams& p, uint32_t* __restric
     }
 }
 
+// 16-bit mask of a piece's non-zero codes, code 0 in bit 0
+__device__ __forceinline__ uint32_t nonzero_codes(const uint4& v) {
+    const uint32_t q[4] = {v.x, v.y, v.z, v.w};
+    uint32_t b[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) b[i] = (((q[i] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) >> 7) & 0x01010101u;   // 1 per non-zero byte
+    const uint32_t lo = __builtin_amdgcn_udot4(b[1], 0x80402010u, __builtin_amdgcn_udot4(b[0], 0x08040201u, 0u, false), false);
+    const uint32_t hi = __builtin_amdgcn_udot4(b[3], 0x80402010u, __builtin_amdgcn_udot4(b[2], 0x08040201u, 0u, false), false);
+    return lo | (hi << 8);
+}
+
 // The bound that follows the data costs a reduction per staged tile: only where the fixed one leaves less than half of the
 // range (R_OF below 64 of the largest products).
 __device__ __forceinline__ bool half_follows_data(const KParams& p) { return p.dyn_bound != 0 && 2.0f * p.fast_thresh < p.rof_a; }
 
-// For how many of the next tiles of 32 steps (0 to 4) no sum of the wave can reach R_OF; mf: this lane's largest |S|.
+// For how many of the next tiles of 32 steps (0 to 8) no sum of the wave can reach R_OF; mf: this lane's largest |S|.
 struct HalfBound {
     float rof, thresh, grow, kcf;
     // the planner's bound is in the FP32 tile's domain (R_UF at 2^-126); 2^112 moves it to R_UF at 2^-14.  grow: 32 of the
     // largest products there are (thresh is rounded down; the factor covers the roundings here)
     __device__ __forceinline__ explicit HalfBound(const KParams& p)
         : rof(p.rof_a * 0x1p112f), thresh(p.fast_thresh * 0x1p112f), grow(1.0001f * (rof - thresh)), kcf((float)as_h2(p.h_kc).x) {}
-    // norms: half_stage's, for the current tile, or null
-    __device__ __forceinline__ int safe(float mf, const uint32_t* norms) const {
-        if (__all(mf < thresh)) return 1 + __all(mf < thresh - grow) + __all(mf < thresh - 2.0f * grow) + __all(mf < thresh - 3.0f * grow);
+    // norms: half_stage's, for the current tile, or null; parts: of how many parts the bound that follows the data is asked
+    __device__ __forceinline__ int safe(float mf, const uint32_t* norms, int parts = 1) const {
+        if (__all(mf < thresh - 3.0f * grow)) return __all(mf < thresh - 7.0f * grow) ? 8 : 4;
+        if (__all(mf < thresh)) return __all(mf < thresh - grow) ? 2 : 1;
         if (!norms) return 0;
-        // Cauchy-Schwarz: 16 products of a row's piece and a column's piece add at most the product of their norms; 32 steps
-        // are two pieces.  (The factor covers the roundings of the norms and of this line.)
+        // Cauchy-Schwarz: 16 products of a row's piece and a column's piece add at most the product of their norms; a part's 32
+        // steps are two pieces.  (The factor covers the roundings of the norms and of this line.)
         const uint32_t m = pk_max_u16(pk_max_u16(norms[0], norms[1]), pk_max_u16(norms[2], norms[3]));
         const float n2 = __uint_as_float(m << 16) * __uint_as_float(m & 0xFFFF0000u);
-        return __all(mf < rof - 2.0f * 1.001f * __builtin_sqrtf(n2) * kcf) ? 1 : 0;
+        return __all(mf < rof - (float)parts * 2.0f * 1.001f * __builtin_sqrtf(n2) * kcf) ? parts : 0;
     }
 };
 
 // k-tiles whose pieces are in flight at a time: one for the large lane blocks (two measured the same); four for the small ones,
 // whose tile takes less time than a load (64 x 1000 x 2048: 47 -> 45 us).
 __host__ __device__ constexpr int half_depth(int TM, int TN) { return TM * TN <= 4 ? kTilesAhead : 1; }
-
-// The work of one workgroup: the BM x BN tile of C at (m0, n0).  smem: two stages.  Structure, clamp-free tiles and their
-// bounds as in fast_body; AMODE as there, and 3, 4 below (every code format decodes alike).
-template <int TM, int TN, int LX, int PM, int ORDER, int AMODE>
-__device__ __forceinline__ void half_body(const KParams& p, uint32_t* __restrict__ smem, int m0, int n0) {
-    using T = HalfTile<TM, TN, LX>;
-    constexpr int BM = T::BM, BN = T::BN;
-    static_assert(Stage<BM, HBK>::kPerLane == 1 && Stage<BN, HBK>::kPerLane == 1, "one piece per lane");
-    static_assert(2 * T::STAGE <= 2 * 32 * 128, "two stages in 32 KB");
-    const int tid = threadIdx.x;
-    const int tx = tid % LX, ty = tid / LX;
-    const int tidb = tid - Stage<BN, HBK>::kTailShift;
-    const uint8_t* pA = p.A + (int64_t)blockIdx.z * p.stride_a;
-    const uint8_t* pB = p.B + (int64_t)blockIdx.z * p.stride_b;
-    float* pC = p.C + (int64_t)blockIdx.z * p.stride_c;
-
-    set_flush_f32();
-    set_round_zero_f16();
-    set_flush_out_f16();
-
-    HalfConst c;
-    c.kc = as_h2(p.h_kc); c.rof = as_h2(p.h_rof); c.nrof = as_h2(p.h_rof ^ 0x80008000u); c.mask = p.h_mask_a; c.maskp = p.h_mask_p;
-    asm volatile("" : "+v"(c.kc), "+v"(c.rof), "+v"(c.nrof), "+v"(c.mask), "+v"(c.maskp));
-
-    h2 acc[TM][TN / 2], top[TM][TN / 2];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN / 2; ++j) { acc[i][j] = as_h2(0u); top[i][j] = as_h2(0u); }
-
-    const int ntiles = (p.K + HBK - 1) / HBK;
-    __shared__ uint32_t half_norm[2][4];                       // per stage and wave: largest squared norm of a piece of A (low half), of B
-    const bool dyn = half_follows_data(p);
-    // How the pieces come.  Aligned rows and im2col rows of whole 16-channel taps (AMODE 0, 2): one aligned load, zeroed at once
-    // outside the operand.  Any other rows (AMODE 3, 4) and the small lane blocks: lba_piece.h, uncorrected loads that stay in
-    // flight (C = 3 under a 7 x 7 filter: two loads a piece instead of sixteen, 279 -> 250 us).  Either kind of
-    // code in the other's kernel, behind a uniform branch, cost the aligned shapes 1 to 4 %.
-    constexpr bool SMALL = TM * TN <= 4, PIECES = SMALL || AMODE >= 3;
-    static_assert(AMODE == 0 || AMODE == 2 || AMODE == 3 || AMODE == 4, "other operand formats decode alike: no AMODE of their own");
-    constexpr bool conv = AMODE == 2 || AMODE == 4;
-    const RowPieces<BM> sa(pA, conv ? 1 : p.M, p.K, conv ? 0 : m0, tid);
-    const RowPieces<BN> sb(pB, p.N, p.K, n0, tidb);
-    ConvPieces sc = {};
-    ConvLane cl = {};
-    if (PIECES && conv) sc = ConvPieces::make<BM>(pA, p, m0, tid);
-    if (!PIECES && AMODE == 2) cl = conv_lane<BM, HBK>(pA, p, m0, tid);
-    // pieces in flight: DEPTH tiles of them (1: asked for at the start of the tile before)
-    constexpr int DEPTH = half_depth(TM, TN);
-    uint4 ra[DEPTH], rc[DEPTH], rb[DEPTH];
-    auto fetch = [&](int t, int d) {
-        const int k0 = tile_start(t);
-        if (PIECES) {
-            if (conv) load_piece(sc, p, k0, ra[d], rc[d]);
-            else      ra[d] = load_piece(sa, k0);
-            rb[d] = load_piece(sb, k0);
-        } else {
-            ra[d] = AMODE == 2 ? fetch_taps(cl, p, k0) : fetch_aligned<BM>(pA, p.M, p.K, m0, k0, tid);
-            rb[d] = fetch_aligned<BN>(pB, p.N, p.K, n0, k0, tidb);
-        }
-    };
-    auto stage = [&](int t, int d) {
-        const uint4 va = !PIECES ? ra[d] : (conv ? sc.codes(p, ra[d], rc[d], t * HBK) : sa.codes(ra[d], t * HBK));
-        const uint4 vb = PIECES ? sb.codes(rb[d], t * HBK) : rb[d];
-        const int st = t & 1;
-        half_stage<BM, BN>(p, smem + st * T::STAGE, smem + st * T::STAGE + T::A_WORDS, va, vb, tid, tidb, dyn, half_norm[st]);
-    };
-#pragma unroll
-    for (int d = 0; d < DEPTH; ++d) fetch(d, d);               // (a tile beyond K reads codes inside the operands that nothing uses)
-    stage(0, 0);
-    if (DEPTH > 1) fetch(DEPTH, 0);
-    __syncthreads();
-
-    const HalfBound bound(p);
-    int safe_tiles = 0;
-    for (int t0 = 0; t0 < ntiles; t0 += DEPTH) {
-#pragma unroll
-        for (int d = 0; d < DEPTH; ++d) {
-            const int t = t0 + d;
-            if (t >= ntiles) break;
-            const uint32_t* As0 = smem + (t & 1) * T::STAGE;
-            const uint32_t* Bs0 = As0 + T::A_WORDS;
-            const bool more = (t + 1) < ntiles;
-            if (DEPTH == 1 && (PIECES || more)) fetch(t + 1, 0);
-            const int parts = p.K - t * HBK > 32 ? 2 : 1;      // steps beyond K are products of zeros: skipped 32 at a time
-            for (int part = 0; part < parts; ++part) {
-                const uint32_t* As = As0 + part * 16 * T::BMP;
-                const uint32_t* Bs = Bs0 + part * 32 * T::BNP;
-                if (safe_tiles == 0) {
-                    uint32_t mx = 0u;
-#pragma unroll
-                    for (int i = 0; i < TM; ++i)
-#pragma unroll
-                        for (int j = 0; j < TN / 2; ++j)
-                            mx = pk_max_u16(mx, as_u32(ORDER == LBA_ORDER_CHUNK16 ? top[i][j] : acc[i][j]) & 0x7FFF7FFFu);
-                    safe_tiles = bound.safe(max_half(mx), dyn ? half_norm[t & 1] : nullptr);
-                }
-                if (safe_tiles > 0) {
-                    --safe_tiles;
-                    half_tile<PM, ORDER, false, TM, TN, T::BMP, T::BNP>(acc, top, As, Bs, tx, ty, c);
-                } else {
-                    half_tile<PM, ORDER, true, TM, TN, T::BMP, T::BNP>(acc, top, As, Bs, tx, ty, c);
-                }
-            }
-            if (more) {
-                constexpr int next = (DEPTH > 1) ? 1 : 0;
-                stage(t + 1, (d + next) % DEPTH);
-                if (DEPTH > 1) fetch(t + 1 + DEPTH, (d + next) % DEPTH);
-            }
-            __syncthreads();
-        }
-    }
-
-    // C = S * 2^out_exp, zero written as +0
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        const int m = m0 + ty * TM + i;
-        if (m >= p.M) continue;
-        const int n = n0 + tx * TN;
-        float v[TN];
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const h2 w = ORDER == LBA_ORDER_CHUNK16 ? top[i][j / 2] : acc[i][j / 2];
-            const float s = (float)(j & 1 ? w.y : w.x);
-            v[j] = __builtin_ldexpf(s, p.out_exp - 112) + 0.0f;    // -0 + 0 is +0
-        }
-        float* dst = pC + (int64_t)m * p.N + n;
-        if (TN == 4 && p.c_vec && n + 3 < p.N) {
-            *reinterpret_cast<f32x4_any*>(dst) = f32x4_any{v[0], v[1], v[TN - 2], v[TN - 1]};
-        } else if (TN == 2 && p.c_vec && n + 1 < p.N) {
-            *reinterpret_cast<f32x2_any*>(dst) = f32x2_any{v[0], v[1]};
-        } else {
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                if (n + j < p.N) dst[j] = v[j];
-        }
-    }
-}
-
-// The grids of lba_fast_kernel and lba_fast_mixed_kernel (the same tiles, numbered the same) on packed carriers.
-// AMODE 0: row-major, 16-byte rows; 3: row-major, any K and alignment; 2: im2col rows, C % 16 == 0 and 16-byte rows; 4: any other.
-template <int TM, int TN, int PM, int ORDER, int AMODE>
-__global__ void __launch_bounds__(256, LBA_FAST_MIN_WAVES) lba_half_kernel(const KParams p) {
-    __shared__ __attribute__((aligned(16))) uint32_t smem[2 * HalfTile<TM, TN, 16>::STAGE];
-    half_body<TM, TN, 16, PM, ORDER, AMODE>(p, smem, blockIdx.x * 16 * TM, blockIdx.y * 16 * TN);
-}
-
-template <int PM, int ORDER, int AMODE>
-__global__ void __launch_bounds__(256, LBA_FAST_MIN_WAVES) lba_half_mixed_kernel(const KParams p) {
-    __shared__ __attribute__((aligned(16))) uint32_t smem[2 * HalfTile<4, 4, 16>::STAGE];
-    const int b = blockIdx.x;
-    if (b < p.mix_main) {                                      // uniform
-        const int by = b / p.mix_gx_main, bx = b - by * p.mix_gx_main;
-        half_body<4, 4, 16, PM, ORDER, AMODE>(p, smem, bx * 64, by * 64);
-    } else if (b < p.mix_main + p.mix_half) {
-        const int t = b - p.mix_main;
-        const int by = t / p.mix_gx_half, bx = t - by * p.mix_gx_half;
-        half_body<3, 4, 16, PM, ORDER, AMODE>(p, smem, p.mix_m_main + bx * 48, by * 64);
-    } else {
-        const int t = b - p.mix_main - p.mix_half;
-        const int by = t / p.mix_gx_tail, bx = t - by * p.mix_gx_tail;
-        if (p.mix_tail16) half_body<1, 2, 8, PM, ORDER, AMODE>(p, smem, p.mix_m_half + bx * 32, by * 16);   // uniform
-        else              half_body<2, 2, 16, PM, ORDER, AMODE>(p, smem, p.mix_m_half + bx * 32, by * 32);
-    }
-}
 
 }  // namespace lba
 #endif

@@ -1,5 +1,5 @@
-// lba_half.hip -- instantiations of the forward kernels on packed FP16 carriers (lba_half.h) for row-major matrices.
-#include "lba_half.h"
+// lba_half.hip -- instantiations of the forward kernels on packed FP16 carriers (lba_rows.h) for row-major matrices.
+#include "lba_rows.h"
 #include "lba_launch.h"
 
 namespace lba {

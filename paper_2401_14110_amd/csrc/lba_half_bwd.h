@@ -60,17 +60,6 @@ struct HalfBwdConst {
     uint32_t bit15;            // 0x80008000
 };
 
-// 16-bit mask of a piece's non-zero codes, code 0 in bit 0
-__device__ __forceinline__ uint32_t nonzero_codes(const uint4& v) {
-    const uint32_t q[4] = {v.x, v.y, v.z, v.w};
-    uint32_t b[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) b[i] = (((q[i] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) >> 7) & 0x01010101u;   // 1 per non-zero byte
-    const uint32_t lo = __builtin_amdgcn_udot4(b[1], 0x80402010u, __builtin_amdgcn_udot4(b[0], 0x08040201u, 0u, false), false);
-    const uint32_t hi = __builtin_amdgcn_udot4(b[3], 0x80402010u, __builtin_amdgcn_udot4(b[2], 0x08040201u, 0u, false), false);
-    return lo | (hi << 8);
-}
-
 // 32 steps with event bits: word [i][j] of chain (i, j) gets step k in bit k (of: 1 = overflow; uf: 1 = underflow or a zero
 // operand, cleared by the caller).  of2 / uf2: the two chunks' bits enter the second-level words at bits pos, pos + 1.
 template <int PM, int ORDER, bool UF, bool QUIET, int TM, int TN, int BMP, int BNP>

@@ -1,5 +1,5 @@
-// lba_half_conv.hip -- instantiations of the forward kernels on packed FP16 carriers (lba_half.h) for im2col rows of an NHWC tensor.
-#include "lba_half.h"
+// lba_half_conv.hip -- instantiations of the forward kernels on packed FP16 carriers (lba_rows.h) for im2col rows of an NHWC tensor.
+#include "lba_rows.h"
 #include "lba_launch.h"
 
 namespace lba {

@@ -10,15 +10,6 @@
 
 namespace lba {
 
-// A piece of a matrix whose rows are 16-byte aligned (K % 16 == 0), zero outside the matrix.
-template <int ROWS>
-__device__ __forceinline__ uint4 fetch_aligned(const uint8_t* __restrict__ G, int rows, int K, int r0, int k0, int c) {
-    const int r = r0 + c % ROWS, k = k0 + c / ROWS * 16;
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (c >= 0 && c < Stage<ROWS, 64>::kChunks && r < rows && k < K) v = *reinterpret_cast<const uint4*>(G + (int64_t)r * K + k);
-    return v;
-}
-
 // A piece of im2col rows whose 16 codes are channels of one tap (fetch_tile_conv_lane's aligned case).
 __device__ __forceinline__ uint4 fetch_taps(const ConvLane& L, const KParams& p, int k0) {
     const int k = k0 + L.kq16;

@@ -1,0 +1,443 @@
+// lba_rows.h -- the forward tile on packed FP16 carriers (lba_half.h has the arithmetic): groups of lanes that own rows of A.
+//
+// What bounds it: VALU issue, so the two things it does are fewer instructions and a better issue rate.
+//
+// Steps whose code of A is zero are not run.  A product of zero leaves the sum as it is (Q_acc(S + 0) = S: S is a value of Q_acc
+// already), so such a step is the identity whatever the other operand, and half of what a layer with a ReLU before it does is
+// such steps.  The chains of a register pair share a row of A, so the 8 lanes of a row can go through a list of its non-zero codes
+// (value and place of the code's row of B in one word), each row of the wave its own; a wave runs as many steps as its longest
+// list.  The wave builds the lists itself (one compare, a count of the lanes below and one store per row of 64 codes), per
+// k-tile and where they save enough: ReLU rows run 38 of 64 steps.  Codes without zeros cost a test of a quarter of them.
+// Which steps run depends on the data, the result does not.
+//
+// Waves take turns by the rate of their instructions.  A full-rate instruction (the mask) issues in half the time of a packed
+// one only when another wave has one too; with waves at random places of their steps it mostly has no partner and takes as long.
+// Packed instructions run at priority 1 and the masks at priority 0, so waves gather at their masks (issue-rate probe: 12.1 ->
+// 10.9 cycles per register and step).  A lone wave per SIMD (the smallest tiles) has nobody to wait for and keeps one priority.
+//
+// Measured (us), 16 chains per lane in 4 x 4 blocks / rows without lists / with; no zeros, then half of A's codes zero:
+//   8192 x 512 x 2304    447 -> 394,  447 -> 394 -> 329
+//   50176 x 128 x 1152   319 -> 294,  319 -> 294 -> 242
+//   12544 x 256 x 2304   335 -> 309,  335 -> 309 -> 258
+//   200704 x 64 x 64      42 ->  41,   42 ->  41 ->  35
+// and without the priorities 433 and 362 for the first shape.  ResNet-50 at batch 64: 11.96 -> 9.33 ms.
+#ifndef LBA_ROWS_H_
+#define LBA_ROWS_H_
+
+#include "lba_half.h"
+
+namespace lba {
+
+
+// Geometry of one workgroup tile: each of the four waves takes RW rows (8, 12 or 16) and all BN = 8 TN columns.  A row set is 8
+// rows of 8 lanes, TN columns per lane; 12 rows are one such set and one of 4 rows of 16 lanes, TN / 2 columns per lane.
+// LDS: two stages of B as words (n, n + 1) of one k, [k][n / 2]; one stage of A, every row written and read by its own wave:
+// its words (k, k + 1), or the list of its non-zero codes (value in the low half, byte offset of the code's row of B in the high).
+template <int N> struct IntConst { static constexpr int value = N; };
+
+template <int RW, int TN>
+struct RowTile {
+    static constexpr int BM = 4 * RW, BN = 8 * TN, SETS = RW / 8;
+    static constexpr bool HALF = RW % 8 != 0;
+    static constexpr int U = TN >= 8 ? 4 : 8;                  // list entries taken at a time
+    static constexpr int BROW = BN / 2, B_WORDS = HBK * BROW;
+    static constexpr int PITCH = HBK + 2 * U + (U == 8 ? 4 : 0);   // words per row of A: 64 and the zeros a list is read on into
+    static constexpr int A_WORDS = BM * PITCH, WORDS = 2 * B_WORDS + A_WORDS;
+};
+
+template <int T>
+__device__ __forceinline__ void read_words(const uint32_t* s, uint32_t (&b)[T]) {
+    static_assert(T == 1 || T == 2 || T == 4, "words per lane");
+    if (T == 4) {
+        const uint4 v = *reinterpret_cast<const uint4*>(s);
+        b[0] = v.x; b[T > 1 ? 1 : 0] = v.y; b[T > 2 ? 2 : 0] = v.z; b[T - 1] = v.w;
+    } else if (T == 2) {
+        const uint2 v = *reinterpret_cast<const uint2*>(s);
+        b[0] = v.x; b[T - 1] = v.y;
+    } else {
+        b[0] = s[0];
+    }
+}
+
+// A list's first 2 U entries.
+template <int U>
+struct ListHead {
+    uint32_t e[U], f[U];
+    static __device__ __forceinline__ void read(const uint32_t* list, uint32_t (&e)[U]) {
+#pragma unroll
+        for (int u = 0; u < U; u += 4) { uint32_t x[4]; read_words<4>(list + u, x); e[u] = x[0]; e[u + 1] = x[1]; e[u + 2] = x[2]; e[u + 3] = x[3]; }
+    }
+    __device__ __forceinline__ explicit ListHead(const uint32_t* list) { read(list, e); read(list + U, f); }
+};
+
+// U steps: entries e with their rows of B in b; the rows of the next entries f are asked for as the registers of a step become
+// free, and the entries after those when the last of e is used.
+template <int PM, bool CLAMP, int T, int U>
+__device__ __forceinline__ void list_round(h2 (&acc)[1][T / 2], uint32_t (&e)[U], const uint32_t (&f)[U], uint32_t (&b)[U][T / 2],
+                                           const uint32_t* after, const char* Bb, const HalfConst& c) {
+    constexpr int W = T / 2;
+    h2 q[1][W];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint32_t a1[1] = {e[u]};
+        half_products<PM, false, 1, T, true>(q, a1, b[u], c);
+        half_sums<PM, false, 1, T>(acc, q, a1, b[u], c);
+        if (u == U - 1) ListHead<U>::read(after, e);
+        read_words<W>(reinterpret_cast<const uint32_t*>(Bb + (f[u] >> 16)), b[u]);
+        half_round<CLAMP, 1, T, true>(acc, c);
+    }
+}
+
+// The steps of a list of n entries, a multiple of U (it is read on for 2 U more).
+template <int PM, bool CLAMP, int T, int U>
+__device__ __forceinline__ void list_steps(h2 (&sums)[T / 2], ListHead<U>& h, const uint32_t* list, const char* Bb, int n, const HalfConst& c) {
+    constexpr int W = T / 2;
+    uint32_t b[U][W];
+    h2 acc[1][W];
+#pragma unroll
+    for (int j = 0; j < W; ++j) acc[0][j] = sums[j];
+#pragma unroll
+    for (int u = 0; u < U; ++u) read_words<W>(reinterpret_cast<const uint32_t*>(Bb + (h.e[u] >> 16)), b[u]);
+    const uint32_t* after = list + 2 * U;
+    issue_first<true>();
+#pragma unroll 1
+    for (int i = 0; i < n; i += 2 * U) {
+        list_round<PM, CLAMP, T, U>(acc, h.e, h.f, b, after, Bb, c);
+        if (i + U >= n) break;
+        list_round<PM, CLAMP, T, U>(acc, h.f, h.e, b, after + U, Bb, c);
+        after += 2 * U;
+    }
+    issue_last<true>();
+#pragma unroll
+    for (int j = 0; j < W; ++j) sums[j] = acc[0][j];
+}
+
+// 32 steps (16 pairs) of S sets of rows, fully unrolled, TN columns a lane.  arow: the lane's row of the first set (the next
+// set's 8 rows on); Bs: the lane's words of the first step, BROW words a step.
+template <int PM, int ORDER, bool CLAMP, bool LONE, int S, int TN, int BROW, int PITCH>
+__device__ __forceinline__ void rows_tile(h2 (&acc)[S][TN / 2], h2 (&top)[S][TN / 2], const uint32_t* arow, const uint32_t* Bs, const HalfConst& c) {
+    constexpr int W = TN / 2;
+    constexpr int AHEAD = S * TN >= 12 ? 1 : (S * TN >= 8 ? 2 : 4), SLOTS = AHEAD + 2;
+    constexpr bool EARLY = LONE;
+    uint32_t a[S][16], b0[SLOTS][W], b1[SLOTS][W];
+    h2 q[2][S][W];
+    auto read_a = [&](int s) {                                 // four pairs of steps
+#pragma unroll
+        for (int i = 0; i < S; ++i) {
+            uint32_t x[4];
+            read_words<4>(arow + i * 8 * PITCH + s, x);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) a[i][s + j] = x[j];
+        }
+    };
+    auto a_of = [&](int s, uint32_t (&x)[S]) {
+#pragma unroll
+        for (int i = 0; i < S; ++i) x[i] = a[i][s];
+    };
+    read_a(0);
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s) {
+        read_words<W>(Bs + 2 * s * BROW, b0[s]);
+        read_words<W>(Bs + (2 * s + 1) * BROW, b1[s]);
+    }
+    uint32_t x[S], y[S];
+    a_of(0, x);
+    issue_first<!EARLY>();
+    if (EARLY) half_products<PM, false, S, TN, !LONE>(q[0], x, b0[0], c);
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+        const int k = s % SLOTS;
+        if (s % 4 == 2 && s < 12) read_a(s + 2);
+        if (s + AHEAD < 16) {
+            read_words<W>(Bs + 2 * (s + AHEAD) * BROW, b0[(s + AHEAD) % SLOTS]);
+            read_words<W>(Bs + (2 * (s + AHEAD) + 1) * BROW, b1[(s + AHEAD) % SLOTS]);
+        }
+        a_of(s, x);
+        if (!EARLY) half_products<PM, false, S, TN, !LONE>(q[0], x, b0[k], c);
+        half_sums<PM, false, S, TN>(acc, q[0], x, b0[k], c);
+        if (EARLY) half_products<PM, true, S, TN, !LONE>(q[1], x, b1[k], c);
+        half_round<CLAMP, S, TN, !LONE>(acc, c);
+        if (!EARLY) half_products<PM, true, S, TN, !LONE>(q[1], x, b1[k], c);
+        half_sums<PM, true, S, TN>(acc, q[1], x, b1[k], c);
+        if (EARLY && s < 15) { a_of(s + 1, y); half_products<PM, false, S, TN, !LONE>(q[0], y, b0[(s + 1) % SLOTS], c); }
+        half_round<CLAMP, S, TN, !LONE>(acc, c);
+        if (ORDER == LBA_ORDER_CHUNK16 && ((s + 1) & 7) == 0) half_level2<CLAMP, S, TN>(top, acc, c);
+    }
+    issue_last<!EARLY>();
+}
+
+typedef uint16_t __attribute__((may_alias)) u16_any;
+
+// A lane's pieces of a row of a matrix whose rows are 16-byte aligned and at least 16 codes long (K % 16 == 0).  A row beyond the matrix reads its first row:
+// what comes of it is not stored.
+struct AlignedRow {
+    const uint8_t* row;
+    int last, kq, K;           // the last piece of the row; the lane's first
+    __device__ __forceinline__ AlignedRow(const uint8_t* G, int rows, int K_, int r, int kq_) : row(G + (int64_t)(r >= 0 && r < rows ? r : 0) * K_), last(K_ - 16), kq(kq_), K(K_) {}
+    // the piece of the tile at k0: zero beyond K
+    __device__ __forceinline__ uint4 codes(const uint4& v, int k0) const {
+        const bool in = k0 + kq < K;
+        return make_uint4(in ? v.x : 0u, in ? v.y : 0u, in ? v.z : 0u, in ? v.w : 0u);
+    }
+};
+__device__ __forceinline__ uint4 load_aligned(const AlignedRow& s, int k0) {
+    return *reinterpret_cast<const uint4*>(s.row + min(k0 + s.kq, s.last));
+}
+
+template <int RW, int TN, int PM, int ORDER, int AMODE>
+__device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict__ smem, int m0, int n0) {
+    using T = RowTile<RW, TN>;
+    constexpr int BM = T::BM, BN = T::BN, S = T::SETS, W = TN / 2, U = T::U;
+    constexpr bool HALF = T::HALF;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tx = lane & 7, g = lane >> 3;
+    // staging: lane = 4 (row of the wave) + (piece of the row); B's pieces go to the lanes that have none of A's where that is possible
+    const int ca = (lane >> 2) < RW ? (lane & 3) * BM + wave * RW + (lane >> 2) : -1;
+    const int tidb = BN * 4 == 256 ? tid : (lane >= 32 && lane - 32 < BN ? wave * BN + lane - 32 : -1);
+    const uint8_t* pA = p.A + (int64_t)blockIdx.z * p.stride_a;
+    const uint8_t* pB = p.B + (int64_t)blockIdx.z * p.stride_b;
+    float* pC = p.C + (int64_t)blockIdx.z * p.stride_c;
+
+    set_flush_f32();
+    set_round_zero_f16();
+    set_flush_out_f16();
+
+    HalfConst c;
+    c.kc = as_h2(p.h_kc); c.rof = as_h2(p.h_rof); c.nrof = as_h2(p.h_rof ^ 0x80008000u); c.mask = p.h_mask_a; c.maskp = p.h_mask_p;
+    asm volatile("" : "+v"(c.kc), "+v"(c.rof), "+v"(c.nrof), "+v"(c.mask), "+v"(c.maskp));
+
+    h2 acc[S][W], top[S][W], acch[1][TN / 4 ? TN / 4 : 1], toph[1][TN / 4 ? TN / 4 : 1];
+#pragma unroll
+    for (int i = 0; i < S; ++i)
+#pragma unroll
+        for (int j = 0; j < W; ++j) { acc[i][j] = as_h2(0u); top[i][j] = as_h2(0u); }
+#pragma unroll
+    for (int j = 0; j < (TN / 4 ? TN / 4 : 1); ++j) { acch[0][j] = as_h2(0u); toph[0][j] = as_h2(0u); }
+
+    uint32_t* const Aw = smem + 2 * T::B_WORDS + wave * RW * T::PITCH;     // the wave's rows of A
+    const int ntiles = (p.K + HBK - 1) / HBK;
+    __shared__ uint32_t half_norm[2][4];                       // per stage and wave: largest squared norm of a piece of A (low half), of B
+    const bool dyn = half_follows_data(p);
+    constexpr bool SMALL = S * TN <= 4, LISTS = ORDER == LBA_ORDER_SEQ && !SMALL, PIECES = SMALL || AMODE >= 3;
+    constexpr bool conv = AMODE == 2 || AMODE == 4;
+    const RowPieces<BM> sa(pA, conv ? 1 : p.M, p.K, conv ? 0 : m0, ca);
+    const RowPieces<BN> sb(pB, p.N, p.K, n0, tidb);
+    ConvPieces sc = {};
+    ConvLane cl = {};
+    if (PIECES && conv) sc = ConvPieces::make<BM>(pA, p, m0, ca);
+    if (!PIECES && AMODE == 2) cl = conv_lane<BM, HBK>(pA, p, m0, ca);
+    constexpr int DEPTH = half_depth(S, TN);
+    uint4 ra[DEPTH], rc[DEPTH], rb[DEPTH];
+    const AlignedRow rowa(pA, conv ? 1 : p.M, p.K, conv ? 0 : m0 + ca % BM, ca >= 0 ? ca / BM * 16 : 0), rowb(pB, p.N, p.K, n0 + tidb % BN, tidb >= 0 ? tidb / BN * 16 : 0);
+    auto fetch = [&](int t, int d) {
+        const int k0 = tile_start(t);
+        if (PIECES) {
+            if (conv) load_piece(sc, p, k0, ra[d], rc[d]);
+            else      ra[d] = load_piece(sa, k0);
+            rb[d] = load_piece(sb, k0);
+        } else {
+            ra[d] = AMODE == 2 ? fetch_taps(cl, p, k0) : load_aligned(rowa, k0);
+            rb[d] = load_aligned(rowb, k0);
+        }
+    };
+    // the tile in LDS: steps of the two row sets' lists, and whether they are lists
+    int n_first = 0, n_second = 0;
+    bool listed = false;
+    int wait = 0, pause = 0;                                   // tiles until zeros are counted again; that many after the next count in vain
+    // Turns the wave's rows of the tile into lists if that saves enough; lane = code of the row.
+    auto list_tile = [&](int t) -> bool {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        uint32_t x[RW];
+#pragma unroll
+        for (int r = 0; r < RW; ++r) x[r] = reinterpret_cast<const u16_any*>(Aw + r * T::PITCH)[lane];
+        uint64_t nz[RW];
+        int most[2] = {0, 0};
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            nz[r] = __ballot(x[r] != 0u);
+            asm("s_max_u32 %0, %0, %1" : "+s"(most[r / 8]) : "s"(__builtin_popcountll(nz[r])) : "scc");
+        }
+        n_first = (most[0] + U - 1) & ~(U - 1);
+        n_second = (most[1] + U - 1) & ~(U - 1);
+        const int steps = p.K - t * HBK > 32 ? 64 : 32;
+        const int dense = S == 2 ? 2 * steps : (HALF ? steps + steps / 2 : steps);
+        // a step of a list takes 9/8 of an unrolled one, and building and starting the lists 12 to 14 of them (8192 x 512 x 2304 by the
+        // share of zeros: 104 us for none left, 3.0 us per step and row set; unrolled 2.7)
+        if ((HALF ? n_first + n_second / 2 : n_first + n_second) * 9 + 110 > dense * 8) return false;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const uint32_t row_of_b = (uint32_t)((t & 1) * T::B_WORDS * 4 + lane * T::BROW * 4) << 16;
+        const uint32_t last = 63u - (uint32_t)lane;
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            // the non-zero codes in order, the zeros behind them from the end (all 64 words are written)
+            const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(nz[r] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)nz[r], 0u));
+            uint32_t slot;
+            asm("v_cndmask_b32 %0, %1, %2, %3" : "=v"(slot) : "v"(at + last), "v"(at), "s"(nz[r]));
+            Aw[r * T::PITCH + slot] = x[r] | row_of_b;
+        }
+        return true;
+    };
+    auto stage = [&](int t, int d) {
+        uint4 va = !PIECES ? ra[d] : (conv ? sc.codes(p, ra[d], rc[d], t * HBK) : sa.codes(ra[d], t * HBK));
+        uint4 vb = PIECES ? sb.codes(rb[d], t * HBK) : rb[d];
+        if (!PIECES && (t + 1) * HBK > p.K) {                  // uniform: steps beyond K
+            if (!conv) va = rowa.codes(va, t * HBK);
+            vb = rowb.codes(vb, t * HBK);
+        }
+        const int st = t & 1;
+        uint32_t wa[8], wb[8];
+        decode_half(vb, p.h_shift_b, p.h_keep_b, p.h_scale_b, wb);
+        store_half_b<BN>(smem + st * T::B_WORDS, tidb, wb);
+        decode_half(va, p.h_shift_a, p.h_keep_a, p.h_scale_a, wa);
+        if (ca >= 0) {
+            uint4* const pairs = reinterpret_cast<uint4*>(Aw + (lane >> 2) * T::PITCH + (lane & 3) * 8);
+            pairs[0] = make_uint4(wa[0], wa[1], wa[2], wa[3]);
+            pairs[1] = make_uint4(wa[4], wa[5], wa[6], wa[7]);
+        }
+        listed = false;
+        if (LISTS) {
+            // worth counting: a zero among the first four codes of most pieces
+            const uint32_t z = (va.x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu;
+            const int hits = __builtin_popcountll(__ballot((z & 0x80808080u) != 0x80808080u && ca >= 0));
+            if (wait > 0) {
+                --wait;
+            } else if (hits >= 4 * RW * 3 / 4) {
+                listed = list_tile(t);
+                pause = listed ? 0 : min(2 * pause + 1, 15);
+                wait = pause;
+            }
+        }
+        if (dyn) {
+            const uint32_t na = __float_as_uint(piece_norm2(wa)), nb = __float_as_uint(piece_norm2(wb));
+            uint32_t m = ((na + 0xFFFFu) >> 16) | ((nb + 0xFFFFu) & 0xFFFF0000u);
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) m = pk_max_u16(m, (uint32_t)__shfl_xor((int)m, o, 64));
+            if (lane == 0) half_norm[st][wave] = m;
+        }
+    };
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) fetch(d, d);               // (a tile beyond K reads codes inside the operands that nothing uses)
+    stage(0, 0);
+    if (DEPTH > 1) fetch(DEPTH, 0);
+    __syncthreads();
+
+    const HalfBound bound(p);
+    int safe_tiles = 0;
+    const uint32_t* const arow = Aw + g * T::PITCH;
+    const uint32_t* const arowh = Aw + (8 + (lane >> 4)) * T::PITCH;       // the 4-row set: 16 lanes a row
+    for (int t0 = 0; t0 < ntiles; t0 += DEPTH) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            const int t = t0 + d;
+            if (t >= ntiles) break;
+            const bool more = (t + 1) < ntiles;
+            if (DEPTH == 1) fetch(t + 1, 0);
+            const int parts = p.K - t * HBK > 32 ? 2 : 1;      // steps beyond K are products of zeros: skipped 32 at a time
+            auto largest = [&]() {
+                uint32_t mx = 0u;
+#pragma unroll
+                for (int i = 0; i < S; ++i)
+#pragma unroll
+                    for (int j = 0; j < W; ++j)
+                        mx = pk_max_u16(mx, as_u32(ORDER == LBA_ORDER_CHUNK16 ? top[i][j] : acc[i][j]) & 0x7FFF7FFFu);
+                if (HALF) {
+#pragma unroll
+                    for (int j = 0; j < TN / 4; ++j)
+                        mx = pk_max_u16(mx, as_u32(ORDER == LBA_ORDER_CHUNK16 ? toph[0][j] : acch[0][j]) & 0x7FFF7FFFu);
+                }
+                return max_half(mx);
+            };
+            if (LISTS && listed) {
+                if (safe_tiles < parts) safe_tiles = bound.safe(largest(), dyn ? half_norm[t & 1] : nullptr, parts);
+                const char* const Bb = reinterpret_cast<const char*>(smem + tx * W);
+                const char* const Bh = reinterpret_cast<const char*>(smem + (lane & 15) * (W / 2));
+                ListHead<U> h0(arow), h1(HALF ? arowh : arow + (S == 2 ? 8 * T::PITCH : 0));
+                if (safe_tiles >= parts) {
+                    safe_tiles -= parts;
+                    list_steps<PM, false, TN, U>(acc[0], h0, arow, Bb, n_first, c);
+                    if constexpr (S == 2) list_steps<PM, false, TN, U>(acc[1], h1, arow + 8 * T::PITCH, Bb, n_second, c);
+                    if constexpr (HALF) list_steps<PM, false, TN / 2, U>(acch[0], h1, arowh, Bh, n_second, c);
+                } else {
+                    safe_tiles = 0;
+                    list_steps<PM, true, TN, U>(acc[0], h0, arow, Bb, n_first, c);
+                    if constexpr (S == 2) list_steps<PM, true, TN, U>(acc[1], h1, arow + 8 * T::PITCH, Bb, n_second, c);
+                    if constexpr (HALF) list_steps<PM, true, TN / 2, U>(acch[0], h1, arowh, Bh, n_second, c);
+                }
+            } else {
+                for (int part = 0; part < parts; ++part) {
+                    const uint32_t* const Bp = smem + (t & 1) * T::B_WORDS + part * 32 * T::BROW;
+                    const uint32_t* const Bs = Bp + tx * W;
+                    const uint32_t* const Bh = Bp + (lane & 15) * (W / 2);
+                    if (safe_tiles == 0) safe_tiles = bound.safe(largest(), dyn ? half_norm[t & 1] : nullptr, 1);
+                    if (safe_tiles > 0) {
+                        --safe_tiles;
+                        rows_tile<PM, ORDER, false, SMALL, S, TN, T::BROW, T::PITCH>(acc, top, arow + part * 16, Bs, c);
+                        if constexpr (HALF) rows_tile<PM, ORDER, false, false, 1, TN / 2, T::BROW, T::PITCH>(acch, toph, arowh + part * 16, Bh, c);
+                    } else {
+                        rows_tile<PM, ORDER, true, SMALL, S, TN, T::BROW, T::PITCH>(acc, top, arow + part * 16, Bs, c);
+                        if constexpr (HALF) rows_tile<PM, ORDER, true, false, 1, TN / 2, T::BROW, T::PITCH>(acch, toph, arowh + part * 16, Bh, c);
+                    }
+                }
+            }
+            if (more) {
+                constexpr int next = (DEPTH > 1) ? 1 : 0;
+                stage(t + 1, (d + next) % DEPTH);
+                if (DEPTH > 1) fetch(t + 1 + DEPTH, (d + next) % DEPTH);
+            }
+            __syncthreads();
+        }
+    }
+
+    // C = S * 2^out_exp, zero written as +0
+    auto store = [&](int m, int n, const h2* s, auto count) {
+        constexpr int CT = decltype(count)::value;
+        if (m >= p.M) return;
+        float v[CT];
+#pragma unroll
+        for (int j = 0; j < CT; ++j) v[j] = __builtin_ldexpf((float)(j & 1 ? s[j / 2].y : s[j / 2].x), p.out_exp - 112) + 0.0f;    // -0 + 0 is +0
+        float* dst = pC + (int64_t)m * p.N + n;
+        if (CT % 4 == 0 && p.c_vec && n + CT - 1 < p.N) {
+#pragma unroll
+            for (int j = 0; j + 3 < CT; j += 4) *reinterpret_cast<f32x4_any*>(dst + j) = f32x4_any{v[j], v[j + 1], v[j + 2], v[j + 3]};
+        } else if (CT == 2 && p.c_vec && n + 1 < p.N) {
+            *reinterpret_cast<f32x2_any*>(dst) = f32x2_any{v[0], v[CT - 1]};
+        } else {
+#pragma unroll
+            for (int j = 0; j < CT; ++j)
+                if (n + j < p.N) dst[j] = v[j];
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < S; ++i) store(m0 + wave * RW + 8 * i + g, n0 + tx * TN, ORDER == LBA_ORDER_CHUNK16 ? top[i] : acc[i], IntConst<TN>{});
+    if constexpr (HALF)
+        store(m0 + wave * RW + 8 + (lane >> 4), n0 + (lane & 15) * (TN / 2), ORDER == LBA_ORDER_CHUNK16 ? toph[0] : acch[0], IntConst<TN / 2>{});
+}
+
+template <int TM, int TN, int PM, int ORDER, int AMODE>
+__global__ void __launch_bounds__(256, LBA_FAST_MIN_WAVES) lba_half_kernel(const KParams p) {
+    constexpr int RW = TM == 4 ? 16 : 8, TR = TN == 4 ? 8 : 4;
+    __shared__ __attribute__((aligned(16))) uint32_t smem[RowTile<RW, TR>::WORDS];
+    rows_body<RW, TR, PM, ORDER, AMODE>(p, smem, blockIdx.x * 16 * TM, blockIdx.y * 16 * TN);
+}
+
+template <int PM, int ORDER, int AMODE>
+__global__ void __launch_bounds__(256, LBA_FAST_MIN_WAVES) lba_half_mixed_kernel(const KParams p) {
+    __shared__ __attribute__((aligned(16))) uint32_t smem[RowTile<16, 8>::WORDS];
+    const int b = blockIdx.x;
+    if (b < p.mix_main) {                                      // uniform
+        const int by = b / p.mix_gx_main, bx = b - by * p.mix_gx_main;
+        rows_body<16, 8, PM, ORDER, AMODE>(p, smem, bx * 64, by * 64);
+    } else if (b < p.mix_main + p.mix_half) {
+        const int t = b - p.mix_main;
+        const int by = t / p.mix_gx_half, bx = t - by * p.mix_gx_half;
+        rows_body<12, 8, PM, ORDER, AMODE>(p, smem, p.mix_m_main + bx * 48, by * 64);
+    } else {
+        const int t = b - p.mix_main - p.mix_half;
+        const int by = t / p.mix_gx_tail, bx = t - by * p.mix_gx_tail;
+        if (p.mix_tail16) rows_body<8, 2, PM, ORDER, AMODE>(p, smem, p.mix_m_half + bx * 32, by * 16);   // uniform
+        else              rows_body<8, 4, PM, ORDER, AMODE>(p, smem, p.mix_m_half + bx * 32, by * 32);
+    }
+}
+
+}  // namespace lba
+#endif
