@@ -117,12 +117,20 @@ struct FastConst {
     int sh, shp;
 };
 
+// A full-rate instruction issues in half the time of a half-rate one only beside a full-rate instruction of another wave, and waves
+// at random places of their steps mostly have none to offer.  Half-rate phases at priority 1 and full-rate ones at priority 0 make
+// waves gather at the latter: mul|fma|cvt, the nearest-even step at M = 7, 11.4 -> 9.1 cycles in the issue-rate probe, the packed
+// step 12.1 -> 10.9.  (One wave per SIMD has nobody to wait for: 13.5 -> 14.6.)
+template <bool ON> __device__ __forceinline__ void issue_first() { if (ON) __builtin_amdgcn_s_setprio(1); }
+template <bool ON> __device__ __forceinline__ void issue_last() { if (ON) __builtin_amdgcn_s_setprio(0); }
+
 // One k-step for a GROUP of NCH independent chains, written phase by phase (all products, then
 // all adds, then all roundings) so that consecutive instructions never depend on each other.
 // CLAMP = false is used for k-tiles in which no chain can reach R_OF (see lba_fast_kernel).
 template <int PM, int RND, bool CLAMP, int I0, int NI, int TM, int NJ>
 __device__ __forceinline__ void fast_group(float (&accf)[TM][NJ], const float (&af)[TM], const float (&b)[NJ],
                                            const FastConst& c) {
+    constexpr bool PRIO = NI * NJ > 4;                         // not the small lane blocks, alone on their SIMD
     float (*acc)[NJ] = &accf[I0];
     const float* a = &af[I0];
     if (PM == PM_IDENT && RND == RND_RNE_ODD) {
@@ -164,6 +172,7 @@ __device__ __forceinline__ void fast_group(float (&accf)[TM][NJ], const float (&
             // the product is exact in FP32, so this is Q_prod's one nearest-even rounding (a carry moves
             // to the next binade by itself); the flush above was decided on the unrounded product
             uint32_t l[NI][NJ];
+            issue_first<PRIO>();
 #pragma unroll
             for (int i = 0; i < NI; ++i)
 #pragma unroll
@@ -172,7 +181,13 @@ __device__ __forceinline__ void fast_group(float (&accf)[TM][NJ], const float (&
 #pragma unroll
             for (int i = 0; i < NI; ++i)
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) q[i][j] = __uint_as_float((__float_as_uint(q[i][j]) + c.halfp + l[i][j]) & c.maskp);
+                for (int j = 0; j < NJ; ++j) q[i][j] = __uint_as_float(__float_as_uint(q[i][j]) + c.halfp + l[i][j]);
+            __builtin_amdgcn_sched_barrier(0);
+            issue_last<PRIO>();
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) q[i][j] = __uint_as_float(__float_as_uint(q[i][j]) & c.maskp);
             __builtin_amdgcn_sched_barrier(0);
         }
         if (PM == PM_FLUSH_CLAMP || PM == PM_TRUNC_CLAMP || PM == PM_RNE_CLAMP) {
@@ -207,13 +222,17 @@ __device__ __forceinline__ void fast_group(float (&accf)[TM][NJ], const float (&
     }
     __builtin_amdgcn_sched_barrier(0);
     if (RND == RND_RNE_BF16) {
+        issue_first<PRIO>();
 #pragma unroll
         for (int i = 0; i < NI; ++i)
 #pragma unroll
             for (int j = 0; j < NJ; ++j) acc[i][j] = rne_to_8_bits(acc[i][j]);
+        __builtin_amdgcn_sched_barrier(0);
+        issue_last<PRIO>();
     } else {
         if (RND == LBA_ROUND_RNE || RND == RND_RNE_ODD) {
             uint32_t l[NI][NJ];
+            issue_first<PRIO>();
 #pragma unroll
             for (int i = 0; i < NI; ++i)
 #pragma unroll
@@ -224,6 +243,7 @@ __device__ __forceinline__ void fast_group(float (&accf)[TM][NJ], const float (&
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) acc[i][j] = __uint_as_float(__float_as_uint(acc[i][j]) + c.half + l[i][j]);
             __builtin_amdgcn_sched_barrier(0);
+            issue_last<PRIO>();
         }
 #pragma unroll
         for (int i = 0; i < NI; ++i)

@@ -120,10 +120,6 @@ __device__ __forceinline__ void store_half_b(uint32_t* __restrict__ dst, int tid
     }
 }
 
-// Priority of a wave's packed instructions over its masks (lba_rows.h: why).
-template <bool ON> __device__ __forceinline__ void issue_first() { if (ON) __builtin_amdgcn_s_setprio(1); }
-template <bool ON> __device__ __forceinline__ void issue_last() { if (ON) __builtin_amdgcn_s_setprio(0); }
-
 // A step's products (PM_IDENT: none).  HI: the step is the odd k of its pair of steps.
 template <int PM, bool HI, int TM, int TN, bool PRIO = (TM * TN > 4)>
 __device__ __forceinline__ void half_products(h2 (&q)[TM][TN / 2], const uint32_t (&a)[TM], const uint32_t (&b)[TN / 2], const HalfConst& c) {
@@ -244,6 +240,7 @@ __device__ __forceinline__ void half_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[TM][T
         read_half_b<TN, BNP>(Bs, 2 * s, tx, b0[s]);
         read_half_b<TN, BNP>(Bs, 2 * s + 1, tx, b1[s]);
     }
+    issue_first<!EARLY>();
     if (EARLY) half_products<PM, false, TM, TN>(q[0], a[0], b0[0], c);
 #pragma unroll
     for (int s = 0; s < 16; ++s) {

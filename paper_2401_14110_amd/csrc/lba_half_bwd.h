@@ -44,10 +44,10 @@ __device__ __forceinline__ uint32_t pk_add_u16_sat(uint32_t a, uint32_t b) {   /
 __device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
 }
-// shift register of two chains: bit 15 of y's halves enters from the top
+// shift register of two chains, shifted by one already: bit 15 of y's halves enters at the top
 __device__ __forceinline__ uint32_t pk_shift_in(uint32_t w, uint32_t y, uint32_t bit15) {
     uint32_t r;
-    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "v"(bit15), "v"(y), "v"(w >> 1));
+    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "v"(bit15), "v"(y), "v"(w));
     return r;
 }
 
@@ -67,6 +67,8 @@ __device__ __forceinline__ void half_bwd_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[T
                                               uint32_t (&of2)[TM][TN], uint32_t (&uf2)[TM][TN], int pos, const uint32_t* As,
                                               const uint32_t* Bs, int tx, int ty, const HalfBwdConst& c) {
     constexpr int NJ = TN / 2;
+    constexpr bool PRIO = TM * TN > 4;
+    issue_first<PRIO>();
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         uint32_t wo[TM][NJ], wu[TM][NJ];
@@ -107,8 +109,12 @@ __device__ __forceinline__ void half_bwd_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[T
                 // phase by phase over the lane's chains, as the forward tile
 #define LBA_EACH for (int i = 0; i < TM; ++i) _Pragma("unroll") for (int j = 0; j < NJ; ++j)
                 __builtin_amdgcn_sched_barrier(0);
+                issue_last<PRIO>();
                 _Pragma("unroll") LBA_EACH acc[i][j] = as_h2(t[i][j] & c.mask);
+                if (!QUIET) { _Pragma("unroll") LBA_EACH wo[i][j] >>= 1; }
+                if (UF) { _Pragma("unroll") LBA_EACH wu[i][j] >>= 1; }
                 __builtin_amdgcn_sched_barrier(0);
+                issue_first<PRIO>();
                 if (!QUIET) {
                     _Pragma("unroll") LBA_EACH asm("v_pk_min_f16 %0, %0, %1" : "+v"(acc[i][j]) : "v"(c.rof));
                     _Pragma("unroll") LBA_EACH asm("v_pk_max_f16 %0, %0, %1" : "+v"(acc[i][j]) : "v"(c.nrof));
@@ -175,6 +181,7 @@ __device__ __forceinline__ void half_bwd_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[T
                 }
             }
     }
+    issue_last<PRIO>();
 }
 
 // Stores a lane's words (one per chain, first step in bit 0) as word `word` of a plane; non-temporal, see store_event_words.
