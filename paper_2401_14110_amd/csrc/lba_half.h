@@ -160,15 +160,17 @@ __device__ __forceinline__ void half_sums(h2 (&acc)[TM][TN / 2], const h2 (&q)[T
 }
 
 // ... and their rounding to M + 1 bits
-template <bool CLAMP, int TM, int TN, bool PRIO = (TM * TN > 4)>
+template <bool CLAMP, int TM, int TN, bool PRIO = (TM * TN > 4), bool MASK = true>
 __device__ __forceinline__ void half_round(h2 (&acc)[TM][TN / 2], const HalfConst& c) {
-    issue_last<PRIO>();
+    if (MASK) {
+        issue_last<PRIO>();
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN / 2; ++j) acc[i][j] = as_h2(as_u32(acc[i][j]) & c.mask);
-    __builtin_amdgcn_sched_barrier(0);
-    issue_first<PRIO>();
+            for (int j = 0; j < TN / 2; ++j) acc[i][j] = as_h2(as_u32(acc[i][j]) & c.mask);
+        __builtin_amdgcn_sched_barrier(0);
+        issue_first<PRIO>();
+    }
     if (CLAMP) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -296,13 +298,12 @@ __device__ __forceinline__ uint32_t nonzero_codes(const uint4& v) {
 // range (R_OF below 64 of the largest products).
 __device__ __forceinline__ bool half_follows_data(const KParams& p) { return p.dyn_bound != 0 && 2.0f * p.fast_thresh < p.rof_a; }
 
-// For how many of the next tiles of 32 steps (0 to 8) no sum of the wave can reach R_OF; mf: this lane's largest |S|.
+// For how many of the next tiles of 32 steps (0 to 8) no sum of the wave can reach R_OF, or the end of FP16's range; mf: this lane's largest |S|.
 struct HalfBound {
     float rof, thresh, grow, kcf;
-    // the planner's bound is in the FP32 tile's domain (R_UF at 2^-126); 2^112 moves it to R_UF at 2^-14.  grow: 32 of the
-    // largest products there are (thresh is rounded down; the factor covers the roundings here)
+    // grow: 32 of the largest products there are (thresh is rounded down; the factor covers the roundings here)
     __device__ __forceinline__ explicit HalfBound(const KParams& p)
-        : rof(p.rof_a * 0x1p112f), thresh(p.fast_thresh * 0x1p112f), grow(1.0001f * (rof - thresh)), kcf((float)as_h2(p.h_kc).x) {}
+        : rof(p.h_top), thresh(p.h_thresh), grow(1.0001f * (rof - thresh)), kcf((float)as_h2(p.h_kc).x) {}
     // norms: half_stage's, for the current tile, or null; parts: of how many parts the bound that follows the data is asked
     __device__ __forceinline__ int safe(float mf, const uint32_t* norms, int parts = 1) const {
         if (__all(mf < thresh - 3.0f * grow)) return __all(mf < thresh - 7.0f * grow) ? 8 : 4;

@@ -63,6 +63,8 @@ struct KParams {
     int32_t map_rbx, map_sbx, map_rbw, map_sbw;
     // packed FP16 carriers (lba_half.h; h_on = 1): two copies of an FP16 value or of a 16-bit mask per word
     int32_t h_on;
+    int32_t h_range;                        // R_OF lies beyond FP16's range: 1, or 2 where M = 10 needs no mask (lba_rows.h)
+    float h_top, h_thresh;                  // R_OF, or the end of FP16's range, and it less 32 of the largest products (as fast_thresh), in the tile's domain
     uint32_t h_kc, h_rof, h_mask_a, h_mask_p;
     uint32_t h_scale_a, h_scale_b;          // a decoded code's image times this is the operand in the tile's domain
     uint32_t h_keep_a, h_keep_b;            // the image's bits: code in the word's high byte >> h_shift, & h_keep

@@ -21,6 +21,7 @@ static hipError_t launch_plan(const Plan& pl, hipStream_t st) {
     if (pl.kernel == KERNEL_FAST && pl.events == 2) return launch_fast_diff(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.events && pl.kp.h_on) return launch_half_bwd(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.events) return launch_fast_bwd(pl, st);
+    if (pl.kernel == KERNEL_FAST && pl.kp.h_on && pl.kp.h_range) return pl.kp.conv ? launch_wide_conv(pl, st) : launch_wide(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.kp.h_on) return pl.kp.conv ? launch_half_conv(pl, st) : launch_half(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.rne_odd) return launch_fast_odd(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.amode == 2) return launch_fast_conv(pl, st);
@@ -65,7 +66,9 @@ static void plan_kernel_name(const Plan& pl, bool uf, char* buf, size_t n) {
         else                      snprintf(buf, n, "lba_fast_bwd_kernel<%d, %d, %d, %s, 0>", pm, pl.round, ord, b);
     } else if (pl.kp.h_on) {
         const int am = (pl.amode == 2 ? 2 : 0) + (pl.kp.K % 16 == 0 ? 0 : (pl.amode == 2 ? 2 : 3));      // (operands on a 16-byte boundary)
-        if (pl.mix_tail > 0) snprintf(buf, n, "lba_half_mixed_kernel<%d, %d, %d>", pm, ord, am);
+        if (pl.kp.h_range && pl.mix_tail > 0) snprintf(buf, n, "lba_wide_mixed_kernel<%d, %d, %d>", ord, am, pl.kp.h_range);
+        else if (pl.kp.h_range)   snprintf(buf, n, "lba_wide_kernel<%d, %d, %d, %d, %d>", pl.tm, pl.tn, ord, am, pl.kp.h_range);
+        else if (pl.mix_tail > 0) snprintf(buf, n, "lba_half_mixed_kernel<%d, %d, %d>", pm, ord, am);
         else                 snprintf(buf, n, "lba_half_kernel<%d, %d, %d, %d, %d>", pl.tm, pl.tn, pm, ord, am);
     } else if (pl.rne_odd) {
         snprintf(buf, n, "lba_fast_kernel<4, 4, %d, %d, 3, %d, 0>", pl.bk, pm, ord);

@@ -30,6 +30,8 @@ hipError_t launch_fast_bwd_in_mixed(const Plan& pl, hipStream_t st);   // plans 
 // forward, packed FP16 carriers (kp.h_on) of any code format with E <= 4: row-major matrices, im2col rows
 hipError_t launch_half(const Plan& pl, hipStream_t st);
 hipError_t launch_half_conv(const Plan& pl, hipStream_t st);
+hipError_t launch_wide(const Plan& pl, hipStream_t st);            // the same, accumulators beyond FP16's range (kp.h_range)
+hipError_t launch_wide_conv(const Plan& pl, hipStream_t st);
 hipError_t launch_half_bwd(const Plan& pl, hipStream_t st);        // plans with events == 1 on packed FP16 carriers (kp.h_on)
 // the DIFF plane, scaled-domain kernel (plans with events == 2)
 hipError_t launch_fast_diff(const Plan& pl, hipStream_t st);

@@ -155,14 +155,17 @@ static bool rne_odd_ok(const lba_qfmt& qp, const lba_qfmt& qa, bool flush, bool 
 
 // Packed FP16 carriers (lba_half.h): fills in kp.h_* and returns true when every step of the chain is exact on them.
 // c_p / c_a: the exponents that put Q_prod's effective R_UF (2^-bpe) and Q_acc's (2^-bae) at 2^-14.  Conditions, in the
-// order of the code: R_OF of Q_acc a normal FP16 number; a product that Q_prod does not truncate at most 11 bits wide
+// order of the code: R_OF of Q_acc a normal FP16 number, or in the forward call beyond FP16's range (kp.h_range); a product that Q_prod does not truncate at most 11 bits wide
 // (PM_IDENT: the multiply-add takes it unrounded); the largest product below FP16's largest number; kc and both scaled
 // operands, down to their subnormal units, FP16 numbers.
-static bool half_carrier(const lba_qfmt& qp, const lba_qfmt& qa, const InSpec& in, int prod_mode, int bpe, int bae, KParams* kp) {
+static bool half_carrier(const lba_qfmt& qp, const lba_qfmt& qa, const InSpec& in, int prod_mode, int bpe, int bae, bool forward_only, KParams* kp) {
     if (in.ea > 4 || in.eb > 4 || qa.man_bits > 10) return false;
     const int c_a = bae - 14, c_p = prod_mode == PM_IDENT ? c_a : bpe - 14;
     const int top = (1 << qa.exp_bits) - qa.bias - 1 + c_a;    // top exponent of Q_acc in the tile's domain
-    if (top < -14 || top > 14) return false;
+    // R_OF beyond FP16's range: sums that could leave it go on in FP32 (lba_rows.h, a slow loop), so the range must be far above a
+    // product: 64 of the largest ones, two tiles from zero
+    const bool beyond = top > 14;
+    if (top < -14 || (beyond && (forward_only == false || prod_mode != PM_FLUSH || std::ldexp(in.max_prod, c_a) * 64.0 > 65504.0))) return false;
     if (prod_mode == PM_FLUSH && in.sig_bits > 11) return false;
     if (prod_mode == PM_TRUNC && qp.man_bits > 10) return false;
     if (prod_mode != PM_IDENT && std::ldexp(in.max_prod, c_p) > 65504.0) return false;
@@ -184,7 +187,8 @@ static bool half_carrier(const lba_qfmt& qp, const lba_qfmt& qa, const InSpec& i
     const auto twice = [](uint32_t h) { return h | (h << 16); };
     const auto pow2 = [&](int e) { return twice(e >= -14 ? (uint32_t)(e + 15) << 10 : 1u << (e + 24)); };
     kp->h_kc = pow2(c_a - c_p);
-    kp->h_rof = twice(((uint32_t)(top + 15) << 10) | ((0x3FFu << (10 - qa.man_bits)) & 0x3FFu));
+    kp->h_rof = beyond ? twice(0x7BFFu) : twice(((uint32_t)(top + 15) << 10) | ((0x3FFu << (10 - qa.man_bits)) & 0x3FFu));
+    kp->h_range = !beyond ? 0 : (qa.man_bits == 10 ? 2 : 1);
     kp->h_mask_a = twice((0xFFFFu << (10 - qa.man_bits)) & 0xFFFFu);
     kp->h_mask_p = qp.man_bits >= 10 ? 0xFFFFFFFFu : twice((0xFFFFu << (10 - qp.man_bits)) & 0xFFFFu);
     kp->h_scale_a = pow2(e_a - img[0]);
@@ -438,9 +442,12 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
         const bool half = N * K >= 16 && K <= kPieceMaxK && (conv || M * K >= 16) && events != 2 && !rne_odd && qa.round == LBA_ROUND_FLOOR && !nouf_a &&
                           (p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH || p.prod_mode == PM_TRUNC) &&
                           (!p.events || p.of_only || half_underflow_ok(qp, in, bpe, bae)) &&
-                          half_carrier(qp, qa, in, p.prod_mode, bpe, bae, &kp);
+                          half_carrier(qp, qa, in, p.prod_mode, bpe, bae, !p.events, &kp);
         const int fp32_slots_x100 = p.valu_per_mac_x100;
-        if (half && (!p.events || p.of_only)) p.valu_per_mac_x100 = p.prod_mode == PM_IDENT ? 200 : (p.prod_mode == PM_FLUSH ? 250 : 300);
+        // (accumulators beyond FP16's range keep the FP32 price, a budget, unless they need no mask: two slots per MAC)
+        if (half && kp.h_range == 1) {}
+        else if (half && kp.h_range == 2) p.valu_per_mac_x100 = 200;
+        else if (half && (!p.events || p.of_only)) p.valu_per_mac_x100 = p.prod_mode == PM_IDENT ? 200 : (p.prod_mode == PM_FLUSH ? 250 : 300);
         const int level2_x100 = order != LBA_ORDER_CHUNK16 ? 0   // add, and [, bfe, add3], zero per 16 steps
                                 : (events == 2 ? 1300 : events ? 900 : (qa.round == LBA_ROUND_RNE ? 700 : 300)) / 16;
         p.valu_per_mac_x100 += level2_x100;
@@ -499,9 +506,16 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
         float g1f = (float)g1;
         if ((double)g1f > g1) g1f = std::nextafterf(g1f, -INFINITY);
         kp.rof_grow1 = g1f;
+        if (kp.h_on) {                                         // (floor rounding; 2^112 moves R_UF from 2^-126 to 2^-14)
+            kp.h_top = kp.h_range ? 65504.0f : std::ldexp(kp.rof_a, 112);
+            const double th = 65504.0 - 32.0 * std::ldexp(pmax, 112);
+            float thf = (float)th;
+            if ((double)thf > th) thf = std::nextafterf(thf, -INFINITY);
+            kp.h_thresh = kp.h_range ? (thf > 0.0f ? thf : -1.0f) : kp.fast_thresh * 0x1p112f;
+        }
         // (floor only: under nearest-even the growth allowance eats most of the margin, and the sweep of 4096^3 formats
         // measured no gain there)
-        kp.dyn_bound = ((p.amode != 1 || kp.h_on) && !p.rne_odd && qa.round == LBA_ROUND_FLOOR && kp.fast_thresh4 <= 0.0f) ? 1 : 0;
+        kp.dyn_bound = (!kp.h_range && (p.amode != 1 || kp.h_on) && !p.rne_odd && qa.round == LBA_ROUND_FLOOR && kp.fast_thresh4 <= 0.0f) ? 1 : 0;
     }
     const int64_t bm = 16 * p.tm, bn = 16 * p.tn;
     p.grid_x = (int)((M + bm - 1) / bm);

@@ -72,7 +72,7 @@ struct ListHead {
 
 // U steps: entries e with their rows of B in b; the rows of the next entries f are asked for as the registers of a step become
 // free, and the entries after those when the last of e is used.
-template <int PM, bool CLAMP, int T, int U>
+template <int PM, bool CLAMP, bool MASK, int T, int U>
 __device__ __forceinline__ void list_round(h2 (&acc)[1][T / 2], uint32_t (&e)[U], const uint32_t (&f)[U], uint32_t (&b)[U][T / 2],
                                            const uint32_t* after, const char* Bb, const HalfConst& c) {
     constexpr int W = T / 2;
@@ -84,12 +84,12 @@ __device__ __forceinline__ void list_round(h2 (&acc)[1][T / 2], uint32_t (&e)[U]
         half_sums<PM, false, 1, T>(acc, q, a1, b[u], c);
         if (u == U - 1) ListHead<U>::read(after, e);
         read_words<W>(reinterpret_cast<const uint32_t*>(Bb + (f[u] >> 16)), b[u]);
-        half_round<CLAMP, 1, T, true>(acc, c);
+        half_round<CLAMP, 1, T, true, MASK>(acc, c);
     }
 }
 
 // The steps of a list of n entries, a multiple of U (it is read on for 2 U more).
-template <int PM, bool CLAMP, int T, int U>
+template <int PM, bool CLAMP, bool MASK, int T, int U>
 __device__ __forceinline__ void list_steps(h2 (&sums)[T / 2], ListHead<U>& h, const uint32_t* list, const char* Bb, int n, const HalfConst& c) {
     constexpr int W = T / 2;
     uint32_t b[U][W];
@@ -99,22 +99,22 @@ __device__ __forceinline__ void list_steps(h2 (&sums)[T / 2], ListHead<U>& h, co
 #pragma unroll
     for (int u = 0; u < U; ++u) read_words<W>(reinterpret_cast<const uint32_t*>(Bb + (h.e[u] >> 16)), b[u]);
     const uint32_t* after = list + 2 * U;
-    issue_first<true>();
+    issue_first<MASK>();
 #pragma unroll 1
     for (int i = 0; i < n; i += 2 * U) {
-        list_round<PM, CLAMP, T, U>(acc, h.e, h.f, b, after, Bb, c);
+        list_round<PM, CLAMP, MASK, T, U>(acc, h.e, h.f, b, after, Bb, c);
         if (i + U >= n) break;
-        list_round<PM, CLAMP, T, U>(acc, h.f, h.e, b, after + U, Bb, c);
+        list_round<PM, CLAMP, MASK, T, U>(acc, h.f, h.e, b, after + U, Bb, c);
         after += 2 * U;
     }
-    issue_last<true>();
+    issue_last<MASK>();
 #pragma unroll
     for (int j = 0; j < W; ++j) sums[j] = acc[0][j];
 }
 
 // 32 steps (16 pairs) of S sets of rows, fully unrolled, TN columns a lane.  arow: the lane's row of the first set (the next
 // set's 8 rows on); Bs: the lane's words of the first step, BROW words a step.
-template <int PM, int ORDER, bool CLAMP, bool LONE, int S, int TN, int BROW, int PITCH>
+template <int PM, int ORDER, bool CLAMP, bool MASK, bool LONE, int S, int TN, int BROW, int PITCH>
 __device__ __forceinline__ void rows_tile(h2 (&acc)[S][TN / 2], h2 (&top)[S][TN / 2], const uint32_t* arow, const uint32_t* Bs, const HalfConst& c) {
     constexpr int W = TN / 2;
     constexpr int AHEAD = S * TN >= 12 ? 1 : (S * TN >= 8 ? 2 : 4), SLOTS = AHEAD + 2;
@@ -142,8 +142,8 @@ __device__ __forceinline__ void rows_tile(h2 (&acc)[S][TN / 2], h2 (&top)[S][TN 
     }
     uint32_t x[S], y[S];
     a_of(0, x);
-    issue_first<!EARLY>();
-    if (EARLY) half_products<PM, false, S, TN, !LONE>(q[0], x, b0[0], c);
+    issue_first<MASK && !EARLY>();
+    if (EARLY) half_products<PM, false, S, TN, MASK && !LONE>(q[0], x, b0[0], c);
 #pragma unroll
     for (int s = 0; s < 16; ++s) {
         const int k = s % SLOTS;
@@ -153,17 +153,17 @@ __device__ __forceinline__ void rows_tile(h2 (&acc)[S][TN / 2], h2 (&top)[S][TN 
             read_words<W>(Bs + (2 * (s + AHEAD) + 1) * BROW, b1[(s + AHEAD) % SLOTS]);
         }
         a_of(s, x);
-        if (!EARLY) half_products<PM, false, S, TN, !LONE>(q[0], x, b0[k], c);
+        if (!EARLY) half_products<PM, false, S, TN, MASK && !LONE>(q[0], x, b0[k], c);
         half_sums<PM, false, S, TN>(acc, q[0], x, b0[k], c);
-        if (EARLY) half_products<PM, true, S, TN, !LONE>(q[1], x, b1[k], c);
-        half_round<CLAMP, S, TN, !LONE>(acc, c);
-        if (!EARLY) half_products<PM, true, S, TN, !LONE>(q[1], x, b1[k], c);
+        if (EARLY) half_products<PM, true, S, TN, MASK && !LONE>(q[1], x, b1[k], c);
+        half_round<CLAMP, S, TN, MASK && !LONE, MASK>(acc, c);
+        if (!EARLY) half_products<PM, true, S, TN, MASK && !LONE>(q[1], x, b1[k], c);
         half_sums<PM, true, S, TN>(acc, q[1], x, b1[k], c);
-        if (EARLY && s < 15) { a_of(s + 1, y); half_products<PM, false, S, TN, !LONE>(q[0], y, b0[(s + 1) % SLOTS], c); }
-        half_round<CLAMP, S, TN, !LONE>(acc, c);
+        if (EARLY && s < 15) { a_of(s + 1, y); half_products<PM, false, S, TN, MASK && !LONE>(q[0], y, b0[(s + 1) % SLOTS], c); }
+        half_round<CLAMP, S, TN, MASK && !LONE, MASK>(acc, c);
         if (ORDER == LBA_ORDER_CHUNK16 && ((s + 1) & 7) == 0) half_level2<CLAMP, S, TN>(top, acc, c);
     }
-    issue_last<!EARLY>();
+    issue_last<MASK && !EARLY>();
 }
 
 typedef uint16_t __attribute__((may_alias)) u16_any;
@@ -184,11 +184,57 @@ __device__ __forceinline__ uint4 load_aligned(const AlignedRow& s, int k0) {
     return *reinterpret_cast<const uint4*>(s.row + min(k0 + s.kq, s.last));
 }
 
-template <int RW, int TN, int PM, int ORDER, int AMODE>
+// Sums beyond FP16's range (accumulators of E >= 5): the constants of the FP32 step (fast_group), R_UF at 2^-126.
+struct BeyondConst {
+    float kc, rof;
+    uint32_t mask, maskp;
+    __device__ __forceinline__ float quantize(float t) const { return med3(__uint_as_float(__float_as_uint(t) & mask), -rof, rof); }
+};
+// n steps (a multiple of 4) of one row in FP32: row: pairs (k, k + 1), or a list; off: byte offset of the first step's words of B.  The
+// rare end of a chain whose sums leave FP16's range: four steps' operands at a time (4096 x 1024 x 2048 all beyond it: 1741 us one
+// step at a time, 1260 so, lba_fast_kernel 513).
+template <int PM, int ORDER, int T, int BROW>
+__device__ __forceinline__ void beyond_steps(float (&sum)[T], float (&top)[T], const uint32_t* row, bool listed, int n, const char* Bb, uint32_t off,
+                                             const BeyondConst& c) {
+#pragma unroll 1
+    for (int k = 0; k < n; k += 4) {
+        uint32_t e[4], b[4][T / 2];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) e[u] = listed ? row[k + u] : row[(k + u) >> 1] >> (16 * (u & 1));
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            read_words<T / 2>(reinterpret_cast<const uint32_t*>(Bb + (listed ? e[u] >> 16 : off + (uint32_t)(k + u) * (BROW * 4))), b[u]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float a = (float)as_h2(e[u]).x * 0x1p-56f;   // (an operand can be as small as 2^-24: half of the 2^-112 to each)
+            float q[T];
+#pragma unroll
+            for (int j = 0; j < T; ++j) {
+                const h2 w = as_h2(b[u][j / 2]);
+                q[j] = ((float)(j & 1 ? w.y : w.x) * 0x1p-56f) * a;   // flushed below Q_prod's R_UF
+            }
+#pragma unroll
+            for (int j = 0; j < T; ++j) {
+                if (PM == PM_TRUNC) q[j] = __uint_as_float(__float_as_uint(q[j]) & c.maskp);
+                sum[j] = c.quantize(__builtin_fmaf(q[j], c.kc, sum[j]));
+            }
+        }
+        if (ORDER == LBA_ORDER_CHUNK16 && (k & 12) == 12) {
+#pragma unroll
+            for (int j = 0; j < T; ++j) { top[j] = c.quantize(top[j] + sum[j]); sum[j] = 0.0f; }
+        }
+    }
+}
+
+// RANGE 0: every sum fits FP16 up to R_OF (half_carrier, lba_plan.cpp).  1, 2: R_OF lies beyond FP16's range; the bound that spares the
+// clamp elsewhere shows that no sum leaves the range in the tile at hand (65504 in place of R_OF), and a wave where it cannot goes
+// on in FP32 to the end of its chains.  2: M = 10, FP16's own mantissa, which needs no mask.  M10E5 on 4096 x 4096 x 4096: 3220 us on FP32
+// carriers, 2070 here.
+template <int RW, int TN, int PM, int ORDER, int AMODE, int RANGE>
 __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict__ smem, int m0, int n0) {
     using T = RowTile<RW, TN>;
     constexpr int BM = T::BM, BN = T::BN, S = T::SETS, W = TN / 2, U = T::U;
-    constexpr bool HALF = T::HALF;
+    constexpr bool HALF = T::HALF, MASK = RANGE != 2;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tx = lane & 7, g = lane >> 3;
     // staging: lane = 4 (row of the wave) + (piece of the row); B's pieces go to the lanes that have none of A's where that is possible
@@ -322,7 +368,7 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
     __syncthreads();
 
     const HalfBound bound(p);
-    int safe_tiles = 0;
+    int safe_tiles = 0, beyond = -1, from = 0;                 // beyond: the tile, from: its part, at which the wave left the packed tile
     const uint32_t* const arow = Aw + g * T::PITCH;
     const uint32_t* const arowh = Aw + (8 + (lane >> 4)) * T::PITCH;       // the 4-row set: 16 lanes a row
     for (int t0 = 0; t0 < ntiles; t0 += DEPTH) {
@@ -354,14 +400,17 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
                 ListHead<U> h0(arow), h1(HALF ? arowh : arow + (S == 2 ? 8 * T::PITCH : 0));
                 if (safe_tiles >= parts) {
                     safe_tiles -= parts;
-                    list_steps<PM, false, TN, U>(acc[0], h0, arow, Bb, n_first, c);
-                    if constexpr (S == 2) list_steps<PM, false, TN, U>(acc[1], h1, arow + 8 * T::PITCH, Bb, n_second, c);
-                    if constexpr (HALF) list_steps<PM, false, TN / 2, U>(acch[0], h1, arowh, Bh, n_second, c);
+                    list_steps<PM, false, MASK, TN, U>(acc[0], h0, arow, Bb, n_first, c);
+                    if constexpr (S == 2) list_steps<PM, false, MASK, TN, U>(acc[1], h1, arow + 8 * T::PITCH, Bb, n_second, c);
+                    if constexpr (HALF) list_steps<PM, false, MASK, TN / 2, U>(acch[0], h1, arowh, Bh, n_second, c);
+                } else if constexpr (RANGE != 0) {
+                    beyond = t;
+                    break;
                 } else {
                     safe_tiles = 0;
-                    list_steps<PM, true, TN, U>(acc[0], h0, arow, Bb, n_first, c);
-                    if constexpr (S == 2) list_steps<PM, true, TN, U>(acc[1], h1, arow + 8 * T::PITCH, Bb, n_second, c);
-                    if constexpr (HALF) list_steps<PM, true, TN / 2, U>(acch[0], h1, arowh, Bh, n_second, c);
+                    list_steps<PM, true, MASK, TN, U>(acc[0], h0, arow, Bb, n_first, c);
+                    if constexpr (S == 2) list_steps<PM, true, MASK, TN, U>(acc[1], h1, arow + 8 * T::PITCH, Bb, n_second, c);
+                    if constexpr (HALF) list_steps<PM, true, MASK, TN / 2, U>(acch[0], h1, arowh, Bh, n_second, c);
                 }
             } else {
                 for (int part = 0; part < parts; ++part) {
@@ -371,13 +420,18 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
                     if (safe_tiles == 0) safe_tiles = bound.safe(largest(), dyn ? half_norm[t & 1] : nullptr, 1);
                     if (safe_tiles > 0) {
                         --safe_tiles;
-                        rows_tile<PM, ORDER, false, SMALL, S, TN, T::BROW, T::PITCH>(acc, top, arow + part * 16, Bs, c);
-                        if constexpr (HALF) rows_tile<PM, ORDER, false, false, 1, TN / 2, T::BROW, T::PITCH>(acch, toph, arowh + part * 16, Bh, c);
+                        rows_tile<PM, ORDER, false, MASK, SMALL, S, TN, T::BROW, T::PITCH>(acc, top, arow + part * 16, Bs, c);
+                        if constexpr (HALF) rows_tile<PM, ORDER, false, MASK, false, 1, TN / 2, T::BROW, T::PITCH>(acch, toph, arowh + part * 16, Bh, c);
+                    } else if constexpr (RANGE != 0) {
+                        beyond = t;
+                        from = part;
+                        break;
                     } else {
-                        rows_tile<PM, ORDER, true, SMALL, S, TN, T::BROW, T::PITCH>(acc, top, arow + part * 16, Bs, c);
-                        if constexpr (HALF) rows_tile<PM, ORDER, true, false, 1, TN / 2, T::BROW, T::PITCH>(acch, toph, arowh + part * 16, Bh, c);
+                        rows_tile<PM, ORDER, true, MASK, SMALL, S, TN, T::BROW, T::PITCH>(acc, top, arow + part * 16, Bs, c);
+                        if constexpr (HALF) rows_tile<PM, ORDER, true, MASK, false, 1, TN / 2, T::BROW, T::PITCH>(acch, toph, arowh + part * 16, Bh, c);
                     }
                 }
+                if (RANGE != 0 && beyond >= 0) break;
             }
             if (more) {
                 constexpr int next = (DEPTH > 1) ? 1 : 0;
@@ -386,15 +440,16 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
             }
             __syncthreads();
         }
+        if (RANGE != 0 && beyond >= 0) break;
     }
 
     // C = S * 2^out_exp, zero written as +0
-    auto store = [&](int m, int n, const h2* s, auto count) {
+    auto store = [&](int m, int n, auto sum, auto count) {
         constexpr int CT = decltype(count)::value;
         if (m >= p.M) return;
         float v[CT];
 #pragma unroll
-        for (int j = 0; j < CT; ++j) v[j] = __builtin_ldexpf((float)(j & 1 ? s[j / 2].y : s[j / 2].x), p.out_exp - 112) + 0.0f;    // -0 + 0 is +0
+        for (int j = 0; j < CT; ++j) v[j] = __builtin_ldexpf(sum(j), p.out_exp - 112) + 0.0f;    // -0 + 0 is +0
         float* dst = pC + (int64_t)m * p.N + n;
         if (CT % 4 == 0 && p.c_vec && n + CT - 1 < p.N) {
 #pragma unroll
@@ -407,37 +462,94 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
                 if (n + j < p.N) dst[j] = v[j];
         }
     };
+    const int row0 = m0 + wave * RW + g, rowh = m0 + wave * RW + 8 + (lane >> 4);
+    const int col0 = n0 + tx * TN, colh = n0 + (lane & 15) * (TN / 2);
+    if constexpr (RANGE != 0) {
+        if (beyond >= 0) {
+            set_round_zero();
+            BeyondConst w;
+            w.kc = (float)as_h2(p.h_kc).x; w.rof = p.rof_a; w.mask = p.mask_a; w.maskp = p.mask_p;
+            float sum[S][TN], tops[S][TN], sumh[TN / 2], toph2[TN / 2];
 #pragma unroll
-    for (int i = 0; i < S; ++i) store(m0 + wave * RW + 8 * i + g, n0 + tx * TN, ORDER == LBA_ORDER_CHUNK16 ? top[i] : acc[i], IntConst<TN>{});
-    if constexpr (HALF)
-        store(m0 + wave * RW + 8 + (lane >> 4), n0 + (lane & 15) * (TN / 2), ORDER == LBA_ORDER_CHUNK16 ? toph[0] : acch[0], IntConst<TN / 2>{});
+            for (int i = 0; i < S; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    sum[i][j] = (float)(j & 1 ? acc[i][j / 2].y : acc[i][j / 2].x) * 0x1p-112f;
+                    tops[i][j] = (float)(j & 1 ? top[i][j / 2].y : top[i][j / 2].x) * 0x1p-112f;
+                }
+            if constexpr (HALF) {
+#pragma unroll
+                for (int j = 0; j < TN / 2; ++j) {
+                    sumh[j] = (float)(j & 1 ? acch[0][j / 2].y : acch[0][j / 2].x) * 0x1p-112f;
+                    toph2[j] = (float)(j & 1 ? toph[0][j / 2].y : toph[0][j / 2].x) * 0x1p-112f;
+                }
+            }
+            const char* const Bb = reinterpret_cast<const char*>(smem + tx * W);
+            const char* const Bh = reinterpret_cast<const char*>(smem + (lane & 15) * (W / 2));
+#pragma unroll 1
+            for (int t = beyond; t < ntiles; ++t) {
+                // (a tile beyond K is never fetched here, so a wave's pieces are asked for and waited for one tile at a time)
+                const int k0 = t == beyond ? 32 * from : 0, n = p.K - t * HBK > 32 ? HBK - k0 : 32 - k0;
+                const uint32_t off = (uint32_t)((t & 1) * T::B_WORDS * 4 + k0 * T::BROW * 4);
+#pragma unroll
+                for (int i = 0; i < S; ++i)
+                    beyond_steps<PM, ORDER, TN, T::BROW>(sum[i], tops[i], arow + i * 8 * T::PITCH + (listed ? 0 : k0 / 2), listed, listed ? (i ? n_second : n_first) : n, Bb, off, w);
+                if constexpr (HALF) beyond_steps<PM, ORDER, TN / 2, T::BROW>(sumh, toph2, arowh + (listed ? 0 : k0 / 2), listed, listed ? n_second : n, Bh, off, w);
+                if (t + 1 < ntiles) {
+                    fetch(t + 1, 0);
+                    stage(t + 1, 0);
+                }
+                __syncthreads();
+            }
+#pragma unroll
+            for (int i = 0; i < S; ++i) store(row0 + 8 * i, col0, [&](int j) { return (ORDER == LBA_ORDER_CHUNK16 ? tops[i][j] : sum[i][j]) * 0x1p112f; }, IntConst<TN>{});
+            if constexpr (HALF) store(rowh, colh, [&](int j) { return (ORDER == LBA_ORDER_CHUNK16 ? toph2[j] : sumh[j]) * 0x1p112f; }, IntConst<TN / 2>{});
+            return;
+        }
+    }
+    auto value = [](const h2* s, int j) { return (float)(j & 1 ? s[j / 2].y : s[j / 2].x); };
+#pragma unroll
+    for (int i = 0; i < S; ++i) store(row0 + 8 * i, col0, [&](int j) { return value(ORDER == LBA_ORDER_CHUNK16 ? top[i] : acc[i], j); }, IntConst<TN>{});
+    if constexpr (HALF) store(rowh, colh, [&](int j) { return value(ORDER == LBA_ORDER_CHUNK16 ? toph[0] : acch[0], j); }, IntConst<TN / 2>{});
 }
 
-template <int TM, int TN, int PM, int ORDER, int AMODE>
-__global__ void __launch_bounds__(256, LBA_FAST_MIN_WAVES) lba_half_kernel(const KParams p) {
+template <int TM, int TN, int PM, int ORDER, int AMODE, int RANGE>
+__device__ __forceinline__ void rows_plain(const KParams& p) {
     constexpr int RW = TM == 4 ? 16 : 8, TR = TN == 4 ? 8 : 4;
     __shared__ __attribute__((aligned(16))) uint32_t smem[RowTile<RW, TR>::WORDS];
-    rows_body<RW, TR, PM, ORDER, AMODE>(p, smem, blockIdx.x * 16 * TM, blockIdx.y * 16 * TN);
+    rows_body<RW, TR, PM, ORDER, AMODE, RANGE>(p, smem, blockIdx.x * 16 * TM, blockIdx.y * 16 * TN);
 }
-
-template <int PM, int ORDER, int AMODE>
-__global__ void __launch_bounds__(256, LBA_FAST_MIN_WAVES) lba_half_mixed_kernel(const KParams p) {
+template <int PM, int ORDER, int AMODE, int RANGE>
+__device__ __forceinline__ void rows_mixed(const KParams& p) {
     __shared__ __attribute__((aligned(16))) uint32_t smem[RowTile<16, 8>::WORDS];
     const int b = blockIdx.x;
     if (b < p.mix_main) {                                      // uniform
         const int by = b / p.mix_gx_main, bx = b - by * p.mix_gx_main;
-        rows_body<16, 8, PM, ORDER, AMODE>(p, smem, bx * 64, by * 64);
+        rows_body<16, 8, PM, ORDER, AMODE, RANGE>(p, smem, bx * 64, by * 64);
     } else if (b < p.mix_main + p.mix_half) {
         const int t = b - p.mix_main;
         const int by = t / p.mix_gx_half, bx = t - by * p.mix_gx_half;
-        rows_body<12, 8, PM, ORDER, AMODE>(p, smem, p.mix_m_main + bx * 48, by * 64);
+        rows_body<12, 8, PM, ORDER, AMODE, RANGE>(p, smem, p.mix_m_main + bx * 48, by * 64);
     } else {
         const int t = b - p.mix_main - p.mix_half;
         const int by = t / p.mix_gx_tail, bx = t - by * p.mix_gx_tail;
-        if (p.mix_tail16) rows_body<8, 2, PM, ORDER, AMODE>(p, smem, p.mix_m_half + bx * 32, by * 16);   // uniform
-        else              rows_body<8, 4, PM, ORDER, AMODE>(p, smem, p.mix_m_half + bx * 32, by * 32);
+        if (p.mix_tail16) rows_body<8, 2, PM, ORDER, AMODE, RANGE>(p, smem, p.mix_m_half + bx * 32, by * 16);   // uniform
+        else              rows_body<8, 4, PM, ORDER, AMODE, RANGE>(p, smem, p.mix_m_half + bx * 32, by * 32);
     }
 }
+
+// The grids of lba_fast_kernel and lba_fast_mixed_kernel (the same tiles, numbered the same) on packed carriers: 16 TM x 16 TN outputs.
+// AMODE 0: row-major, 16-byte rows; 3: row-major, any K and alignment; 2: im2col rows, C % 16 == 0 and 16-byte rows; 4: any other.
+template <int TM, int TN, int PM, int ORDER, int AMODE>
+__global__ void __launch_bounds__(256, LBA_FAST_MIN_WAVES) lba_half_kernel(const KParams p) { rows_plain<TM, TN, PM, ORDER, AMODE, 0>(p); }
+template <int PM, int ORDER, int AMODE>
+__global__ void __launch_bounds__(256, LBA_FAST_MIN_WAVES) lba_half_mixed_kernel(const KParams p) { rows_mixed<PM, ORDER, AMODE, 0>(p); }
+
+// Accumulators whose R_OF lies beyond FP16's range (RANGE 1, 2).
+template <int TM, int TN, int ORDER, int AMODE, int RANGE>
+__global__ void __launch_bounds__(256, LBA_FAST_MIN_WAVES) lba_wide_kernel(const KParams p) { rows_plain<TM, TN, PM_FLUSH, ORDER, AMODE, RANGE>(p); }
+template <int ORDER, int AMODE, int RANGE>
+__global__ void __launch_bounds__(256, LBA_FAST_MIN_WAVES) lba_wide_mixed_kernel(const KParams p) { rows_mixed<PM_FLUSH, ORDER, AMODE, RANGE>(p); }
 
 }  // namespace lba
 #endif
