@@ -23,8 +23,20 @@ static hipError_t launch_order(const Plan& pl, hipStream_t st) {
     return hipErrorInvalidValue;
 }
 
+template <int PM>
+static hipError_t launch_staged(const Plan& pl, hipStream_t st) {
+    const dim3 grid(pl.grid_x, pl.grid_y, pl.kp.batch), block(512);
+    if (pl.mix_tail > 0) hipLaunchKernelGGL((lba_half_staged_kernel<2, PM>), grid, block, 0, st, pl.kp);
+    else                 hipLaunchKernelGGL((lba_half_staged_kernel<4, PM>), grid, block, 0, st, pl.kp);
+    return hipGetLastError();
+}
+
 hipError_t launch_half(const Plan& pl, hipStream_t st) {
     if (pl.events || pl.round != LBA_ROUND_FLOOR || pl.kp.conv || !pl.kp.h_on) return hipErrorInvalidValue;
+    if (pl.staged) {                                           // 32 x 16 tiles throughout, or 32 x 32
+        if (pl.order != LBA_ORDER_SEQ || (pl.mix_tail > 0 ? !pl.kp.mix_tail16 || pl.kp.mix_main + pl.kp.mix_half != 0 : pl.tm != 2 || pl.tn != 2)) return hipErrorInvalidValue;
+        return pl.prod_mode == PM_IDENT ? launch_staged<PM_IDENT>(pl, st) : pl.prod_mode == PM_FLUSH ? launch_staged<PM_FLUSH>(pl, st) : hipErrorInvalidValue;
+    }
     if (pl.kp.ld_align == 16)
         return pl.order == LBA_ORDER_CHUNK16 ? launch_order<LBA_ORDER_CHUNK16, 0>(pl, st) : launch_order<LBA_ORDER_SEQ, 0>(pl, st);
     return pl.order == LBA_ORDER_CHUNK16 ? launch_order<LBA_ORDER_CHUNK16, 3>(pl, st) : launch_order<LBA_ORDER_SEQ, 3>(pl, st);

@@ -513,6 +513,188 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
     if constexpr (HALF) store(rowh, colh, [&](int j) { return value(ORDER == LBA_ORDER_CHUNK16 ? toph[0] : acch[0], j); }, IntConst<TN / 2>{});
 }
 
+// The smallest grids, at most one or two workgroups per CU: four waves run the chains of a 32 x BN tile (8 rows each, BN / 8 columns
+// per lane) and four others fetch and decode the k-tile after it.  What bounds such a call is one wave's issue and the latency of its
+// chain (24 cycles a step in the issue-rate probe for multiply-add, next product and mask), so everything else leaves that wave:
+// staging, which cost 1500 cycles a k-tile beside the chain's 1550, and most LDS reads (B lies in groups of steps, one 16-byte read
+// for four or two of them).  Lists of non-zero codes do not pay here: a step then needs a read and an address of its own (40
+// cycles).  64 x 1000 x 2048: 44 us with four waves that do both, 27 here; 300 x 300 x 1500 36 -> 21, 512 x 512 x 512 16 -> 13.
+template <int TN>
+struct StagedTile {
+    static constexpr int BM = 32, BN = 8 * TN, W = TN / 2, GROUP = 4 / W;  // steps of B in 16 bytes
+    static constexpr int B_WORDS = HBK * BN / 2, PAIRS = HBK / 2 + 4;      // a row's words (k, k + 1), and a shift of its banks
+    static constexpr int STAGE = B_WORDS + BM * PAIRS, WORDS = 2 * STAGE;
+};
+
+// store_half_b for that layout: [k / GROUP][lane of 8][k % GROUP][word]
+template <int TN>
+__device__ __forceinline__ void store_staged_b(uint32_t* __restrict__ dst, int c, const uint32_t (&w)[8]) {
+    using T = StagedTile<TN>;
+    if (c < 0) return;
+    const int col = c % T::BN, kq = c / T::BN, pair = col >> 1;
+    const uint32_t sel = (col & 1) ? 0x03020706u : 0x05040100u;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[j], 0xB1, 0xF, 0xF, true);   // the neighbour's word
+        const int k = kq * 16 + 2 * j + (col & 1);
+        dst[((k / T::GROUP * 8 + pair / T::W) * T::GROUP + k % T::GROUP) * T::W + pair % T::W] = __builtin_amdgcn_perm(other, w[j], sel);
+    }
+}
+
+// 32 steps of the lane's chains; operands are read eight steps ahead, products taken before the sum ahead of them is rounded.
+template <int PM, bool CLAMP, int TN>
+__device__ __forceinline__ void staged_steps(h2 (&sum)[1][TN / 2], const uint32_t* arow, const uint32_t* Bs, const HalfConst& c) {
+    using T = StagedTile<TN>;
+    constexpr int W = T::W, G = T::GROUP, GROUPS = 32 / G, AHEAD = 8 / G;
+    uint32_t a[16], b[GROUPS][4];
+    h2 q[2][1][W];
+    auto read_a = [&](int s) {
+        uint32_t x[4];
+        read_words<4>(arow + s, x);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a[s + j] = x[j];
+    };
+    auto product = [&](int k) {
+        const uint32_t x[1] = {a[k / 2]};
+        uint32_t y[W];
+#pragma unroll
+        for (int j = 0; j < W; ++j) y[j] = b[k / G][k % G * W + j];
+        if (k & 1) half_products<PM, true, 1, TN, false>(q[1], x, y, c);
+        else       half_products<PM, false, 1, TN, false>(q[0], x, y, c);
+    };
+    read_a(0);
+    read_a(4);
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) read_words<4>(Bs + i * 32, b[i]);
+    product(0);
+#pragma unroll
+    for (int k = 0; k < 32; ++k) {
+        if (k % 8 == 0 && k < 16) read_a(8 + k / 2);
+        if (k % G == 0 && k / G + AHEAD < GROUPS) read_words<4>(Bs + (k / G + AHEAD) * 32, b[k / G + AHEAD]);
+        const uint32_t x[1] = {a[k / 2]};
+        uint32_t y[W];
+#pragma unroll
+        for (int j = 0; j < W; ++j) y[j] = b[k / G][k % G * W + j];
+        if (k & 1) half_sums<PM, true, 1, TN>(sum, q[1], x, y, c);
+        else       half_sums<PM, false, 1, TN>(sum, q[0], x, y, c);
+        if (k < 31) product(k + 1);
+        half_round<CLAMP, 1, TN, false>(sum, c);
+    }
+}
+
+template <int TN, int PM>
+__device__ __forceinline__ void staged_body(const KParams& p, uint32_t* __restrict__ smem, int m0, int n0) {
+    using T = StagedTile<TN>;
+    constexpr int W = TN / 2, AHEAD = kTilesAhead;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;
+    const bool stager = __builtin_amdgcn_readfirstlane(tid >> 8) != 0;
+    const uint8_t* pA = p.A + (int64_t)blockIdx.z * p.stride_a;
+    const uint8_t* pB = p.B + (int64_t)blockIdx.z * p.stride_b;
+    __shared__ uint32_t half_norm[2][4];
+    const bool dyn = half_follows_data(p);
+    const int ntiles = (p.K + HBK - 1) / HBK;
+    set_flush_f32();
+    set_round_zero_f16();
+    set_flush_out_f16();
+
+    // One barrier a tile: behind it the tile is staged and the stage before it no longer read.
+    if (stager) {
+        // lanes 0 .. 31: pieces of the wave's 8 rows of A; 32 and up: pieces of B
+        const bool isb = lane >= 32;
+        const int ca = isb ? -1 : (lane & 3) * T::BM + wave * 8 + (lane >> 2), cb = isb && lane - 32 < T::BN ? wave * T::BN + lane - 32 : -1;
+        RowPieces<T::BM> s(pA, p.M, p.K, m0, ca);
+        const RowPieces<T::BN> sb(pB, p.N, p.K, n0, cb);
+        if (isb) { s.row = sb.row; s.kq = sb.kq; s.room = sb.room; s.end = sb.end; s.ok = sb.ok; }
+        const int shift = isb ? p.h_shift_b : p.h_shift_a;
+        const uint32_t keep = isb ? p.h_keep_b : p.h_keep_a, scale = isb ? p.h_scale_b : p.h_scale_a;
+        uint4 r[AHEAD];
+#pragma unroll
+        for (int d = 0; d < AHEAD; ++d) r[d] = load_piece(s, tile_start(d));   // (a tile beyond K reads codes inside the operands that nothing uses)
+        for (int t0 = 0; t0 < ntiles; t0 += AHEAD) {
+#pragma unroll
+            for (int d = 0; d < AHEAD; ++d) {
+                const int t = t0 + d;
+                if (t >= ntiles) break;
+                uint32_t* const st = smem + (t & 1) * T::STAGE;
+                const uint4 v = s.codes(r[d], t * HBK);
+                uint32_t w[8];
+                decode_half(v, shift, keep, scale, w);
+                store_staged_b<TN>(st, cb, w);
+                if (!isb) {
+                    uint4* const pairs = reinterpret_cast<uint4*>(st + T::B_WORDS + (wave * 8 + (lane >> 2)) * T::PAIRS + (lane & 3) * 8);
+                    pairs[0] = make_uint4(w[0], w[1], w[2], w[3]);
+                    pairs[1] = make_uint4(w[4], w[5], w[6], w[7]);
+                }
+                if (dyn) {
+                    const uint32_t n2 = __float_as_uint(piece_norm2(w)) + 0xFFFFu;
+                    uint32_t m = isb ? n2 & 0xFFFF0000u : n2 >> 16;
+#pragma unroll
+                    for (int o = 32; o > 0; o >>= 1) m = pk_max_u16(m, (uint32_t)__shfl_xor((int)m, o, 64));
+                    if (lane == 0) half_norm[t & 1][wave] = m;
+                }
+                r[d] = load_piece(s, tile_start(t + AHEAD));
+                __syncthreads();
+            }
+        }
+        return;
+    }
+
+    HalfConst c;
+    c.kc = as_h2(p.h_kc); c.rof = as_h2(p.h_rof); c.nrof = as_h2(p.h_rof ^ 0x80008000u); c.mask = p.h_mask_a; c.maskp = p.h_mask_p;
+    asm volatile("" : "+v"(c.kc), "+v"(c.rof), "+v"(c.nrof), "+v"(c.mask), "+v"(c.maskp));
+    h2 acc[1][W];
+#pragma unroll
+    for (int j = 0; j < W; ++j) acc[0][j] = as_h2(0u);
+    const int tx = lane & 7, g = lane >> 3;
+    const HalfBound bound(p);
+    int safe_tiles = 0;
+    __builtin_amdgcn_s_setprio(3);                             // the chain is what everything waits for
+    for (int t = 0; t < ntiles; ++t) {
+        __syncthreads();
+        const uint32_t* const Bs = smem + (t & 1) * T::STAGE + tx * 4;
+        const uint32_t* const arow = smem + (t & 1) * T::STAGE + T::B_WORDS + (wave * 8 + g) * T::PAIRS;
+        const int parts = p.K - t * HBK > 32 ? 2 : 1;
+        for (int part = 0; part < parts; ++part) {
+            if (safe_tiles == 0) {
+                uint32_t mx = 0u;
+#pragma unroll
+                for (int j = 0; j < W; ++j) mx = pk_max_u16(mx, as_u32(acc[0][j]) & 0x7FFF7FFFu);
+                safe_tiles = bound.safe(max_half(mx), dyn ? half_norm[t & 1] : nullptr);
+            }
+            const uint32_t* const Bp = Bs + part * (T::B_WORDS / 2);
+            if (safe_tiles > 0) {
+                --safe_tiles;
+                staged_steps<PM, false, TN>(acc, arow + part * 16, Bp, c);
+            } else {
+                staged_steps<PM, true, TN>(acc, arow + part * 16, Bp, c);
+            }
+        }
+    }
+    const int m = m0 + wave * 8 + g, n = n0 + tx * TN;
+    if (m >= p.M) return;
+    float* const dst = p.C + (int64_t)blockIdx.z * p.stride_c + (int64_t)m * p.N + n;
+    float v[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) v[j] = __builtin_ldexpf((float)(j & 1 ? acc[0][j / 2].y : acc[0][j / 2].x), p.out_exp - 112) + 0.0f;   // -0 + 0 is +0
+    if (TN == 4 && p.c_vec && n + 3 < p.N) {
+        *reinterpret_cast<f32x4_any*>(dst) = f32x4_any{v[0], v[1], v[TN - 2], v[TN - 1]};
+    } else if (TN == 2 && p.c_vec && n + 1 < p.N) {
+        *reinterpret_cast<f32x2_any*>(dst) = f32x2_any{v[0], v[1]};
+    } else {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+            if (n + j < p.N) dst[j] = v[j];
+    }
+}
+
+// Row-major operands of any alignment, the sequential order; 512 lanes.
+template <int TN, int PM>
+__global__ void __launch_bounds__(512, 4) lba_half_staged_kernel(const KParams p) {
+    __shared__ __attribute__((aligned(16))) uint32_t smem[StagedTile<TN>::WORDS];
+    const int by = TN == 2 ? blockIdx.x / p.mix_gx_tail : blockIdx.y, bx = TN == 2 ? blockIdx.x - by * p.mix_gx_tail : blockIdx.x;
+    staged_body<TN, PM>(p, smem, bx * 32, by * 8 * TN);
+}
+
 template <int TM, int TN, int PM, int ORDER, int AMODE, int RANGE>
 __device__ __forceinline__ void rows_plain(const KParams& p) {
     constexpr int RW = TM == 4 ? 16 : 8, TR = TN == 4 ? 8 : 4;
