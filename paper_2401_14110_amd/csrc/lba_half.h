@@ -226,44 +226,6 @@ __device__ __forceinline__ void read_half_b(const uint32_t* Bs, int k, int tx, u
     }
 }
 
-// 32 steps (16 pairs) from LDS, fully unrolled; operands are read AHEAD pairs of steps before their use.  A lane block of one
-// or two pairs of chains takes the next step's products between a step's sums and their rounding: nothing else separates the
-// dependent instructions there (the compiler puts a wait between a packed instruction and one that reads it at once).
-template <int PM, int ORDER, bool CLAMP, int TM, int TN, int BMP, int BNP>
-__device__ __forceinline__ void half_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[TM][TN / 2], const uint32_t* As, const uint32_t* Bs,
-                                          int tx, int ty, const HalfConst& c) {
-    constexpr int AHEAD = TM * TN >= 12 ? 1 : (TM * TN >= 8 ? 2 : 4), SLOTS = AHEAD + 2;
-    constexpr bool EARLY = TM * TN <= 4;
-    uint32_t a[SLOTS][TM], b0[SLOTS][TN / 2], b1[SLOTS][TN / 2];
-    h2 q[2][TM][TN / 2];
-#pragma unroll
-    for (int s = 0; s < AHEAD; ++s) {
-        read_half_a<TM, BMP>(As, s, ty, a[s]);
-        read_half_b<TN, BNP>(Bs, 2 * s, tx, b0[s]);
-        read_half_b<TN, BNP>(Bs, 2 * s + 1, tx, b1[s]);
-    }
-    issue_first<!EARLY>();
-    if (EARLY) half_products<PM, false, TM, TN>(q[0], a[0], b0[0], c);
-#pragma unroll
-    for (int s = 0; s < 16; ++s) {
-        const int x = s % SLOTS;
-        if (s + AHEAD < 16) {
-            read_half_a<TM, BMP>(As, s + AHEAD, ty, a[(s + AHEAD) % SLOTS]);
-            read_half_b<TN, BNP>(Bs, 2 * (s + AHEAD), tx, b0[(s + AHEAD) % SLOTS]);
-            read_half_b<TN, BNP>(Bs, 2 * (s + AHEAD) + 1, tx, b1[(s + AHEAD) % SLOTS]);
-        }
-        if (!EARLY) half_products<PM, false, TM, TN>(q[0], a[x], b0[x], c);
-        half_sums<PM, false, TM, TN>(acc, q[0], a[x], b0[x], c);
-        if (EARLY) half_products<PM, true, TM, TN>(q[1], a[x], b1[x], c);
-        half_round<CLAMP, TM, TN>(acc, c);
-        if (!EARLY) half_products<PM, true, TM, TN>(q[1], a[x], b1[x], c);
-        half_sums<PM, true, TM, TN>(acc, q[1], a[x], b1[x], c);
-        if (EARLY && s < 15) half_products<PM, false, TM, TN>(q[0], a[(s + 1) % SLOTS], b0[(s + 1) % SLOTS], c);
-        half_round<CLAMP, TM, TN>(acc, c);
-        if (ORDER == LBA_ORDER_CHUNK16 && ((s + 1) & 7) == 0) half_level2<CLAMP, TM, TN>(top, acc, c);
-    }
-}
-
 // Decodes and stores the pieces of one k-tile.  dyn: also leaves the largest squared norm of a piece of A (low half) and of
 // B, to 8 bits, rounded up, per wave.
 template <int BM, int BN>

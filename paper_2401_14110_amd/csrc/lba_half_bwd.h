@@ -58,14 +58,20 @@ struct HalfBwdConst {
     uint32_t of_bias;          // 0x8000 - bits of R_OF
     uint32_t two, minus2, uf_bias;   // 2, -2, 0x8000 - 0x7FE
     uint32_t bit15;            // 0x80008000
+    __device__ __forceinline__ explicit HalfBwdConst(const KParams& p)
+        : kc(as_h2(p.h_kc)), rof(as_h2(p.h_rof)), nrof(as_h2(p.h_rof ^ 0x80008000u)), mask(p.h_mask_a), maskp(p.h_mask_p), absmask(p.h_mask_a & 0x7FFF7FFFu),
+          of_bias(pk_add_u16(0x80008000u, pk_add_u16(~p.h_rof, 0x00010001u))), two(0x00020002u), minus2(0xFFFEFFFEu), uf_bias(0x78027802u), bit15(0x80008000u) {
+        asm volatile("" : "+v"(kc), "+v"(rof), "+v"(nrof), "+v"(mask), "+v"(maskp), "+v"(absmask), "+v"(of_bias), "+v"(two), "+v"(minus2), "+v"(uf_bias), "+v"(bit15));
+    }
 };
 
 // 32 steps with event bits: word [i][j] of chain (i, j) gets step k in bit k (of: 1 = overflow; uf: 1 = underflow or a zero
 // operand, cleared by the caller).  of2 / uf2: the two chunks' bits enter the second-level words at bits pos, pos + 1.
-template <int PM, int ORDER, bool UF, bool QUIET, int TM, int TN, int BMP, int BNP>
+// read_a(k / 2, words of the rows), read_b(k, words of the columns).
+template <int PM, int ORDER, bool UF, bool QUIET, int TM, int TN, class ReadA, class ReadB>
 __device__ __forceinline__ void half_bwd_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[TM][TN / 2], uint32_t (&of)[TM][TN], uint32_t (&uf)[TM][TN],
-                                              uint32_t (&of2)[TM][TN], uint32_t (&uf2)[TM][TN], int pos, const uint32_t* As,
-                                              const uint32_t* Bs, int tx, int ty, const HalfBwdConst& c) {
+                                              uint32_t (&of2)[TM][TN], uint32_t (&uf2)[TM][TN], int pos, ReadA read_a, ReadB read_b,
+                                              const HalfBwdConst& c) {
     constexpr int NJ = TN / 2;
     constexpr bool PRIO = TM * TN > 4;
     issue_first<PRIO>();
@@ -79,9 +85,9 @@ __device__ __forceinline__ void half_bwd_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[T
 #pragma unroll 2
         for (int s = 0; s < 8; ++s) {
             uint32_t a[TM], b[2][NJ];
-            read_half_a<TM, BMP>(As, 8 * h + s, ty, a);
-            read_half_b<TN, BNP>(Bs, 16 * h + 2 * s, tx, b[0]);
-            read_half_b<TN, BNP>(Bs, 16 * h + 2 * s + 1, tx, b[1]);
+            read_a(8 * h + s, a);
+            read_b(16 * h + 2 * s, b[0]);
+            read_b(16 * h + 2 * s + 1, b[1]);
             uint32_t q[2][TM][NJ];
             // both steps' products under one mode: below Q_prod's R_UF they are flushed
             if (UF) half_flush_out();
@@ -217,7 +223,8 @@ __device__ __forceinline__ void mark_bricks_lsb(const uint32_t (&of)[TM][TN], in
     mark_bricks_of_wave<TM, TN>(any, m0, n0, w, tx, ty, p);
 }
 
-template <int TM, int TN, int PM, int ORDER, bool UF, int AMODE>
+// The recompute call with an underflow plane (without one: rows_body, lba_rows.h).
+template <int TM, int TN, int PM, int ORDER, int AMODE>
 __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __restrict__ smem, int m0, int n0) {
     using T = HalfTile<TM, TN, 16>;
     constexpr int BM = T::BM, BN = T::BN, NJ = TN / 2;
@@ -229,16 +236,7 @@ __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __rest
     set_round_zero_f16();
     set_flush_out_f16();
 
-    HalfConst fc;
-    fc.kc = as_h2(p.h_kc); fc.rof = as_h2(p.h_rof); fc.nrof = as_h2(p.h_rof ^ 0x80008000u); fc.mask = p.h_mask_a; fc.maskp = p.h_mask_p;
-    HalfBwdConst c;
-    c.kc = fc.kc; c.rof = fc.rof; c.nrof = fc.nrof; c.mask = fc.mask; c.maskp = fc.maskp;
-    c.absmask = p.h_mask_a & 0x7FFF7FFFu;
-    c.of_bias = pk_add_u16(0x80008000u, pk_add_u16(~p.h_rof, 0x00010001u));
-    c.two = 0x00020002u; c.minus2 = 0xFFFEFFFEu; c.uf_bias = 0x78027802u; c.bit15 = 0x80008000u;
-    asm volatile("" : "+v"(c.kc), "+v"(c.rof), "+v"(c.nrof), "+v"(c.mask), "+v"(c.maskp), "+v"(c.absmask), "+v"(c.of_bias), "+v"(c.two), "+v"(c.minus2), "+v"(c.uf_bias), "+v"(c.bit15));
-    fc.kc = c.kc; fc.rof = c.rof; fc.nrof = c.nrof; fc.mask = c.mask; fc.maskp = c.maskp;
-
+    const HalfBwdConst c(p);
     h2 acc[TM][NJ], top[TM][NJ];
     uint32_t of2[TM][TN], uf2[TM][TN];
 #pragma unroll
@@ -270,7 +268,7 @@ __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __rest
         const uint4 vb = sb.codes(rb, t * HBK);
         const int st = t & 1;
         half_stage<BM, BN>(p, smem + st * T::STAGE, smem + st * T::STAGE + T::A_WORDS, va, vb, tid, tidb, dyn, half_norm[st]);
-        if (UF) {
+        {
             if (tid < Stage<BM, HBK>::kChunks) nza[st][tid % BM][tid / BM] = (uint16_t)nonzero_codes(va);
             if (tidb >= 0 && tidb < Stage<BN, HBK>::kChunks) nzb[st][tidb % BN][tidb / BN] = (uint16_t)nonzero_codes(vb);
         }
@@ -291,6 +289,8 @@ __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __rest
         for (int part = 0; part < parts; ++part) {
             const uint32_t* As = As0 + part * 16 * T::BMP;
             const uint32_t* Bs = Bs0 + part * 32 * T::BNP;
+            auto read_a = [&](int k, uint32_t (&a)[TM]) { read_half_a<TM, T::BMP>(As, k, ty, a); };
+            auto read_b = [&](int k, uint32_t (&b)[NJ]) { read_half_b<TN, T::BNP>(Bs, k, tx, b); };
             const int w = 2 * t + part;                        // plane word of this part's steps
             if (safe_tiles == 0) {
                 uint32_t mx = 0u;
@@ -310,10 +310,9 @@ __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __rest
             const bool quiet = safe_tiles > 0;
             if (quiet) {
                 --safe_tiles;
-                if (UF) half_bwd_tile<PM, ORDER, UF, true, TM, TN, T::BMP, T::BNP>(acc, top, of, uf, of2, uf2, pos, As, Bs, tx, ty, c);
-                else    half_tile<PM, ORDER, false, TM, TN, T::BMP, T::BNP>(acc, top, As, Bs, tx, ty, fc);
+                half_bwd_tile<PM, ORDER, true, true, TM, TN>(acc, top, of, uf, of2, uf2, pos, read_a, read_b, c);
             } else {
-                half_bwd_tile<PM, ORDER, UF, false, TM, TN, T::BMP, T::BNP>(acc, top, of, uf, of2, uf2, pos, As, Bs, tx, ty, c);
+                half_bwd_tile<PM, ORDER, true, false, TM, TN>(acc, top, of, uf, of2, uf2, pos, read_a, read_b, c);
                 const int valid = p.K - 32 * w;                // a saturated sum stays at R_OF beyond K
                 if (valid < 32) {
 #pragma unroll
@@ -324,7 +323,7 @@ __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __rest
                 if (ORDER == LBA_ORDER_SEQ && p.map_dx) mark_bricks_lsb<TM, TN>(of, m0, n0, w, tx, ty, p);
             }
             if (p.of_mask) store_half_words<TM, TN>(p.of_mask, w, of, m0, n0, tx, ty, p);
-            if (UF && p.uf_mask) {
+            if (p.uf_mask) {
 #pragma unroll
                 for (int i = 0; i < TM; ++i) {
                     const uint32_t na = *reinterpret_cast<const uint32_t*>(&nza[t & 1][ty * TM + i][2 * part]);
@@ -342,7 +341,7 @@ __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __rest
 #pragma unroll
                     for (int j = 0; j < TN; ++j) { of2[i][j] &= vmask; uf2[i][j] &= vmask; }
                 if (p.of_mask2) store_half_words<TM, TN>(p.of_mask2, w >> 4, of2, m0, n0, tx, ty, p);
-                if (UF && p.uf_mask2) store_half_words<TM, TN>(p.uf_mask2, w >> 4, uf2, m0, n0, tx, ty, p);
+                if (p.uf_mask2) store_half_words<TM, TN>(p.uf_mask2, w >> 4, uf2, m0, n0, tx, ty, p);
 #pragma unroll
                 for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -376,28 +375,6 @@ __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __rest
             for (int j = 0; j < TN; ++j)
                 if (n + j < p.N) dst[j] = v[j];
         }
-    }
-}
-
-// The grids of lba_fast_bwd_kernel and lba_fast_bwd_mixed_kernel.  AMODE 0: a row-major matrix of any code format with E <= 4,
-// 2: im2col rows of an NHWC tensor.
-template <int PM, int ORDER, bool UF, int AMODE>
-__global__ void __launch_bounds__(256, ORDER == LBA_ORDER_CHUNK16 && UF ? 2 : UF || ORDER == LBA_ORDER_CHUNK16 ? 3 : 4) lba_half_bwd_kernel(const KParams p) {
-    __shared__ __attribute__((aligned(16))) uint32_t smem[2 * HalfTile<4, 4, 16>::STAGE];
-    half_bwd_body<4, 4, PM, ORDER, UF, AMODE>(p, smem, blockIdx.x * 64, blockIdx.y * 64);
-}
-
-template <int PM, bool UF, int AMODE>
-__global__ void __launch_bounds__(256, UF ? 3 : 4) lba_half_bwd_mixed_kernel(const KParams p) {
-    __shared__ __attribute__((aligned(16))) uint32_t smem[2 * HalfTile<4, 4, 16>::STAGE];
-    const int b = blockIdx.x;
-    if (b < p.mix_main) {                                      // uniform
-        const int by = b / p.mix_gx_main, bx = b - by * p.mix_gx_main;
-        half_bwd_body<4, 4, PM, LBA_ORDER_SEQ, UF, AMODE>(p, smem, bx * 64, by * 64);
-    } else {
-        const int t = b - p.mix_main;
-        const int by = t / p.mix_gx_tail, bx = t - by * p.mix_gx_tail;
-        half_bwd_body<2, 2, PM, LBA_ORDER_SEQ, UF, AMODE>(p, smem, p.mix_m_main + bx * 32, by * 32);
     }
 }
 

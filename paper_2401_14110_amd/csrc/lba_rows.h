@@ -24,7 +24,7 @@
 #ifndef LBA_ROWS_H_
 #define LBA_ROWS_H_
 
-#include "lba_half.h"
+#include "lba_half_bwd.h"
 
 namespace lba {
 
@@ -184,6 +184,30 @@ __device__ __forceinline__ uint4 load_aligned(const AlignedRow& s, int k0) {
     return *reinterpret_cast<const uint4*>(s.row + min(k0 + s.kq, s.last));
 }
 
+// mark_bricks (lba_device.h) for the rows of a wave: RW rows inside one group of 32, 8 TN columns (two groups of 32 when TN = 8), first
+// step in bit 0 and steps beyond K cleared; word w of the plane.
+template <int RW, int TN>
+__device__ __forceinline__ void mark_bricks_of_rows(const uint32_t (&of)[RW / 8][TN], int m0, int n0, int w, const KParams& p) {
+    const int lane = threadIdx.x & 63, first = m0 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * RW;
+    uint32_t any = 0u;
+#pragma unroll
+    for (int i = 0; i < RW / 8; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+            if (first + 8 * i + (lane >> 3) < p.M && n0 + (lane & 7) * TN + j < p.N) any |= of[i][j];
+    const uint64_t dirty = __builtin_amdgcn_ballot_w64(any != 0u);
+    if (dirty == 0) return;                                    // uniform; the usual case
+    if (lane == 0) {
+        const int64_t kb = w >> 3;
+        uint8_t* bw = p.map_dw + (kb * p.map_rbw + (n0 >> 7)) * p.map_sbw + (first >> 5);
+        if (!*bw) *bw = 1;                                     // racing stores write the same value
+        uint8_t* bx = p.map_dx + (kb * p.map_rbx + (first >> 7)) * p.map_sbx + (n0 >> 5);
+        const uint64_t low = TN == 8 ? 0x0F0F0F0F0F0F0F0Full : ~0ull;   // lanes whose columns lie in the first group
+        if ((dirty & low) && !*bx) *bx = 1;
+        if (TN == 8 && (dirty & ~low) && !bx[1]) bx[1] = 1;
+    }
+}
+
 // Sums beyond FP16's range (accumulators of E >= 5): the constants of the FP32 step (fast_group), R_UF at 2^-126.
 struct BeyondConst {
     float kc, rof;
@@ -230,7 +254,10 @@ __device__ __forceinline__ void beyond_steps(float (&sum)[T], float (&top)[T], c
 // clamp elsewhere shows that no sum leaves the range in the tile at hand (65504 in place of R_OF), and a wave where it cannot goes
 // on in FP32 to the end of its chains.  2: M = 10, FP16's own mantissa, which needs no mask.  M10E5 on 4096 x 4096 x 4096: 3220 us on FP32
 // carriers, 2070 here.
-template <int RW, int TN, int PM, int ORDER, int AMODE, int RANGE>
+// EVENTS: the recompute call for the overflow plane alone (RANGE 0, no set of four rows): a part of a tile in which no sum can reach R_OF
+// is the forward call's and its words are zero; any other runs half_bwd_tile.  A tile becomes lists only where the fixed bound covers it,
+// since the steps a list leaves out have no event there (a saturated sum would repeat its own).
+template <int RW, int TN, int PM, int ORDER, int AMODE, int RANGE, bool EVENTS = false>
 __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict__ smem, int m0, int n0) {
     using T = RowTile<RW, TN>;
     constexpr int BM = T::BM, BN = T::BN, S = T::SETS, W = TN / 2, U = T::U;
@@ -243,6 +270,7 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
     const uint8_t* pA = p.A + (int64_t)blockIdx.z * p.stride_a;
     const uint8_t* pB = p.B + (int64_t)blockIdx.z * p.stride_b;
     float* pC = p.C + (int64_t)blockIdx.z * p.stride_c;
+    static_assert(!EVENTS || (RANGE == 0 && !HALF), "the recompute call's tiles");
 
     set_flush_f32();
     set_round_zero_f16();
@@ -272,7 +300,7 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
     ConvLane cl = {};
     if (PIECES && conv) sc = ConvPieces::make<BM>(pA, p, m0, ca);
     if (!PIECES && AMODE == 2) cl = conv_lane<BM, HBK>(pA, p, m0, ca);
-    constexpr int DEPTH = half_depth(S, TN);
+    constexpr int DEPTH = EVENTS ? 1 : half_depth(S, TN);
     uint4 ra[DEPTH], rc[DEPTH], rb[DEPTH];
     const AlignedRow rowa(pA, conv ? 1 : p.M, p.K, conv ? 0 : m0 + ca % BM, ca >= 0 ? ca / BM * 16 : 0), rowb(pB, p.N, p.K, n0 + tidb % BN, tidb >= 0 ? tidb / BN * 16 : 0);
     auto fetch = [&](int t, int d) {
@@ -323,6 +351,22 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
         }
         return true;
     };
+                auto largest = [&]() {
+                    uint32_t mx = 0u;
+#pragma unroll
+                    for (int i = 0; i < S; ++i)
+#pragma unroll
+                        for (int j = 0; j < W; ++j)
+                            mx = pk_max_u16(mx, as_u32(ORDER == LBA_ORDER_CHUNK16 ? top[i][j] : acc[i][j]) & 0x7FFF7FFFu);
+                    if (HALF) {
+#pragma unroll
+                        for (int j = 0; j < TN / 4; ++j)
+                            mx = pk_max_u16(mx, as_u32(ORDER == LBA_ORDER_CHUNK16 ? toph[0][j] : acch[0][j]) & 0x7FFF7FFFu);
+                    }
+                    return max_half(mx);
+                };
+    const HalfBound bound(p);
+    int safe_tiles = 0;
     auto stage = [&](int t, int d) {
         uint4 va = !PIECES ? ra[d] : (conv ? sc.codes(p, ra[d], rc[d], t * HBK) : sa.codes(ra[d], t * HBK));
         uint4 vb = PIECES ? sb.codes(rb[d], t * HBK) : rb[d];
@@ -345,9 +389,10 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
             // worth counting: a zero among the first four codes of most pieces
             const uint32_t z = (va.x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu;
             const int hits = __builtin_popcountll(__ballot((z & 0x80808080u) != 0x80808080u && ca >= 0));
+            if (EVENTS && safe_tiles < 2) safe_tiles = bound.safe(largest(), nullptr);
             if (wait > 0) {
                 --wait;
-            } else if (hits >= 4 * RW * 3 / 4) {
+            } else if (hits >= 4 * RW * 3 / 4 && (!EVENTS || safe_tiles >= 2)) {
                 listed = list_tile(t);
                 pause = listed ? 0 : min(2 * pause + 1, 15);
                 wait = pause;
@@ -367,8 +412,48 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
     if (DEPTH > 1) fetch(DEPTH, 0);
     __syncthreads();
 
-    const HalfBound bound(p);
-    int safe_tiles = 0, beyond = -1, from = 0;                 // beyond: the tile, from: its part, at which the wave left the packed tile
+    int beyond = -1, from = 0;                                 // the tile and its part at which the wave left the packed tile
+    // a lane's words of its rows (one per chain) as word `word` of a plane; non-temporal, see store_event_words
+    uint32_t of2[S][TN] = {};
+    auto store_words = [&](uint32_t* plane, int word, const uint32_t (&w)[S][TN]) {
+        if (!plane) return;
+#pragma unroll
+        for (int i = 0; i < S; ++i) {
+            const int m = m0 + wave * RW + 8 * i + g, n = n0 + tx * TN;
+            if (m >= p.M) continue;
+            uint32_t* dst = plane + ((int64_t)word * p.M + m) * p.N + n;
+            if (p.c_vec && n + TN - 1 < p.N) {
+#pragma unroll
+                for (int j = 0; j + 3 < TN; j += 4)
+                    __builtin_nontemporal_store(u32x4_any{w[i][j], w[i][j + 1], w[i][j + 2], w[i][j + 3]}, reinterpret_cast<u32x4_any*>(dst + j));
+            } else {
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    if (n + j < p.N) __builtin_nontemporal_store(w[i][j], dst + j);
+            }
+        }
+    };
+    // the wave's words where nothing overflows: whole rows by a store, 16 bytes a lane (a lane's own eight words in two stores with gaps
+    // between them went to memory as partial lines: 3985 x 770 x 771 in chunks 300 us instead of 170)
+    auto store_no_events = [&](int word) {
+        constexpr int LANES = BN / 4, ROWS = 64 / LANES;
+        if (!p.of_mask) return;
+        int l = lane;
+        asm volatile("" : "+v"(l));                          // addresses made here, not kept in registers over the loop
+#pragma unroll
+        for (int i = 0; i < RW; i += ROWS) {
+            const int m = m0 + wave * RW + i + l / LANES, n = n0 + l % LANES * 4;
+            if (m >= p.M) continue;
+            uint32_t* dst = p.of_mask + ((int64_t)word * p.M + m) * p.N + n;
+            if (p.c_vec && n + 3 < p.N) {
+                __builtin_nontemporal_store(u32x4_any{0u, 0u, 0u, 0u}, reinterpret_cast<u32x4_any*>(dst));
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (n + j < p.N) __builtin_nontemporal_store(0u, dst + j);
+            }
+        }
+    };
     const uint32_t* const arow = Aw + g * T::PITCH;
     const uint32_t* const arowh = Aw + (8 + (lane >> 4)) * T::PITCH;       // the 4-row set: 16 lanes a row
     for (int t0 = 0; t0 < ntiles; t0 += DEPTH) {
@@ -379,24 +464,13 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
             const bool more = (t + 1) < ntiles;
             if (DEPTH == 1) fetch(t + 1, 0);
             const int parts = p.K - t * HBK > 32 ? 2 : 1;      // steps beyond K are products of zeros: skipped 32 at a time
-            auto largest = [&]() {
-                uint32_t mx = 0u;
-#pragma unroll
-                for (int i = 0; i < S; ++i)
-#pragma unroll
-                    for (int j = 0; j < W; ++j)
-                        mx = pk_max_u16(mx, as_u32(ORDER == LBA_ORDER_CHUNK16 ? top[i][j] : acc[i][j]) & 0x7FFF7FFFu);
-                if (HALF) {
-#pragma unroll
-                    for (int j = 0; j < TN / 4; ++j)
-                        mx = pk_max_u16(mx, as_u32(ORDER == LBA_ORDER_CHUNK16 ? toph[0][j] : acch[0][j]) & 0x7FFF7FFFu);
-                }
-                return max_half(mx);
-            };
             if (LISTS && listed) {
                 if (safe_tiles < parts) safe_tiles = bound.safe(largest(), dyn ? half_norm[t & 1] : nullptr, parts);
                 const char* const Bb = reinterpret_cast<const char*>(smem + tx * W);
                 const char* const Bh = reinterpret_cast<const char*>(smem + (lane & 15) * (W / 2));
+                if constexpr (EVENTS) {
+                    for (int part = 0; part < parts; ++part) store_no_events(2 * t + part);
+                }
                 ListHead<U> h0(arow), h1(HALF ? arowh : arow + (S == 2 ? 8 * T::PITCH : 0));
                 if (safe_tiles >= parts) {
                     safe_tiles -= parts;
@@ -418,10 +492,34 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
                     const uint32_t* const Bs = Bp + tx * W;
                     const uint32_t* const Bh = Bp + (lane & 15) * (W / 2);
                     if (safe_tiles == 0) safe_tiles = bound.safe(largest(), dyn ? half_norm[t & 1] : nullptr, 1);
+                    const int word = 2 * t + part;             // of the planes
                     if (safe_tiles > 0) {
                         --safe_tiles;
+                        if constexpr (EVENTS) store_no_events(word);
                         rows_tile<PM, ORDER, false, MASK, SMALL, S, TN, T::BROW, T::PITCH>(acc, top, arow + part * 16, Bs, c);
                         if constexpr (HALF) rows_tile<PM, ORDER, false, MASK, false, 1, TN / 2, T::BROW, T::PITCH>(acch, toph, arowh + part * 16, Bh, c);
+                    } else if constexpr (EVENTS) {
+                        const HalfBwdConst cb(p);
+                        uint32_t of[S][TN], none[S][TN], none2[S][TN];
+#pragma unroll
+                        for (int i = 0; i < S; ++i)
+#pragma unroll
+                            for (int j = 0; j < TN; ++j) { of[i][j] = 0u; none[i][j] = 0u; none2[i][j] = 0u; }
+                        half_bwd_tile<PM, ORDER, false, false, S, TN>(acc, top, of, none, of2, none2, 2 * (word & 15),
+                            [&](int k, uint32_t (&a)[S]) {
+#pragma unroll
+                                for (int i = 0; i < S; ++i) a[i] = arow[i * 8 * T::PITCH + part * 16 + k];
+                            },
+                            [&](int k, uint32_t (&b)[W]) { read_words<W>(Bs + k * T::BROW, b); }, cb);
+                        const int valid = p.K - 32 * word;     // a saturated sum stays at R_OF beyond K
+                        if (valid < 32) {
+#pragma unroll
+                            for (int i = 0; i < S; ++i)
+#pragma unroll
+                                for (int j = 0; j < TN; ++j) of[i][j] &= (1u << valid) - 1u;
+                        }
+                        if (ORDER == LBA_ORDER_SEQ && p.map_dx) mark_bricks_of_rows<RW, TN>(of, m0, n0, word, p);
+                        store_words(p.of_mask, word, of);
                     } else if constexpr (RANGE != 0) {
                         beyond = t;
                         from = part;
@@ -433,6 +531,23 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
                 }
                 if (RANGE != 0 && beyond >= 0) break;
             }
+            if constexpr (EVENTS && ORDER == LBA_ORDER_CHUNK16) {
+                // two chunks a word of the plane: a second-level word is complete after 16 of them
+                const int word = 2 * t + parts - 1;
+                if ((word & 15) == 15 || t + 1 == ntiles) {
+                    const int left = ((p.K + 15) >> 4) - 32 * (word >> 4);
+                    const uint32_t vmask = left >= 32 ? 0xFFFFFFFFu : (1u << left) - 1u;
+#pragma unroll
+                    for (int i = 0; i < S; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j) of2[i][j] &= vmask;
+                    if (p.of_mask2) store_words(p.of_mask2, word >> 4, of2);
+#pragma unroll
+                    for (int i = 0; i < S; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j) of2[i][j] = 0u;
+                }
+            }
             if (more) {
                 constexpr int next = (DEPTH > 1) ? 1 : 0;
                 stage(t + 1, (d + next) % DEPTH);
@@ -443,6 +558,7 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
         if (RANGE != 0 && beyond >= 0) break;
     }
 
+    if (EVENTS && !p.C) return;
     // C = S * 2^out_exp, zero written as +0
     auto store = [&](int m, int n, auto sum, auto count) {
         constexpr int CT = decltype(count)::value;
