@@ -36,6 +36,8 @@
 
 namespace lba {
 
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -163,9 +165,9 @@ __device__ __forceinline__ void add_unsplit(const float* __restrict__ G, const u
 
 // S_CONTIG: G(r, s) = G[r * ld + s] (dX); else G(r, s) = G[s * ld + r] (dW).  MASKED: L (same layout as G)
 // holds last-overflow indices and g' = [L < k0] g.  GVEC: G is 16-byte aligned and N % 4 == 0, so that a patch row is one
-// 16-byte load that lies inside the matrix or outside; otherwise its four values are loaded one by one (identity, 3985 x 770 x
-// 771: dX 68 us, dW 95 us, bound by the chain load -> split -> LDS -> barrier like the others; the vector kernel took such
-// shapes before, 873 and 747 us).
+// 16-byte load that lies inside the matrix or outside; otherwise it lies on a 4-byte boundary and the last group of a row is loaded value by
+// value (identity, 3985 x 770 x 771: dX 40 us, dW 49 us, bound by the chain load -> split -> LDS -> barrier like the others; every value by itself
+// 68 and 95 us).
 template <bool S_CONTIG, bool MASKED, int DTK, bool BYTES = false, bool GVEC = true>
 __global__ void __launch_bounds__(256, 2) lba_grad_dense_kernel(const float* __restrict__ G, const uint8_t* __restrict__ V,
                                                                 const int32_t* __restrict__ L,
@@ -201,16 +203,20 @@ __global__ void __launch_bounds__(256, 2) lba_grad_dense_kernel(const float* __r
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             float4 g = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (!GVEC) {                                       // the loads are unconditional, from addresses inside the matrix
-                float e[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int r = r0 + 4 * a_pr + (S_CONTIG ? q : u), s = sb + 4 * a_ps + (S_CONTIG ? u : q);
-                    const int rc = min(r, d.R - 1), sc = min(s, s_end - 1);
-                    const float x = G[S_CONTIG ? (int64_t)rc * d.ld_g + sc : (int64_t)sc * d.ld_g + rc];
-                    e[u] = (r < d.R && s < s_end) ? x : 0.0f;
+            if (!GVEC) {                                       // four values on a 4-byte boundary; one by one at the edge of the matrix
+                const int r = r0 + 4 * a_pr + (S_CONTIG ? q : 0), s = sb + 4 * a_ps + (S_CONTIG ? 0 : q);
+                const float* src = G + (S_CONTIG ? (int64_t)r * d.ld_g + s : (int64_t)s * d.ld_g + r);
+                const int left = S_CONTIG ? s_end - s : d.R - r;           // values of the group that exist
+                if ((S_CONTIG ? r < d.R : s < s_end) && left > 0) {
+                    if (left >= 4) {
+                        const f32x4_any x = *reinterpret_cast<const f32x4_any*>(src);
+                        g = make_float4(x.x, x.y, x.z, x.w);
+                    } else {
+                        g.x = src[0];
+                        if (left > 1) g.y = src[1];
+                        if (left > 2) g.z = src[2];
+                    }
                 }
-                g = make_float4(e[0], e[1], e[2], e[3]);
             } else if (S_CONTIG) {                                    // q: row within the patch; the float4 runs along s (S % 4 == 0 and
                                                                // s_chunk % 32 == 0: it is inside the range or outside, never across)
                 const int r = r0 + 4 * a_pr + q, s = sb + 4 * a_ps;
