@@ -16,6 +16,7 @@ data recipe: per-shape profiles).
 import argparse
 import json
 import os
+import re
 import sys
 import time
 
@@ -460,6 +461,7 @@ def run(args):
                                     args.workload, "single GEMM %s, ReLU activations, He weights" % args.workload),
                    "macs_per_step": total_macs, "qprod": "M%dE%d b=%d" % (prod_fmt[1], prod_fmt[0], prod_fmt[2]), "qacc": "M%dE%d b=%d" % (acc_fmt[1], acc_fmt[0], acc_fmt[2]) + (" (12-bit)" if acc_fmt == ACC_FMT else ""),
                    "call": ("%s, %s estimator: dX and dW (2 masked MACs per forward MAC)" % ({"immediate": "lba_grad_ws", "premapped": "lba_grad_premapped"}.get(args.grad, "lba_grad_ws" if args.ws else "lba_grad"), "immediate" if args.grad == "premapped" else args.grad)) if args.grad else ("lba_gemm_bwd_diff (C + DIFF plane, eps2 = %g)" % args.diff) if args.diff is not None else ("lba_gemm_bwd_chunked (C + four planes)" if order == 1 else (("lba_gemm_bwd_ws" if args.maps else ("lba_conv2d_bwd" if args.implicit else "lba_gemm_bwd")) + (" (C + OF plane)" if args.of_only else " (C + OF and UF planes)"))) if args.bwd else ("lba_conv2d" if args.implicit else "lba_gemm"), "round": args.round, "order": "sequential" if order == 0 else "chunks of 16", "scale": "per-tensor power of two, folded into b",
+                   "zero_codes": "a step whose code of A is zero is the identity; the forward tile may leave it out (operands here: about half are zero behind a ReLU), every MAC of the definition is counted",
                    "conv": "implicit im2col from NHWC activations (lba_conv2d)" if args.implicit else "operand A is the written-out im2col matrix",
                    "operands": ("E%dM%d codes with per-tensor flex bias (lba_gemm_in)" % in_fmt) if in_fmt else "E4M3"},
         "roofline": roofline,
@@ -606,9 +608,14 @@ def conv_kernel_name(name):
             return conv + name[len(plain):]
     if (name.startswith("lba_fast_kernel<") or name.startswith("lba_fast_bwd_kernel<")) and name.endswith(", 0>"):
         return name[:-4] + ", 2>"
+    staged = re.match(r"lba_half_staged_kernel<(\d), (\d)>$", name)
+    if staged:                                     # row-major operands only
+        return ("lba_half_mixed_kernel<%s, 0, 2>" if staged.group(1) == "2" else "lba_half_kernel<2, 2, %s, 0, 2>") % staged.group(2)
+    if name.startswith("lba_wide_"):               # the fetch is the last argument but one
+        return re.sub(r", ([03]), (\d)>$", lambda m: ", %d, %s>" % (2 if m.group(1) == "0" else 4, m.group(2)), name)
     if name.startswith("lba_half_") and name.endswith(", 0>"):
         return name[:-4] + ", 2>"
-    if name.startswith("lba_half_") and not name.startswith("lba_half_bwd") and name.endswith(", 3>"):
+    if name.startswith("lba_half_") and name.endswith(", 3>"):
         return name[:-4] + ", 4>"                  # K % 16 != 0: rows of any alignment, im2col rows of any channel count
     return name
 

@@ -10,7 +10,8 @@
 
 enum { OP_FMA, OP_MUL, OP_ADD, OP_AND_V, OP_AND_S, OP_XOR_V, OP_ADDU_V, OP_MED3, OP_MAX, OP_BFE, OP_ADD3,
        OP_CMP, OP_LDEXP, OP_PKFMA16, OP_CVTBF, MIX_MFA_DEP, MIX_MFA, MIX_FA, MIX_MFAC, MIX_RNE, MIX_MFCVT,
-       MIX_PK, MIX_PKT, MIX_PKE, MIX_PKL };          // packed FP16 steps: two chains per register
+       MIX_PK, MIX_PKT, MIX_PKE, MIX_PKL,            // packed FP16 steps: two chains per register
+       MIX_PK_FIRST, MIX_MFCVT_FIRST };              // half-rate phases at priority 1
 
 template <int OP, int NCH>
 __global__ void __launch_bounds__(256) probe(float* out, int iters, float a, float b, uint32_t mask) {
@@ -28,6 +29,24 @@ __global__ void __launch_bounds__(256) probe(float* out, int iters, float a, flo
                     asm volatile("v_fmac_f32 %0, %1, %2" : "+v"(x[i]) : "v"(vm), "v"(q[i]));
                     asm volatile("v_and_b32 %0, %1, %0" : "+v"(x[i]) : "v"(vm));
                 }
+            } else if (OP == MIX_PK_FIRST) {         // multiplies and multiply-adds before other waves' masks
+                __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+                for (int i = 0; i < NCH; ++i) asm volatile("v_pk_mul_f16 %0, %1, %2 op_sel_hi:[0,1]" : "=v"(q[i]) : "v"(a), "v"(b));
+#pragma unroll
+                for (int i = 0; i < NCH; ++i) asm volatile("v_pk_fma_f16 %0, %1, %2, %0" : "+v"(x[i]) : "v"(q[i]), "v"(vm));
+                __builtin_amdgcn_s_setprio(0);
+#pragma unroll
+                for (int i = 0; i < NCH; ++i) asm volatile("v_and_b32 %0, %1, %0" : "+v"(x[i]) : "v"(vm));
+            } else if (OP == MIX_MFCVT_FIRST) {      // conversions before other waves' multiplies and multiply-adds
+                __builtin_amdgcn_s_setprio(0);
+#pragma unroll
+                for (int i = 0; i < NCH; ++i) asm volatile("v_mul_f32 %0, %1, %2" : "=v"(q[i]) : "v"(a), "v"(b));
+#pragma unroll
+                for (int i = 0; i < NCH; ++i) asm volatile("v_fmac_f32 %0, %1, %2" : "+v"(x[i]) : "v"(vm), "v"(q[i]));
+                __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+                for (int i = 0; i < NCH; ++i) asm volatile("v_cvt_pk_bf16_f32 %0, 0, %0" : "+v"(x[i]));
             } else if (OP == MIX_PKL) {              // the next step's product between a sum and its rounding
 #pragma unroll
                 for (int i = 0; i < NCH; ++i) {
@@ -163,6 +182,8 @@ int main() {
         run<MIX_PK, 8>("pk_mul|pk_fma|and, slots", 5, w);
         run<MIX_PKT, 8>("pk_mul|and|pk_fma|and, slots", 6, w);
         run<MIX_PKE, 8>("pk step and event bits, slots", 16, w);
+        run<MIX_PK_FIRST, 8>("pk step, priorities, slots", 5, w);
+        run<MIX_MFCVT_FIRST, 16>("mul|fma|cvt_bf16, priorities", 3, w);
     }
     // the latency of a step: one register of a lone wave
     run<MIX_PK, 1>("pk_mul,pk_fma,and latency", 3, 1);
