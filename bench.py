@@ -611,6 +611,9 @@ def conv_kernel_name(name):
     staged = re.match(r"lba_half_staged_kernel<(\d), (\d)>$", name)
     if staged:                                     # row-major operands only
         return ("lba_half_mixed_kernel<%s, 0, 2>" if staged.group(1) == "2" else "lba_half_kernel<2, 2, %s, 0, 2>") % staged.group(2)
+    staged = re.match(r"lba_fast_staged_kernel<(\d), (\d), (\d)>$", name)
+    if staged:
+        return ("lba_fast_conv_mixed_kernel<32, %s, %s, 0>" if staged.group(1) == "2" else "lba_fast_kernel<2, 2, 32, %s, %s, 0, 2>") % staged.group(2, 3)
     if name.startswith("lba_wide_"):               # the fetch is the last argument but one
         return re.sub(r", ([03]), (\d)>$", lambda m: ", %d, %s>" % (2 if m.group(1) == "0" else 4, m.group(2)), name)
     if name.startswith("lba_half_") and name.endswith(", 0>"):

@@ -23,6 +23,7 @@ static hipError_t launch_plan(const Plan& pl, hipStream_t st) {
     if (pl.kernel == KERNEL_FAST && pl.events) return launch_fast_bwd(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.kp.h_on && pl.kp.h_range) return pl.kp.conv ? launch_wide_conv(pl, st) : launch_wide(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.kp.h_on) return pl.kp.conv ? launch_half_conv(pl, st) : launch_half(pl, st);
+    if (pl.kernel == KERNEL_FAST && pl.staged) return launch_fast_staged(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.rne_odd) return launch_fast_odd(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.amode == 2) return launch_fast_conv(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.amode == 1 && pl.mix_tail > 0)
@@ -71,6 +72,8 @@ static void plan_kernel_name(const Plan& pl, bool uf, char* buf, size_t n) {
         else if (pl.staged)       snprintf(buf, n, "lba_half_staged_kernel<%d, %d>", pl.mix_tail > 0 ? 2 : 4, pm);
         else if (pl.mix_tail > 0) snprintf(buf, n, "lba_half_mixed_kernel<%d, %d, %d>", pm, ord, am);
         else                 snprintf(buf, n, "lba_half_kernel<%d, %d, %d, %d, %d>", pl.tm, pl.tn, pm, ord, am);
+    } else if (pl.staged) {
+        snprintf(buf, n, "lba_fast_staged_kernel<%d, %d, %d>", pl.mix_tail > 0 ? 2 : 4, pm, pl.kp.sh_a == 16 ? 2 : 1);
     } else if (pl.rne_odd) {
         snprintf(buf, n, "lba_fast_kernel<4, 4, %d, %d, 3, %d, 0>", pl.bk, pm, ord);
     } else {

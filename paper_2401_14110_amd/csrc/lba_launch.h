@@ -32,6 +32,7 @@ hipError_t launch_half(const Plan& pl, hipStream_t st);
 hipError_t launch_half_conv(const Plan& pl, hipStream_t st);
 hipError_t launch_wide(const Plan& pl, hipStream_t st);            // the same, accumulators beyond FP16's range (kp.h_range)
 hipError_t launch_wide_conv(const Plan& pl, hipStream_t st);
+hipError_t launch_fast_staged(const Plan& pl, hipStream_t st);     // forward, nearest-even, the smallest grids (staged, not kp.h_on)
 hipError_t launch_half_bwd(const Plan& pl, hipStream_t st);        // plans with events == 1 on packed FP16 carriers (kp.h_on)
 // the DIFF plane, scaled-domain kernel (plans with events == 2)
 hipError_t launch_fast_diff(const Plan& pl, hipStream_t st);
