@@ -187,7 +187,7 @@ def run(args):
                 # tiles that can add a clamp, a compare and a carry-in add per MAC, which this count leaves out
                 fwd = lb.lba_plan_query(l["M"], l["N"], l["K"], l["qp"], l["qa"], order, 0)
                 l["plan"] = dict(l["plan"], valu_per_mac_x100=fwd["valu_per_mac_x100"])
-            if args.implicit:
+            if args.implicit and l["desc"][4:] != (1, 1, 1, 0):    # (a pointwise convolution runs the row-major kernels)
                 l["kname"] = conv_kernel_name(l["kname"])
         if args.bwd and args.diff is None and not args.of_only and l["kname"].startswith("lba_half_bwd"):
             # both planes on packed FP16 carriers: 8 slots of the packed step (9 instructions for two chains, 7 at half rate; half

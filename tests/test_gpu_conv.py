@@ -122,6 +122,28 @@ def test_conv2d_on_every_lane_block_and_on_mixed_grids(ref):
     assert {(False, True, True), (True, True, True), (True, False, True)} <= rounded, rounded
 
 
+# Pointwise convolutions run the row-major kernels: the smallest grids, whole chunks side by side, ragged channels, tensors off alignment
+@pytest.mark.parametrize("n,h,w,c,cout", [(1, 7, 7, 64, 40), (1, 9, 5, 3, 17), (2, 14, 14, 75, 100), (6, 28, 28, 48, 136)])
+@pytest.mark.parametrize("off", [0, 1])
+def test_pointwise_convolutions(ref, n, h, w, c, cout, off):
+    rng = np.random.default_rng(c)
+    X, W = codes(rng, (n, h, w, c), 3, 12), codes(rng, (cout, 1, 1, c), 3, 12)
+    buf = torch.empty(X.size + off, dtype=torch.uint8, device=DEV)
+    tX = buf[off:].view(n, h, w, c).copy_(torch.from_numpy(X))
+    tW = torch.from_numpy(W).to(DEV)
+    A, B = X.reshape(-1, c), W.reshape(cout, c)
+    for (qp, qa), rnd, order in itertools.product([((5, 7, 15), (4, 7, 7)), ((5, 4, 15), (4, 7, 7)), ((5, 7, 12), (5, 9, 12))], (0, 1), (0, 1)):
+        qpf, qaf = qp + (rnd,), qa + (rnd,)
+        Y = lb.conv2d(tX, tW, qpf, qaf, stride=1, pad=0, order=order)
+        want = ref.gemm(A, B, ref.QFmt(*qpf), ref.QFmt(*qaf), order=order)
+        assert Y.shape == (n, h, w, cout) and np.array_equal(bits(Y.cpu().numpy().reshape(want.shape)), bits(want)), (qpf, qaf, order)
+        if order == 0:
+            Y, of, uf = lb.conv2d(tX, tW, qpf, qaf, stride=1, pad=0, planes=True)
+            wc, wof, wuf = ref.gemm_bwd(A, B, ref.QFmt(*qpf), ref.QFmt(*qaf))
+            assert np.array_equal(bits(Y.cpu().numpy().reshape(wc.shape)), bits(wc))
+            assert np.array_equal(of.cpu().numpy().view(np.uint32), wof) and np.array_equal(uf.cpu().numpy().view(np.uint32), wuf)
+
+
 def test_conv2d_unaligned_tensor_and_status_codes(ref):
     rng = np.random.default_rng(125)
     n, h, w, c, cout = 2, 10, 10, 32, 40
