@@ -29,8 +29,24 @@ static hipError_t launch_order(const Plan& pl, hipStream_t st) {
     return hipErrorInvalidValue;
 }
 
+template <int PM, int CONV>
+static hipError_t launch_staged(const Plan& pl, hipStream_t st) {
+    const dim3 grid(pl.grid_x, pl.grid_y, pl.kp.batch), block(512);
+    if (pl.mix_tail > 0) hipLaunchKernelGGL((lba_half_staged_conv_kernel<2, PM, CONV>), grid, block, 0, st, pl.kp);
+    else                 hipLaunchKernelGGL((lba_half_staged_conv_kernel<4, PM, CONV>), grid, block, 0, st, pl.kp);
+    return hipGetLastError();
+}
+template <int CONV>
+static hipError_t launch_staged(const Plan& pl, hipStream_t st) {
+    return pl.prod_mode == PM_IDENT ? launch_staged<PM_IDENT, CONV>(pl, st) : pl.prod_mode == PM_FLUSH ? launch_staged<PM_FLUSH, CONV>(pl, st) : hipErrorInvalidValue;
+}
+
 hipError_t launch_half_conv(const Plan& pl, hipStream_t st) {
     if (pl.events || pl.round != LBA_ROUND_FLOOR || !pl.kp.conv || !pl.kp.h_on) return hipErrorInvalidValue;
+    if (pl.staged) {                                           // 32 x 16 tiles throughout, or 32 x 32
+        if (pl.order != LBA_ORDER_SEQ || (pl.mix_tail > 0 ? !pl.kp.mix_tail16 || pl.kp.mix_main + pl.kp.mix_half != 0 : pl.tm != 2 || pl.tn != 2)) return hipErrorInvalidValue;
+        return pl.kp.cv_vec ? launch_staged<1>(pl, st) : launch_staged<2>(pl, st);
+    }
     if (pl.kp.cv_vec && pl.kp.ld_align == 16)
         return pl.order == LBA_ORDER_CHUNK16 ? launch_order<LBA_ORDER_CHUNK16, 2>(pl, st) : launch_order<LBA_ORDER_SEQ, 2>(pl, st);
     return pl.order == LBA_ORDER_CHUNK16 ? launch_order<LBA_ORDER_CHUNK16, 4>(pl, st) : launch_order<LBA_ORDER_SEQ, 4>(pl, st);

@@ -139,8 +139,9 @@ static int run(const uint8_t* A, const uint8_t* B, float* C, uint32_t* of_mask, 
         // images of 56 x 56 to 256 channels 25 us against 38, 64 images of 224 x 224 to 64 channels 524 against 686) except on
         // the smallest grids, 32 x 16 tiles throughout (2 images of 14 x 14 to 64 channels 12.5 against 10.6).
         const bool narrow = conv->kw * conv->c < 16 && !(pl.kp.mix_tail16 && pl.kp.mix_main + pl.kp.mix_half == 0);
-        if ((int64_t)conv->n * conv->h * conv->w * conv->c < 16 || narrow) kp.h_on = 0;
+        if ((int64_t)conv->n * conv->h * conv->w * conv->c < 16 || narrow) kp.h_on = pl.staged = 0;
         kp.cv_vec = ((conv->c % 16) == 0 && ((uintptr_t)A % 16) == 0) ? 1 : 0;
+        if (!kp.cv_vec && conv->kw * conv->c < 16) pl.staged = 0;   // (gathered byte by byte)
         kp.cv_magic_c = (((uint64_t)1 << 40) + (uint64_t)conv->c - 1) / (uint64_t)conv->c;
         kp.cv_magic_kw = (((uint64_t)1 << 40) + (uint64_t)conv->kw - 1) / (uint64_t)conv->kw;
         la = lb;
@@ -291,11 +292,11 @@ static int run_conv(const uint8_t* X, const uint8_t* W, float* Y, uint32_t* of_m
     int32_t oh = 0, ow = 0;
     const int rc = lba_conv2d_out_shape(d, &oh, &ow);
     if (rc != LBA_OK) return rc;
-    return lba::run(X, W, Y, of_mask, uf_mask, (int64_t)d.n * oh * ow, cout, (int64_t)d.kh * d.kw * d.c, qprod, qacc,
     // a pointwise convolution's im2col rows are the tensor itself: the row-major kernels, whose fetch needs no taps and which have
     // waves that stage for the smallest grids and run chunks side by side there (7 x 7 x 2048 to 512 channels, one image, 72 -> 40 us, in
     // chunks 73 -> 23)
     const bool plain = d.kh == 1 && d.kw == 1 && d.stride == 1 && d.pad == 0;
+    return lba::run(X, W, Y, of_mask, uf_mask, (int64_t)d.n * oh * ow, cout, (int64_t)d.kh * d.kw * d.c, qprod, qacc,
                     order, events, hip_stream, 1, 0, 0, 0, nullptr, nullptr, nullptr, plain ? nullptr : &d, oh, ow);
 }
 

@@ -163,15 +163,18 @@ struct ConvPieces {
     }
     LBA_HOST_DEVICE const uint8_t* second(const KParams& p, int k0) const { return X + clamped(offset(p, at(p, k0 + kq).kh + 1, 0)); }
 
+    // the same where p.cv_vec: one tap
+    template <class V>
+    LBA_HOST_DEVICE V tap_codes(const KParams& p, const V& u, int k0) const {
+        const int k = k0 + kq;
+        const At a = at(p, k);
+        const bool in = k < p.K && inside(p, a.kh) && a.r >= lo && a.r < hi;
+        return in ? u : as_words<V>({0, 0});
+    }
     // the codes of the tile at k0 in what first(k0) and second(k0) hold (v is not read where p.cv_vec)
     template <class V>
     LBA_HOST_DEVICE V codes(const KParams& p, const V& u, const V& v, int k0) const {
-        if (p.cv_vec) {                                        // uniform: one tap
-            const int k = k0 + kq;
-            const At a = at(p, k);
-            const bool in = k < p.K && inside(p, a.kh) && a.r >= lo && a.r < hi;
-            return in ? u : as_words<V>({0, 0});
-        }
+        if (p.cv_vec) return tap_codes(p, u, k0);              // uniform
         if (!spans) {                                          // uniform: a few channels under a narrow filter, byte by byte
             Bytes16 b = {0, 0};
 #pragma unroll 1
@@ -183,6 +186,11 @@ struct ConvPieces {
             }
             return as_words<V>(b);
         }
+        return row_codes(p, u, v, k0);
+    }
+    // the same for filter rows that a piece may span, two at most (spans)
+    template <class V>
+    LBA_HOST_DEVICE V row_codes(const KParams& p, const V& u, const V& v, int k0) const {
         const int k = k0 + kq, n = p.K - k < 16 ? p.K - k : 16;   // codes of the piece below K
         const At a = at(p, k);
         const int left = p.cv_kw * p.cv_c - a.r, n1 = n < left ? n : left;   // of them in the first filter row

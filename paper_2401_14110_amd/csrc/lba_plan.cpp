@@ -543,7 +543,7 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
     // 32 x 16 tiles throughout, or the 2 x 2 lane block's 32 x 32: a lone wave per SIMD gets a second one that stages for it
     // (packed carriers, or FP32 ones under nearest-even: E4M3 operands in pieces of 16 codes, fetched ahead of the chain)
     const bool rne32 = p.kernel == KERNEL_FAST && !kp.h_on && qa.round == LBA_ROUND_RNE && !p.rne_odd && p.amode == 0 && N * K >= 16 && M * K >= 16 && K <= kPieceMaxK;
-    p.staged = ((kp.h_on && !kp.h_range) || rne32) && !conv && !p.events && order == LBA_ORDER_SEQ && (p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH) &&
+    p.staged = ((kp.h_on && !kp.h_range) || rne32) && !p.events && order == LBA_ORDER_SEQ && (p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH) &&
                (p.mix_tail > 0 ? kp.mix_tail16 && kp.mix_main + kp.mix_half == 0 : p.tm == 2 && p.tn == 2);
     *out = p;
     return LBA_OK;

@@ -505,7 +505,7 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
                         for (int i = 0; i < S; ++i)
 #pragma unroll
                             for (int j = 0; j < TN; ++j) { of[i][j] = 0u; none[i][j] = 0u; none2[i][j] = 0u; }
-                        half_bwd_tile<PM, ORDER, false, false, S, TN>(acc, top, of, none, of2, none2, 2 * (word & 15),
+                        half_bwd_tile<PM, ORDER, false, false, S, TN, (S * TN > 4)>(acc, top, of, none, of2, none2, 2 * (word & 15),
                             [&](int k, uint32_t (&a)[S]) {
 #pragma unroll
                                 for (int i = 0; i < S; ++i) a[i] = arow[i * 8 * T::PITCH + part * 16 + k];
@@ -698,7 +698,7 @@ __device__ __forceinline__ void staged_steps(h2 (&sum)[1][TN / 2], const uint32_
     }
 }
 
-template <int TN, int PM>
+template <int TN, int PM, int CONV>
 __device__ __forceinline__ void staged_body(const KParams& p, uint32_t* __restrict__ smem, int m0, int n0) {
     using T = StagedTile<TN>;
     constexpr int W = TN / 2, AHEAD = kTilesAhead;
@@ -718,21 +718,46 @@ __device__ __forceinline__ void staged_body(const KParams& p, uint32_t* __restri
         // lanes 0 .. 31: pieces of the wave's 8 rows of A; 32 and up: pieces of B
         const bool isb = lane >= 32;
         const int ca = isb ? -1 : (lane & 3) * T::BM + wave * 8 + (lane >> 2), cb = isb && lane - 32 < T::BN ? wave * T::BN + lane - 32 : -1;
-        RowPieces<T::BM> s(pA, p.M, p.K, m0, ca);
+        RowPieces<T::BM> s(pA, CONV ? 1 : p.M, p.K, CONV ? 0 : m0, ca);
         const RowPieces<T::BN> sb(pB, p.N, p.K, n0, cb);
-        if (isb) { s.row = sb.row; s.kq = sb.kq; s.room = sb.room; s.end = sb.end; s.ok = sb.ok; }
+        if (isb || CONV) { s.row = sb.row; s.kq = sb.kq; s.room = sb.room; s.end = sb.end; s.ok = sb.ok; }
+        ConvPieces sc = {};
+        if (CONV) sc = ConvPieces::make<T::BM>(pA, p, m0, ca);
         const int shift = isb ? p.h_shift_b : p.h_shift_a;
         const uint32_t keep = isb ? p.h_keep_b : p.h_keep_a, scale = isb ? p.h_scale_b : p.h_scale_a;
-        uint4 r[AHEAD];
+        uint4 r[AHEAD], r2[CONV == 2 ? AHEAD : 1];
+        auto fetch = [&](int t, int d) {                       // (a tile beyond K reads codes inside the operands that nothing uses)
+            const int k0 = tile_start(t);
+            if (CONV) {
+                const uint8_t* const a = sc.first(p, k0);
+                const uint8_t* const b = s.address(k0);
+                r[d] = load_16(isb ? b : a);
+                if constexpr (CONV == 2) {
+                    const uint8_t* const a2 = sc.second(p, k0);
+                    r2[d] = load_16(isb ? b : a2);
+                }
+            } else {
+                r[d] = load_piece(s, k0);
+            }
+        };
 #pragma unroll
-        for (int d = 0; d < AHEAD; ++d) r[d] = load_piece(s, tile_start(d));   // (a tile beyond K reads codes inside the operands that nothing uses)
+        for (int d = 0; d < AHEAD; ++d) fetch(d, d);
         for (int t0 = 0; t0 < ntiles; t0 += AHEAD) {
 #pragma unroll
             for (int d = 0; d < AHEAD; ++d) {
                 const int t = t0 + d;
                 if (t >= ntiles) break;
                 uint32_t* const st = smem + (t & 1) * T::STAGE;
-                const uint4 v = s.codes(r[d], t * HBK);
+                uint4 v = r[d];
+                if (CONV) {
+                    const uint4 row = s.codes(v, t * HBK);
+                    uint4 tap;
+                    if constexpr (CONV == 2) tap = sc.row_codes(p, v, r2[d], t * HBK);
+                    else                     tap = sc.tap_codes(p, v, t * HBK);
+                    v = make_uint4(isb ? row.x : tap.x, isb ? row.y : tap.y, isb ? row.z : tap.z, isb ? row.w : tap.w);
+                } else {
+                    v = s.codes(v, t * HBK);
+                }
                 uint32_t w[8];
                 decode_half(v, shift, keep, scale, w);
                 store_staged_b<TN>(st, cb, w);
@@ -748,7 +773,7 @@ __device__ __forceinline__ void staged_body(const KParams& p, uint32_t* __restri
                     for (int o = 32; o > 0; o >>= 1) m = pk_max_u16(m, (uint32_t)__shfl_xor((int)m, o, 64));
                     if (lane == 0) half_norm[t & 1][wave] = m;
                 }
-                r[d] = load_piece(s, tile_start(t + AHEAD));
+                fetch(t + AHEAD, d);
                 __syncthreads();
             }
         }
@@ -803,13 +828,20 @@ __device__ __forceinline__ void staged_body(const KParams& p, uint32_t* __restri
     }
 }
 
-// Row-major operands of any alignment, the sequential order; 512 lanes.
-template <int TN, int PM>
-__global__ void __launch_bounds__(512, 4) lba_half_staged_kernel(const KParams p) {
+template <int TN, int PM, int CONV>
+__device__ __forceinline__ void staged_grid(const KParams& p) {
     __shared__ __attribute__((aligned(16))) uint32_t smem[StagedTile<TN>::WORDS];
     const int by = TN == 2 ? blockIdx.x / p.mix_gx_tail : blockIdx.y, bx = TN == 2 ? blockIdx.x - by * p.mix_gx_tail : blockIdx.x;
-    staged_body<TN, PM>(p, smem, bx * 32, by * 8 * TN);
+    staged_body<TN, PM, CONV>(p, smem, bx * 32, by * 8 * TN);
 }
+// The sequential order; 512 lanes.  Row-major operands of any alignment; im2col rows, CONV 1: pieces are channels of one tap (cv_vec), 2: pieces
+// span at most two filter rows.  One kernel for both waited for its loads where the branch around the second one met (3 x 3 on 56 x 56 x
+// 64 29.6 us, 17.5 so).  lba_half_kernel -> here, one image: 7 x 7 x 512 to 512 channels, 3 x 3, 155 -> 84 us, 14 x 14 x 256 81 -> 45, 28 x
+// 28 x 128 42 -> 24, 56 x 56 x 64 25.3 -> 17.6, a stem (112 x 112 x 3, 7 x 7) 12.6 -> 10.5; 8 of 7 x 7 x 512 177 -> 113.
+template <int TN, int PM>
+__global__ void __launch_bounds__(512, 4) lba_half_staged_kernel(const KParams p) { staged_grid<TN, PM, 0>(p); }
+template <int TN, int PM, int CONV>
+__global__ void __launch_bounds__(512, 4) lba_half_staged_conv_kernel(const KParams p) { staged_grid<TN, PM, CONV>(p); }
 
 template <int TM, int TN, int PM, int ORDER, int AMODE, int RANGE>
 __device__ __forceinline__ void rows_plain(const KParams& p) {

@@ -144,6 +144,26 @@ def test_pointwise_convolutions(ref, n, h, w, c, cout, off):
             assert np.array_equal(of.cpu().numpy().view(np.uint32), wof) and np.array_equal(uf.cpu().numpy().view(np.uint32), wuf)
 
 
+# The smallest grids under floor rounding: 32 x 16 tiles, then 32 x 32; taps of whole pieces and filter rows that
+# pieces span (waves of their own stage), filters narrower than a piece, tensors off alignment; sums that never, now and then and nearly always saturate
+@pytest.mark.parametrize("n,h,w,c,cout,k,stride,pad", [(1, 7, 7, 64, 40, 3, 1, 1), (2, 9, 5, 20, 17, 3, 2, 4), (1, 1, 3, 16, 5, 1, 1, 2), (1, 30, 33, 3, 48, 7, 2, 3),
+                                                       (2, 14, 14, 3, 64, 3, 1, 1), (2, 28, 28, 48, 260, 3, 1, 1), (3, 31, 29, 25, 131, 3, 2, 0)])
+@pytest.mark.parametrize("off", [0, 1])
+def test_smallest_grids(ref, n, h, w, c, cout, k, stride, pad, off):
+    rng = np.random.default_rng(c + k)
+    X, W = codes(rng, (n, h, w, c)), codes(rng, (cout, k, k, c))
+    X = np.where(rng.random(X.shape) < 0.4, 0, X).astype(np.uint8)
+    tX = torch.empty(X.size + off, dtype=torch.uint8, device=DEV)[off:].view(n, h, w, c).copy_(torch.from_numpy(X))
+    A, B = ref.im2col_nhwc(X, k, k, stride, pad), W.reshape(cout, -1)
+    rows = np.sort(rng.choice(A.shape[0], min(A.shape[0], 150), replace=False))
+    for qp, qa in [((5, 7, 4, 0), (4, 7, -4, 0)), ((5, 7, 12, 0), (4, 1, 16, 0)), ((5, 7, 4, 0), (4, 7, 0, 0)), ((6, 7, 40, 0), (4, 7, -4, 0))]:
+        if k > 1:       # (the row-major plan of the same shape is staged, so this one is, but for filters narrower than a piece)
+            assert lb.lba_plan_kernel_name(A.shape[0], cout, A.shape[1], qp, qa, 0).startswith("lba_half_staged_kernel"), (qp, qa)
+        Y = lb.conv2d(tX, torch.from_numpy(W).to(DEV), qp, qa, stride=stride, pad=pad)
+        want = ref.gemm(np.ascontiguousarray(A[rows]), B, ref.QFmt(*qp), ref.QFmt(*qa))
+        assert np.array_equal(bits(Y.cpu().numpy().reshape(-1, cout)[rows]), bits(want)), (qp, qa)
+
+
 def test_conv2d_unaligned_tensor_and_status_codes(ref):
     rng = np.random.default_rng(125)
     n, h, w, c, cout = 2, 10, 10, 32, 40
