@@ -68,12 +68,11 @@ struct HalfBwdConst {
 // 32 steps with event bits: word [i][j] of chain (i, j) gets step k in bit k (of: 1 = overflow; uf: 1 = underflow or a zero
 // operand, cleared by the caller).  of2 / uf2: the two chunks' bits enter the second-level words at bits pos, pos + 1.
 // read_a(k / 2, words of the rows), read_b(k, words of the columns).
-template <int PM, int ORDER, bool UF, bool QUIET, int TM, int TN, class ReadA, class ReadB>
+template <int PM, int ORDER, bool UF, bool QUIET, int TM, int TN, bool PRIO, class ReadA, class ReadB>
 __device__ __forceinline__ void half_bwd_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[TM][TN / 2], uint32_t (&of)[TM][TN], uint32_t (&uf)[TM][TN],
                                               uint32_t (&of2)[TM][TN], uint32_t (&uf2)[TM][TN], int pos, ReadA read_a, ReadB read_b,
                                               const HalfBwdConst& c) {
     constexpr int NJ = TN / 2;
-    constexpr bool PRIO = TM * TN > 4;
     issue_first<PRIO>();
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -236,6 +235,8 @@ __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __rest
     set_round_zero_f16();
     set_flush_out_f16();
 
+    constexpr bool TURNS = TM * TN > 4;
+    const bool turns = gridDim.x * gridDim.y > 256;           // a lone wave per SIMD has nobody to wait for (128 x 192 x 656 144 -> 139 us)
     const HalfBwdConst c(p);
     h2 acc[TM][NJ], top[TM][NJ];
     uint32_t of2[TM][TN], uf2[TM][TN];
@@ -310,9 +311,11 @@ __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __rest
             const bool quiet = safe_tiles > 0;
             if (quiet) {
                 --safe_tiles;
-                half_bwd_tile<PM, ORDER, true, true, TM, TN>(acc, top, of, uf, of2, uf2, pos, read_a, read_b, c);
+                if (TURNS && turns) half_bwd_tile<PM, ORDER, true, true, TM, TN, TURNS>(acc, top, of, uf, of2, uf2, pos, read_a, read_b, c);
+                else                half_bwd_tile<PM, ORDER, true, true, TM, TN, false>(acc, top, of, uf, of2, uf2, pos, read_a, read_b, c);
             } else {
-                half_bwd_tile<PM, ORDER, true, false, TM, TN>(acc, top, of, uf, of2, uf2, pos, read_a, read_b, c);
+                if (TURNS && turns) half_bwd_tile<PM, ORDER, true, false, TM, TN, TURNS>(acc, top, of, uf, of2, uf2, pos, read_a, read_b, c);
+                else                half_bwd_tile<PM, ORDER, true, false, TM, TN, false>(acc, top, of, uf, of2, uf2, pos, read_a, read_b, c);
                 const int valid = p.K - 32 * w;                // a saturated sum stays at R_OF beyond K
                 if (valid < 32) {
 #pragma unroll
