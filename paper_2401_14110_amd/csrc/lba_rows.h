@@ -25,25 +25,11 @@
 #define LBA_ROWS_H_
 
 #include "lba_half_bwd.h"
+#include "lba_list_index.h"
 
 namespace lba {
 
-
-// Geometry of one workgroup tile: each of the four waves takes RW rows (8, 12 or 16) and all BN = 8 TN columns.  A row set is 8
-// rows of 8 lanes, TN columns per lane; 12 rows are one such set and one of 4 rows of 16 lanes, TN / 2 columns per lane.
-// LDS: two stages of B as words (n, n + 1) of one k, [k][n / 2]; one stage of A, every row written and read by its own wave:
-// its words (k, k + 1), or the list of its non-zero codes (value in the low half, byte offset of the code's row of B in the high).
 template <int N> struct IntConst { static constexpr int value = N; };
-
-template <int RW, int TN>
-struct RowTile {
-    static constexpr int BM = 4 * RW, BN = 8 * TN, SETS = RW / 8;
-    static constexpr bool HALF = RW % 8 != 0;
-    static constexpr int U = TN >= 8 ? 4 : 8;                  // list entries taken at a time
-    static constexpr int BROW = BN / 2, B_WORDS = HBK * BROW;
-    static constexpr int PITCH = HBK + 2 * U + (U == 8 ? 4 : 0);   // words per row of A: 64 and the zeros a list is read on into
-    static constexpr int A_WORDS = BM * PITCH, WORDS = 2 * B_WORDS + A_WORDS;
-};
 
 template <int T>
 __device__ __forceinline__ void read_words(const uint32_t* s, uint32_t (&b)[T]) {
@@ -98,15 +84,10 @@ __device__ __forceinline__ void list_steps(h2 (&sums)[T / 2], ListHead<U>& h, co
     for (int j = 0; j < W; ++j) acc[0][j] = sums[j];
 #pragma unroll
     for (int u = 0; u < U; ++u) read_words<W>(reinterpret_cast<const uint32_t*>(Bb + (h.e[u] >> 16)), b[u]);
-    const uint32_t* after = list + 2 * U;
+    const uint32_t* const after = list + 2 * U;
     issue_first<MASK>();
-#pragma unroll 1
-    for (int i = 0; i < n; i += 2 * U) {
-        list_round<PM, CLAMP, MASK, T, U>(acc, h.e, h.f, b, after, Bb, c);
-        if (i + U >= n) break;
-        list_round<PM, CLAMP, MASK, T, U>(acc, h.f, h.e, b, after + U, Bb, c);
-        after += 2 * U;
-    }
+    walk_list<U>(n, [&](int i) { list_round<PM, CLAMP, MASK, T, U>(acc, h.e, h.f, b, after + i, Bb, c); },
+                 [&](int i) { list_round<PM, CLAMP, MASK, T, U>(acc, h.f, h.e, b, after + i, Bb, c); });
     issue_last<MASK>();
 #pragma unroll
     for (int j = 0; j < W; ++j) sums[j] = acc[0][j];
@@ -408,6 +389,7 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
     };
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) fetch(d, d);               // (a tile beyond K reads codes inside the operands that nothing uses)
+    if (LISTS && ca >= 0) pad_row<T>(lane & 3, [&](int w) { Aw[(lane >> 2) * T::PITCH + w] = 0u; });
     stage(0, 0);
     if (DEPTH > 1) fetch(DEPTH, 0);
     __syncthreads();

@@ -1,4 +1,4 @@
-// Host build of the piece arithmetic of the packed FP16 tiles (csrc/lba_piece_index.h) under the address and
+// Host build of the piece and list arithmetic of the packed FP16 tiles (csrc/lba_piece_index.h, lba_list_index.h) under the address and
 // undefined-behaviour sanitizers: every address stays inside its operand and every piece holds the codes that the definition
 // (64-bit indices, one byte at a time) gives.  Operands of 2 GiB and more are reserved address space of which only the rows
 // under test are ever written.  tests/test_sanitizers_cpu.py compiles and runs it, one check at a time; nothing touches a GPU.
@@ -11,6 +11,7 @@
 
 #include <vector>
 
+#include "lba_list_index.h"
 #include "lba_piece_index.h"
 
 static int failures = 0;
@@ -175,12 +176,40 @@ static void convolutions() {
     }
 }
 
+// lists of non-zero codes of every length over one row of a row tile, after a tile or a longer list whose words stay behind: every
+// entry that serves as an address was written by the list or the pad, its row of B lies inside a stage, and no read leaves the row
+template <int RW, int TN>
+static void check_lists() {
+    using T = lba::RowTile<RW, TN>;
+    for (int len = 0; len <= 64; ++len) {
+        std::vector<int64_t> row((size_t)T::PITCH, -1);        // -1: never written
+        for (int l = 0; l < 4; ++l) lba::pad_row<T>(l, [&](int w) { CHECK(w >= 64 && w < T::PITCH, "pad word %d", w); row.at((size_t)w) = 0; });
+        for (int w = 0; w < 64; ++w) row[(size_t)w] = (int64_t)((w < len ? 0x3C00 + w : 0) | (uint32_t)(T::B_WORDS * 4 + w * T::BROW * 4) << 16);
+        const int n = (len + T::U - 1) & ~(T::U - 1);
+        int next = 0;
+        const auto round = [&](int i) {
+            CHECK(i == next, "round at %d, not %d", i, next);
+            for (int u = 0; u < T::U; ++u) {                   // the rows asked for: entries i + U ..., read two rounds ago
+                const int64_t e = row.at((size_t)(i + T::U + u));
+                CHECK(e >= 0 && (int)(e >> 16) % (T::BROW * 4) == 0 && (int)(e >> 16) + T::BROW * 4 <= 2 * T::B_WORDS * 4,
+                      "list of %d: entry %d is an address and was never written", len, i + T::U + u);
+            }
+            CHECK(i + 3 * T::U <= T::PITCH, "list of %d: entries read up to %d", len, i + 3 * T::U);
+            next += T::U;
+        };
+        lba::walk_list<T::U>(n, round, round);
+        CHECK(next == n, "list of %d: %d entries taken", len, next);
+    }
+}
+static void lists() { check_lists<16, 8>(); check_lists<12, 8>(); check_lists<8, 8>(); check_lists<8, 4>(); check_lists<8, 2>(); }
+
 int main(int argc, char** argv) {
     if (argc != 2) { std::printf("usage: %s <check>\n", argv[0]); return 2; }
     if (!std::strcmp(argv[1], "far_rows")) far_rows();
     else if (!std::strcmp(argv[1], "long_chains")) long_chains();
     else if (!std::strcmp(argv[1], "convolutions")) convolutions();
     else if (!std::strcmp(argv[1], "wide_padding")) wide_padding();
+    else if (!std::strcmp(argv[1], "lists")) lists();
     else { std::printf("no such check\n"); return 2; }
     if (failures) { std::printf("%d failures\n", failures); return 1; }
     std::printf("pieces ok\n");

@@ -53,7 +53,7 @@ def pieces(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["far_rows", "long_chains", "convolutions", "wide_padding"])
+@pytest.mark.parametrize("check", ["far_rows", "long_chains", "convolutions", "wide_padding", "lists"])
 def test_pieces_of_the_packed_tiles(pieces, check):
     run = subprocess.run([pieces, check], capture_output=True, text=True, env=dict(os.environ, UBSAN_OPTIONS="print_stacktrace=1"))
     assert run.returncode == 0 and "pieces ok" in run.stdout, (run.returncode, run.stdout[-3000:], run.stderr[-3000:])
