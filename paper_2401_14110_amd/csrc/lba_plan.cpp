@@ -162,8 +162,8 @@ static bool half_carrier(const lba_qfmt& qp, const lba_qfmt& qa, const InSpec& i
     if (in.ea > 4 || in.eb > 4 || qa.man_bits > 10) return false;
     const int c_a = bae - 14, c_p = prod_mode == PM_IDENT ? c_a : bpe - 14;
     const int top = (1 << qa.exp_bits) - qa.bias - 1 + c_a;    // top exponent of Q_acc in the tile's domain
-    // R_OF beyond FP16's range: sums that could leave it go on in FP32 (lba_rows.h, a slow loop), so the range must be far above a
-    // product: 64 of the largest ones, two tiles from zero
+    // R_OF beyond FP16's range: sums that could leave it go on in FP32 until they are back (lba_rows.h), at the FP32 tile's pace, so the
+    // range must be far above a product: 64 of the largest ones, two tiles from zero
     const bool beyond = top > 14;
     if (top < -14 || (beyond && (forward_only == false || prod_mode != PM_FLUSH || std::ldexp(in.max_prod, c_a) * 64.0 > 65504.0))) return false;
     if (prod_mode == PM_FLUSH && in.sig_bits > 11) return false;

@@ -189,52 +189,134 @@ __device__ __forceinline__ void mark_bricks_of_rows(const uint32_t (&of)[RW / 8]
     }
 }
 
-// Sums beyond FP16's range (accumulators of E >= 5): the constants of the FP32 step (fast_group), R_UF at 2^-126.
+// Sums beyond FP16's range (accumulators of E >= 5), in FP32 at R_UF = 2^-126: the products of two chains stay packed, v_fma_mix_f32 adds
+// one half of them to an FP32 sum (exactly, rounded once toward zero, flushed below R_UF), then the mask and, where R_OF is near, the
+// clamp of the FP32 step.  No operand is converted, and the masks take turns with the rest as in the packed tile: 7.8 cycles per
+// chain and step in the issue-rate probe at four waves per SIMD (FP32 step 7.4, packed step 5.4 to 6.3).
+// All sums beyond the range, lba_fast_kernel / operands converted to FP32, four steps at a time and to the end of the chain / here, us:
+//   4096 x 1024 x 2048   M7E6  463 / 1140 /  471, half of A's codes zero 463 /  840 / 386
+//   4096 x 4096 x 4096   M7E6 3201 /10000 / 3343, ...                   3200 / 6489 /2613; M10E5, products of both signs 3238 / 3772 /2625
+//   64 x 1000 x 2048     M7E6   61 /   86 /   62, ...                     61 /   71 /  56
+// M10E5, where every sum saturates: 491 / 1252 / 528 for the first shape (the clamp has the same price for both, beside fewer instructions).
 struct BeyondConst {
-    float kc, rof;
-    uint32_t mask, maskp;
-    __device__ __forceinline__ float quantize(float t) const { return med3(__uint_as_float(__float_as_uint(t) & mask), -rof, rof); }
+    float kc, rof, nrof;       // kc * 2^-112 (kc < 2^-14 never gets here: products below 4 carry no sum of 11 bits past 8192)
+    uint32_t mask;
+    __device__ __forceinline__ explicit BeyondConst(const KParams& p) : kc(p.kc * 0x1p-112f), rof(p.rof_a), nrof(-p.rof_a), mask(p.mask_a) {
+        asm volatile("" : "+v"(kc), "+v"(rof), "+v"(nrof), "+v"(mask));
+    }
 };
-// n steps (a multiple of 4) of one row in FP32: row: pairs (k, k + 1), or a list; off: byte offset of the first step's words of B.  The
-// rare end of a chain whose sums leave FP16's range: four steps' operands at a time (4096 x 1024 x 2048 all beyond it: 1741 us one
-// step at a time, 1260 so, lba_fast_kernel 513).
-template <int PM, int ORDER, int T, int BROW>
-__device__ __forceinline__ void beyond_steps(float (&sum)[T], float (&top)[T], const uint32_t* row, bool listed, int n, const char* Bb, uint32_t off,
-                                             const BeyondConst& c) {
-#pragma unroll 1
-    for (int k = 0; k < n; k += 4) {
-        uint32_t e[4], b[4][T / 2];
+
+// a step's products added to the sums, unrounded
+template <int S, int TN>
+__device__ __forceinline__ void beyond_sums(float (&sum)[S][TN], const h2 (&q)[S][TN / 2], const BeyondConst& w) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) e[u] = listed ? row[k + u] : row[(k + u) >> 1] >> (16 * (u & 1));
+    for (int i = 0; i < S; ++i)
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            read_words<T / 2>(reinterpret_cast<const uint32_t*>(Bb + (listed ? e[u] >> 16 : off + (uint32_t)(k + u) * (BROW * 4))), b[u]);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float a = (float)as_h2(e[u]).x * 0x1p-56f;   // (an operand can be as small as 2^-24: half of the 2^-112 to each)
-            float q[T];
-#pragma unroll
-            for (int j = 0; j < T; ++j) {
-                const h2 w = as_h2(b[u][j / 2]);
-                q[j] = ((float)(j & 1 ? w.y : w.x) * 0x1p-56f) * a;   // flushed below Q_prod's R_UF
-            }
-#pragma unroll
-            for (int j = 0; j < T; ++j) {
-                if (PM == PM_TRUNC) q[j] = __uint_as_float(__float_as_uint(q[j]) & c.maskp);
-                sum[j] = c.quantize(__builtin_fmaf(q[j], c.kc, sum[j]));
-            }
+        for (int j = 0; j < TN / 2; ++j) {
+            asm("v_fma_mix_f32 %0, %1, %2, %0 op_sel_hi:[1,0,0]" : "+v"(sum[i][2 * j]) : "v"(q[i][j]), "v"(w.kc));
+            asm("v_fma_mix_f32 %0, %1, %2, %0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(sum[i][2 * j + 1]) : "v"(q[i][j]), "v"(w.kc));
         }
-        if (ORDER == LBA_ORDER_CHUNK16 && (k & 12) == 12) {
+    __builtin_amdgcn_sched_barrier(0);
+}
+template <bool CLAMP, bool PRIO, int S, int TN>
+__device__ __forceinline__ void beyond_round(float (&sum)[S][TN], const BeyondConst& w) {
+    issue_last<PRIO>();
 #pragma unroll
-            for (int j = 0; j < T; ++j) { top[j] = c.quantize(top[j] + sum[j]); sum[j] = 0.0f; }
-        }
+    for (int i = 0; i < S; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) sum[i][j] = __uint_as_float(__float_as_uint(sum[i][j]) & w.mask);
+    __builtin_amdgcn_sched_barrier(0);
+    issue_first<PRIO>();
+    if (CLAMP) {
+#pragma unroll
+        for (int i = 0; i < S; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) sum[i][j] = med3(sum[i][j], w.nrof, w.rof);
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
+// 32 steps, as rows_tile: operands are read a pair ahead, or four where a lone wave has few chains to wait with (LONE: there the next
+// step's products stand between a sum and its mask)
+template <int PM, int ORDER, bool CLAMP, bool LONE, int S, int TN, int BROW, int PITCH>
+__device__ __forceinline__ void beyond_tile(float (&sum)[S][TN], float (&top)[S][TN], const uint32_t* arow, const uint32_t* Bs, const HalfConst& c,
+                                            const BeyondConst& w) {
+    constexpr int W = TN / 2, AHEAD = LONE ? 4 : 1, SLOTS = 2 * AHEAD, GROUP = LONE ? 8 : 4;
+    constexpr bool PRIO = !LONE;
+    uint32_t a[SLOTS][S], b0[SLOTS][W], b1[SLOTS][W];
+    auto read = [&](int s, int k) {
+#pragma unroll
+        for (int i = 0; i < S; ++i) a[k][i] = arow[i * 8 * PITCH + s];
+        read_words<W>(Bs + 2 * s * BROW, b0[k]);
+        read_words<W>(Bs + (2 * s + 1) * BROW, b1[k]);
+    };
+    h2 q[2][S][W];
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s) read(s, s);
+    issue_first<PRIO>();
+    if (LONE) half_products<PM, false, S, TN, PRIO>(q[0], a[0], b0[0], c);
+#pragma unroll 1
+    for (int g = 0; g < 16; g += GROUP) {
+#pragma unroll
+        for (int u = 0; u < GROUP; ++u) {
+            const int k = u % SLOTS, next = (u + 1) % SLOTS;
+            read(u + AHEAD < GROUP ? g + u + AHEAD : min(g + u + AHEAD, 15), (u + AHEAD) % SLOTS);   // (the last ones again at the end)
+            if (!LONE) half_products<PM, false, S, TN, PRIO>(q[0], a[k], b0[k], c);
+            beyond_sums(sum, q[0], w);
+            if (LONE) half_products<PM, true, S, TN, PRIO>(q[1], a[k], b1[k], c);
+            beyond_round<CLAMP, PRIO>(sum, w);
+            if (!LONE) half_products<PM, true, S, TN, PRIO>(q[1], a[k], b1[k], c);
+            beyond_sums(sum, q[1], w);
+            if (LONE) half_products<PM, false, S, TN, PRIO>(q[0], a[next], b0[next], c);
+            beyond_round<CLAMP, PRIO>(sum, w);
+        }
+        if (ORDER == LBA_ORDER_CHUNK16 && (LONE || (g & 4))) {
+#pragma unroll
+            for (int i = 0; i < S; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) { top[i][j] += sum[i][j]; sum[i][j] = 0.0f; }
+            __builtin_amdgcn_sched_barrier(0);
+            beyond_round<CLAMP, PRIO>(top, w);
+        }
+    }
+    issue_last<PRIO>();
+}
+
+// the steps of a list, as list_steps
+template <int PM, bool CLAMP, int T, int U>
+__device__ __forceinline__ void beyond_list(float (&sums)[T], const uint32_t* list, const char* Bb, int n, const HalfConst& c, const BeyondConst& w) {
+    constexpr int W = T / 2;
+    ListHead<U> h(list);
+    uint32_t b[U][W];
+    float sum[1][T];
+#pragma unroll
+    for (int j = 0; j < T; ++j) sum[0][j] = sums[j];
+#pragma unroll
+    for (int u = 0; u < U; ++u) read_words<W>(reinterpret_cast<const uint32_t*>(Bb + (h.e[u] >> 16)), b[u]);
+    const uint32_t* const after = list + 2 * U;
+    const auto round = [&](uint32_t (&e)[U], const uint32_t (&f)[U], int i) {
+        h2 q[1][W];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t a1[1] = {e[u]};
+            half_products<PM, false, 1, T, true>(q, a1, b[u], c);
+            if (u == U - 1) ListHead<U>::read(after + i, e);
+            read_words<W>(reinterpret_cast<const uint32_t*>(Bb + (f[u] >> 16)), b[u]);
+            beyond_sums(sum, q, w);
+            beyond_round<CLAMP, true>(sum, w);
+        }
+    };
+    issue_first<true>();
+    walk_list<U>(n, [&](int i) { round(h.e, h.f, i); }, [&](int i) { round(h.f, h.e, i); });
+    issue_last<true>();
+#pragma unroll
+    for (int j = 0; j < T; ++j) sums[j] = sum[0][j];
+}
+
 // RANGE 0: every sum fits FP16 up to R_OF (half_carrier, lba_plan.cpp).  1, 2: R_OF lies beyond FP16's range; the bound that spares the
-// clamp elsewhere shows that no sum leaves the range in the tile at hand (65504 in place of R_OF), and a wave where it cannot goes
-// on in FP32 to the end of its chains.  2: M = 10, FP16's own mantissa, which needs no mask.  M10E5 on 4096 x 4096 x 4096: 3220 us on FP32
-// carriers, 2070 here.
+// clamp elsewhere shows that no sum leaves the range in the tile at hand (65504 in place of R_OF); a wave where it cannot goes on in FP32
+// until its sums lie a whole tile inside the range again.  2: M = 10, FP16's own mantissa, which needs no mask.  M10E5 on 4096 x 4096 x 4096:
+// 3220 us on FP32 carriers, 2070 here.
 // EVENTS: the recompute call for the overflow plane alone (RANGE 0, no set of four rows): a part of a tile in which no sum can reach R_OF
 // is the forward call's and its words are zero; any other runs half_bwd_tile.  A tile becomes lists only where the fixed bound covers it,
 // since the steps a list leaves out have no event there (a saturated sum would repeat its own).
@@ -256,6 +338,7 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
     set_flush_f32();
     set_round_zero_f16();
     set_flush_out_f16();
+    if (RANGE != 0) set_round_zero();                          // of the FP32 sums; the bounds here have room for it
 
     HalfConst c;
     c.kc = as_h2(p.h_kc); c.rof = as_h2(p.h_rof); c.nrof = as_h2(p.h_rof ^ 0x80008000u); c.mask = p.h_mask_a; c.maskp = p.h_mask_p;
@@ -394,7 +477,7 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
     if (DEPTH > 1) fetch(DEPTH, 0);
     __syncthreads();
 
-    int beyond = -1, from = 0;                                 // the tile and its part at which the wave left the packed tile
+    int base = 0, beyond = -1, from = 0;                       // the tile a packed stretch starts at; the tile and its part where it ends
     // a lane's words of its rows (one per chain) as word `word` of a plane; non-temporal, see store_event_words
     uint32_t of2[S][TN] = {};
     auto store_words = [&](uint32_t* plane, int word, const uint32_t (&w)[S][TN]) {
@@ -438,7 +521,29 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
     };
     const uint32_t* const arow = Aw + g * T::PITCH;
     const uint32_t* const arowh = Aw + (8 + (lane >> 4)) * T::PITCH;       // the 4-row set: 16 lanes a row
-    for (int t0 = 0; t0 < ntiles; t0 += DEPTH) {
+    // C = S * 2^out_exp, zero written as +0
+    auto store = [&](int m, int n, auto sum, auto count) {
+        constexpr int CT = decltype(count)::value;
+        if (m >= p.M) return;
+        float v[CT];
+#pragma unroll
+        for (int j = 0; j < CT; ++j) v[j] = __builtin_ldexpf(sum(j), p.out_exp - 112) + 0.0f;    // -0 + 0 is +0
+        float* dst = pC + (int64_t)m * p.N + n;
+        if (CT % 4 == 0 && p.c_vec && n + CT - 1 < p.N) {
+#pragma unroll
+            for (int j = 0; j + 3 < CT; j += 4) *reinterpret_cast<f32x4_any*>(dst + j) = f32x4_any{v[j], v[j + 1], v[j + 2], v[j + 3]};
+        } else if (CT == 2 && p.c_vec && n + 1 < p.N) {
+            *reinterpret_cast<f32x2_any*>(dst) = f32x2_any{v[0], v[CT - 1]};
+        } else {
+#pragma unroll
+            for (int j = 0; j < CT; ++j)
+                if (n + j < p.N) dst[j] = v[j];
+        }
+    };
+    const int row0 = m0 + wave * RW + g, rowh = m0 + wave * RW + 8 + (lane >> 4);
+    const int col0 = n0 + tx * TN, colh = n0 + (lane & 15) * (TN / 2);
+    for (;;) {
+    for (int t0 = base; t0 < ntiles; t0 += DEPTH) {
 #pragma unroll
         for (int d = 0; d < DEPTH; ++d) {
             const int t = t0 + d;
@@ -540,71 +645,103 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
         if (RANGE != 0 && beyond >= 0) break;
     }
 
-    if (EVENTS && !p.C) return;
-    // C = S * 2^out_exp, zero written as +0
-    auto store = [&](int m, int n, auto sum, auto count) {
-        constexpr int CT = decltype(count)::value;
-        if (m >= p.M) return;
-        float v[CT];
+    if constexpr (RANGE == 0) {
+        break;
+    } else {
+        if (beyond < 0) break;
+        // a stretch in FP32
+        constexpr int HT = HALF ? TN / 2 : 2;
+        const BeyondConst w(p);
+        float sum[S][TN], tops[S][TN], sumh[1][HT], toph2[1][HT];
+        auto wide = [](const h2* s, int j) { return (float)(j & 1 ? s[j / 2].y : s[j / 2].x) * 0x1p-112f; };
 #pragma unroll
-        for (int j = 0; j < CT; ++j) v[j] = __builtin_ldexpf(sum(j), p.out_exp - 112) + 0.0f;    // -0 + 0 is +0
-        float* dst = pC + (int64_t)m * p.N + n;
-        if (CT % 4 == 0 && p.c_vec && n + CT - 1 < p.N) {
+        for (int i = 0; i < S; ++i)
 #pragma unroll
-            for (int j = 0; j + 3 < CT; j += 4) *reinterpret_cast<f32x4_any*>(dst + j) = f32x4_any{v[j], v[j + 1], v[j + 2], v[j + 3]};
-        } else if (CT == 2 && p.c_vec && n + 1 < p.N) {
-            *reinterpret_cast<f32x2_any*>(dst) = f32x2_any{v[0], v[CT - 1]};
-        } else {
+            for (int j = 0; j < TN; ++j) { sum[i][j] = wide(acc[i], j); tops[i][j] = wide(top[i], j); }
+        if constexpr (HALF) {
 #pragma unroll
-            for (int j = 0; j < CT; ++j)
-                if (n + j < p.N) dst[j] = v[j];
+            for (int j = 0; j < HT; ++j) { sumh[0][j] = wide(acch[0], j); toph2[0][j] = wide(toph[0], j); }
         }
-    };
-    const int row0 = m0 + wave * RW + g, rowh = m0 + wave * RW + 8 + (lane >> 4);
-    const int col0 = n0 + tx * TN, colh = n0 + (lane & 15) * (TN / 2);
-    if constexpr (RANGE != 0) {
-        if (beyond >= 0) {
-            set_round_zero();
-            BeyondConst w;
-            w.kc = (float)as_h2(p.h_kc).x; w.rof = p.rof_a; w.mask = p.mask_a; w.maskp = p.mask_p;
-            float sum[S][TN], tops[S][TN], sumh[TN / 2], toph2[TN / 2];
+        auto most = [&]() {
+            float m = 0.0f;
 #pragma unroll
             for (int i = 0; i < S; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    sum[i][j] = (float)(j & 1 ? acc[i][j / 2].y : acc[i][j / 2].x) * 0x1p-112f;
-                    tops[i][j] = (float)(j & 1 ? top[i][j / 2].y : top[i][j / 2].x) * 0x1p-112f;
-                }
+                for (int j = 0; j < TN; ++j) m = __builtin_fmaxf(m, __builtin_fabsf(ORDER == LBA_ORDER_CHUNK16 ? tops[i][j] : sum[i][j]));
             if constexpr (HALF) {
 #pragma unroll
-                for (int j = 0; j < TN / 2; ++j) {
-                    sumh[j] = (float)(j & 1 ? acch[0][j / 2].y : acch[0][j / 2].x) * 0x1p-112f;
-                    toph2[j] = (float)(j & 1 ? toph[0][j / 2].y : toph[0][j / 2].x) * 0x1p-112f;
+                for (int j = 0; j < HT; ++j) m = __builtin_fmaxf(m, __builtin_fabsf(ORDER == LBA_ORDER_CHUNK16 ? toph2[0][j] : sumh[0][j]));
+            }
+            return m;
+        };
+        int t = beyond, quiet = 0;                             // parts in which no sum reaches R_OF
+        float mx = most();
+        for (;;) {
+            fetch(t + 1, 0);
+            const int parts = p.K - t * HBK > 32 ? 2 : 1;
+            if (LISTS && listed) {
+                const char* const Bb = reinterpret_cast<const char*>(smem + tx * W);
+                const char* const Bh = reinterpret_cast<const char*>(smem + (lane & 15) * (W / 2));
+                const auto lists = [&](auto clamp) {
+                    constexpr bool CLAMP = decltype(clamp)::value != 0;
+                    beyond_list<PM, CLAMP, TN, U>(sum[0], arow, Bb, n_first, c, w);
+                    if constexpr (S == 2) beyond_list<PM, CLAMP, TN, U>(sum[1], arow + 8 * T::PITCH, Bb, n_second, c, w);
+                    if constexpr (HALF) beyond_list<PM, CLAMP, TN / 2, U>(sumh[0], arowh, Bh, n_second, c, w);
+                };
+                if (quiet < parts && __all(mx < p.fast_thresh4)) quiet = 4;
+                if (quiet >= parts) { quiet -= parts; lists(IntConst<0>{}); }
+                else                { quiet = 0; lists(IntConst<1>{}); }
+                mx = most();
+            } else {
+                for (int part = from; part < parts; ++part) {
+                    const uint32_t* const Bp = smem + (t & 1) * T::B_WORDS + part * 32 * T::BROW;
+                    const uint32_t* const Bs = Bp + tx * W;
+                    const uint32_t* const Bh = Bp + (lane & 15) * (W / 2);
+                    const auto tile = [&](auto clamp) {
+                        constexpr bool CLAMP = decltype(clamp)::value != 0;
+                        beyond_tile<PM, ORDER, CLAMP, SMALL, S, TN, T::BROW, T::PITCH>(sum, tops, arow + part * 16, Bs, c, w);
+                        if constexpr (HALF) beyond_tile<PM, ORDER, CLAMP, false, 1, TN / 2, T::BROW, T::PITCH>(sumh, toph2, arowh + part * 16, Bh, c, w);
+                    };
+                    if (quiet == 0) quiet = __all(mx < p.fast_thresh4) ? 4 : (__all(mx < p.fast_thresh) ? 1 : 0);
+                    if (quiet > 0) { --quiet; tile(IntConst<0>{}); }
+                    else           tile(IntConst<1>{});
+                    mx = most();
                 }
             }
-            const char* const Bb = reinterpret_cast<const char*>(smem + tx * W);
-            const char* const Bh = reinterpret_cast<const char*>(smem + (lane & 15) * (W / 2));
-#pragma unroll 1
-            for (int t = beyond; t < ntiles; ++t) {
-                // (a tile beyond K is never fetched here, so a wave's pieces are asked for and waited for one tile at a time)
-                const int k0 = t == beyond ? 32 * from : 0, n = p.K - t * HBK > 32 ? HBK - k0 : 32 - k0;
-                const uint32_t off = (uint32_t)((t & 1) * T::B_WORDS * 4 + k0 * T::BROW * 4);
+            from = 0;
+            const bool more = t + 1 < ntiles;
+            if (more) stage(t + 1, 0);
+            __syncthreads();                                   // (one a tile, as in the packed stretch of other waves)
+            ++t;
+            if (!more) {
 #pragma unroll
-                for (int i = 0; i < S; ++i)
-                    beyond_steps<PM, ORDER, TN, T::BROW>(sum[i], tops[i], arow + i * 8 * T::PITCH + (listed ? 0 : k0 / 2), listed, listed ? (i ? n_second : n_first) : n, Bb, off, w);
-                if constexpr (HALF) beyond_steps<PM, ORDER, TN / 2, T::BROW>(sumh, toph2, arowh + (listed ? 0 : k0 / 2), listed, listed ? n_second : n, Bh, off, w);
-                if (t + 1 < ntiles) {
-                    fetch(t + 1, 0);
-                    stage(t + 1, 0);
-                }
-                __syncthreads();
+                for (int i = 0; i < S; ++i) store(row0 + 8 * i, col0, [&](int j) { return (ORDER == LBA_ORDER_CHUNK16 ? tops[i][j] : sum[i][j]) * 0x1p112f; }, IntConst<TN>{});
+                if constexpr (HALF) store(rowh, colh, [&](int j) { return (ORDER == LBA_ORDER_CHUNK16 ? toph2[0][j] : sumh[0][j]) * 0x1p112f; }, IntConst<TN / 2>{});
+                return;
             }
+            safe_tiles = bound.safe(mx * 0x1p112f, nullptr);
+            if (safe_tiles >= 2) break;
+        }
+        // back: every sum is inside FP16's range and has at most 11 bits, at 2^-14 or above
+        auto narrow = [](float x, float y) { return __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(x * 0x1p112f, y * 0x1p112f)); };
 #pragma unroll
-            for (int i = 0; i < S; ++i) store(row0 + 8 * i, col0, [&](int j) { return (ORDER == LBA_ORDER_CHUNK16 ? tops[i][j] : sum[i][j]) * 0x1p112f; }, IntConst<TN>{});
-            if constexpr (HALF) store(rowh, colh, [&](int j) { return (ORDER == LBA_ORDER_CHUNK16 ? toph2[j] : sumh[j]) * 0x1p112f; }, IntConst<TN / 2>{});
-            return;
+        for (int i = 0; i < S; ++i)
+#pragma unroll
+            for (int j = 0; j < W; ++j) { acc[i][j] = narrow(sum[i][2 * j], sum[i][2 * j + 1]); top[i][j] = narrow(tops[i][2 * j], tops[i][2 * j + 1]); }
+        if constexpr (HALF) {
+#pragma unroll
+            for (int j = 0; j < HT / 2; ++j) { acch[0][j] = narrow(sumh[0][2 * j], sumh[0][2 * j + 1]); toph[0][j] = narrow(toph2[0][2 * j], toph2[0][2 * j + 1]); }
+        }
+        base = t;
+        beyond = -1;
+        if (DEPTH > 1) {                                       // the tiles ahead, in the slots the loop expects them in
+#pragma unroll
+            for (int d = 1; d <= DEPTH; ++d) fetch(base + d, d % DEPTH);
         }
     }
+    }
+
+    if (EVENTS && !p.C) return;
     auto value = [](const h2* s, int j) { return (float)(j & 1 ? s[j / 2].y : s[j / 2].x); };
 #pragma unroll
     for (int i = 0; i < S; ++i) store(row0 + 8 * i, col0, [&](int j) { return value(ORDER == LBA_ORDER_CHUNK16 ? top[i] : acc[i], j); }, IntConst<TN>{});

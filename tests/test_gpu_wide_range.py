@@ -59,6 +59,27 @@ def test_chains_around_the_range(ref, M, N, kernel, e, m):
         compare(ref, A, B, qp, qa, order, rows)
 
 
+# chains that leave the range and come back several times, at steps that differ by row and fall anywhere in a k-tile; a share of zeros
+# by group of rows, so that tiles are lists on one stretch or the other; E = 5 saturates in between
+@pytest.mark.parametrize("M,N", [(4160, 512), (12544, 256), (1000, 1024), (300, 500), (40, 70)])
+@pytest.mark.parametrize("e,m", [(5, 10), (6, 7)])
+def test_leaving_and_coming_back(ref, M, N, e, m):
+    rng = np.random.default_rng(M + e)
+    K = 787
+    qp, qa = (6, 7, 10, 0), (e, m, 6, 0)
+    A = codes(rng, (M, K), 12, 15, signs=False)
+    period = rng.integers(40, 400, -(-M // 8)).repeat(8)[:M, None]          # a wave's groups of 8 rows differ
+    down = (np.arange(K)[None, :] + rng.integers(0, 400, (M, 1))) % (2 * period) >= period
+    A = np.where(down, A | 0x80, A)
+    share = rng.choice([0.0, 0.5, 0.6, 0.9], (-(-M // 16), 1)).repeat(16, 0)[:M]
+    A = np.where(rng.random((M, K)) < share, 0, A).astype(np.uint8)
+    B = codes(rng, (N, K), 13, 15, signs=False)
+    B[1::7] = codes(rng, B[1::7].shape, 2, 8)
+    rows = None if M * N < 100000 else np.sort(rng.choice(M, 96, replace=False))
+    for order in (0, 1):
+        compare(ref, A, B, qp, qa, order, rows)
+
+
 # both sides of the admission line (64 of the largest products inside the range) and ragged K
 @pytest.mark.parametrize("K", [1, 31, 33, 64, 65, 147])
 def test_admission_line_and_k(ref, K):
