@@ -266,16 +266,21 @@ struct HalfBound {
     // grow: 32 of the largest products there are (thresh is rounded down; the factor covers the roundings here)
     __device__ __forceinline__ explicit HalfBound(const KParams& p)
         : rof(p.h_top), thresh(p.h_thresh), grow(1.0001f * (rof - thresh)), kcf((float)as_h2(p.h_kc).x) {}
-    // norms: half_stage's, for the current tile, or null; parts: of how many parts the bound that follows the data is asked
-    __device__ __forceinline__ int safe(float mf, const uint32_t* norms, int parts = 1) const {
-        if (__all(mf < thresh - 3.0f * grow)) return __all(mf < thresh - 7.0f * grow) ? 8 : 4;
-        if (__all(mf < thresh)) return __all(mf < thresh - grow) ? 2 : 1;
-        if (!norms) return 0;
-        // Cauchy-Schwarz: 16 products of a row's piece and a column's piece add at most the product of their norms; a part's 32
-        // steps are two pieces.  (The factor covers the roundings of the norms and of this line.)
+    // whether n steps from here cannot
+    __device__ __forceinline__ bool covers(float mf, int n) const { return __all(mf < rof - grow * ((float)n * 0x1p-5f)); }
+    // ... nor parts of the current tile, by half_stage's norms of its pieces.  Cauchy-Schwarz: 16 products of a row's piece and a column's
+    // piece add at most the product of their norms; a part's 32 steps are two pieces.  (The factor covers the roundings of the
+    // norms and of this line.)
+    __device__ __forceinline__ bool follows(float mf, const uint32_t* norms, int parts) const {
         const uint32_t m = pk_max_u16(pk_max_u16(norms[0], norms[1]), pk_max_u16(norms[2], norms[3]));
         const float n2 = __uint_as_float(m << 16) * __uint_as_float(m & 0xFFFF0000u);
-        return __all(mf < rof - (float)parts * 2.0f * 1.001f * __builtin_sqrtf(n2) * kcf) ? parts : 0;
+        return __all(mf < rof - (float)parts * 2.0f * 1.001f * __builtin_sqrtf(n2) * kcf);
+    }
+    // norms: or null
+    __device__ __forceinline__ int safe(float mf, const uint32_t* norms) const {
+        if (__all(mf < thresh - 3.0f * grow)) return __all(mf < thresh - 7.0f * grow) ? 8 : 4;
+        if (__all(mf < thresh)) return __all(mf < thresh - grow) ? 2 : 1;
+        return norms && follows(mf, norms, 1) ? 1 : 0;
     }
 };
 

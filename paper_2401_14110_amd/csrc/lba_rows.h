@@ -378,6 +378,22 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
             rb[d] = load_aligned(rowb, k0);
         }
     };
+    auto largest = [&]() {
+        uint32_t mx = 0u;
+#pragma unroll
+        for (int i = 0; i < S; ++i)
+#pragma unroll
+            for (int j = 0; j < W; ++j)
+                mx = pk_max_u16(mx, as_u32(ORDER == LBA_ORDER_CHUNK16 ? top[i][j] : acc[i][j]) & 0x7FFF7FFFu);
+        if (HALF) {
+#pragma unroll
+            for (int j = 0; j < TN / 4; ++j)
+                mx = pk_max_u16(mx, as_u32(ORDER == LBA_ORDER_CHUNK16 ? toph[0][j] : acch[0][j]) & 0x7FFF7FFFu);
+        }
+        return max_half(mx);
+    };
+    const HalfBound bound(p);
+    int safe_tiles = 0;
     // the tile in LDS: steps of the two row sets' lists, and whether they are lists
     int n_first = 0, n_second = 0;
     bool listed = false;
@@ -402,6 +418,18 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
         // a step of a list takes 9/8 of an unrolled one, and building and starting the lists 12 to 14 of them (8192 x 512 x 2304 by the
         // share of zeros: 104 us for none left, 3.0 us per step and row set; unrolled 2.7)
         if ((HALF ? n_first + n_second / 2 : n_first + n_second) * 9 + 110 > dense * 8) return false;
+        // A list runs with the clamp (or in FP32) unless the bound holds for all of its steps at once; where it does not but holds for the
+        // 32 steps of an unrolled part, the parts most often run without, one after the other, and a clamped list takes half as long
+        // again as one without (R_OF just above the sums, 50176 x 128 x 1152 behind a ReLU: 370 us with such lists, 263 so; 344
+        // before there were lists)
+        if (!EVENTS && !dyn && safe_tiles < 2) {
+            const float mf = largest();
+            safe_tiles = bound.safe(mf, nullptr);
+            if (safe_tiles < 2) {
+                if (bound.covers(mf, max(n_first, n_second))) safe_tiles = 2;
+                else if (safe_tiles > 0) return false;
+            }
+        }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         const uint32_t row_of_b = (uint32_t)((t & 1) * T::B_WORDS * 4 + lane * T::BROW * 4) << 16;
         const uint32_t last = 63u - (uint32_t)lane;
@@ -415,22 +443,6 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
         }
         return true;
     };
-                auto largest = [&]() {
-                    uint32_t mx = 0u;
-#pragma unroll
-                    for (int i = 0; i < S; ++i)
-#pragma unroll
-                        for (int j = 0; j < W; ++j)
-                            mx = pk_max_u16(mx, as_u32(ORDER == LBA_ORDER_CHUNK16 ? top[i][j] : acc[i][j]) & 0x7FFF7FFFu);
-                    if (HALF) {
-#pragma unroll
-                        for (int j = 0; j < TN / 4; ++j)
-                            mx = pk_max_u16(mx, as_u32(ORDER == LBA_ORDER_CHUNK16 ? toph[0][j] : acch[0][j]) & 0x7FFF7FFFu);
-                    }
-                    return max_half(mx);
-                };
-    const HalfBound bound(p);
-    int safe_tiles = 0;
     auto stage = [&](int t, int d) {
         uint4 va = !PIECES ? ra[d] : (conv ? sc.codes(p, ra[d], rc[d], t * HBK) : sa.codes(ra[d], t * HBK));
         uint4 vb = PIECES ? sb.codes(rb[d], t * HBK) : rb[d];
@@ -552,7 +564,11 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
             if (DEPTH == 1) fetch(t + 1, 0);
             const int parts = p.K - t * HBK > 32 ? 2 : 1;      // steps beyond K are products of zeros: skipped 32 at a time
             if (LISTS && listed) {
-                if (safe_tiles < parts) safe_tiles = bound.safe(largest(), dyn ? half_norm[t & 1] : nullptr, parts);
+                if (safe_tiles < parts && dyn) {
+                    const float mf = largest();
+                    safe_tiles = bound.safe(mf, nullptr);
+                    if (safe_tiles < parts) safe_tiles = bound.follows(mf, half_norm[t & 1], parts) ? parts : 0;
+                }
                 const char* const Bb = reinterpret_cast<const char*>(smem + tx * W);
                 const char* const Bh = reinterpret_cast<const char*>(smem + (lane & 15) * (W / 2));
                 if constexpr (EVENTS) {
@@ -578,7 +594,7 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
                     const uint32_t* const Bp = smem + (t & 1) * T::B_WORDS + part * 32 * T::BROW;
                     const uint32_t* const Bs = Bp + tx * W;
                     const uint32_t* const Bh = Bp + (lane & 15) * (W / 2);
-                    if (safe_tiles == 0) safe_tiles = bound.safe(largest(), dyn ? half_norm[t & 1] : nullptr, 1);
+                    if (safe_tiles == 0) safe_tiles = bound.safe(largest(), dyn ? half_norm[t & 1] : nullptr);
                     const int word = 2 * t + part;             // of the planes
                     if (safe_tiles > 0) {
                         --safe_tiles;

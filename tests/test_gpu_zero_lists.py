@@ -74,6 +74,24 @@ def test_list_lengths(ref, order):
     assert np.array_equal(got.view(np.uint32), np.ascontiguousarray(want).view(np.uint32))
 
 
+# chains that drift towards R_OF at different paces (columns of one sign and of both) behind half of zeros: lists the fixed bound covers, tiles
+# left unrolled because it covers one part only, clamped lists, and the bound that follows the data (R_OF by the last format's bias)
+@pytest.mark.parametrize("M,N", [(4160, 512), (3136, 512), (1000, 333)])
+@pytest.mark.parametrize("ba", [-6, -5, -4, -3, -2, 0])
+def test_lists_near_the_bound(ref, M, N, ba):
+    rng = np.random.default_rng(M + ba + 10)
+    K = 1100
+    A = ((rng.integers(9, 15, (M, K)) << 3) | rng.integers(0, 8, (M, K))).astype(np.uint8)
+    A = np.where(rng.random((M, K)) < rng.choice([0.5, 0.55, 0.8], (M, 1)), 0, A).astype(np.uint8)
+    B = ((rng.integers(7, 13, (N, K)) << 3) | rng.integers(0, 8, (N, K))).astype(np.uint8)
+    B = np.where(rng.random((N, K)) < rng.choice([0.0, 0.4, 0.5, 0.5], (N, 1)), B | 0x80, B).astype(np.uint8)
+    rows = np.sort(rng.choice(M, 64, replace=False))
+    qp, qa = (5, 7, 4, 0), (4, 7, ba, 0)
+    got = binding.gemm(torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda(), qp, qa).cpu().numpy()[rows]
+    want = ref.gemm(np.ascontiguousarray(A[rows]), B, ref.QFmt(*qp), ref.QFmt(*qa))
+    assert np.array_equal(got.view(np.uint32), np.ascontiguousarray(want).view(np.uint32))
+
+
 # im2col rows: zeros of the image, and whole taps outside it under a wide padding
 @pytest.mark.parametrize("c,pad", [(16, 1), (48, 4), (20, 2)])
 def test_convolutions(ref, c, pad):
