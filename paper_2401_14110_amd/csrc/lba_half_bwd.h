@@ -12,14 +12,14 @@
 //         the two events, so one minimum and one add put "no event" into bit 15.  Steps with a zero operand are cleared
 //         afterwards, a word at a time, from per-row masks of non-zero codes left by the staging.
 //   Bit 15 of both halves enters a shift register from the top: after 16 steps bit j of each half is step j.
-// A k-tile in which no sum can reach R_OF (HalfBound) has no overflow test, and no underflow plane asked for it is the
-// forward tile.
+// A k-tile in which no sum can reach R_OF (HalfBound) has no overflow test.  Without an underflow plane such a tile is the forward call's
+// (rows_body, lba_rows.h), and half_bwd_tile runs the others.
 //
 // What bounds it: VALU issue, nine instructions for two chains with the underflow plane and a quiet tile (7 of them at half
 // rate: 18.4 cycles per chain and step by the issue-rate probe).  The FP32 kernel (compares to 64-bit masks, scalar logic, one
 // carry-in add per chain and plane) takes 27.  Measured against it, both planes of 4096 x 768 x 3072: 1703 -> 1396 us (22.7
-// cycles; 2.4 GB of planes leave at 1.7 TB/s); the overflow plane alone of 12544 x 256 x 2304: 533 -> 440 us.  Reading
-// operands a step ahead, or two waves per SIMD instead of three for the underflow plane, changed nothing.
+// cycles; 2.4 GB of planes leave at 1.7 TB/s), with turns (lba_device.h) 1240.  Reading
+// operands a step ahead, or two waves per SIMD instead of three, changed nothing.
 #ifndef LBA_HALF_BWD_H_
 #define LBA_HALF_BWD_H_
 
@@ -116,8 +116,8 @@ __device__ __forceinline__ void half_bwd_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[T
                 __builtin_amdgcn_sched_barrier(0);
                 issue_last<PRIO>();
                 _Pragma("unroll") LBA_EACH acc[i][j] = as_h2(t[i][j] & c.mask);
-                if (!QUIET) { _Pragma("unroll") LBA_EACH wo[i][j] >>= 1; }
-                if (UF) { _Pragma("unroll") LBA_EACH wu[i][j] >>= 1; }
+                if (PRIO && !QUIET) { _Pragma("unroll") LBA_EACH wo[i][j] >>= 1; }   // full-rate as well
+                if (PRIO && UF) { _Pragma("unroll") LBA_EACH wu[i][j] >>= 1; }
                 __builtin_amdgcn_sched_barrier(0);
                 issue_first<PRIO>();
                 if (!QUIET) {
@@ -127,7 +127,7 @@ __device__ __forceinline__ void half_bwd_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[T
                     uint32_t y[TM][NJ];
                     _Pragma("unroll") LBA_EACH y[i][j] = pk_add_u16(t[i][j] & c.absmask, c.of_bias);
                     __builtin_amdgcn_sched_barrier(0);
-                    _Pragma("unroll") LBA_EACH wo[i][j] = pk_shift_in(wo[i][j], y[i][j], c.bit15);
+                    _Pragma("unroll") LBA_EACH wo[i][j] = pk_shift_in(PRIO ? wo[i][j] : wo[i][j] >> 1, y[i][j], c.bit15);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 if (UF) {
@@ -138,7 +138,7 @@ __device__ __forceinline__ void half_bwd_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[T
                     __builtin_amdgcn_sched_barrier(0);
                     _Pragma("unroll") LBA_EACH t[i][j] = pk_add_u16_sat(t[i][j], c.uf_bias);
                     __builtin_amdgcn_sched_barrier(0);
-                    _Pragma("unroll") LBA_EACH wu[i][j] = pk_shift_in(wu[i][j], t[i][j], c.bit15);
+                    _Pragma("unroll") LBA_EACH wu[i][j] = pk_shift_in(PRIO ? wu[i][j] : wu[i][j] >> 1, t[i][j], c.bit15);
                     __builtin_amdgcn_sched_barrier(0);
                 }
 #undef LBA_EACH
@@ -222,8 +222,8 @@ __device__ __forceinline__ void mark_bricks_lsb(const uint32_t (&of)[TM][TN], in
     mark_bricks_of_wave<TM, TN>(any, m0, n0, w, tx, ty, p);
 }
 
-// The recompute call with an underflow plane (without one: rows_body, lba_rows.h).
-template <int TM, int TN, int PM, int ORDER, int AMODE>
+// The recompute call with an underflow plane (without one: rows_body, lba_rows.h).  TURNS: not where a wave has its SIMD to itself.
+template <int TM, int TN, int PM, int ORDER, int AMODE, bool TURNS = (TM * TN > 4)>
 __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __restrict__ smem, int m0, int n0) {
     using T = HalfTile<TM, TN, 16>;
     constexpr int BM = T::BM, BN = T::BN, NJ = TN / 2;
@@ -235,8 +235,6 @@ __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __rest
     set_round_zero_f16();
     set_flush_out_f16();
 
-    constexpr bool TURNS = TM * TN > 4;
-    const bool turns = gridDim.x * gridDim.y > 256;           // a lone wave per SIMD has nobody to wait for (128 x 192 x 656 144 -> 139 us)
     const HalfBwdConst c(p);
     h2 acc[TM][NJ], top[TM][NJ];
     uint32_t of2[TM][TN], uf2[TM][TN];
@@ -311,11 +309,9 @@ __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __rest
             const bool quiet = safe_tiles > 0;
             if (quiet) {
                 --safe_tiles;
-                if (TURNS && turns) half_bwd_tile<PM, ORDER, true, true, TM, TN, TURNS>(acc, top, of, uf, of2, uf2, pos, read_a, read_b, c);
-                else                half_bwd_tile<PM, ORDER, true, true, TM, TN, false>(acc, top, of, uf, of2, uf2, pos, read_a, read_b, c);
+                half_bwd_tile<PM, ORDER, true, true, TM, TN, TURNS>(acc, top, of, uf, of2, uf2, pos, read_a, read_b, c);
             } else {
-                if (TURNS && turns) half_bwd_tile<PM, ORDER, true, false, TM, TN, TURNS>(acc, top, of, uf, of2, uf2, pos, read_a, read_b, c);
-                else                half_bwd_tile<PM, ORDER, true, false, TM, TN, false>(acc, top, of, uf, of2, uf2, pos, read_a, read_b, c);
+                half_bwd_tile<PM, ORDER, true, false, TM, TN, TURNS>(acc, top, of, uf, of2, uf2, pos, read_a, read_b, c);
                 const int valid = p.K - 32 * w;                // a saturated sum stays at R_OF beyond K
                 if (valid < 32) {
 #pragma unroll

@@ -6,8 +6,8 @@ namespace lba {
 
 // The grids of lba_fast_bwd_kernel and lba_fast_bwd_mixed_kernel.  With an underflow plane AMODE 0: a row-major matrix of any code format
 // with E <= 4, 2: im2col rows of an NHWC tensor; without one as lba_half_kernel.
-// Chunks without an underflow plane: at four waves per SIMD 33 registers are spilled, which 3985 x 770 x 771 hides (training step 648 us
-// against 665 at three) and grids of a few tiles do not (704 x 96 x 1616 259 against 240, 1523 x 34 x 2830 475 against 416).
+// Chunks without an underflow plane: at four waves per SIMD 33 registers are spilled, which 819 workgroups and more hide (3985 x 770 x 771,
+// training step 648 us against 662 at three) and 257 to 768 do not (24576 x 64 x 1024 114 against 109).
 template <int PM, int ORDER, bool UF, int AMODE>
 __global__ void __launch_bounds__(256, ORDER == LBA_ORDER_CHUNK16 && UF ? 2 : UF || ORDER == LBA_ORDER_CHUNK16 ? 3 : 4) lba_half_bwd_kernel(const KParams p) {
     __shared__ __attribute__((aligned(16))) uint32_t smem[UF ? 2 * HalfTile<4, 4, 16>::STAGE : RowTile<16, 8>::WORDS];

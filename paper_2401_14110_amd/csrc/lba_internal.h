@@ -90,6 +90,7 @@ struct Plan {
     int kpar;                // > 0 (chunked order, forward): lba_kpar_kernel; 1: 32 x 32 outputs per workgroup and 4 chunks in flight,
                              // 3: 8 x 16 outputs and 16 chunks
     int staged;              // 1: lba_half_staged_kernel, _conv_kernel, lba_fast_staged_kernel: the smallest grids, waves of their own that stage
+    int alone;               // 1: on packed FP16 carriers, a wave of the large tiles has its SIMD to itself (lba_half_alone.hip)
     int amode;               // 1: A is read as im2col rows and / or an operand is not E4M3 (4 x 4 lane block only);
                              // 2: A is read as im2col rows, E4M3 operands, forward call (any lane block, mixed grids)
     KParams kp;

@@ -19,9 +19,10 @@ __global__ void lba_fill_zero_kernel(float* C, int64_t n) {
 static hipError_t launch_plan(const Plan& pl, hipStream_t st) {
     if (pl.kernel == KERNEL_FAST && pl.kpar > 0) return launch_kpar(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.events == 2) return launch_fast_diff(pl, st);
-    if (pl.kernel == KERNEL_FAST && pl.events && pl.kp.h_on) return launch_half_bwd(pl, st);
+    if (pl.kernel == KERNEL_FAST && pl.events && pl.kp.h_on) return pl.alone ? launch_half_bwd_alone(pl, st) : launch_half_bwd(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.events) return launch_fast_bwd(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.kp.h_on && pl.kp.h_range) return pl.kp.conv ? launch_wide_conv(pl, st) : launch_wide(pl, st);
+    if (pl.kernel == KERNEL_FAST && pl.kp.h_on && pl.alone) return launch_half_alone(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.kp.h_on) return pl.kp.conv ? launch_half_conv(pl, st) : launch_half(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.staged) return launch_fast_staged(pl, st);
     if (pl.kernel == KERNEL_FAST && pl.rne_odd) return launch_fast_odd(pl, st);
@@ -56,8 +57,9 @@ static void plan_kernel_name(const Plan& pl, bool uf, char* buf, size_t n) {
         snprintf(buf, n, pl.mix_tail > 0 ? "lba_fast_diff_mixed_kernel<%d, %d, %d>" : "lba_fast_diff_kernel<%d, %d, %d>", pm, pl.round, ord);
     } else if (pl.events && pl.kp.h_on) {
         const int am = (pl.kp.conv || pl.amode == 2 ? 2 : 0) + (uf || pl.kp.K % 16 == 0 ? 0 : (pl.kp.conv || pl.amode == 2 ? 2 : 3));   // (operands on a 16-byte boundary)
-        if (pl.mix_tail > 0) snprintf(buf, n, "lba_half_bwd_mixed_kernel<%d, %s, %d>", pm, uf ? "true" : "false", am);
-        else                 snprintf(buf, n, "lba_half_bwd_kernel<%d, %d, %s, %d>", pm, ord, uf ? "true" : "false", am);
+        if (pl.alone)             snprintf(buf, n, "lba_half_bwd_alone_kernel<%d, %d, %s, %d>", pm, ord, uf ? "true" : "false", am);
+        else if (pl.mix_tail > 0) snprintf(buf, n, "lba_half_bwd_mixed_kernel<%d, %s, %d>", pm, uf ? "true" : "false", am);
+        else                      snprintf(buf, n, "lba_half_bwd_kernel<%d, %d, %s, %d>", pm, ord, uf ? "true" : "false", am);
     } else if (pl.events) {
         if (pl.amode == 2 && pl.mix_tail > 0) snprintf(buf, n, "lba_fast_bwd_conv_mixed_kernel<%d, 0, %s>", pm, b);
         else if (pl.amode == 2)   snprintf(buf, n, "lba_fast_bwd_kernel<%d, 0, 0, %s, 2>", pm, b);
@@ -70,6 +72,8 @@ static void plan_kernel_name(const Plan& pl, bool uf, char* buf, size_t n) {
         if (pl.kp.h_range && pl.mix_tail > 0) snprintf(buf, n, "lba_wide_mixed_kernel<%d, %d, %d>", ord, am, pl.kp.h_range);
         else if (pl.kp.h_range)   snprintf(buf, n, "lba_wide_kernel<%d, %d, %d, %d, %d>", pl.tm, pl.tn, ord, am, pl.kp.h_range);
         else if (pl.staged)       snprintf(buf, n, "lba_half_staged_kernel<%d, %d>", pl.mix_tail > 0 ? 2 : 4, pm);
+        else if (pl.alone && pl.mix_tail > 0) snprintf(buf, n, "lba_half_alone_mixed_kernel<%d, %d, %d>", pm, ord, am);
+        else if (pl.alone)        snprintf(buf, n, "lba_half_alone_kernel<%d, %d, %d>", pm, ord, am);
         else if (pl.mix_tail > 0) snprintf(buf, n, "lba_half_mixed_kernel<%d, %d, %d>", pm, ord, am);
         else                 snprintf(buf, n, "lba_half_kernel<%d, %d, %d, %d, %d>", pl.tm, pl.tn, pm, ord, am);
     } else if (pl.staged) {

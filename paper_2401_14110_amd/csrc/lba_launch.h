@@ -34,6 +34,8 @@ hipError_t launch_wide(const Plan& pl, hipStream_t st);            // the same, 
 hipError_t launch_wide_conv(const Plan& pl, hipStream_t st);
 hipError_t launch_fast_staged(const Plan& pl, hipStream_t st);     // forward, nearest-even, the smallest grids (staged, not kp.h_on)
 hipError_t launch_half_bwd(const Plan& pl, hipStream_t st);        // plans with events == 1 on packed FP16 carriers (kp.h_on)
+hipError_t launch_half_alone(const Plan& pl, hipStream_t st);      // plans of either kind on packed FP16 carriers that are alone
+hipError_t launch_half_bwd_alone(const Plan& pl, hipStream_t st);
 // the DIFF plane, scaled-domain kernel (plans with events == 2)
 hipError_t launch_fast_diff(const Plan& pl, hipStream_t st);
 // general kernel (forward and recompute)

@@ -545,6 +545,12 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
     const bool rne32 = p.kernel == KERNEL_FAST && !kp.h_on && qa.round == LBA_ROUND_RNE && !p.rne_odd && p.amode == 0 && N * K >= 16 && M * K >= 16 && K <= kPieceMaxK;
     p.staged = ((kp.h_on && !kp.h_range) || rne32) && !p.events && order == LBA_ORDER_SEQ && (p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH) &&
                (p.mix_tail > 0 ? kp.mix_tail16 && kp.mix_main + kp.mix_half == 0 : p.tm == 2 && p.tn == 2);
+    // Waves alone on their SIMDs (lba_half_alone.hip, which has the figures): at most one workgroup of 64 x 64 per CU (only the recompute call
+    // and truncated products have so few: pick_tile), or one of 48 x 64 with fewer of the tail's 32 x 32 behind them than there are CUs
+    const int64_t total = (int64_t)p.grid_x * p.grid_y * std::max<int64_t>(batch, 1);
+    p.alone = kp.h_on && !kp.h_range && p.kpar == 0 && !p.staged &&
+              (p.mix_tail > 0 ? !p.events && p.prod_mode == PM_FLUSH && kp.mix_main == 0 && kp.mix_half > 0 && total < 512
+                              : p.tm == 4 && p.tn == 4 && total <= 256 && (p.events || (p.prod_mode == PM_TRUNC && !conv)));
     *out = p;
     return LBA_OK;
 }

@@ -13,7 +13,8 @@
 // Waves take turns by the rate of their instructions.  A full-rate instruction (the mask) issues in half the time of a packed
 // one only when another wave has one too; with waves at random places of their steps it mostly has no partner and takes as long.
 // Packed instructions run at priority 1 and the masks at priority 0, so waves gather at their masks (issue-rate probe: 12.1 ->
-// 10.9 cycles per register and step).  A lone wave per SIMD (the smallest tiles) has nobody to wait for and keeps one priority.
+// 10.9 cycles per register and step).  A lone wave per SIMD (the smallest tiles, lba_half_alone.hip) has nobody to wait for and keeps one
+// priority.
 //
 // Measured (us), 16 chains per lane in 4 x 4 blocks / rows without lists / with; no zeros, then half of A's codes zero:
 //   8192 x 512 x 2304    447 -> 394,  447 -> 394 -> 329
@@ -95,10 +96,10 @@ __device__ __forceinline__ void list_steps(h2 (&sums)[T / 2], ListHead<U>& h, co
 
 // 32 steps (16 pairs) of S sets of rows, fully unrolled, TN columns a lane.  arow: the lane's row of the first set (the next
 // set's 8 rows on); Bs: the lane's words of the first step, BROW words a step.
-template <int PM, int ORDER, bool CLAMP, bool MASK, bool LONE, int S, int TN, int BROW, int PITCH>
+template <int PM, int ORDER, bool CLAMP, bool MASK, bool LONE, int AHEAD, int S, int TN, int BROW, int PITCH>
 __device__ __forceinline__ void rows_tile(h2 (&acc)[S][TN / 2], h2 (&top)[S][TN / 2], const uint32_t* arow, const uint32_t* Bs, const HalfConst& c) {
     constexpr int W = TN / 2;
-    constexpr int AHEAD = S * TN >= 12 ? 1 : (S * TN >= 8 ? 2 : 4), SLOTS = AHEAD + 2;
+    constexpr int SLOTS = AHEAD + 2;
     constexpr bool EARLY = LONE;
     uint32_t a[S][16], b0[SLOTS][W], b1[SLOTS][W];
     h2 q[2][S][W];
@@ -320,7 +321,8 @@ __device__ __forceinline__ void beyond_list(float (&sums)[T], const uint32_t* li
 // EVENTS: the recompute call for the overflow plane alone (RANGE 0, no set of four rows): a part of a tile in which no sum can reach R_OF
 // is the forward call's and its words are zero; any other runs half_bwd_tile.  A tile becomes lists only where the fixed bound covers it,
 // since the steps a list leaves out have no event there (a saturated sum would repeat its own).
-template <int RW, int TN, int PM, int ORDER, int AMODE, int RANGE, bool EVENTS = false>
+// ALONE: a wave has its SIMD to itself (lba_half_alone.hip): no turns, no lists, operands read further ahead.
+template <int RW, int TN, int PM, int ORDER, int AMODE, int RANGE, bool EVENTS = false, bool ALONE = false>
 __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict__ smem, int m0, int n0) {
     using T = RowTile<RW, TN>;
     constexpr int BM = T::BM, BN = T::BN, S = T::SETS, W = TN / 2, U = T::U;
@@ -356,7 +358,8 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
     const int ntiles = (p.K + HBK - 1) / HBK;
     __shared__ uint32_t half_norm[2][4];                       // per stage and wave: largest squared norm of a piece of A (low half), of B
     const bool dyn = half_follows_data(p);
-    constexpr bool SMALL = S * TN <= 4, LISTS = ORDER == LBA_ORDER_SEQ && !SMALL, PIECES = SMALL || AMODE >= 3;
+    constexpr bool SMALL = S * TN <= 4, LONE = SMALL || ALONE, LISTS = ORDER == LBA_ORDER_SEQ && !LONE, PIECES = SMALL || AMODE >= 3;
+    constexpr int AHEAD = LONE ? 4 : (S * TN >= 12 ? 1 : 2);   // pairs of steps whose operands are read ahead
     constexpr bool conv = AMODE == 2 || AMODE == 4;
     const RowPieces<BM> sa(pA, conv ? 1 : p.M, p.K, conv ? 0 : m0, ca);
     const RowPieces<BN> sb(pB, p.N, p.K, n0, tidb);
@@ -516,7 +519,7 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
         constexpr int LANES = BN / 4, ROWS = 64 / LANES;
         if (!p.of_mask) return;
         int l = lane;
-        asm volatile("" : "+v"(l));                          // addresses made here, not kept in registers over the loop
+        if (!ALONE) asm volatile("" : "+v"(l));              // addresses made here, not kept in registers over the loop
 #pragma unroll
         for (int i = 0; i < RW; i += ROWS) {
             const int m = m0 + wave * RW + i + l / LANES, n = n0 + l % LANES * 4;
@@ -599,8 +602,8 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
                     if (safe_tiles > 0) {
                         --safe_tiles;
                         if constexpr (EVENTS) store_no_events(word);
-                        rows_tile<PM, ORDER, false, MASK, SMALL, S, TN, T::BROW, T::PITCH>(acc, top, arow + part * 16, Bs, c);
-                        if constexpr (HALF) rows_tile<PM, ORDER, false, MASK, false, 1, TN / 2, T::BROW, T::PITCH>(acch, toph, arowh + part * 16, Bh, c);
+                        rows_tile<PM, ORDER, false, MASK, LONE, AHEAD, S, TN, T::BROW, T::PITCH>(acc, top, arow + part * 16, Bs, c);
+                        if constexpr (HALF) rows_tile<PM, ORDER, false, MASK, ALONE, ALONE ? 4 : (TN / 2 >= 8 ? 2 : 4), 1, TN / 2, T::BROW, T::PITCH>(acch, toph, arowh + part * 16, Bh, c);
                     } else if constexpr (EVENTS) {
                         const HalfBwdConst cb(p);
                         uint32_t of[S][TN], none[S][TN], none2[S][TN];
@@ -608,7 +611,7 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
                         for (int i = 0; i < S; ++i)
 #pragma unroll
                             for (int j = 0; j < TN; ++j) { of[i][j] = 0u; none[i][j] = 0u; none2[i][j] = 0u; }
-                        half_bwd_tile<PM, ORDER, false, false, S, TN, (S * TN > 4)>(acc, top, of, none, of2, none2, 2 * (word & 15),
+                        half_bwd_tile<PM, ORDER, false, false, S, TN, !LONE>(acc, top, of, none, of2, none2, 2 * (word & 15),
                             [&](int k, uint32_t (&a)[S]) {
 #pragma unroll
                                 for (int i = 0; i < S; ++i) a[i] = arow[i * 8 * T::PITCH + part * 16 + k];
@@ -628,8 +631,8 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
                         from = part;
                         break;
                     } else {
-                        rows_tile<PM, ORDER, true, MASK, SMALL, S, TN, T::BROW, T::PITCH>(acc, top, arow + part * 16, Bs, c);
-                        if constexpr (HALF) rows_tile<PM, ORDER, true, MASK, false, 1, TN / 2, T::BROW, T::PITCH>(acch, toph, arowh + part * 16, Bh, c);
+                        rows_tile<PM, ORDER, true, MASK, LONE, AHEAD, S, TN, T::BROW, T::PITCH>(acc, top, arow + part * 16, Bs, c);
+                        if constexpr (HALF) rows_tile<PM, ORDER, true, MASK, ALONE, ALONE ? 4 : (TN / 2 >= 8 ? 2 : 4), 1, TN / 2, T::BROW, T::PITCH>(acch, toph, arowh + part * 16, Bh, c);
                     }
                 }
                 if (RANGE != 0 && beyond >= 0) break;
@@ -984,17 +987,17 @@ __device__ __forceinline__ void rows_plain(const KParams& p) {
     __shared__ __attribute__((aligned(16))) uint32_t smem[RowTile<RW, TR>::WORDS];
     rows_body<RW, TR, PM, ORDER, AMODE, RANGE>(p, smem, blockIdx.x * 16 * TM, blockIdx.y * 16 * TN);
 }
-template <int PM, int ORDER, int AMODE, int RANGE>
+template <int PM, int ORDER, int AMODE, int RANGE, bool ALONE = false>
 __device__ __forceinline__ void rows_mixed(const KParams& p) {
     __shared__ __attribute__((aligned(16))) uint32_t smem[RowTile<16, 8>::WORDS];
     const int b = blockIdx.x;
     if (b < p.mix_main) {                                      // uniform
         const int by = b / p.mix_gx_main, bx = b - by * p.mix_gx_main;
-        rows_body<16, 8, PM, ORDER, AMODE, RANGE>(p, smem, bx * 64, by * 64);
+        rows_body<16, 8, PM, ORDER, AMODE, RANGE, false, ALONE>(p, smem, bx * 64, by * 64);
     } else if (b < p.mix_main + p.mix_half) {
         const int t = b - p.mix_main;
         const int by = t / p.mix_gx_half, bx = t - by * p.mix_gx_half;
-        rows_body<12, 8, PM, ORDER, AMODE, RANGE>(p, smem, p.mix_m_main + bx * 48, by * 64);
+        rows_body<12, 8, PM, ORDER, AMODE, RANGE, false, ALONE>(p, smem, p.mix_m_main + bx * 48, by * 64);
     } else {
         const int t = b - p.mix_main - p.mix_half;
         const int by = t / p.mix_gx_tail, bx = t - by * p.mix_gx_tail;
