@@ -18,7 +18,7 @@
 // What bounds it: VALU issue, nine instructions for two chains with the underflow plane and a quiet tile (7 of them at half
 // rate: 18.4 cycles per chain and step by the issue-rate probe).  The FP32 kernel (compares to 64-bit masks, scalar logic, one
 // carry-in add per chain and plane) takes 27.  Measured against it, both planes of 4096 x 768 x 3072: 1703 -> 1396 us (22.7
-// cycles; 2.4 GB of planes leave at 1.7 TB/s), with turns (lba_device.h) 1240.  Reading
+// cycles; 2.4 GB of planes leave at 1.7 TB/s), with turns (lba_device.h) 1229, with the 32 steps unrolled 1210 (by four 1240).  Reading
 // operands a step ahead, or two waves per SIMD instead of three, changed nothing.
 #ifndef LBA_HALF_BWD_H_
 #define LBA_HALF_BWD_H_
@@ -81,7 +81,7 @@ __device__ __forceinline__ void half_bwd_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[T
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < NJ; ++j) { wo[i][j] = 0u; wu[i][j] = 0u; }
-#pragma unroll 2
+#pragma unroll
         for (int s = 0; s < 8; ++s) {
             uint32_t a[TM], b[2][NJ];
             read_a(8 * h + s, a);
