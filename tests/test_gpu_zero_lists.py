@@ -56,7 +56,7 @@ def test_shares_of_zeros(ref, M, N, K, qp, qa):
 
 
 # lists of every length, the full 64 and none among them, alone in a row set and next to others; zeros by columns, so that tiles
-# with and without lists alternate along K
+# with and without lists alternate along K (the sequential order; the chunked one has no lists and runs the same codes unrolled)
 @pytest.mark.parametrize("order", [0, 1])
 def test_list_lengths(ref, order):
     rng = np.random.default_rng(5)
