@@ -4,15 +4,31 @@
 
 namespace lba {
 
+// (truncated products come on the 4 x 4 lane block and mixed grids only, the 2 x 2 one of the sequential order has waves that stage)
 template <int PM, int ORDER, int AMODE>
 static hipError_t launch_one(const Plan& pl, hipStream_t st) {
     const dim3 grid(pl.grid_x, pl.grid_y, pl.kp.batch), block(256);
-    if (pl.mix_tail > 0)                    hipLaunchKernelGGL((lba_half_mixed_kernel<PM, ORDER, AMODE>), grid, block, 0, st, pl.kp);
-    else if (pl.tm == 4 && pl.tn == 4)      hipLaunchKernelGGL((lba_half_kernel<4, 4, PM, ORDER, AMODE>), grid, block, 0, st, pl.kp);
-    else if (pl.tm == 2 && pl.tn == 4)      hipLaunchKernelGGL((lba_half_kernel<2, 4, PM, ORDER, AMODE>), grid, block, 0, st, pl.kp);
-    else if (pl.tm == 2 && pl.tn == 2)      hipLaunchKernelGGL((lba_half_kernel<2, 2, PM, ORDER, AMODE>), grid, block, 0, st, pl.kp);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
+    if (pl.mix_tail > 0) {
+        hipLaunchKernelGGL((lba_half_mixed_kernel<PM, ORDER, AMODE>), grid, block, 0, st, pl.kp);
+        return hipGetLastError();
+    }
+    if (pl.tm == 4 && pl.tn == 4) {
+        hipLaunchKernelGGL((lba_half_kernel<4, 4, PM, ORDER, AMODE>), grid, block, 0, st, pl.kp);
+        return hipGetLastError();
+    }
+    if constexpr (PM != PM_TRUNC) {
+        if (pl.tm == 2 && pl.tn == 4) {
+            hipLaunchKernelGGL((lba_half_kernel<2, 4, PM, ORDER, AMODE>), grid, block, 0, st, pl.kp);
+            return hipGetLastError();
+        }
+        if constexpr (ORDER == LBA_ORDER_CHUNK16) {
+            if (pl.tm == 2 && pl.tn == 2) {
+                hipLaunchKernelGGL((lba_half_kernel<2, 2, PM, ORDER, AMODE>), grid, block, 0, st, pl.kp);
+                return hipGetLastError();
+            }
+        }
+    }
+    return hipErrorInvalidValue;
 }
 
 template <int ORDER, int AMODE>
