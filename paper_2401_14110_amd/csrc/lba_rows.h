@@ -367,14 +367,15 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
     ConvLane cl = {};
     if (PIECES && conv) sc = ConvPieces::make<BM>(pA, p, m0, ca);
     if (!PIECES && AMODE == 2) cl = conv_lane<BM, HBK>(pA, p, m0, ca);
-    constexpr int DEPTH = EVENTS ? 1 : half_depth(S, TN);
+    constexpr int DEPTH = EVENTS ? 1 : AMODE == 4 && SMALL ? 2 : half_depth(S, TN);   // (two loads a piece: fewer tiles in flight)
     uint4 ra[DEPTH], rc[DEPTH], rb[DEPTH];
     const AlignedRow rowa(pA, conv ? 1 : p.M, p.K, conv ? 0 : m0 + ca % BM, ca >= 0 ? ca / BM * 16 : 0), rowb(pB, p.N, p.K, n0 + tidb % BN, tidb >= 0 ? tidb / BN * 16 : 0);
     auto fetch = [&](int t, int d) {
         const int k0 = tile_start(t);
         if (PIECES) {
-            if (conv) load_piece(sc, p, k0, ra[d], rc[d]);
-            else      ra[d] = load_piece(sa, k0);
+            if (AMODE == 4)  load_piece(sc, p, k0, ra[d], rc[d]);
+            else if (conv)   ra[d] = load_16(sc.first(p, k0)); // one tap
+            else             ra[d] = load_piece(sa, k0);
             rb[d] = load_piece(sb, k0);
         } else {
             ra[d] = AMODE == 2 ? fetch_taps(cl, p, k0) : load_aligned(rowa, k0);
@@ -447,7 +448,11 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
         return true;
     };
     auto stage = [&](int t, int d) {
-        uint4 va = !PIECES ? ra[d] : (conv ? sc.codes(p, ra[d], rc[d], t * HBK) : sa.codes(ra[d], t * HBK));
+        uint4 va = ra[d];
+        if (AMODE == 4 && SMALL) va = sc.codes(p, ra[d], rc[d], t * HBK);
+        else if (AMODE == 4)     va = p.cv_vec ? sc.tap_codes(p, ra[d], t * HBK) : sc.row_codes(p, ra[d], rc[d], t * HBK);   // (filter rows shorter than a piece: the smallest grids alone)
+        else if (PIECES && conv) va = sc.tap_codes(p, ra[d], t * HBK);
+        else if (PIECES)         va = sa.codes(ra[d], t * HBK);
         uint4 vb = PIECES ? sb.codes(rb[d], t * HBK) : rb[d];
         if (!PIECES && (t + 1) * HBK > p.K) {                  // uniform: steps beyond K
             if (!conv) va = rowa.codes(va, t * HBK);
@@ -558,206 +563,207 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
     const int row0 = m0 + wave * RW + g, rowh = m0 + wave * RW + 8 + (lane >> 4);
     const int col0 = n0 + tx * TN, colh = n0 + (lane & 15) * (TN / 2);
     for (;;) {
-    for (int t0 = base; t0 < ntiles; t0 += DEPTH) {
+        for (int t0 = base; t0 < ntiles; t0 += DEPTH) {
 #pragma unroll
-        for (int d = 0; d < DEPTH; ++d) {
-            const int t = t0 + d;
-            if (t >= ntiles) break;
-            const bool more = (t + 1) < ntiles;
-            if (DEPTH == 1) fetch(t + 1, 0);
-            const int parts = p.K - t * HBK > 32 ? 2 : 1;      // steps beyond K are products of zeros: skipped 32 at a time
-            if (LISTS && listed) {
-                if (safe_tiles < parts && dyn) {
-                    const float mf = largest();
-                    safe_tiles = bound.safe(mf, nullptr);
-                    if (safe_tiles < parts) safe_tiles = bound.follows(mf, half_norm[t & 1], parts) ? parts : 0;
-                }
-                const char* const Bb = reinterpret_cast<const char*>(smem + tx * W);
-                const char* const Bh = reinterpret_cast<const char*>(smem + (lane & 15) * (W / 2));
-                if constexpr (EVENTS) {
-                    for (int part = 0; part < parts; ++part) store_no_events(2 * t + part);
-                }
-                ListHead<U> h0(arow), h1(HALF ? arowh : arow + (S == 2 ? 8 * T::PITCH : 0));
-                if (safe_tiles >= parts) {
-                    safe_tiles -= parts;
-                    list_steps<PM, false, MASK, TN, U>(acc[0], h0, arow, Bb, n_first, c);
-                    if constexpr (S == 2) list_steps<PM, false, MASK, TN, U>(acc[1], h1, arow + 8 * T::PITCH, Bb, n_second, c);
-                    if constexpr (HALF) list_steps<PM, false, MASK, TN / 2, U>(acch[0], h1, arowh, Bh, n_second, c);
-                } else if constexpr (RANGE != 0) {
-                    beyond = t;
-                    break;
+            for (int d = 0; d < DEPTH; ++d) {
+                const int t = t0 + d;
+                if (t >= ntiles) break;
+                const bool more = (t + 1) < ntiles;
+                if (DEPTH == 1) fetch(t + 1, 0);
+                const int parts = p.K - t * HBK > 32 ? 2 : 1;      // steps beyond K are products of zeros: skipped 32 at a time
+                if (LISTS && listed) {
+                    if (safe_tiles < parts && dyn) {
+                        const float mf = largest();
+                        safe_tiles = bound.safe(mf, nullptr);
+                        if (safe_tiles < parts) safe_tiles = bound.follows(mf, half_norm[t & 1], parts) ? parts : 0;
+                    }
+                    const char* const Bb = reinterpret_cast<const char*>(smem + tx * W);
+                    const char* const Bh = reinterpret_cast<const char*>(smem + (lane & 15) * (W / 2));
+                    if constexpr (EVENTS) {
+                        for (int part = 0; part < parts; ++part) store_no_events(2 * t + part);
+                    }
+                    ListHead<U> h0(arow), h1(HALF ? arowh : arow + (S == 2 ? 8 * T::PITCH : 0));
+                    if (safe_tiles >= parts) {
+                        safe_tiles -= parts;
+                        list_steps<PM, false, MASK, TN, U>(acc[0], h0, arow, Bb, n_first, c);
+                        if constexpr (S == 2) list_steps<PM, false, MASK, TN, U>(acc[1], h1, arow + 8 * T::PITCH, Bb, n_second, c);
+                        if constexpr (HALF) list_steps<PM, false, MASK, TN / 2, U>(acch[0], h1, arowh, Bh, n_second, c);
+                    } else if constexpr (RANGE != 0) {
+                        beyond = t;
+                        break;
+                    } else {
+                        safe_tiles = 0;
+                        list_steps<PM, true, MASK, TN, U>(acc[0], h0, arow, Bb, n_first, c);
+                        if constexpr (S == 2) list_steps<PM, true, MASK, TN, U>(acc[1], h1, arow + 8 * T::PITCH, Bb, n_second, c);
+                        if constexpr (HALF) list_steps<PM, true, MASK, TN / 2, U>(acch[0], h1, arowh, Bh, n_second, c);
+                    }
                 } else {
-                    safe_tiles = 0;
-                    list_steps<PM, true, MASK, TN, U>(acc[0], h0, arow, Bb, n_first, c);
-                    if constexpr (S == 2) list_steps<PM, true, MASK, TN, U>(acc[1], h1, arow + 8 * T::PITCH, Bb, n_second, c);
-                    if constexpr (HALF) list_steps<PM, true, MASK, TN / 2, U>(acch[0], h1, arowh, Bh, n_second, c);
-                }
-            } else {
-                for (int part = 0; part < parts; ++part) {
-                    const uint32_t* const Bp = smem + (t & 1) * T::B_WORDS + part * 32 * T::BROW;
-                    const uint32_t* const Bs = Bp + tx * W;
-                    const uint32_t* const Bh = Bp + (lane & 15) * (W / 2);
-                    if (safe_tiles == 0) safe_tiles = bound.safe(largest(), dyn ? half_norm[t & 1] : nullptr);
-                    const int word = 2 * t + part;             // of the planes
-                    if (safe_tiles > 0) {
-                        --safe_tiles;
-                        if constexpr (EVENTS) store_no_events(word);
-                        rows_tile<PM, ORDER, false, MASK, LONE, AHEAD, S, TN, T::BROW, T::PITCH>(acc, top, arow + part * 16, Bs, c);
-                        if constexpr (HALF) rows_tile<PM, ORDER, false, MASK, ALONE, ALONE ? 4 : (TN / 2 >= 8 ? 2 : 4), 1, TN / 2, T::BROW, T::PITCH>(acch, toph, arowh + part * 16, Bh, c);
-                    } else if constexpr (EVENTS) {
-                        const HalfBwdConst cb(p);
-                        uint32_t of[S][TN], none[S][TN], none2[S][TN];
-#pragma unroll
-                        for (int i = 0; i < S; ++i)
-#pragma unroll
-                            for (int j = 0; j < TN; ++j) { of[i][j] = 0u; none[i][j] = 0u; none2[i][j] = 0u; }
-                        half_bwd_tile<PM, ORDER, false, false, S, TN, !LONE>(acc, top, of, none, of2, none2, 2 * (word & 15),
-                            [&](int k, uint32_t (&a)[S]) {
-#pragma unroll
-                                for (int i = 0; i < S; ++i) a[i] = arow[i * 8 * T::PITCH + part * 16 + k];
-                            },
-                            [&](int k, uint32_t (&b)[W]) { read_words<W>(Bs + k * T::BROW, b); }, cb);
-                        const int valid = p.K - 32 * word;     // a saturated sum stays at R_OF beyond K
-                        if (valid < 32) {
+                    for (int part = 0; part < parts; ++part) {
+                        const uint32_t* const Bp = smem + (t & 1) * T::B_WORDS + part * 32 * T::BROW;
+                        const uint32_t* const Bs = Bp + tx * W;
+                        const uint32_t* const Bh = Bp + (lane & 15) * (W / 2);
+                        if (safe_tiles == 0) safe_tiles = bound.safe(largest(), dyn ? half_norm[t & 1] : nullptr);
+                        const int word = 2 * t + part;             // of the planes
+                        if (safe_tiles > 0) {
+                            --safe_tiles;
+                            if constexpr (EVENTS) store_no_events(word);
+                            rows_tile<PM, ORDER, false, MASK, LONE, AHEAD, S, TN, T::BROW, T::PITCH>(acc, top, arow + part * 16, Bs, c);
+                            if constexpr (HALF) rows_tile<PM, ORDER, false, MASK, ALONE, ALONE ? 4 : (TN / 2 >= 8 ? 2 : 4), 1, TN / 2, T::BROW, T::PITCH>(acch, toph, arowh + part * 16, Bh, c);
+                        } else if constexpr (EVENTS) {
+                            const HalfBwdConst cb(p);
+                            uint32_t of[S][TN], none[S][TN], none2[S][TN];
 #pragma unroll
                             for (int i = 0; i < S; ++i)
 #pragma unroll
-                                for (int j = 0; j < TN; ++j) of[i][j] &= (1u << valid) - 1u;
+                                for (int j = 0; j < TN; ++j) { of[i][j] = 0u; none[i][j] = 0u; none2[i][j] = 0u; }
+                            half_bwd_tile<PM, ORDER, false, false, S, TN, !LONE>(acc, top, of, none, of2, none2, 2 * (word & 15),
+                                [&](int k, uint32_t (&a)[S]) {
+#pragma unroll
+                                    for (int i = 0; i < S; ++i) a[i] = arow[i * 8 * T::PITCH + part * 16 + k];
+                                },
+                                [&](int k, uint32_t (&b)[W]) { read_words<W>(Bs + k * T::BROW, b); }, cb);
+                            const int valid = p.K - 32 * word;     // a saturated sum stays at R_OF beyond K
+                            if (valid < 32) {
+#pragma unroll
+                                for (int i = 0; i < S; ++i)
+#pragma unroll
+                                    for (int j = 0; j < TN; ++j) of[i][j] &= (1u << valid) - 1u;
+                            }
+                            if (ORDER == LBA_ORDER_SEQ && p.map_dx) mark_bricks_of_rows<RW, TN>(of, m0, n0, word, p);
+                            store_words(p.of_mask, word, of);
+                        } else if constexpr (RANGE != 0) {
+                            beyond = t;
+                            from = part;
+                            break;
+                        } else {
+                            rows_tile<PM, ORDER, true, MASK, LONE, AHEAD, S, TN, T::BROW, T::PITCH>(acc, top, arow + part * 16, Bs, c);
+                            if constexpr (HALF) rows_tile<PM, ORDER, true, MASK, ALONE, ALONE ? 4 : (TN / 2 >= 8 ? 2 : 4), 1, TN / 2, T::BROW, T::PITCH>(acch, toph, arowh + part * 16, Bh, c);
                         }
-                        if (ORDER == LBA_ORDER_SEQ && p.map_dx) mark_bricks_of_rows<RW, TN>(of, m0, n0, word, p);
-                        store_words(p.of_mask, word, of);
-                    } else if constexpr (RANGE != 0) {
-                        beyond = t;
-                        from = part;
-                        break;
-                    } else {
-                        rows_tile<PM, ORDER, true, MASK, LONE, AHEAD, S, TN, T::BROW, T::PITCH>(acc, top, arow + part * 16, Bs, c);
-                        if constexpr (HALF) rows_tile<PM, ORDER, true, MASK, ALONE, ALONE ? 4 : (TN / 2 >= 8 ? 2 : 4), 1, TN / 2, T::BROW, T::PITCH>(acch, toph, arowh + part * 16, Bh, c);
+                    }
+                    if (RANGE != 0 && beyond >= 0) break;
+                }
+                if constexpr (EVENTS && ORDER == LBA_ORDER_CHUNK16) {
+                    // two chunks a word of the plane: a second-level word is complete after 16 of them
+                    const int word = 2 * t + parts - 1;
+                    if ((word & 15) == 15 || t + 1 == ntiles) {
+                        const int left = ((p.K + 15) >> 4) - 32 * (word >> 4);
+                        const uint32_t vmask = left >= 32 ? 0xFFFFFFFFu : (1u << left) - 1u;
+#pragma unroll
+                        for (int i = 0; i < S; ++i)
+#pragma unroll
+                            for (int j = 0; j < TN; ++j) of2[i][j] &= vmask;
+                        if (p.of_mask2) store_words(p.of_mask2, word >> 4, of2);
+#pragma unroll
+                        for (int i = 0; i < S; ++i)
+#pragma unroll
+                            for (int j = 0; j < TN; ++j) of2[i][j] = 0u;
                     }
                 }
-                if (RANGE != 0 && beyond >= 0) break;
-            }
-            if constexpr (EVENTS && ORDER == LBA_ORDER_CHUNK16) {
-                // two chunks a word of the plane: a second-level word is complete after 16 of them
-                const int word = 2 * t + parts - 1;
-                if ((word & 15) == 15 || t + 1 == ntiles) {
-                    const int left = ((p.K + 15) >> 4) - 32 * (word >> 4);
-                    const uint32_t vmask = left >= 32 ? 0xFFFFFFFFu : (1u << left) - 1u;
-#pragma unroll
-                    for (int i = 0; i < S; ++i)
-#pragma unroll
-                        for (int j = 0; j < TN; ++j) of2[i][j] &= vmask;
-                    if (p.of_mask2) store_words(p.of_mask2, word >> 4, of2);
-#pragma unroll
-                    for (int i = 0; i < S; ++i)
-#pragma unroll
-                        for (int j = 0; j < TN; ++j) of2[i][j] = 0u;
+                if (more) {
+                    constexpr int next = (DEPTH > 1) ? 1 : 0;
+                    stage(t + 1, (d + next) % DEPTH);
+                    if (DEPTH > 1) fetch(t + 1 + DEPTH, (d + next) % DEPTH);
                 }
+                __syncthreads();
             }
-            if (more) {
-                constexpr int next = (DEPTH > 1) ? 1 : 0;
-                stage(t + 1, (d + next) % DEPTH);
-                if (DEPTH > 1) fetch(t + 1 + DEPTH, (d + next) % DEPTH);
-            }
-            __syncthreads();
+            if (RANGE != 0 && beyond >= 0) break;
         }
-        if (RANGE != 0 && beyond >= 0) break;
-    }
 
-    if constexpr (RANGE == 0) {
-        break;
-    } else {
-        if (beyond < 0) break;
-        // a stretch in FP32
-        constexpr int HT = HALF ? TN / 2 : 2;
-        const BeyondConst w(p);
-        float sum[S][TN], tops[S][TN], sumh[1][HT], toph2[1][HT];
-        auto wide = [](const h2* s, int j) { return (float)(j & 1 ? s[j / 2].y : s[j / 2].x) * 0x1p-112f; };
-#pragma unroll
-        for (int i = 0; i < S; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) { sum[i][j] = wide(acc[i], j); tops[i][j] = wide(top[i], j); }
-        if constexpr (HALF) {
-#pragma unroll
-            for (int j = 0; j < HT; ++j) { sumh[0][j] = wide(acch[0], j); toph2[0][j] = wide(toph[0], j); }
-        }
-        auto most = [&]() {
-            float m = 0.0f;
+        if constexpr (RANGE == 0) {
+            break;
+        } else {
+            if (beyond < 0) break;
+            // a stretch in FP32
+            constexpr int HT = HALF ? TN / 2 : 2;
+            const BeyondConst w(p);
+            float sum[S][TN], tops[S][TN], sumh[1][HT], toph2[1][HT];
+            auto wide = [](const h2* s, int j) { return (float)(j & 1 ? s[j / 2].y : s[j / 2].x) * 0x1p-112f; };
 #pragma unroll
             for (int i = 0; i < S; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) m = __builtin_fmaxf(m, __builtin_fabsf(ORDER == LBA_ORDER_CHUNK16 ? tops[i][j] : sum[i][j]));
+                for (int j = 0; j < TN; ++j) { sum[i][j] = wide(acc[i], j); tops[i][j] = wide(top[i], j); }
             if constexpr (HALF) {
 #pragma unroll
-                for (int j = 0; j < HT; ++j) m = __builtin_fmaxf(m, __builtin_fabsf(ORDER == LBA_ORDER_CHUNK16 ? toph2[0][j] : sumh[0][j]));
+                for (int j = 0; j < HT; ++j) { sumh[0][j] = wide(acch[0], j); toph2[0][j] = wide(toph[0], j); }
             }
-            return m;
-        };
-        int t = beyond, quiet = 0;                             // parts in which no sum reaches R_OF
-        float mx = most();
-        for (;;) {
-            fetch(t + 1, 0);
-            const int parts = p.K - t * HBK > 32 ? 2 : 1;
-            if (LISTS && listed) {
-                const char* const Bb = reinterpret_cast<const char*>(smem + tx * W);
-                const char* const Bh = reinterpret_cast<const char*>(smem + (lane & 15) * (W / 2));
-                const auto lists = [&](auto clamp) {
-                    constexpr bool CLAMP = decltype(clamp)::value != 0;
-                    beyond_list<PM, CLAMP, TN, U>(sum[0], arow, Bb, n_first, c, w);
-                    if constexpr (S == 2) beyond_list<PM, CLAMP, TN, U>(sum[1], arow + 8 * T::PITCH, Bb, n_second, c, w);
-                    if constexpr (HALF) beyond_list<PM, CLAMP, TN / 2, U>(sumh[0], arowh, Bh, n_second, c, w);
-                };
-                if (quiet < parts && __all(mx < p.fast_thresh4)) quiet = 4;
-                if (quiet >= parts) { quiet -= parts; lists(IntConst<0>{}); }
-                else                { quiet = 0; lists(IntConst<1>{}); }
-                mx = most();
-            } else {
-                for (int part = from; part < parts; ++part) {
-                    const uint32_t* const Bp = smem + (t & 1) * T::B_WORDS + part * 32 * T::BROW;
-                    const uint32_t* const Bs = Bp + tx * W;
-                    const uint32_t* const Bh = Bp + (lane & 15) * (W / 2);
-                    const auto tile = [&](auto clamp) {
-                        constexpr bool CLAMP = decltype(clamp)::value != 0;
-                        beyond_tile<PM, ORDER, CLAMP, SMALL, S, TN, T::BROW, T::PITCH>(sum, tops, arow + part * 16, Bs, c, w);
-                        if constexpr (HALF) beyond_tile<PM, ORDER, CLAMP, false, 1, TN / 2, T::BROW, T::PITCH>(sumh, toph2, arowh + part * 16, Bh, c, w);
-                    };
-                    if (quiet == 0) quiet = __all(mx < p.fast_thresh4) ? 4 : (__all(mx < p.fast_thresh) ? 1 : 0);
-                    if (quiet > 0) { --quiet; tile(IntConst<0>{}); }
-                    else           tile(IntConst<1>{});
-                    mx = most();
+            auto most = [&]() {
+                float m = 0.0f;
+#pragma unroll
+                for (int i = 0; i < S; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) m = __builtin_fmaxf(m, __builtin_fabsf(ORDER == LBA_ORDER_CHUNK16 ? tops[i][j] : sum[i][j]));
+                if constexpr (HALF) {
+#pragma unroll
+                    for (int j = 0; j < HT; ++j) m = __builtin_fmaxf(m, __builtin_fabsf(ORDER == LBA_ORDER_CHUNK16 ? toph2[0][j] : sumh[0][j]));
                 }
+                return m;
+            };
+            int t = beyond, quiet = 0;                             // parts in which no sum reaches R_OF
+            float mx = most();
+            for (;;) {
+                if (AMODE != 4) fetch(t + 1, 0);               // (two loads a piece would cost the packed stretch its registers)
+                const int parts = p.K - t * HBK > 32 ? 2 : 1;
+                if (LISTS && listed) {
+                    const char* const Bb = reinterpret_cast<const char*>(smem + tx * W);
+                    const char* const Bh = reinterpret_cast<const char*>(smem + (lane & 15) * (W / 2));
+                    const auto lists = [&](auto clamp) {
+                        constexpr bool CLAMP = decltype(clamp)::value != 0;
+                        beyond_list<PM, CLAMP, TN, U>(sum[0], arow, Bb, n_first, c, w);
+                        if constexpr (S == 2) beyond_list<PM, CLAMP, TN, U>(sum[1], arow + 8 * T::PITCH, Bb, n_second, c, w);
+                        if constexpr (HALF) beyond_list<PM, CLAMP, TN / 2, U>(sumh[0], arowh, Bh, n_second, c, w);
+                    };
+                    if (quiet < parts && __all(mx < p.fast_thresh4)) quiet = 4;
+                    if (quiet >= parts) { quiet -= parts; lists(IntConst<0>{}); }
+                    else                { quiet = 0; lists(IntConst<1>{}); }
+                    mx = most();
+                } else {
+                    for (int part = from; part < parts; ++part) {
+                        const uint32_t* const Bp = smem + (t & 1) * T::B_WORDS + part * 32 * T::BROW;
+                        const uint32_t* const Bs = Bp + tx * W;
+                        const uint32_t* const Bh = Bp + (lane & 15) * (W / 2);
+                        const auto tile = [&](auto clamp) {
+                            constexpr bool CLAMP = decltype(clamp)::value != 0;
+                            beyond_tile<PM, ORDER, CLAMP, SMALL, S, TN, T::BROW, T::PITCH>(sum, tops, arow + part * 16, Bs, c, w);
+                            if constexpr (HALF) beyond_tile<PM, ORDER, CLAMP, false, 1, TN / 2, T::BROW, T::PITCH>(sumh, toph2, arowh + part * 16, Bh, c, w);
+                        };
+                        if (quiet == 0) quiet = __all(mx < p.fast_thresh4) ? 4 : (__all(mx < p.fast_thresh) ? 1 : 0);
+                        if (quiet > 0) { --quiet; tile(IntConst<0>{}); }
+                        else           tile(IntConst<1>{});
+                        mx = most();
+                    }
+                }
+                from = 0;
+                const bool more = t + 1 < ntiles;
+                if (AMODE == 4) fetch(t + 1, 0);
+                if (more) stage(t + 1, 0);
+                __syncthreads();                                   // (one a tile, as in the packed stretch of other waves)
+                ++t;
+                if (!more) {
+#pragma unroll
+                    for (int i = 0; i < S; ++i) store(row0 + 8 * i, col0, [&](int j) { return (ORDER == LBA_ORDER_CHUNK16 ? tops[i][j] : sum[i][j]) * 0x1p112f; }, IntConst<TN>{});
+                    if constexpr (HALF) store(rowh, colh, [&](int j) { return (ORDER == LBA_ORDER_CHUNK16 ? toph2[0][j] : sumh[0][j]) * 0x1p112f; }, IntConst<TN / 2>{});
+                    return;
+                }
+                safe_tiles = bound.safe(mx * 0x1p112f, nullptr);
+                if (safe_tiles >= 2) break;
             }
-            from = 0;
-            const bool more = t + 1 < ntiles;
-            if (more) stage(t + 1, 0);
-            __syncthreads();                                   // (one a tile, as in the packed stretch of other waves)
-            ++t;
-            if (!more) {
+            // back: every sum is inside FP16's range and has at most 11 bits, at 2^-14 or above
+            auto narrow = [](float x, float y) { return __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(x * 0x1p112f, y * 0x1p112f)); };
 #pragma unroll
-                for (int i = 0; i < S; ++i) store(row0 + 8 * i, col0, [&](int j) { return (ORDER == LBA_ORDER_CHUNK16 ? tops[i][j] : sum[i][j]) * 0x1p112f; }, IntConst<TN>{});
-                if constexpr (HALF) store(rowh, colh, [&](int j) { return (ORDER == LBA_ORDER_CHUNK16 ? toph2[0][j] : sumh[0][j]) * 0x1p112f; }, IntConst<TN / 2>{});
-                return;
+            for (int i = 0; i < S; ++i)
+#pragma unroll
+                for (int j = 0; j < W; ++j) { acc[i][j] = narrow(sum[i][2 * j], sum[i][2 * j + 1]); top[i][j] = narrow(tops[i][2 * j], tops[i][2 * j + 1]); }
+            if constexpr (HALF) {
+#pragma unroll
+                for (int j = 0; j < HT / 2; ++j) { acch[0][j] = narrow(sumh[0][2 * j], sumh[0][2 * j + 1]); toph[0][j] = narrow(toph2[0][2 * j], toph2[0][2 * j + 1]); }
             }
-            safe_tiles = bound.safe(mx * 0x1p112f, nullptr);
-            if (safe_tiles >= 2) break;
+            base = t;
+            beyond = -1;
+            if (DEPTH > 1) {                                       // the tiles ahead, in the slots the loop expects them in
+#pragma unroll
+                for (int d = 1; d <= DEPTH; ++d) fetch(base + d, d % DEPTH);
+            }
         }
-        // back: every sum is inside FP16's range and has at most 11 bits, at 2^-14 or above
-        auto narrow = [](float x, float y) { return __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(x * 0x1p112f, y * 0x1p112f)); };
-#pragma unroll
-        for (int i = 0; i < S; ++i)
-#pragma unroll
-            for (int j = 0; j < W; ++j) { acc[i][j] = narrow(sum[i][2 * j], sum[i][2 * j + 1]); top[i][j] = narrow(tops[i][2 * j], tops[i][2 * j + 1]); }
-        if constexpr (HALF) {
-#pragma unroll
-            for (int j = 0; j < HT / 2; ++j) { acch[0][j] = narrow(sumh[0][2 * j], sumh[0][2 * j + 1]); toph[0][j] = narrow(toph2[0][2 * j], toph2[0][2 * j + 1]); }
-        }
-        base = t;
-        beyond = -1;
-        if (DEPTH > 1) {                                       // the tiles ahead, in the slots the loop expects them in
-#pragma unroll
-            for (int d = 1; d <= DEPTH; ++d) fetch(base + d, d % DEPTH);
-        }
-    }
     }
 
     if (EVENTS && !p.C) return;
@@ -1013,9 +1019,11 @@ __global__ void __launch_bounds__(256, LBA_FAST_MIN_WAVES) lba_half_kernel(const
 template <int PM, int ORDER, int AMODE>
 __global__ void __launch_bounds__(256, LBA_FAST_MIN_WAVES) lba_half_mixed_kernel(const KParams p) { rows_mixed<PM, ORDER, AMODE, 0>(p); }
 
-// Accumulators whose R_OF lies beyond FP16's range (RANGE 1, 2).
+// Accumulators whose R_OF lies beyond FP16's range (RANGE 1, 2).  (im2col rows of any channel count: with a fourth wave per SIMD the two forms of
+// the tile spill on the square lane blocks, 37 x 225 x 226 x 3, 7 x 7: 223 us, 200 so; the others are
+// faster with it)
 template <int TM, int TN, int ORDER, int AMODE, int RANGE>
-__global__ void __launch_bounds__(256, LBA_FAST_MIN_WAVES) lba_wide_kernel(const KParams p) { rows_plain<TM, TN, PM_FLUSH, ORDER, AMODE, RANGE>(p); }
+__global__ void __launch_bounds__(256, AMODE == 4 && TM == TN ? 3 : LBA_FAST_MIN_WAVES) lba_wide_kernel(const KParams p) { rows_plain<TM, TN, PM_FLUSH, ORDER, AMODE, RANGE>(p); }
 template <int ORDER, int AMODE, int RANGE>
 __global__ void __launch_bounds__(256, LBA_FAST_MIN_WAVES) lba_wide_mixed_kernel(const KParams p) { rows_mixed<PM_FLUSH, ORDER, AMODE, RANGE>(p); }
 
