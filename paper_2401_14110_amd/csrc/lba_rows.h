@@ -192,8 +192,8 @@ __device__ __forceinline__ void mark_bricks_of_rows(const uint32_t (&of)[RW / 8]
 
 // Sums beyond FP16's range (accumulators of E >= 5), in FP32 at R_UF = 2^-126: the products of two chains stay packed, v_fma_mix_f32 adds
 // one half of them to an FP32 sum (exactly, rounded once toward zero, flushed below R_UF), then the mask and, where R_OF is near, the
-// clamp of the FP32 step.  No operand is converted, and the masks take turns with the rest as in the packed tile: 7.8 cycles per
-// chain and step in the issue-rate probe at four waves per SIMD (FP32 step 7.4, packed step 5.4 to 6.3).
+// clamp of the FP32 step.  No operand is converted, and the masks take turns with the rest as in the packed tile: 7.1 cycles per
+// chain and step in the issue-rate probe at four waves per SIMD (FP32 step 6.8, packed step 5.6).
 // All sums beyond the range, lba_fast_kernel / operands converted to FP32, four steps at a time and to the end of the chain / here, us:
 //   4096 x 1024 x 2048   M7E6  463 / 1140 /  471, half of A's codes zero 463 /  840 / 386
 //   4096 x 4096 x 4096   M7E6 3201 /10000 / 3343, ...                   3200 / 6489 /2613; M10E5, products of both signs 3238 / 3772 /2625

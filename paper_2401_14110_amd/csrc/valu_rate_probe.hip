@@ -11,7 +11,8 @@
 enum { OP_FMA, OP_MUL, OP_ADD, OP_AND_V, OP_AND_S, OP_XOR_V, OP_ADDU_V, OP_MED3, OP_MAX, OP_BFE, OP_ADD3,
        OP_CMP, OP_LDEXP, OP_PKFMA16, OP_CVTBF, MIX_MFA_DEP, MIX_MFA, MIX_FA, MIX_MFAC, MIX_RNE, MIX_MFCVT,
        MIX_PK, MIX_PKT, MIX_PKE, MIX_PKL,            // packed FP16 steps: two chains per register
-       MIX_PK_FIRST, MIX_MFCVT_FIRST };              // half-rate phases at priority 1
+       MIX_PK_FIRST, MIX_MFCVT_FIRST,                // half-rate phases at priority 1
+       MIX_MIXED };                                  // packed products added to FP32 sums, likewise
 
 template <int OP, int NCH>
 __global__ void __launch_bounds__(256) probe(float* out, int iters, float a, float b, uint32_t mask) {
@@ -35,6 +36,18 @@ __global__ void __launch_bounds__(256) probe(float* out, int iters, float a, flo
                 for (int i = 0; i < NCH; ++i) asm volatile("v_pk_mul_f16 %0, %1, %2 op_sel_hi:[0,1]" : "=v"(q[i]) : "v"(a), "v"(b));
 #pragma unroll
                 for (int i = 0; i < NCH; ++i) asm volatile("v_pk_fma_f16 %0, %1, %2, %0" : "+v"(x[i]) : "v"(q[i]), "v"(vm));
+                __builtin_amdgcn_s_setprio(0);
+#pragma unroll
+                for (int i = 0; i < NCH; ++i) asm volatile("v_and_b32 %0, %1, %0" : "+v"(x[i]) : "v"(vm));
+            } else if (OP == MIX_MIXED) {            // x: FP32 sums; q: products of two of them
+                __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+                for (int i = 0; i < NCH; i += 2) asm volatile("v_pk_mul_f16 %0, %1, %2 op_sel_hi:[0,1]" : "=v"(q[i]) : "v"(a), "v"(b));
+#pragma unroll
+                for (int i = 0; i < NCH; i += 2) {
+                    asm volatile("v_fma_mix_f32 %0, %1, %2, %0 op_sel_hi:[1,0,0]" : "+v"(x[i]) : "v"(q[i]), "v"(vm));
+                    asm volatile("v_fma_mix_f32 %0, %1, %2, %0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(x[i + 1]) : "v"(q[i]), "v"(vm));
+                }
                 __builtin_amdgcn_s_setprio(0);
 #pragma unroll
                 for (int i = 0; i < NCH; ++i) asm volatile("v_and_b32 %0, %1, %0" : "+v"(x[i]) : "v"(vm));
@@ -184,6 +197,7 @@ int main() {
         run<MIX_PKE, 8>("pk step and event bits, slots", 16, w);
         run<MIX_PK_FIRST, 8>("pk step, priorities, slots", 5, w);
         run<MIX_MFCVT_FIRST, 16>("mul|fma|cvt_bf16, priorities", 3, w);
+        run<MIX_MIXED, 16>("pk_mul|fma_mix|and, priorities", 3, w);
     }
     // the latency of a step: one register of a lone wave
     run<MIX_PK, 1>("pk_mul,pk_fma,and latency", 3, 1);
