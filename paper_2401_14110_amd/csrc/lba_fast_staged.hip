@@ -4,19 +4,22 @@
 // chain, so everything else leaves that wave: lba_fast_kernel's fetches sit behind branches and are waited for where those meet, and
 // its decode and stores to LDS run between two parts of the chain.  Four waves run the chains of a 32 x BN tile here (8 rows each,
 // BN / 8 columns per lane) and four others fetch, four k-tiles ahead, and decode the k-tile after it; operands lie in groups of
-// steps, a 16-byte read each (lba_half_staged_kernel, lba_rows.h, is the same on packed carriers).
-// lba_fast_kernel -> here, us (M = 7; M = 9): 64 x 64 x 256 12.9 -> 8.6 (14.7 -> 10.2), 64 x 1000 x 2048 79 -> 48 (93 -> 61), 300 x 300 x 1500
-// 67 -> 37 (77 -> 46), 512 x 512 x 512 29.1 -> 23.5, 128 x 4096 x 1024 (512 workgroups) 75 -> 65, 64 x 64 x 64 7.7 -> 7.6.
+// steps, a 16-byte read each (lba_half_staged_kernel, lba_rows.h, is the same on packed carriers and says why it goes straight through a tile).
+// lba_fast_kernel -> parts of 32 steps -> here, us (M = 7; M = 9): 64 x 1000 x 2048 79 -> 41 -> 37 (93 -> 53 -> 50), 300 x 300 x 1500
+// 67 -> 30.3 -> 28.0 (77 -> 40 -> 38), 512 x 512 x 512 29.1 -> 23.3 -> 22.1, 64 x 64 x 256 12.9 -> 8.4 -> 8.4.
 #include "lba_piece.h"
 #include "lba_launch.h"
 
 namespace lba {
 
+template <int N> struct Choice { static constexpr int value = N; };
+
 template <int TN>
 struct FastStagedTile {
     static constexpr int BM = 32, BN = 8 * TN, GROUP = 4 / TN;             // steps of B in 16 bytes
-    static constexpr int B_WORDS = HBK * BN, PITCH = HBK + 4;              // a row of A, and a shift of its banks
-    static constexpr int STAGE = B_WORDS + BM * PITCH, WORDS = 2 * STAGE;
+    static constexpr int B16 = 16 * BN + 16;                               // 16 steps of B, and a shift of their banks for the lanes that write them
+    static constexpr int B_WORDS = HBK / 16 * B16, PITCH = HBK + 4;        // a row of A, and a shift of its banks
+    static constexpr int STAGE = B_WORDS + BM * PITCH, STAGES = 4, WORDS = STAGES * STAGE;
 };
 
 // The 16 values of a piece, times scale; the two NaN codes read as +-480 (store_tile_cvt).
@@ -40,31 +43,48 @@ __device__ __forceinline__ void decode_fp32(const uint4& v, float scale, float (
     }
 }
 
-// 32 steps of the lane's chains; operands are read eight steps ahead, products taken before the sum ahead of them is rounded.
-template <int PM, int RND, bool CLAMP, int TN>
-__device__ __forceinline__ void fast_staged_steps(float (&sum)[TN], const float* arow, const float* Bs, const FastConst& c) {
-    constexpr int G = FastStagedTile<TN>::GROUP, GROUPS = 32 / G, AHEAD = 8 / G;
-    float4 a[8], b[GROUPS];
-    float q[2][TN];
-    auto part = [](const float4& v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; };
-    auto product = [&](int k) {
+// The operands of a lane's chains ahead of the steps (StagedAhead, lba_rows.h): quads of A's values (four steps each) and of B's (GROUP
+// steps each), and the products of the step to come.
+template <int TN>
+struct FastAhead {
+    using T = FastStagedTile<TN>;
+    static constexpr int G = T::GROUP, STEPS = TN == 2 ? 8 : 4, AQ = STEPS / 4 * 2, BQ = STEPS / G * 2;
+    float4 a[AQ], b[BQ];
+    float q[TN];
+    __device__ __forceinline__ void read_a(const float* base, int i) { a[i % AQ] = *reinterpret_cast<const float4*>(base + 4 * i); }
+    __device__ __forceinline__ void read_b(const float* base, int i) { b[i % BQ] = *reinterpret_cast<const float4*>(base + i / (16 / G) * T::B16 + i % (16 / G) * 32); }
+    static __device__ __forceinline__ float part(const float4& v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
+    __device__ __forceinline__ float of_a(int k) const { return part(a[k / 4 % AQ], k % 4); }
+    __device__ __forceinline__ float of_b(int k, int j) const { return part(b[k / G % BQ], k % G * TN + j); }
+    __device__ __forceinline__ void product(int k) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) q[k & 1][j] = part(a[k / 4], k % 4) * part(b[k / G], k % G * TN + j);   // exact; flushed below Q_prod's R_UF
-    };
+        for (int j = 0; j < TN; ++j) q[j] = of_a(k) * of_b(k, j);   // exact; flushed below Q_prod's R_UF
+    }
+};
+
+// Steps FROM to FROM + 31 of a tile (staged_steps, lba_rows.h)
+template <int PM, int RND, bool CLAMP, int TN, int FROM>
+__device__ __forceinline__ void fast_staged_steps(float (&sum)[TN], FastAhead<TN>& o, const float* ab, const float* Bb, const float* an, const float* Bn,
+                                                  const FastConst& c) {
+    using S = FastAhead<TN>;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) a[i] = *reinterpret_cast<const float4*>(arow + 4 * i);
-#pragma unroll
-    for (int i = 0; i < AHEAD; ++i) b[i] = *reinterpret_cast<const float4*>(Bs + i * 32);
-    if (PM != PM_IDENT) product(0);
-#pragma unroll
-    for (int k = 0; k < 32; ++k) {
-        if (k % 4 == 0 && k / 4 + 2 < 8) a[k / 4 + 2] = *reinterpret_cast<const float4*>(arow + k + 8);
-        if (k % G == 0 && k / G + AHEAD < GROUPS) b[k / G + AHEAD] = *reinterpret_cast<const float4*>(Bs + (k / G + AHEAD) * 32);
+    for (int k = FROM; k < FROM + 32; ++k) {
+        if (k % 4 == 0 || k % S::G == 0) asm volatile("" ::: "memory");   // (reads stay where they are)
+        if (k % 4 == 0) {
+            const int i = (k + S::STEPS) / 4;
+            if (i < HBK / 4) o.read_a(ab, i);
+            else             o.read_a(an, i - HBK / 4);
+        }
+        if (k % S::G == 0) {
+            const int i = (k + S::STEPS) / S::G;
+            if (i < HBK / S::G) o.read_b(Bb, i);
+            else                o.read_b(Bn, i - HBK / S::G);
+        }
 #pragma unroll
         for (int j = 0; j < TN; ++j)                           // one rounding of the exact sum
-            sum[j] = PM == PM_IDENT ? __builtin_fmaf(part(a[k / 4], k % 4), part(b[k / G], k % G * TN + j), sum[j]) : __builtin_fmaf(q[k & 1][j], c.kc, sum[j]);
+            sum[j] = PM == PM_IDENT ? __builtin_fmaf(o.of_a(k), o.of_b(k, j), sum[j]) : __builtin_fmaf(o.q[j], c.kc, sum[j]);
         __builtin_amdgcn_sched_barrier(0);
-        if (PM != PM_IDENT && k < 31) product(k + 1);
+        if (PM != PM_IDENT) o.product((k + 1) % HBK);
         __builtin_amdgcn_sched_barrier(0);
         if (RND == RND_RNE_BF16) {
 #pragma unroll
@@ -94,77 +114,83 @@ __global__ void __launch_bounds__(512, 4) lba_fast_staged_kernel(const KParams p
     const int ntiles = (p.K + HBK - 1) / HBK;
     set_flush_f32();
 
-    // One barrier a tile: behind it the tile is staged and the stage before it no longer read.
+    // A barrier in front of the first tile, which is staged then, and one in the middle of every tile (staged_body, lba_rows.h)
     if (stager) {
         const uint8_t* const pA = p.A + (int64_t)blockIdx.z * p.stride_a;
         const uint8_t* const pB = p.B + (int64_t)blockIdx.z * p.stride_b;
-        // lanes 0 .. 31: pieces of the wave's 8 rows of A; 32 and up: pieces of B, 16 steps a wave
-        const bool isb = lane >= 32;
-        const int ca = isb ? -1 : (lane & 3) * T::BM + wave * 8 + (lane >> 2), cb = isb && lane - 32 < T::BN ? wave * T::BN + lane - 32 : -1;
-        RowPieces<T::BM> s(pA, p.M, p.K, m0, ca);
-        const RowPieces<T::BN> sb(pB, p.N, p.K, n0, cb);
-        if (isb) { s.row = sb.row; s.kq = sb.kq; s.room = sb.room; s.end = sb.end; s.ok = sb.ok; }
+        // waves 0 and 1: 16 rows of A each, four lanes a row; the others: 16 columns of B each (with TN = 2 the last has none)
+        const bool isb = wave >= 2;                            // uniform, as all that follows from it
+        const int line = (wave & 1) * 16 + (lane >> 2), kq = lane & 3;
+        const bool mine = !isb || line < T::BN;
+        int rows_a = p.M, rows_b = p.N;
+        asm("" : "+s"(rows_a), "+s"(rows_b));                  // (staged_body, lba_rows.h)
+        const RowPieces<32> s(isb ? pB : pA, isb ? rows_b : rows_a, p.K, isb ? n0 : m0, mine ? kq * 32 + line : -1);
         const float scale = __builtin_ldexpf(1.0f, isb ? p.exp_b : p.exp_a);
         uint4 r[AHEAD];
 #pragma unroll
         for (int d = 0; d < AHEAD; ++d) r[d] = load_piece(s, tile_start(d));   // (a tile beyond K reads codes inside the operands that nothing uses)
+        static_assert(AHEAD == T::STAGES, "a tile's stage is its slot of the loads in flight");
         for (int t0 = 0; t0 < ntiles; t0 += AHEAD) {
 #pragma unroll
             for (int d = 0; d < AHEAD; ++d) {
                 const int t = t0 + d;
                 if (t >= ntiles) break;
-                float* const st = smem + (t & 1) * T::STAGE;
+                float* const st = smem + d * T::STAGE;
                 float f[16];
                 decode_fp32(s.codes(r[d], t * HBK), scale, f);
                 if (!isb) {
-                    float4* const row = reinterpret_cast<float4*>(st + T::B_WORDS + (wave * 8 + (lane >> 2)) * T::PITCH + (lane & 3) * 16);
+                    float4* const row = reinterpret_cast<float4*>(st + T::B_WORDS + line * T::PITCH + kq * 16);
 #pragma unroll
                     for (int j = 0; j < 4; ++j) row[j] = make_float4(f[4 * j], f[4 * j + 1], f[4 * j + 2], f[4 * j + 3]);
-                } else if (cb >= 0) {                          // [k / GROUP][lane of 8][k % GROUP][column]
-                    const int col = lane - 32;
+                } else if (mine) {                             // [k / GROUP][lane of 8][k % GROUP][column]
+                    float* const to = st + kq * T::B16 + line / TN * 4 + line % TN;
 #pragma unroll
-                    for (int j = 0; j < 16; ++j) {
-                        const int k = wave * 16 + j;
-                        st[((k / T::GROUP * 8 + col / TN) * T::GROUP + k % T::GROUP) * TN + col % TN] = f[j];
-                    }
+                    for (int j = 0; j < 16; ++j) to[(j / T::GROUP * 8 * T::GROUP + j % T::GROUP) * TN] = f[j];
                 }
                 r[d] = load_piece(s, tile_start(t + AHEAD));
                 __syncthreads();
             }
         }
+        __syncthreads();
         return;
     }
 
     FastConst c;
     c.kc = p.kc; c.rof = p.rof_a; c.mask = p.mask_a; c.half = p.half_a; c.sh = p.sh_a;
-    float thresh = p.fast_thresh, thresh4 = p.fast_thresh4;
-    asm volatile("" : "+v"(c.kc), "+v"(c.rof), "+v"(c.mask), "+v"(c.half), "+v"(thresh), "+v"(thresh4));
+    float thresh4 = p.fast_thresh4;                            // fast_body's bounds: below it no sum reaches R_OF in four parts of 32 steps,
+    float thresh2 = 0.9999f * (2.0f * p.fast_thresh - p.rof_a);   // ... in two: the bound of n parts, R_OF / g^n - n d, is convex in n
+    asm volatile("" : "+v"(c.kc), "+v"(c.rof), "+v"(c.mask), "+v"(c.half), "+v"(thresh4), "+v"(thresh2));
     float sum[TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j) sum[j] = 0.0f;
     const int tx = lane & 7, g = lane >> 3;
-    int safe_tiles = 0;
     __builtin_amdgcn_s_setprio(3);                             // the chain is what everything waits for
-    for (int t = 0; t < ntiles; ++t) {
-        __syncthreads();
-        const float* const Bs = smem + (t & 1) * T::STAGE + tx * 4;
-        const float* const arow = smem + (t & 1) * T::STAGE + T::B_WORDS + (wave * 8 + g) * T::PITCH;
-        const int parts = p.K - t * HBK > 32 ? 2 : 1;
-        for (int part = 0; part < parts; ++part) {
-            if (safe_tiles == 0) {                             // fast_body's bound: no sum reaches R_OF in that many tiles of 32 steps
-                float mx = 0.0f;
+    const float* const Bl = smem + tx * 4;
+    const float* const al = smem + T::B_WORDS + (wave * 8 + g) * T::PITCH;
+    FastAhead<TN> o;
+    __syncthreads();
 #pragma unroll
-                for (int j = 0; j < TN; ++j) mx = __builtin_fmaxf(mx, __builtin_fabsf(sum[j]));
-                safe_tiles = __all(mx < thresh4) ? 4 : (__all(mx < thresh) ? 1 : 0);
-            }
-            const float* const Bp = Bs + part * (T::B_WORDS / 2);
-            if (safe_tiles > 0) {
-                --safe_tiles;
-                fast_staged_steps<PM, RND, false, TN>(sum, arow + part * 32, Bp, c);
-            } else {
-                fast_staged_steps<PM, RND, true, TN>(sum, arow + part * 32, Bp, c);
-            }
+    for (int i = 0; i < FastAhead<TN>::STEPS / 4; ++i) o.read_a(al, i);
+#pragma unroll
+    for (int i = 0; i < FastAhead<TN>::STEPS / T::GROUP; ++i) o.read_b(Bl, i);
+    if (PM != PM_IDENT) o.product(0);
+    int t = 0;                                                 // the tile to come (steps beyond K are products of zeros)
+    const auto tiles = [&](auto clamp, int n) {
+#pragma unroll 1
+        for (n = min(n, ntiles - t); n > 0; --n) {
+            const int at = (t & 3) * T::STAGE, then = (++t & 3) * T::STAGE;
+            fast_staged_steps<PM, RND, decltype(clamp)::value != 0, TN, 0>(sum, o, al + at, Bl + at, al + then, Bl + then, c);
+            __syncthreads();
+            fast_staged_steps<PM, RND, decltype(clamp)::value != 0, TN, 32>(sum, o, al + at, Bl + at, al + then, Bl + then, c);
         }
+    };
+    while (t < ntiles) {
+        float mx = 0.0f;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) mx = __builtin_fmaxf(mx, __builtin_fabsf(sum[j]));
+        if (__all(mx < thresh4))      tiles(Choice<0>{}, 2);
+        else if (__all(mx < thresh2)) tiles(Choice<0>{}, 1);
+        else                          tiles(Choice<1>{}, 2);
     }
     // C = S * 2^out_exp, zero written as +0
     const int m = m0 + wave * 8 + g, n = n0 + tx * TN;

@@ -35,10 +35,23 @@ __device__ __forceinline__ void set_round_zero_f16()  { asm volatile("s_setreg_i
 // FP16: denormal inputs are read, denormal results flushed
 __device__ __forceinline__ void set_flush_out_f16()   { asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 6, 2), 1\n\ts_nop 1" ::: "memory"); }
 
+template <int N> struct IntConst { static constexpr int value = N; };
+
 __device__ __forceinline__ h2 as_h2(uint32_t u) { return __builtin_bit_cast(h2, u); }
 __device__ __forceinline__ uint32_t as_u32(h2 h) { return __builtin_bit_cast(uint32_t, h); }
 __device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+// the largest of the wave's values in both halves of a word, in lane 63
+__device__ __forceinline__ uint32_t wave_max_u16(uint32_t m) {
+    const auto step = [&](auto ctrl) { m = pk_max_u16(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, decltype(ctrl)::value, 0xF, 0xF, true)); };
+    step(IntConst<0xB1>{});                                    // lane ^ 1, lane ^ 2, the other half of 8 and of 16
+    step(IntConst<0x4E>{});
+    step(IntConst<0x141>{});
+    step(IntConst<0x140>{});
+    m = pk_max_u16(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x142, 0xA, 0xF, false));   // row 0 to 1, 2 to 3
+    m = pk_max_u16(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x143, 0xC, 0xF, false));   // row 1 to 2 and 3
+    return m;
 }
 // the larger half of a word of two non-negative FP16 numbers, as a float
 __device__ __forceinline__ float max_half(uint32_t m) {

@@ -30,8 +30,6 @@
 
 namespace lba {
 
-template <int N> struct IntConst { static constexpr int value = N; };
-
 template <int T>
 __device__ __forceinline__ void read_words(const uint32_t* s, uint32_t (&b)[T]) {
     static_assert(T == 1 || T == 2 || T == 4, "words per lane");
@@ -774,70 +772,84 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
 }
 
 // The smallest grids, at most one or two workgroups per CU: four waves run the chains of a 32 x BN tile (8 rows each, BN / 8 columns
-// per lane) and four others fetch and decode the k-tile after it.  What bounds such a call is one wave's issue and the latency of its
-// chain (24 cycles a step in the issue-rate probe for multiply-add, next product and mask), so everything else leaves that wave:
-// staging, which cost 1500 cycles a k-tile beside the chain's 1550, and most LDS reads (B lies in groups of steps, one 16-byte read
-// for four or two of them).  Lists of non-zero codes do not pay here: a step then needs a read and an address of its own (40
-// cycles).  64 x 1000 x 2048: 44 us with four waves that do both, 27 here; 300 x 300 x 1500 36 -> 21, 512 x 512 x 512 16 -> 13.
+// per lane) and four others fetch and decode the k-tile after it.  What bounds such a call is one wave's issue, 4 cycles an instruction and
+// 12 a step (multiply-add, next product, mask), so everything else leaves that wave: staging, most LDS reads (B lies in groups of steps, one
+// 16-byte read for four or two of them, 8 cycles each among other instructions), and branches: a taken one costs a lone wave 40 to 130
+// cycles (measured with loops of 16 to 256 steps).  So a tile of 64 steps is run straight through, its operands read ahead across its
+// end, and a loop has one branch a tile.  Lists of non-zero codes do not pay here: a step then needs a read and an address of its own.
+// Four waves that do both -> parts of 32 steps that start anew -> here, us: 64 x 1000 x 2048 44 -> 27 -> 21, 300 x 300 x 1500 36 -> 20.2 ->
+// 16.7, 512 x 512 x 512 16 -> 12.6 -> 11.4, 416 x 480 x 3312 64.6 -> 57.2 for the last two, with R_OF near the sums (clamped) 300 x 300 x 1500
+// 29 -> 22.
 template <int TN>
 struct StagedTile {
     static constexpr int BM = 32, BN = 8 * TN, W = TN / 2, GROUP = 4 / W;  // steps of B in 16 bytes
-    static constexpr int B_WORDS = HBK * BN / 2, PAIRS = HBK / 2 + 4;      // a row's words (k, k + 1), and a shift of its banks
-    static constexpr int STAGE = B_WORDS + BM * PAIRS, WORDS = 2 * STAGE;
+    static constexpr int B16 = 16 * BN / 2 + 16;                           // words of 16 steps of B, and a shift of their banks for the lanes that write them
+    static constexpr int B_WORDS = HBK / 16 * B16, PAIRS = HBK / 2 + 4;    // a row's words (k, k + 1), and a shift of its banks
+    static constexpr int STAGE = B_WORDS + BM * PAIRS, STAGES = 4, WORDS = STAGES * STAGE;
 };
 
-// store_half_b for that layout: [k / GROUP][lane of 8][k % GROUP][word]
+// The 16 codes of a column's piece in that layout, [k / GROUP][lane of 8][k % GROUP][word], as half words: the lane has nothing else to
+// wait for, and the pairs of columns need no exchange between lanes.
 template <int TN>
-__device__ __forceinline__ void store_staged_b(uint32_t* __restrict__ dst, int c, const uint32_t (&w)[8]) {
+__device__ __forceinline__ void store_staged_b(uint32_t* __restrict__ dst, int col, int kq, const uint32_t (&w)[8]) {
     using T = StagedTile<TN>;
-    if (c < 0) return;
-    const int col = c % T::BN, kq = c / T::BN, pair = col >> 1;
-    const uint32_t sel = (col & 1) ? 0x03020706u : 0x05040100u;
+    u16_any* const to = reinterpret_cast<u16_any*>(dst + kq * T::B16) + col / TN * 8 + col % TN;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[j], 0xB1, 0xF, 0xF, true);   // the neighbour's word
-        const int k = kq * 16 + 2 * j + (col & 1);
-        dst[((k / T::GROUP * 8 + pair / T::W) * T::GROUP + k % T::GROUP) * T::W + pair % T::W] = __builtin_amdgcn_perm(other, w[j], sel);
-    }
+    for (int j = 0; j < 16; ++j) to[(j / T::GROUP * 8 * T::GROUP + j % T::GROUP) * TN] = (uint16_t)(w[j / 2] >> (j & 1 ? 16 : 0));
 }
 
-// 32 steps of the lane's chains; operands are read eight steps ahead, products taken before the sum ahead of them is rounded.
-template <int PM, bool CLAMP, int TN>
-__device__ __forceinline__ void staged_steps(h2 (&sum)[1][TN / 2], const uint32_t* arow, const uint32_t* Bs, const HalfConst& c) {
+// The operands of a lane's chains ahead of the steps: quads of A's words (eight steps each) and of B's (GROUP steps each), and the
+// products of the step to come.
+template <int TN>
+struct StagedAhead {
     using T = StagedTile<TN>;
-    constexpr int W = T::W, G = T::GROUP, GROUPS = 32 / G, AHEAD = 8 / G;
-    uint32_t a[16], b[GROUPS][4];
-    h2 q[2][1][W];
-    auto read_a = [&](int s) {
-        uint32_t x[4];
-        read_words<4>(arow + s, x);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) a[s + j] = x[j];
-    };
-    auto product = [&](int k) {
-        const uint32_t x[1] = {a[k / 2]};
+    static constexpr int W = T::W, G = T::GROUP, STEPS = TN == 2 ? 16 : 8, AQ = STEPS / 8 * 2, BQ = STEPS / G * 2;
+    uint32_t a[AQ][4], b[BQ][4];
+    h2 q[1][W];
+    // quads i of the tile at a base
+    __device__ __forceinline__ void read_a(const uint32_t* base, int i) { read_words<4>(base + 4 * i, a[i % AQ]); }
+    __device__ __forceinline__ void read_b(const uint32_t* base, int i) { read_words<4>(base + i / (16 / G) * T::B16 + i % (16 / G) * 32, b[i % BQ]); }
+    // the words of step k: A's, whose half is k & 1, and B's
+    __device__ __forceinline__ uint32_t word_a(int k) const { return a[k / 8 % AQ][k / 2 % 4]; }
+    template <int PM>
+    __device__ __forceinline__ void product(int k, const HalfConst& c) {
+        const uint32_t x[1] = {word_a(k)};
         uint32_t y[W];
 #pragma unroll
-        for (int j = 0; j < W; ++j) y[j] = b[k / G][k % G * W + j];
-        if (k & 1) half_products<PM, true, 1, TN, false>(q[1], x, y, c);
-        else       half_products<PM, false, 1, TN, false>(q[0], x, y, c);
-    };
-    read_a(0);
-    read_a(4);
+        for (int j = 0; j < W; ++j) y[j] = b[k / G % BQ][k % G * W + j];
+        if (k & 1) half_products<PM, true, 1, TN, false>(q, x, y, c);
+        else       half_products<PM, false, 1, TN, false>(q, x, y, c);
+    }
+};
+
+// Steps FROM to FROM + 31 of a tile whose operands are at (ab, Bb), the next tile's at (an, Bn).  Operands are read STEPS steps ahead, across
+// the end of the tile, and products are taken before the sum ahead of them is rounded: a tile starts with everything it needs in
+// registers.
+template <int PM, bool CLAMP, int TN, int FROM>
+__device__ __forceinline__ void staged_steps(h2 (&sum)[1][TN / 2], StagedAhead<TN>& o, const uint32_t* ab, const uint32_t* Bb, const uint32_t* an,
+                                             const uint32_t* Bn, const HalfConst& c) {
+    using S = StagedAhead<TN>;
+    constexpr int W = S::W, G = S::G, AHEAD = S::STEPS;
 #pragma unroll
-    for (int i = 0; i < AHEAD; ++i) read_words<4>(Bs + i * 32, b[i]);
-    product(0);
-#pragma unroll
-    for (int k = 0; k < 32; ++k) {
-        if (k % 8 == 0 && k < 16) read_a(8 + k / 2);
-        if (k % G == 0 && k / G + AHEAD < GROUPS) read_words<4>(Bs + (k / G + AHEAD) * 32, b[k / G + AHEAD]);
-        const uint32_t x[1] = {a[k / 2]};
+    for (int k = FROM; k < FROM + 32; ++k) {
+        if (k % 8 == 0 || k % G == 0) asm volatile("" ::: "memory");   // (reads stay where they are)
+        if (k % 8 == 0) {
+            const int i = (k + AHEAD) / 8;
+            if (i < HBK / 8) o.read_a(ab, i);
+            else             o.read_a(an, i - HBK / 8);
+        }
+        if (k % G == 0) {
+            const int i = (k + AHEAD) / G;
+            if (i < HBK / G) o.read_b(Bb, i);
+            else             o.read_b(Bn, i - HBK / G);
+        }
+        const uint32_t x[1] = {o.word_a(k)};
         uint32_t y[W];
 #pragma unroll
-        for (int j = 0; j < W; ++j) y[j] = b[k / G][k % G * W + j];
-        if (k & 1) half_sums<PM, true, 1, TN>(sum, q[1], x, y, c);
-        else       half_sums<PM, false, 1, TN>(sum, q[0], x, y, c);
-        if (k < 31) product(k + 1);
+        for (int j = 0; j < W; ++j) y[j] = o.b[k / G % S::BQ][k % G * W + j];
+        if (k & 1) half_sums<PM, true, 1, TN>(sum, o.q, x, y, c);
+        else       half_sums<PM, false, 1, TN>(sum, o.q, x, y, c);
+        o.template product<PM>((k + 1) % HBK, c);
         half_round<CLAMP, 1, TN, false>(sum, c);
     }
 }
@@ -850,35 +862,37 @@ __device__ __forceinline__ void staged_body(const KParams& p, uint32_t* __restri
     const bool stager = __builtin_amdgcn_readfirstlane(tid >> 8) != 0;
     const uint8_t* pA = p.A + (int64_t)blockIdx.z * p.stride_a;
     const uint8_t* pB = p.B + (int64_t)blockIdx.z * p.stride_b;
-    __shared__ uint32_t half_norm[2][4];
+    __shared__ uint32_t half_norm[4][4];                       // of tiles t & 3 (the tile ahead and one being staged beside the tile read)
     const bool dyn = half_follows_data(p);
     const int ntiles = (p.K + HBK - 1) / HBK;
     set_flush_f32();
     set_round_zero_f16();
     set_flush_out_f16();
 
-    // One barrier a tile: behind it the tile is staged and the stage before it no longer read.
+    // A barrier in front of the first tile, which is staged then, and one in the middle of every tile: the next one is staged, and the
+    // stage of the one before is no longer read.
     if (stager) {
-        // lanes 0 .. 31: pieces of the wave's 8 rows of A; 32 and up: pieces of B
-        const bool isb = lane >= 32;
-        const int ca = isb ? -1 : (lane & 3) * T::BM + wave * 8 + (lane >> 2), cb = isb && lane - 32 < T::BN ? wave * T::BN + lane - 32 : -1;
-        RowPieces<T::BM> s(pA, CONV ? 1 : p.M, p.K, CONV ? 0 : m0, ca);
-        const RowPieces<T::BN> sb(pB, p.N, p.K, n0, cb);
-        if (isb || CONV) { s.row = sb.row; s.kq = sb.kq; s.room = sb.room; s.end = sb.end; s.ok = sb.ok; }
+        // waves 0 and 1: 16 rows of A each, four lanes a row; the others: 16 columns of B each (with TN = 2 the last has none)
+        const bool isb = wave >= 2;                            // uniform, as all that follows from it
+        const int line = (wave & 1) * 16 + (lane >> 2), kq = lane & 3;
+        const bool mine = !isb || line < T::BN;
+        int rows_a = CONV ? 1 : p.M, rows_b = p.N;
+        asm("" : "+s"(rows_a), "+s"(rows_b));                  // (two neighbours in p and a choice of them went through scratch memory)
+        const RowPieces<32> s(isb ? pB : pA, isb ? rows_b : rows_a, p.K, isb ? n0 : (CONV ? 0 : m0), mine && (isb || !CONV) ? kq * 32 + line : -1);
         ConvPieces sc = {};
-        if (CONV) sc = ConvPieces::make<T::BM>(pA, p, m0, ca);
+        if (CONV && !isb) sc = ConvPieces::make<T::BM>(pA, p, m0, kq * 32 + line);
         const int shift = isb ? p.h_shift_b : p.h_shift_a;
         const uint32_t keep = isb ? p.h_keep_b : p.h_keep_a, scale = isb ? p.h_scale_b : p.h_scale_a;
         uint4 r[AHEAD], r2[CONV == 2 ? AHEAD : 1];
         auto fetch = [&](int t, int d) {                       // (a tile beyond K reads codes inside the operands that nothing uses)
             const int k0 = tile_start(t);
             if (CONV) {
-                const uint8_t* const a = sc.first(p, k0);
-                const uint8_t* const b = s.address(k0);
-                r[d] = load_16(isb ? b : a);
+                const uint8_t* a = s.address(k0);
+                if (!isb) a = sc.first(p, k0);
+                r[d] = load_16(a);
                 if constexpr (CONV == 2) {
-                    const uint8_t* const a2 = sc.second(p, k0);
-                    r2[d] = load_16(isb ? b : a2);
+                    if (!isb) a = sc.second(p, k0);
+                    r2[d] = load_16(a);
                 }
             } else {
                 r[d] = load_piece(s, k0);
@@ -886,41 +900,35 @@ __device__ __forceinline__ void staged_body(const KParams& p, uint32_t* __restri
         };
 #pragma unroll
         for (int d = 0; d < AHEAD; ++d) fetch(d, d);
+        static_assert(AHEAD == T::STAGES, "a tile's stage is its slot of the loads in flight");
         for (int t0 = 0; t0 < ntiles; t0 += AHEAD) {
 #pragma unroll
             for (int d = 0; d < AHEAD; ++d) {
                 const int t = t0 + d;
                 if (t >= ntiles) break;
-                uint32_t* const st = smem + (t & 1) * T::STAGE;
+                uint32_t* const st = smem + d * T::STAGE;
                 uint4 v = r[d];
-                if (CONV) {
-                    const uint4 row = s.codes(v, t * HBK);
-                    uint4 tap;
-                    if constexpr (CONV == 2) tap = sc.row_codes(p, v, r2[d], t * HBK);
-                    else                     tap = sc.tap_codes(p, v, t * HBK);
-                    v = make_uint4(isb ? row.x : tap.x, isb ? row.y : tap.y, isb ? row.z : tap.z, isb ? row.w : tap.w);
-                } else {
-                    v = s.codes(v, t * HBK);
-                }
+                if (!CONV || isb)             v = s.codes(v, t * HBK);
+                else if constexpr (CONV == 2) v = sc.row_codes(p, v, r2[d], t * HBK);
+                else                          v = sc.tap_codes(p, v, t * HBK);
                 uint32_t w[8];
                 decode_half(v, shift, keep, scale, w);
-                store_staged_b<TN>(st, cb, w);
-                if (!isb) {
-                    uint4* const pairs = reinterpret_cast<uint4*>(st + T::B_WORDS + (wave * 8 + (lane >> 2)) * T::PAIRS + (lane & 3) * 8);
+                if (isb) {
+                    if (mine) store_staged_b<TN>(st, line, kq, w);
+                } else {
+                    uint4* const pairs = reinterpret_cast<uint4*>(st + T::B_WORDS + line * T::PAIRS + kq * 8);
                     pairs[0] = make_uint4(w[0], w[1], w[2], w[3]);
                     pairs[1] = make_uint4(w[4], w[5], w[6], w[7]);
                 }
                 if (dyn) {
-                    const uint32_t n2 = __float_as_uint(piece_norm2(w)) + 0xFFFFu;
-                    uint32_t m = isb ? n2 & 0xFFFF0000u : n2 >> 16;
-#pragma unroll
-                    for (int o = 32; o > 0; o >>= 1) m = pk_max_u16(m, (uint32_t)__shfl_xor((int)m, o, 64));
-                    if (lane == 0) half_norm[t & 1][wave] = m;
+                    const uint32_t n2 = wave_max_u16((__float_as_uint(piece_norm2(w)) + 0xFFFFu) >> 16);
+                    if (lane == 63) half_norm[t & 3][wave] = isb ? n2 << 16 : n2;
                 }
                 fetch(t + AHEAD, d);
                 __syncthreads();
             }
         }
+        __syncthreads();
         return;
     }
 
@@ -932,28 +940,40 @@ __device__ __forceinline__ void staged_body(const KParams& p, uint32_t* __restri
     for (int j = 0; j < W; ++j) acc[0][j] = as_h2(0u);
     const int tx = lane & 7, g = lane >> 3;
     const HalfBound bound(p);
-    int safe_tiles = 0;
     __builtin_amdgcn_s_setprio(3);                             // the chain is what everything waits for
-    for (int t = 0; t < ntiles; ++t) {
-        __syncthreads();
-        const uint32_t* const Bs = smem + (t & 1) * T::STAGE + tx * 4;
-        const uint32_t* const arow = smem + (t & 1) * T::STAGE + T::B_WORDS + (wave * 8 + g) * T::PAIRS;
-        const int parts = p.K - t * HBK > 32 ? 2 : 1;
-        for (int part = 0; part < parts; ++part) {
-            if (safe_tiles == 0) {
-                uint32_t mx = 0u;
+    const uint32_t* const Bl = smem + tx * 4;
+    const uint32_t* const al = smem + T::B_WORDS + (wave * 8 + g) * T::PAIRS;
+    StagedAhead<TN> o;
+    __syncthreads();
 #pragma unroll
-                for (int j = 0; j < W; ++j) mx = pk_max_u16(mx, as_u32(acc[0][j]) & 0x7FFF7FFFu);
-                safe_tiles = bound.safe(max_half(mx), dyn ? half_norm[t & 1] : nullptr);
-            }
-            const uint32_t* const Bp = Bs + part * (T::B_WORDS / 2);
-            if (safe_tiles > 0) {
-                --safe_tiles;
-                staged_steps<PM, false, TN>(acc, arow + part * 16, Bp, c);
-            } else {
-                staged_steps<PM, true, TN>(acc, arow + part * 16, Bp, c);
-            }
+    for (int i = 0; i < StagedAhead<TN>::STEPS / 8; ++i) o.read_a(al, i);
+#pragma unroll
+    for (int i = 0; i < StagedAhead<TN>::STEPS / T::GROUP; ++i) o.read_b(Bl, i);
+    o.template product<PM>(0, c);
+    const auto largest = [&]() {
+        uint32_t mx = 0u;
+#pragma unroll
+        for (int j = 0; j < W; ++j) mx = pk_max_u16(mx, as_u32(acc[0][j]) & 0x7FFF7FFFu);
+        return max_half(mx);
+    };
+    // n tiles.  A loop for each form, straight through a tile: a taken branch costs a lone wave 40 to 130 cycles (three or four of them for every
+    // 32 steps were as much again as the steps), an instruction 4.
+    int t = 0;                                                 // the tile to come (steps beyond K are products of zeros)
+    const auto tiles = [&](auto clamp, int n) {
+#pragma unroll 1
+        for (n = min(n, ntiles - t); n > 0; --n) {
+            const int at = (t & 3) * T::STAGE, then = (++t & 3) * T::STAGE;
+            staged_steps<PM, decltype(clamp)::value != 0, TN, 0>(acc, o, al + at, Bl + at, al + then, Bl + then, c);
+            __syncthreads();
+            staged_steps<PM, decltype(clamp)::value != 0, TN, 32>(acc, o, al + at, Bl + at, al + then, Bl + then, c);
         }
+    };
+    while (t < ntiles) {
+        const float mf = largest();
+        const int safe = bound.safe(mf, nullptr);
+        if (safe >= 2)                                                    tiles(IntConst<0>{}, safe / 2);
+        else if (dyn && bound.follows(mf, half_norm[t & 3], 2))           tiles(IntConst<0>{}, 1);
+        else                                                              tiles(IntConst<1>{}, dyn ? 1 : 2);
     }
     const int m = m0 + wave * 8 + g, n = n0 + tx * TN;
     if (m >= p.M) return;
@@ -981,7 +1001,8 @@ __device__ __forceinline__ void staged_grid(const KParams& p) {
 // The sequential order; 512 lanes.  Row-major operands of any alignment; im2col rows, CONV 1: pieces are channels of one tap (cv_vec), 2: pieces
 // span at most two filter rows.  One kernel for both waited for its loads where the branch around the second one met (3 x 3 on 56 x 56 x
 // 64 29.6 us, 17.5 so).  lba_half_kernel -> here, one image: 7 x 7 x 512 to 512 channels, 3 x 3, 155 -> 84 us, 14 x 14 x 256 81 -> 45, 28 x
-// 28 x 128 42 -> 24, 56 x 56 x 64 25.3 -> 17.6, a stem (112 x 112 x 3, 7 x 7) 12.6 -> 10.5; 8 of 7 x 7 x 512 177 -> 113.
+// 28 x 128 42 -> 24, 56 x 56 x 64 25.3 -> 17.6, a stem (112 x 112 x 3, 7 x 7) 12.6 -> 10.5; 8 of 7 x 7 x 512 177 -> 113 (since tiles are run
+// straight through another 5 to 23 % less, the stem as before).
 template <int TN, int PM>
 __global__ void __launch_bounds__(512, 4) lba_half_staged_kernel(const KParams p) { staged_grid<TN, PM, 0>(p); }
 template <int TN, int PM, int CONV>
