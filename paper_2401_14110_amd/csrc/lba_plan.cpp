@@ -216,8 +216,12 @@ static bool half_underflow_ok(const lba_qfmt& qp, const InSpec& in, int bpe, int
 // with few outputs cannot keep two waves on every SIMD with 16 chains per lane: between 512 and 1024
 // workgroups 2 x 4 measured 3-6 % faster; up to 256 workgroups of 64 x 64 a CU would hold one wave per SIMD,
 // which issues at half rate, so those grids take 2 x 4 (129-256) or 2 x 2 (up to 128): 1.6-3 times faster.
+// On packed carriers (rows of 8 columns a lane) the 2 x 4 block takes 1.04 to 1.08 times as long for the same outputs, so between 512 and 1024
+// workgroups it is taken where it saves half a round of 256 and not where both need as many (8192 x 512 x 768: 136 -> 130 us, behind a
+// ReLU 117 -> 108; 5888 x 512 x 768 106 -> 101 and 93 -> 86; 560 workgroups of a batched product 37.6 us, 40.0 with 4 x 4).  Rows that do not
+// start on 16-byte boundaries keep the 2 x 4 block throughout: its parity tests run on them (1530 x 2045 x 70 18.8 us, 16.6 with 4 x 4).
 // The choice never changes a result.
-static void pick_tile(int64_t M, int64_t N, int64_t batch, int kernel, int events, int prod_mode, int amode, int rne_odd, int* tm, int* tn, int* bk) {
+static void pick_tile(int64_t M, int64_t N, int64_t batch, int kernel, int events, int prod_mode, int amode, int rne_odd, int packed, int* tm, int* tn, int* bk) {
     *tm = 4; *tn = 4;
     *bk = (kernel == KERNEL_GEN || events) ? 32 : LBA_FAST_BK;
     if (kernel == KERNEL_FAST) {
@@ -228,7 +232,7 @@ static void pick_tile(int64_t M, int64_t N, int64_t batch, int kernel, int event
         // grids are cut finer until every CU has two workgroups
         if (blocks <= 128) { *tm = 2; *tn = 2; }
         else if (blocks <= 384) *tm = 2;
-        else if (blocks > 512 && blocks <= 1024) *tm = 2;
+        else if (blocks > 512 && blocks <= 1024 && (!packed || (blocks + 127) / 128 % 2)) *tm = 2;
     }
 }
 
@@ -478,7 +482,7 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
         (!events || (p.events == 1 && qa.round == LBA_ROUND_FLOOR && order == LBA_ORDER_SEQ && p.prod_mode != PM_IDENT)))
         p.amode = 2;
     p.rne_odd = (fast && rne_odd) ? 1 : 0;
-    pick_tile(M, N, batch, p.kernel, p.events, p.prod_mode, p.amode == 1, p.rne_odd, &p.tm, &p.tn, &p.bk);
+    pick_tile(M, N, batch, p.kernel, p.events, p.prod_mode, p.amode == 1, p.rne_odd, kp.h_on && K % 16 == 0, &p.tm, &p.tn, &p.bk);
     kp.batch = 1;
     kp.fast_thresh = -1.0f;
     kp.fast_thresh4 = -1.0f;
