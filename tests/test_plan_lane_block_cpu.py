@@ -7,7 +7,7 @@ FLOOR, RNE = ((5, 7, -2, 0), (4, 7, -10, 0)), ((5, 7, -2, 1), (4, 7, -10, 1))
 
 
 # packed carriers: the finer block where it saves half a round of 256 workgroups; FP32 carriers and rows off 16-byte boundaries: always
-@pytest.mark.parametrize("gx,half_round", [(43, 1), (44, 1), (48, 0), (58, 1), (63, 0), (64, 0)])
+@pytest.mark.parametrize("gx,half_round", [(33, 1), (40, 1), (41, 0), (48, 0), (49, 1), (56, 1), (63, 0), (64, 0)])
 def test_blocks(gx, half_round):
     M, N = 64 * gx, 1024
     for (qp, qa), K, packed in ((FLOOR, 768, True), (FLOOR, 771, False), (RNE, 768, False)):
