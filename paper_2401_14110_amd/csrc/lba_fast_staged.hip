@@ -157,9 +157,9 @@ __global__ void __launch_bounds__(512, 4) lba_fast_staged_kernel(const KParams p
 
     FastConst c;
     c.kc = p.kc; c.rof = p.rof_a; c.mask = p.mask_a; c.half = p.half_a; c.sh = p.sh_a;
-    float thresh4 = p.fast_thresh4;                            // fast_body's bounds: below it no sum reaches R_OF in four parts of 32 steps,
+    float thresh = p.fast_thresh, thresh4 = p.fast_thresh4;    // fast_body's bounds: below them no sum reaches R_OF in a part of 32 steps, in four,
     float thresh2 = 0.9999f * (2.0f * p.fast_thresh - p.rof_a);   // ... in two: the bound of n parts, R_OF / g^n - n d, is convex in n
-    asm volatile("" : "+v"(c.kc), "+v"(c.rof), "+v"(c.mask), "+v"(c.half), "+v"(thresh4), "+v"(thresh2));
+    asm volatile("" : "+v"(c.kc), "+v"(c.rof), "+v"(c.mask), "+v"(c.half), "+v"(thresh), "+v"(thresh4), "+v"(thresh2));
     float sum[TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j) sum[j] = 0.0f;
@@ -174,23 +174,39 @@ __global__ void __launch_bounds__(512, 4) lba_fast_staged_kernel(const KParams p
 #pragma unroll
     for (int i = 0; i < FastAhead<TN>::STEPS / T::GROUP; ++i) o.read_b(Bl, i);
     if (PM != PM_IDENT) o.product(0);
-    int t = 0;                                                 // the tile to come (steps beyond K are products of zeros)
+    const bool half = ((p.K - 1) & 32) == 0;                   // the last tile's second half lies beyond K (other steps there are products of zeros)
+    int t = 0;                                                 // the tile to come
     const auto tiles = [&](auto clamp, int n) {
 #pragma unroll 1
         for (n = min(n, ntiles - t); n > 0; --n) {
             const int at = (t & 3) * T::STAGE, then = (++t & 3) * T::STAGE;
             fast_staged_steps<PM, RND, decltype(clamp)::value != 0, TN, 0>(sum, o, al + at, Bl + at, al + then, Bl + then, c);
             __syncthreads();
+            if (t == ntiles && half) break;
             fast_staged_steps<PM, RND, decltype(clamp)::value != 0, TN, 32>(sum, o, al + at, Bl + at, al + then, Bl + then, c);
         }
     };
-    while (t < ntiles) {
+    const auto below = [&](float bound) {
         float mx = 0.0f;
 #pragma unroll
         for (int j = 0; j < TN; ++j) mx = __builtin_fmaxf(mx, __builtin_fabsf(sum[j]));
-        if (__all(mx < thresh4))      tiles(Choice<0>{}, 2);
-        else if (__all(mx < thresh2)) tiles(Choice<0>{}, 1);
-        else                          tiles(Choice<1>{}, 2);
+        return __all(mx < bound) != 0;
+    };
+    while (t < ntiles) {
+        if (below(thresh4)) {
+            tiles(Choice<0>{}, 2);
+        } else if (below(thresh2)) {
+            tiles(Choice<0>{}, 1);
+        } else if (below(thresh)) {                            // a part at a time
+            const int at = (t & 3) * T::STAGE, then = (++t & 3) * T::STAGE;
+            fast_staged_steps<PM, RND, false, TN, 0>(sum, o, al + at, Bl + at, al + then, Bl + then, c);
+            __syncthreads();
+            if (t == ntiles && half) break;
+            if (below(thresh)) fast_staged_steps<PM, RND, false, TN, 32>(sum, o, al + at, Bl + at, al + then, Bl + then, c);
+            else               fast_staged_steps<PM, RND, true, TN, 32>(sum, o, al + at, Bl + at, al + then, Bl + then, c);
+        } else {
+            tiles(Choice<1>{}, 2);
+        }
     }
     // C = S * 2^out_exp, zero written as +0
     const int m = m0 + wave * 8 + g, n = n0 + tx * TN;

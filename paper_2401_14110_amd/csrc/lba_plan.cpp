@@ -242,7 +242,7 @@ static void pick_tile(int64_t M, int64_t N, int64_t batch, int kernel, int event
 // efficiency), which the launch then finishes in quarter rounds.  Used when the model says 3 % or more.
 // Fills in a mixed grid: gx_main tile rows of 64 x 64 workgroups, then gx_half tile rows of 48 x 64 ones, then
 // 32 x 32 workgroups on whatever rows are left.  False when the counts do not fit a launch.
-static bool set_mixed_grid(int64_t M, int64_t N, int64_t gx_main, int64_t gx_half, Plan* p) {
+static bool set_mixed_grid(int64_t M, int64_t N, int64_t gx_main, int64_t gx_half, Plan* p, int64_t most_tail16 = 128) {
     const int64_t gy = (N + 63) / 64;
     const int64_t m_main = gx_main * 64, m_half = m_main + gx_half * 48;
     if (gx_main < 0 || gx_half < 0 || m_half > M) return false;
@@ -252,7 +252,7 @@ static bool set_mixed_grid(int64_t M, int64_t N, int64_t gx_main, int64_t gx_hal
     // (a lone wave per SIMD issues at half rate; twice the workgroups of half the size, still at most one per CU, take
     // less time: the 12544 x 256 x 2304 layer 451 -> 437 us; with two per CU, 200704 x 64 x 576, nothing is gained).
     const int64_t before = (gx_main + gx_half) * gy;
-    const bool tail16 = p->events == 0 && before % 1024 == 0 && gx_tail > 0 && gx_tail * ((N + 31) / 32) <= 128;
+    const bool tail16 = p->events == 0 && before % 1024 == 0 && gx_tail > 0 && gx_tail * ((N + 31) / 32) <= most_tail16;
     const int64_t gy_tail = tail16 ? (N + 15) / 16 : (N + 31) / 32, tail = gx_tail * gy_tail;
     p->kp.mix_tail16 = tail16 ? 1 : 0;
     const int64_t total = (gx_main + gx_half) * gy + tail;
@@ -271,7 +271,8 @@ static bool set_mixed_grid(int64_t M, int64_t N, int64_t gx_main, int64_t gx_hal
     return true;
 }
 
-static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, Plan* p) {
+// staged: waves of their own stage where the grid is 32 x 16 or 32 x 32 tiles throughout
+static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, Plan* p) {
     p->mix_tail = 0;
     if (p->kernel != KERNEL_FAST || p->rne_odd || batch != 1) return;
     // other operand formats, rounded products: the forward call (lba_fast_in_mixed_kernel) and the recompute call's OF / UF
@@ -288,7 +289,13 @@ static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, Plan* p) {
     if (p->amode == 1 && blocks <= 256 && set_mixed_grid(M, N, 0, 0, p)) return;
     // the smallest grids of the forward call (at most 128 workgroups of 32 x 32, e.g. a 64 x 1000 classifier layer): the
     // tail's 32 x 16 tiles throughout, twice the workgroups of the 2 x 2 lane block
-    if (p->events == 0 && ((M + 31) / 32) * ((N + 31) / 32) <= 128 && set_mixed_grid(M, N, 0, 0, p)) return;
+    const int64_t b32 = ((M + 31) / 32) * ((N + 31) / 32), b16 = ((M + 31) / 32) * ((N + 15) / 16);
+    if (p->events == 0 && b32 <= 128 && set_mixed_grid(M, N, 0, 0, p)) return;
+    // Where other waves stage, two or three workgroups of 32 x 16 on a CU take less time than one or two of 32 x 32, whose waves run two pairs
+    // of chains (512 columns, K = 768, M = 288 to 512: 15.4 -> 14.8 us, to 768: 22.8 -> 21.5, above: 22.9 against 26.8; nearest-even 26.6 ->
+    // 21.5 up to two a CU).  Chains of three k-tiles gain nothing, and im2col rows whose pieces span filter rows lose (3 x 56 x 56 x 3, 7 x 7, to
+    // 64 channels 9.0 us, 10.0 so): there the stages are what takes the time.
+    if (staged && p->kp.K >= 224 && !(p->amode == 2 && p->kp.K % 16) && (p->round == LBA_ROUND_FLOOR ? b32 <= 384 : b16 <= 480) && set_mixed_grid(M, N, 0, 0, p, b32)) return;
     if (blocks > 256 * 16) return;
     // Rounds of 48 x 64 workgroups (forward call only; measured on M sweeps at N = 256 and 512, whose rates depend on
     // blocks / 256 alone): a CU that holds three 64 x 64 workgroups, or one, issues well below one that holds four or
@@ -543,12 +550,12 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
             p.valu_per_mac_x100 = kpar_slots_x100;
         }
     }
-    if (p.kpar == 0) plan_mixed_grid(M, N, batch, &p);
     // 32 x 16 tiles throughout, or the 2 x 2 lane block's 32 x 32: a lone wave per SIMD gets a second one that stages for it
     // (packed carriers, or FP32 ones under nearest-even: E4M3 operands in pieces of 16 codes, fetched ahead of the chain)
     const bool rne32 = p.kernel == KERNEL_FAST && !kp.h_on && qa.round == LBA_ROUND_RNE && !p.rne_odd && p.amode == 0 && N * K >= 16 && M * K >= 16 && K <= kPieceMaxK;
-    p.staged = ((kp.h_on && !kp.h_range) || rne32) && !p.events && order == LBA_ORDER_SEQ && (p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH) &&
-               (p.mix_tail > 0 ? kp.mix_tail16 && kp.mix_main + kp.mix_half == 0 : p.tm == 2 && p.tn == 2);
+    const bool staged = ((kp.h_on && !kp.h_range) || rne32) && !p.events && order == LBA_ORDER_SEQ && (p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH);
+    if (p.kpar == 0) plan_mixed_grid(M, N, batch, staged, &p);
+    p.staged = staged && (p.mix_tail > 0 ? kp.mix_tail16 && kp.mix_main + kp.mix_half == 0 : p.tm == 2 && p.tn == 2);
     // Waves alone on their SIMDs (lba_half_alone.hip, which has the figures): at most one workgroup of 64 x 64 per CU (only the recompute call
     // and truncated products have so few: pick_tile), or one of 48 x 64 with fewer of the tail's 32 x 32 behind them than there are CUs
     const int64_t total = (int64_t)p.grid_x * p.grid_y * std::max<int64_t>(batch, 1);

@@ -958,13 +958,15 @@ __device__ __forceinline__ void staged_body(const KParams& p, uint32_t* __restri
     };
     // n tiles.  A loop for each form, straight through a tile: a taken branch costs a lone wave 40 to 130 cycles (three or four of them for every
     // 32 steps were as much again as the steps), an instruction 4.
-    int t = 0;                                                 // the tile to come (steps beyond K are products of zeros)
+    const bool half = ((p.K - 1) & 32) == 0;                   // the last tile's second half lies beyond K (other steps there are products of zeros)
+    int t = 0;                                                 // the tile to come
     const auto tiles = [&](auto clamp, int n) {
 #pragma unroll 1
         for (n = min(n, ntiles - t); n > 0; --n) {
             const int at = (t & 3) * T::STAGE, then = (++t & 3) * T::STAGE;
             staged_steps<PM, decltype(clamp)::value != 0, TN, 0>(acc, o, al + at, Bl + at, al + then, Bl + then, c);
             __syncthreads();
+            if (t == ntiles && half) break;
             staged_steps<PM, decltype(clamp)::value != 0, TN, 32>(acc, o, al + at, Bl + at, al + then, Bl + then, c);
         }
     };
