@@ -608,9 +608,9 @@ def conv_kernel_name(name):
             return conv + name[len(plain):]
     if (name.startswith("lba_fast_kernel<") or name.startswith("lba_fast_bwd_kernel<")) and name.endswith(", 0>"):
         return name[:-4] + ", 2>"
-    staged = re.match(r"lba_half_staged_kernel<(\d), (\d)>$", name)
+    staged = re.match(r"lba_half_staged_kernel<(\d), (\d), (\d)>$", name)
     if staged:
-        return "lba_half_staged_conv_kernel<%s, %s, 1>" % staged.groups()   # (whole taps)
+        return "lba_half_staged_conv_kernel<%s, %s, 1, %s>" % staged.groups()   # (whole taps)
     staged = re.match(r"lba_fast_staged_kernel<(\d), (\d), (\d)>$", name)
     if staged:
         return ("lba_fast_conv_mixed_kernel<32, %s, %s, 0>" if staged.group(1) == "2" else "lba_fast_kernel<2, 2, 32, %s, %s, 0, 2>") % staged.group(2, 3)

@@ -4,7 +4,7 @@
 
 namespace lba {
 
-// (truncated products come on the 4 x 4 lane block and mixed grids only, the 2 x 2 one of the sequential order has waves that stage)
+// (truncated products come on the 4 x 4 lane block and mixed grids only; the 2 x 2 block has waves that stage)
 template <int PM, int ORDER, int AMODE>
 static hipError_t launch_one(const Plan& pl, hipStream_t st) {
     const dim3 grid(pl.grid_x, pl.grid_y, pl.kp.batch), block(256);
@@ -21,12 +21,6 @@ static hipError_t launch_one(const Plan& pl, hipStream_t st) {
             hipLaunchKernelGGL((lba_half_kernel<2, 4, PM, ORDER, AMODE>), grid, block, 0, st, pl.kp);
             return hipGetLastError();
         }
-        if constexpr (ORDER == LBA_ORDER_CHUNK16) {
-            if (pl.tm == 2 && pl.tn == 2) {
-                hipLaunchKernelGGL((lba_half_kernel<2, 2, PM, ORDER, AMODE>), grid, block, 0, st, pl.kp);
-                return hipGetLastError();
-            }
-        }
     }
     return hipErrorInvalidValue;
 }
@@ -39,23 +33,24 @@ static hipError_t launch_order(const Plan& pl, hipStream_t st) {
     return hipErrorInvalidValue;
 }
 
-template <int PM, int CONV>
+template <int PM, int CONV, int ORDER>
 static hipError_t launch_staged(const Plan& pl, hipStream_t st) {
     const dim3 grid(pl.grid_x, pl.grid_y, pl.kp.batch), block(512);
-    if (pl.mix_tail > 0) hipLaunchKernelGGL((lba_half_staged_conv_kernel<2, PM, CONV>), grid, block, 0, st, pl.kp);
-    else                 hipLaunchKernelGGL((lba_half_staged_conv_kernel<4, PM, CONV>), grid, block, 0, st, pl.kp);
+    if (pl.mix_tail > 0) hipLaunchKernelGGL((lba_half_staged_conv_kernel<2, PM, CONV, ORDER>), grid, block, 0, st, pl.kp);
+    else                 hipLaunchKernelGGL((lba_half_staged_conv_kernel<4, PM, CONV, ORDER>), grid, block, 0, st, pl.kp);
     return hipGetLastError();
 }
-template <int CONV>
+template <int CONV, int ORDER>
 static hipError_t launch_staged(const Plan& pl, hipStream_t st) {
-    return pl.prod_mode == PM_IDENT ? launch_staged<PM_IDENT, CONV>(pl, st) : pl.prod_mode == PM_FLUSH ? launch_staged<PM_FLUSH, CONV>(pl, st) : hipErrorInvalidValue;
+    return pl.prod_mode == PM_IDENT ? launch_staged<PM_IDENT, CONV, ORDER>(pl, st) : pl.prod_mode == PM_FLUSH ? launch_staged<PM_FLUSH, CONV, ORDER>(pl, st) : hipErrorInvalidValue;
 }
 
 hipError_t launch_half_conv(const Plan& pl, hipStream_t st) {
     if (pl.events || pl.round != LBA_ROUND_FLOOR || !pl.kp.conv || !pl.kp.h_on) return hipErrorInvalidValue;
     if (pl.staged) {                                           // 32 x 16 tiles throughout, or 32 x 32
-        if (pl.order != LBA_ORDER_SEQ || (pl.mix_tail > 0 ? !pl.kp.mix_tail16 || pl.kp.mix_main + pl.kp.mix_half != 0 : pl.tm != 2 || pl.tn != 2)) return hipErrorInvalidValue;
-        return pl.kp.cv_vec ? launch_staged<1>(pl, st) : launch_staged<2>(pl, st);
+        if (pl.mix_tail > 0 ? !pl.kp.mix_tail16 || pl.kp.mix_main + pl.kp.mix_half != 0 : pl.tm != 2 || pl.tn != 2) return hipErrorInvalidValue;
+        if (pl.order == LBA_ORDER_CHUNK16) return pl.kp.cv_vec ? launch_staged<1, LBA_ORDER_CHUNK16>(pl, st) : launch_staged<2, LBA_ORDER_CHUNK16>(pl, st);
+        return pl.kp.cv_vec ? launch_staged<1, LBA_ORDER_SEQ>(pl, st) : launch_staged<2, LBA_ORDER_SEQ>(pl, st);
     }
     if (pl.kp.cv_vec && pl.kp.ld_align == 16)
         return pl.order == LBA_ORDER_CHUNK16 ? launch_order<LBA_ORDER_CHUNK16, 2>(pl, st) : launch_order<LBA_ORDER_SEQ, 2>(pl, st);

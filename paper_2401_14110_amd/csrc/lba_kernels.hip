@@ -71,7 +71,7 @@ static void plan_kernel_name(const Plan& pl, bool uf, char* buf, size_t n) {
         const int am = (pl.amode == 2 ? 2 : 0) + (pl.kp.K % 16 == 0 ? 0 : (pl.amode == 2 ? 2 : 3));      // (operands on a 16-byte boundary)
         if (pl.kp.h_range && pl.mix_tail > 0) snprintf(buf, n, "lba_wide_mixed_kernel<%d, %d, %d>", ord, am, pl.kp.h_range);
         else if (pl.kp.h_range)   snprintf(buf, n, "lba_wide_kernel<%d, %d, %d, %d, %d>", pl.tm, pl.tn, ord, am, pl.kp.h_range);
-        else if (pl.staged)       snprintf(buf, n, "lba_half_staged_kernel<%d, %d>", pl.mix_tail > 0 ? 2 : 4, pm);
+        else if (pl.staged)       snprintf(buf, n, "lba_half_staged_kernel<%d, %d, %d>", pl.mix_tail > 0 ? 2 : 4, pm, ord);
         else if (pl.alone && pl.mix_tail > 0) snprintf(buf, n, "lba_half_alone_mixed_kernel<%d, %d, %d>", pm, ord, am);
         else if (pl.alone)        snprintf(buf, n, "lba_half_alone_kernel<%d, %d, %d>", pm, ord, am);
         else if (pl.mix_tail > 0) snprintf(buf, n, "lba_half_mixed_kernel<%d, %d, %d>", pm, ord, am);

@@ -275,6 +275,14 @@ static bool set_mixed_grid(int64_t M, int64_t N, int64_t gx_main, int64_t gx_hal
 static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, Plan* p) {
     p->mix_tail = 0;
     if (p->kernel != KERNEL_FAST || p->rne_odd || batch != 1) return;
+    const int64_t b32 = ((M + 31) / 32) * ((N + 31) / 32), b16 = ((M + 31) / 32) * ((N + 15) / 16);
+    // Where other waves stage: 32 x 16 tiles throughout up to 128 workgroups of 32 x 32 (one on a CU), and beyond them where two or
+    // three of 32 x 16 on a CU take less time than one or two of 32 x 32, whose waves run two pairs of chains (512 columns, K = 768, M = 288
+    // to 512: 15.4 -> 14.8 us, to 768: 22.8 -> 21.5, above: 22.9 against 26.8; nearest-even 26.6 -> 21.5 up to two a CU).  Chains of three
+    // k-tiles gain nothing, and im2col rows whose pieces span filter rows lose (3 x 56 x 56 x 3, 7 x 7, to 64 channels 9.0 us, 10.0 so):
+    // there the stages are what takes the time.
+    const bool shares = p->kp.K >= 224 && !(p->amode == 2 && p->kp.K % 16) && (p->round == LBA_ROUND_FLOOR ? b32 <= 384 : b16 <= 480);
+    if (staged && (b32 <= 128 || shares) && set_mixed_grid(M, N, 0, 0, p, b32)) return;
     // other operand formats, rounded products: the forward call (lba_fast_in_mixed_kernel) and the recompute call's OF / UF
     // planes (lba_fast_bwd_in_mixed_kernel: floor, the product modes that have a scaled recompute kernel)
     if (p->amode == 1 && (p->events == 2 || (p->events == 1 && p->round != LBA_ROUND_FLOOR))) return;
@@ -289,13 +297,7 @@ static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, Pl
     if (p->amode == 1 && blocks <= 256 && set_mixed_grid(M, N, 0, 0, p)) return;
     // the smallest grids of the forward call (at most 128 workgroups of 32 x 32, e.g. a 64 x 1000 classifier layer): the
     // tail's 32 x 16 tiles throughout, twice the workgroups of the 2 x 2 lane block
-    const int64_t b32 = ((M + 31) / 32) * ((N + 31) / 32), b16 = ((M + 31) / 32) * ((N + 15) / 16);
     if (p->events == 0 && b32 <= 128 && set_mixed_grid(M, N, 0, 0, p)) return;
-    // Where other waves stage, two or three workgroups of 32 x 16 on a CU take less time than one or two of 32 x 32, whose waves run two pairs
-    // of chains (512 columns, K = 768, M = 288 to 512: 15.4 -> 14.8 us, to 768: 22.8 -> 21.5, above: 22.9 against 26.8; nearest-even 26.6 ->
-    // 21.5 up to two a CU).  Chains of three k-tiles gain nothing, and im2col rows whose pieces span filter rows lose (3 x 56 x 56 x 3, 7 x 7, to
-    // 64 channels 9.0 us, 10.0 so): there the stages are what takes the time.
-    if (staged && p->kp.K >= 224 && !(p->amode == 2 && p->kp.K % 16) && (p->round == LBA_ROUND_FLOOR ? b32 <= 384 : b16 <= 480) && set_mixed_grid(M, N, 0, 0, p, b32)) return;
     if (blocks > 256 * 16) return;
     // Rounds of 48 x 64 workgroups (forward call only; measured on M sweeps at N = 256 and 512, whose rates depend on
     // blocks / 256 alone): a CU that holds three 64 x 64 workgroups, or one, issues well below one that holds four or
@@ -553,7 +555,11 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
     // 32 x 16 tiles throughout, or the 2 x 2 lane block's 32 x 32: a lone wave per SIMD gets a second one that stages for it
     // (packed carriers, or FP32 ones under nearest-even: E4M3 operands in pieces of 16 codes, fetched ahead of the chain)
     const bool rne32 = p.kernel == KERNEL_FAST && !kp.h_on && qa.round == LBA_ROUND_RNE && !p.rne_odd && p.amode == 0 && N * K >= 16 && M * K >= 16 && K <= kPieceMaxK;
-    const bool staged = ((kp.h_on && !kp.h_range) || rne32) && !p.events && order == LBA_ORDER_SEQ && (p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH);
+    // (truncated products ran on 256-lane workgroups of 64 x 64 or 32 x 32, up to 4.7 times as long: lba_rows.h.  Their short chains on few
+    // workgroups still do, at 8 to 21 us where the launch is most of it)
+    const bool stages = p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH ||
+                        (p.prod_mode == PM_TRUNC && !conv && (K > 512 || (K >= 224 && ((M + 31) / 32) * ((N + 31) / 32) > 64)));
+    const bool staged = !p.events && (kp.h_on ? !kp.h_range && stages : rne32 && order == LBA_ORDER_SEQ && (p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH));
     if (p.kpar == 0) plan_mixed_grid(M, N, batch, staged, &p);
     p.staged = staged && (p.mix_tail > 0 ? kp.mix_tail16 && kp.mix_main + kp.mix_half == 0 : p.tm == 2 && p.tn == 2);
     // Waves alone on their SIMDs (lba_half_alone.hip, which has the figures): at most one workgroup of 64 x 64 per CU (only the recompute call

@@ -825,8 +825,8 @@ struct StagedAhead {
 // Steps FROM to FROM + 31 of a tile whose operands are at (ab, Bb), the next tile's at (an, Bn).  Operands are read STEPS steps ahead, across
 // the end of the tile, and products are taken before the sum ahead of them is rounded: a tile starts with everything it needs in
 // registers.
-template <int PM, bool CLAMP, int TN, int FROM>
-__device__ __forceinline__ void staged_steps(h2 (&sum)[1][TN / 2], StagedAhead<TN>& o, const uint32_t* ab, const uint32_t* Bb, const uint32_t* an,
+template <int PM, int ORDER, bool CLAMP, int TN, int FROM>
+__device__ __forceinline__ void staged_steps(h2 (&sum)[1][TN / 2], h2 (&top)[1][TN / 2], StagedAhead<TN>& o, const uint32_t* ab, const uint32_t* Bb, const uint32_t* an,
                                              const uint32_t* Bn, const HalfConst& c) {
     using S = StagedAhead<TN>;
     constexpr int W = S::W, G = S::G, AHEAD = S::STEPS;
@@ -851,10 +851,11 @@ __device__ __forceinline__ void staged_steps(h2 (&sum)[1][TN / 2], StagedAhead<T
         else       half_sums<PM, false, 1, TN>(sum, o.q, x, y, c);
         o.template product<PM>((k + 1) % HBK, c);
         half_round<CLAMP, 1, TN, false>(sum, c);
+        if (ORDER == LBA_ORDER_CHUNK16 && k % 16 == 15) half_level2<CLAMP, 1, TN>(top, sum, c);
     }
 }
 
-template <int TN, int PM, int CONV>
+template <int TN, int PM, int CONV, int ORDER>
 __device__ __forceinline__ void staged_body(const KParams& p, uint32_t* __restrict__ smem, int m0, int n0) {
     using T = StagedTile<TN>;
     constexpr int W = TN / 2, AHEAD = kTilesAhead;
@@ -935,9 +936,10 @@ __device__ __forceinline__ void staged_body(const KParams& p, uint32_t* __restri
     HalfConst c;
     c.kc = as_h2(p.h_kc); c.rof = as_h2(p.h_rof); c.nrof = as_h2(p.h_rof ^ 0x80008000u); c.mask = p.h_mask_a; c.maskp = p.h_mask_p;
     asm volatile("" : "+v"(c.kc), "+v"(c.rof), "+v"(c.nrof), "+v"(c.mask), "+v"(c.maskp));
-    h2 acc[1][W];
+    h2 acc[1][W], top[1][W];
 #pragma unroll
-    for (int j = 0; j < W; ++j) acc[0][j] = as_h2(0u);
+    for (int j = 0; j < W; ++j) { acc[0][j] = as_h2(0u); top[0][j] = as_h2(0u); }
+    const h2 (&kept)[1][W] = ORDER == LBA_ORDER_CHUNK16 ? top : acc;
     const int tx = lane & 7, g = lane >> 3;
     const HalfBound bound(p);
     __builtin_amdgcn_s_setprio(3);                             // the chain is what everything waits for
@@ -953,7 +955,7 @@ __device__ __forceinline__ void staged_body(const KParams& p, uint32_t* __restri
     const auto largest = [&]() {
         uint32_t mx = 0u;
 #pragma unroll
-        for (int j = 0; j < W; ++j) mx = pk_max_u16(mx, as_u32(acc[0][j]) & 0x7FFF7FFFu);
+        for (int j = 0; j < W; ++j) mx = pk_max_u16(mx, as_u32(kept[0][j]) & 0x7FFF7FFFu);
         return max_half(mx);
     };
     // n tiles.  A loop for each form, straight through a tile: a taken branch costs a lone wave 40 to 130 cycles (three or four of them for every
@@ -964,10 +966,10 @@ __device__ __forceinline__ void staged_body(const KParams& p, uint32_t* __restri
 #pragma unroll 1
         for (n = min(n, ntiles - t); n > 0; --n) {
             const int at = (t & 3) * T::STAGE, then = (++t & 3) * T::STAGE;
-            staged_steps<PM, decltype(clamp)::value != 0, TN, 0>(acc, o, al + at, Bl + at, al + then, Bl + then, c);
+            staged_steps<PM, ORDER, decltype(clamp)::value != 0, TN, 0>(acc, top, o, al + at, Bl + at, al + then, Bl + then, c);
             __syncthreads();
             if (t == ntiles && half) break;
-            staged_steps<PM, decltype(clamp)::value != 0, TN, 32>(acc, o, al + at, Bl + at, al + then, Bl + then, c);
+            staged_steps<PM, ORDER, decltype(clamp)::value != 0, TN, 32>(acc, top, o, al + at, Bl + at, al + then, Bl + then, c);
         }
     };
     while (t < ntiles) {
@@ -982,7 +984,7 @@ __device__ __forceinline__ void staged_body(const KParams& p, uint32_t* __restri
     float* const dst = p.C + (int64_t)blockIdx.z * p.stride_c + (int64_t)m * p.N + n;
     float v[TN];
 #pragma unroll
-    for (int j = 0; j < TN; ++j) v[j] = __builtin_ldexpf((float)(j & 1 ? acc[0][j / 2].y : acc[0][j / 2].x), p.out_exp - 112) + 0.0f;   // -0 + 0 is +0
+    for (int j = 0; j < TN; ++j) v[j] = __builtin_ldexpf((float)(j & 1 ? kept[0][j / 2].y : kept[0][j / 2].x), p.out_exp - 112) + 0.0f;   // -0 + 0 is +0
     if (TN == 4 && p.c_vec && n + 3 < p.N) {
         *reinterpret_cast<f32x4_any*>(dst) = f32x4_any{v[0], v[1], v[TN - 2], v[TN - 1]};
     } else if (TN == 2 && p.c_vec && n + 1 < p.N) {
@@ -994,21 +996,23 @@ __device__ __forceinline__ void staged_body(const KParams& p, uint32_t* __restri
     }
 }
 
-template <int TN, int PM, int CONV>
+template <int TN, int PM, int CONV, int ORDER>
 __device__ __forceinline__ void staged_grid(const KParams& p) {
     __shared__ __attribute__((aligned(16))) uint32_t smem[StagedTile<TN>::WORDS];
     const int by = TN == 2 ? blockIdx.x / p.mix_gx_tail : blockIdx.y, bx = TN == 2 ? blockIdx.x - by * p.mix_gx_tail : blockIdx.x;
-    staged_body<TN, PM, CONV>(p, smem, bx * 32, by * 8 * TN);
+    staged_body<TN, PM, CONV, ORDER>(p, smem, bx * 32, by * 8 * TN);
 }
-// The sequential order; 512 lanes.  Row-major operands of any alignment; im2col rows, CONV 1: pieces are channels of one tap (cv_vec), 2: pieces
+// 512 lanes.  Row-major operands of any alignment; im2col rows, CONV 1: pieces are channels of one tap (cv_vec), 2: pieces
 // span at most two filter rows.  One kernel for both waited for its loads where the branch around the second one met (3 x 3 on 56 x 56 x
 // 64 29.6 us, 17.5 so).  lba_half_kernel -> here, one image: 7 x 7 x 512 to 512 channels, 3 x 3, 155 -> 84 us, 14 x 14 x 256 81 -> 45, 28 x
 // 28 x 128 42 -> 24, 56 x 56 x 64 25.3 -> 17.6, a stem (112 x 112 x 3, 7 x 7) 12.6 -> 10.5; 8 of 7 x 7 x 512 177 -> 113 (since tiles are run
-// straight through another 5 to 23 % less, the stem as before).
-template <int TN, int PM>
-__global__ void __launch_bounds__(512, 4) lba_half_staged_kernel(const KParams p) { staged_grid<TN, PM, 0>(p); }
-template <int TN, int PM, int CONV>
-__global__ void __launch_bounds__(512, 4) lba_half_staged_conv_kernel(const KParams p) { staged_grid<TN, PM, CONV>(p); }
+// straight through another 5 to 23 % less, the stem as before).  Products that Q_prod truncates and the chunked order, 256-lane workgroups of 32 x 32 or 64 x 64
+// -> here: 350 x 350 x 700 M4E3 27.9 -> 13.7 us, chunked 28.4 -> 14.2, E4M3 with 5-bit products 55.7 -> 11.9; 700 x 500 x 500 31.7 -> 21.6; chunked 3 x 3 on
+// 14 x 14 x 256 50.0 -> 27.6, 8 of 7 x 7 x 512 125 -> 81; a batch of 60 64 x 64 x 256 11.8 -> 7.9.
+template <int TN, int PM, int ORDER>
+__global__ void __launch_bounds__(512, 4) lba_half_staged_kernel(const KParams p) { staged_grid<TN, PM, 0, ORDER>(p); }
+template <int TN, int PM, int CONV, int ORDER>
+__global__ void __launch_bounds__(512, 4) lba_half_staged_conv_kernel(const KParams p) { staged_grid<TN, PM, CONV, ORDER>(p); }
 
 template <int TM, int TN, int PM, int ORDER, int AMODE, int RANGE>
 __device__ __forceinline__ void rows_plain(const KParams& p) {
