@@ -58,7 +58,7 @@ static void plan_kernel_name(const Plan& pl, bool uf, char* buf, size_t n) {
     } else if (pl.events && pl.kp.h_on) {
         const int am = (pl.kp.conv || pl.amode == 2 ? 2 : 0) + (uf || pl.kp.K % 16 == 0 ? 0 : (pl.kp.conv || pl.amode == 2 ? 2 : 3));   // (operands on a 16-byte boundary)
         if (pl.alone)             snprintf(buf, n, "lba_half_bwd_alone_kernel<%d, %d, %s, %d>", pm, ord, uf ? "true" : "false", am);
-        else if (pl.mix_tail > 0) snprintf(buf, n, "lba_half_bwd_mixed_kernel<%d, %s, %d>", pm, uf ? "true" : "false", am);
+        else if (pl.mix_tail > 0) snprintf(buf, n, "lba_half_bwd_mixed_kernel<%d, %d, %s, %d>", pm, ord, uf ? "true" : "false", am);
         else                      snprintf(buf, n, "lba_half_bwd_kernel<%d, %d, %s, %d>", pm, ord, uf ? "true" : "false", am);
     } else if (pl.events) {
         if (pl.amode == 2 && pl.mix_tail > 0) snprintf(buf, n, "lba_fast_bwd_conv_mixed_kernel<%d, 0, %s>", pm, b);
@@ -236,7 +236,8 @@ int lba_gemm_bwd_diff(const uint8_t* A, const uint8_t* B, float* C, uint32_t* di
 int lba_gemm_bwd_chunked(const uint8_t* A, const uint8_t* B, float* C,
                          uint32_t* of_mask, uint32_t* uf_mask, uint32_t* of_mask2, uint32_t* uf_mask2,
                          int64_t M, int64_t N, int64_t K, lba_qfmt qprod, lba_qfmt qacc, void* hip_stream) {
-    return lba::run(A, B, C, of_mask, uf_mask, M, N, K, qprod, qacc, LBA_ORDER_CHUNK16, 1, hip_stream,
+    const int events = ((of_mask || of_mask2) && !uf_mask && !uf_mask2) ? 3 : 1;
+    return lba::run(A, B, C, of_mask, uf_mask, M, N, K, qprod, qacc, LBA_ORDER_CHUNK16, events, hip_stream,
                     1, 0, 0, 0, of_mask2, uf_mask2);
 }
 

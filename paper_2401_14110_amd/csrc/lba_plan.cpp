@@ -288,8 +288,9 @@ static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, Pl
     if (p->amode == 1 && (p->events == 2 || (p->events == 1 && p->round != LBA_ROUND_FLOOR))) return;
     if (p->amode == 1 && p->events == 1 && p->prod_mode != PM_FLUSH && p->prod_mode != PM_FLUSH_CLAMP &&
         p->prod_mode != PM_TRUNC && p->prod_mode != PM_TRUNC_CLAMP) return;
-    // the recompute call has the mixed grid under the sequential order, and for the DIFF plane under both
-    if (p->events == 1 && p->order != LBA_ORDER_SEQ) return;
+    // the recompute call has the mixed grid under the sequential order, for the DIFF plane and the overflow planes on packed carriers under both
+    const bool chunk_of = p->events == 1 && p->order != LBA_ORDER_SEQ;
+    if (chunk_of && !(p->of_only && p->kp.h_on)) return;
     if (p->amode != 1 && p->prod_mode != PM_IDENT && p->prod_mode != PM_FLUSH && p->prod_mode != PM_FLUSH_CLAMP) return;
     const int64_t gx = (M + 63) / 64, gy = (N + 63) / 64, blocks = gx * gy;
     // those kernels have the 4 x 4 lane block alone outside the mixed grid: a grid too small for it (a single wave per
@@ -329,6 +330,10 @@ static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, Pl
     const int64_t m_main = gx_main * 64;
     const int64_t gx_tail = (M - m_main + 31) / 32, gy_tail = (N + 31) / 32, tail = gx_tail * gy_tail;
     if (gx_main * gy + tail > 2147483647LL) return;
+    // Chunks with their overflow planes: three workgroups to a CU, so that up to 512 are a round either way (12 to 9 us more with a tail), and
+    // beyond them a last round of a few, alone on their CUs, is what a tail takes less time than (3985 x 770 x 771: 819 workgroups
+    // 221 us, 767 and 175 of 32 x 32 187; 12544 x 256 x 768 -31, 10500 x 512 x 768 -24); a tail of more than one to a CU gains nothing.
+    if (chunk_of && (blocks <= 512 || tail > 256)) return;
     double plain = (double)((blocks + 255) / 256);
     if (p->tm == 2 && p->tn == 4) plain = 0.5 * (double)((2 * blocks + 255) / 256) / 0.95;   // the 32 x 64 choice
     const double mixed = (double)(gx_main * gy) / 256.0 + (double)((tail + 255) / 256) * 0.25 / 0.8;
