@@ -11,15 +11,17 @@
 //         (the planner admits kc >= 2^-10).  2|q| and 2|t| - 2 (a zero sum wraps to the top) are below 0x7FE exactly for
 //         the two events, so one minimum and one add put "no event" into bit 15.  Steps with a zero operand are cleared
 //         afterwards, a word at a time, from per-row masks of non-zero codes left by the staging.
-//   Bit 15 of both halves enters a shift register from the top: after 16 steps bit j of each half is step j.
+//   Bit 15 of both halves of two registers enters a shift register of four bytes from the top: after 8 steps bit j of each byte is step j.
 // A k-tile in which no sum can reach R_OF (HalfBound) has no overflow test.  Without an underflow plane such a tile is the forward call's
 // (rows_body, lba_rows.h), and half_bwd_tile runs the others.
 //
-// What bounds it: VALU issue, nine instructions for two chains with the underflow plane and a quiet tile (7 of them at half
-// rate: 18.4 cycles per chain and step by the issue-rate probe).  The FP32 kernel (compares to 64-bit masks, scalar logic, one
-// carry-in add per chain and plane) takes 27.  Measured against it, both planes of 4096 x 768 x 3072: 1703 -> 1396 us (22.7
-// cycles; 2.4 GB of planes leave at 1.7 TB/s), with turns (lba_device.h) 1229, with the 32 steps unrolled 1210 (by four 1240).  Reading
-// operands a step ahead, or two waves per SIMD instead of three, changed nothing.
+// What bounds it: VALU issue, eight and a half instructions for two chains with the underflow plane and a quiet tile (6.5 of them at
+// half rate; full-rate ones of three waves hardly ever meet, so that their number counts: 1209 -> 1399 us with ands and adds for the
+// underflow test, 11 instructions).  The FP32 kernel (compares to 64-bit masks, scalar logic, one carry-in add per chain and plane)
+// takes 27 cycles per chain and step.  Measured against it, both planes of 4096 x 768 x 3072: 1703 -> 1396 us (2.4 GB of planes leave at
+// 1.7 TB/s), with turns (lba_device.h) 1229, with the 32 steps unrolled 1210 (by four 1240), the flags of two registers gathered into
+// one on their way to the shift register (8.5 instructions for 9; 11.5 for 13 where sums can reach R_OF) 1183 and, every sum loud,
+// 1944 -> 1896.  Reading operands a step ahead, or two waves per SIMD instead of three, changed nothing.
 #ifndef LBA_HALF_BWD_H_
 #define LBA_HALF_BWD_H_
 
@@ -44,11 +46,18 @@ __device__ __forceinline__ uint32_t pk_add_u16_sat(uint32_t a, uint32_t b) {   /
 __device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
 }
-// shift register of two chains, shifted by one already: bit 15 of y's halves enters at the top
-__device__ __forceinline__ uint32_t pk_shift_in(uint32_t w, uint32_t y, uint32_t bit15) {
+// shift register of four chains, a byte each, shifted by one already: bit 15 of the halves of y0 and y1 enters at the top
+__device__ __forceinline__ uint32_t pk_shift_in(uint32_t w, uint32_t y0, uint32_t y1, uint32_t tops) {
     uint32_t r;
-    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "v"(bit15), "v"(y), "v"(w));
+    asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0xd8" : "=v"(r) : "v"(w), "v"(__builtin_amdgcn_perm(y1, y0, 0x07050301u)), "v"(tops));   // tops ? y : w
     return r;
+}
+// w[q]: steps 8 q to 8 q + 7 of four chains, a byte each -> w[c]: the 32 steps of chain c
+__device__ __forceinline__ void bytes_to_chains(uint32_t& w0, uint32_t& w1, uint32_t& w2, uint32_t& w3) {
+    const uint32_t a = __builtin_amdgcn_perm(w1, w0, 0x05010400u), b = __builtin_amdgcn_perm(w1, w0, 0x07030602u);
+    const uint32_t c = __builtin_amdgcn_perm(w3, w2, 0x05010400u), d = __builtin_amdgcn_perm(w3, w2, 0x07030602u);
+    w0 = __builtin_amdgcn_perm(c, a, 0x05040100u); w1 = __builtin_amdgcn_perm(c, a, 0x07060302u);
+    w2 = __builtin_amdgcn_perm(d, b, 0x05040100u); w3 = __builtin_amdgcn_perm(d, b, 0x07060302u);
 }
 
 struct HalfBwdConst {
@@ -57,11 +66,11 @@ struct HalfBwdConst {
     uint32_t absmask;          // the accumulator's mask without the sign
     uint32_t of_bias;          // 0x8000 - bits of R_OF
     uint32_t two, minus2, uf_bias;   // 2, -2, 0x8000 - 0x7FE
-    uint32_t bit15;            // 0x80008000
+    uint32_t tops;             // 0x80808080
     __device__ __forceinline__ explicit HalfBwdConst(const KParams& p)
         : kc(as_h2(p.h_kc)), rof(as_h2(p.h_rof)), nrof(as_h2(p.h_rof ^ 0x80008000u)), mask(p.h_mask_a), maskp(p.h_mask_p), absmask(p.h_mask_a & 0x7FFF7FFFu),
-          of_bias(pk_add_u16(0x80008000u, pk_add_u16(~p.h_rof, 0x00010001u))), two(0x00020002u), minus2(0xFFFEFFFEu), uf_bias(0x78027802u), bit15(0x80008000u) {
-        asm volatile("" : "+v"(kc), "+v"(rof), "+v"(nrof), "+v"(mask), "+v"(maskp), "+v"(absmask), "+v"(of_bias), "+v"(two), "+v"(minus2), "+v"(uf_bias), "+v"(bit15));
+          of_bias(pk_add_u16(0x80008000u, pk_add_u16(~p.h_rof, 0x00010001u))), two(0x00020002u), minus2(0xFFFEFFFEu), uf_bias(0x78027802u), tops(0x80808080u) {
+        asm volatile("" : "+v"(kc), "+v"(rof), "+v"(nrof), "+v"(mask), "+v"(maskp), "+v"(absmask), "+v"(of_bias), "+v"(two), "+v"(minus2), "+v"(uf_bias), "+v"(tops));
     }
 };
 
@@ -72,15 +81,14 @@ template <int PM, int ORDER, bool UF, bool QUIET, int TM, int TN, bool PRIO, cla
 __device__ __forceinline__ void half_bwd_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[TM][TN / 2], uint32_t (&of)[TM][TN], uint32_t (&uf)[TM][TN],
                                               uint32_t (&of2)[TM][TN], uint32_t (&uf2)[TM][TN], int pos, ReadA read_a, ReadB read_b,
                                               const HalfBwdConst& c) {
-    constexpr int NJ = TN / 2;
+    constexpr int NJ = TN / 2, G = TM * NJ / 2;                // G: groups of two registers, four chains
+    static_assert(TM * NJ % 2 == 0, "registers in twos");
+    uint32_t wo[G], wu[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) { wo[g] = 0u; wu[g] = 0u; }
     issue_first<PRIO>();
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        uint32_t wo[TM][NJ], wu[TM][NJ];
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) { wo[i][j] = 0u; wu[i][j] = 0u; }
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
             uint32_t a[TM], b[2][NJ];
@@ -112,12 +120,13 @@ __device__ __forceinline__ void half_bwd_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[T
 #pragma unroll
                     for (int j = 0; j < NJ; ++j) asm volatile("v_pk_fma_f16 %0, %1, %2, %3" : "=v"(t[i][j]) : "v"(q[u][i][j]), "v"(c.kc), "v"(acc[i][j]));
                 // phase by phase over the lane's chains, as the forward tile
+#define LBA_GROUP for (int g = 0; g < G; ++g)
 #define LBA_EACH for (int i = 0; i < TM; ++i) _Pragma("unroll") for (int j = 0; j < NJ; ++j)
                 __builtin_amdgcn_sched_barrier(0);
                 issue_last<PRIO>();
                 _Pragma("unroll") LBA_EACH acc[i][j] = as_h2(t[i][j] & c.mask);
-                if (PRIO && !QUIET) { _Pragma("unroll") LBA_EACH wo[i][j] >>= 1; }   // full-rate as well
-                if (PRIO && UF) { _Pragma("unroll") LBA_EACH wu[i][j] >>= 1; }
+                if (!QUIET) { _Pragma("unroll") LBA_GROUP wo[g] >>= 1; }   // full-rate as well
+                if (UF) { _Pragma("unroll") LBA_GROUP wu[g] >>= 1; }
                 __builtin_amdgcn_sched_barrier(0);
                 issue_first<PRIO>();
                 if (!QUIET) {
@@ -125,9 +134,9 @@ __device__ __forceinline__ void half_bwd_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[T
                     _Pragma("unroll") LBA_EACH asm("v_pk_max_f16 %0, %0, %1" : "+v"(acc[i][j]) : "v"(c.nrof));
                     __builtin_amdgcn_sched_barrier(0);
                     uint32_t y[TM][NJ];
-                    _Pragma("unroll") LBA_EACH y[i][j] = pk_add_u16(t[i][j] & c.absmask, c.of_bias);
+                    _Pragma("unroll") LBA_EACH y[i][j] = (t[i][j] & c.absmask) + c.of_bias;   // at most 0x7FFF + 0x8000: no carry between the halves
                     __builtin_amdgcn_sched_barrier(0);
-                    _Pragma("unroll") LBA_EACH wo[i][j] = pk_shift_in(PRIO ? wo[i][j] : wo[i][j] >> 1, y[i][j], c.bit15);
+                    _Pragma("unroll") LBA_GROUP wo[g] = pk_shift_in(wo[g], y[2 * g / NJ][2 * g % NJ], y[(2 * g + 1) / NJ][(2 * g + 1) % NJ], c.tops);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 if (UF) {
@@ -138,10 +147,19 @@ __device__ __forceinline__ void half_bwd_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[T
                     __builtin_amdgcn_sched_barrier(0);
                     _Pragma("unroll") LBA_EACH t[i][j] = pk_add_u16_sat(t[i][j], c.uf_bias);
                     __builtin_amdgcn_sched_barrier(0);
-                    _Pragma("unroll") LBA_EACH wu[i][j] = pk_shift_in(PRIO ? wu[i][j] : wu[i][j] >> 1, t[i][j], c.bit15);
+                    _Pragma("unroll") LBA_GROUP wu[g] = pk_shift_in(wu[g], t[2 * g / NJ][2 * g % NJ], t[(2 * g + 1) / NJ][(2 * g + 1) % NJ], c.tops);
                     __builtin_amdgcn_sched_barrier(0);
                 }
 #undef LBA_EACH
+#undef LBA_GROUP
+            }
+            if (s % 4 == 3) {                                  // eight steps
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const int ch = 4 * g + 2 * h + s / 4;
+                    of[ch / TN][ch % TN] = wo[g];
+                    if (UF) uf[ch / TN][ch % TN] = wu[g];
+                }
             }
         }
         if (ORDER == LBA_ORDER_CHUNK16) {                      // the mode is the multiply-add's (UF) or the forward call's
@@ -169,22 +187,18 @@ __device__ __forceinline__ void half_bwd_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[T
                     }
                 }
         }
+    }
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+    for (int ch = 0; ch < TM * TN; ch += 4) {
+        const auto each = [&](uint32_t (&w)[TM][TN]) {
+            bytes_to_chains(w[ch / TN][ch % TN], w[(ch + 1) / TN][(ch + 1) % TN], w[(ch + 2) / TN][(ch + 2) % TN], w[(ch + 3) / TN][(ch + 3) % TN]);
+        };
+        each(of);
+        if (UF) {
+            each(uf);
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                if (h == 0) {
-                    of[i][2 * j] = wo[i][j]; uf[i][2 * j] = wu[i][j];      // both halves' first 16 steps, sorted below
-                } else {
-                    const uint32_t o = of[i][2 * j], x = uf[i][2 * j];
-                    of[i][2 * j]     = __builtin_amdgcn_perm(wo[i][j], o, 0x05040100u);
-                    of[i][2 * j + 1] = __builtin_amdgcn_perm(wo[i][j], o, 0x07060302u);
-                    if (UF) {                                  // bits say "no event": inverted
-                        uf[i][2 * j]     = ~__builtin_amdgcn_perm(wu[i][j], x, 0x05040100u);
-                        uf[i][2 * j + 1] = ~__builtin_amdgcn_perm(wu[i][j], x, 0x07060302u);
-                    }
-                }
-            }
+            for (int u = ch; u < ch + 4; ++u) uf[u / TN][u % TN] = ~uf[u / TN][u % TN];   // bits say "no event": inverted
+        }
     }
     issue_last<PRIO>();
 }
