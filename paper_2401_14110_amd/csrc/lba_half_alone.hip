@@ -15,11 +15,16 @@
 
 namespace lba {
 
-template <int PM, int ORDER, bool UF, int AMODE>
-__global__ void __launch_bounds__(256, UF ? (ORDER == LBA_ORDER_CHUNK16 ? 2 : 3) : 1) lba_half_bwd_alone_kernel(const KParams p) {
-    __shared__ __attribute__((aligned(16))) uint32_t smem[UF ? 2 * HalfTile<4, 4, 16>::STAGE : RowTile<16, 8>::WORDS];
-    if constexpr (UF) half_bwd_body<4, 4, PM, ORDER, AMODE, false>(p, smem, blockIdx.x * 64, blockIdx.y * 64);
-    else              rows_body<16, 8, PM, ORDER, AMODE, 0, true, true>(p, smem, blockIdx.x * 64, blockIdx.y * 64);
+// The recompute call on at most 256 workgroups of 64 x 64.  T 2: workgroups of 32 x 32, a CU's share of which is the smaller the fewer
+// there are, and whose chains are a fourth of a wave's work.  T 4: 64 x 64, for the overflow plane under the sequential order on more than 192
+// of them, where a wave alone on its SIMD issues as much as the four of the small ones (900 x 900 x 700, training step, 151 us, 152).
+// 64 x 64 -> 32 x 32, both planes: 500 x 500 x 700 143 -> 60 us, 700 x 700 145 -> 78, 1024 x 1024 142 -> 122; training steps, K = 700:
+// 500 x 500 115 -> 84, 700 x 700 125 -> 103, 1024 x 700 145 -> 133, in chunks 149 -> 108, 179 -> 131, 194 -> 180, 1024 x 1024 210 -> 207.
+template <int T, int PM, int ORDER, bool UF, int AMODE>
+__global__ void __launch_bounds__(256, UF ? (ORDER == LBA_ORDER_CHUNK16 ? 2 : 3) : (T == 4 ? 1 : 2)) lba_half_bwd_alone_kernel(const KParams p) {
+    __shared__ __attribute__((aligned(16))) uint32_t smem[UF ? 2 * HalfTile<T, T, 16>::STAGE : RowTile<4 * T, 2 * T>::WORDS];
+    if constexpr (UF) half_bwd_body<T, T, PM, ORDER, AMODE, false>(p, smem, blockIdx.x * 16 * T, blockIdx.y * 16 * T);
+    else              rows_body<4 * T, 2 * T, PM, ORDER, AMODE, 0, true, true>(p, smem, blockIdx.x * 16 * T, blockIdx.y * 16 * T);
 }
 template <int PM, int ORDER, int AMODE>
 __global__ void __launch_bounds__(256, 1) lba_half_alone_kernel(const KParams p) {
@@ -31,7 +36,10 @@ __global__ void __launch_bounds__(256, 2) lba_half_alone_mixed_kernel(const KPar
 
 template <int PM, int ORDER, bool UF, int AMODE>
 static hipError_t launch_bwd(const Plan& pl, hipStream_t st) {
-    hipLaunchKernelGGL((lba_half_bwd_alone_kernel<PM, ORDER, UF, AMODE>), dim3(pl.grid_x, pl.grid_y, 1), dim3(256), 0, st, pl.kp);
+    const dim3 grid(pl.grid_x, pl.grid_y, 1), block(256);
+    if (pl.tm == 2)                                        hipLaunchKernelGGL((lba_half_bwd_alone_kernel<2, PM, ORDER, UF, AMODE>), grid, block, 0, st, pl.kp);
+    else if constexpr (!UF && ORDER == LBA_ORDER_SEQ) hipLaunchKernelGGL((lba_half_bwd_alone_kernel<4, PM, ORDER, UF, AMODE>), grid, block, 0, st, pl.kp);
+    else                                                   return hipErrorInvalidValue;
     return hipGetLastError();
 }
 template <int PM, int ORDER>
@@ -47,6 +55,7 @@ static hipError_t launch_bwd(const Plan& pl, hipStream_t st) {
 }
 // truncated products under the sequential order only (lba_half_bwd.hip)
 hipError_t launch_half_bwd_alone(const Plan& pl, hipStream_t st) {
+    if (pl.events != 1 || pl.mix_tail != 0 || pl.tm != pl.tn || (pl.tm != 2 && pl.tm != 4)) return hipErrorInvalidValue;
     if (pl.prod_mode == PM_TRUNC) return pl.order == LBA_ORDER_SEQ ? launch_bwd<PM_TRUNC, LBA_ORDER_SEQ>(pl, st) : hipErrorInvalidValue;
     if (pl.prod_mode != PM_FLUSH) return hipErrorInvalidValue;
     return pl.order == LBA_ORDER_SEQ ? launch_bwd<PM_FLUSH, LBA_ORDER_SEQ>(pl, st) : launch_bwd<PM_FLUSH, LBA_ORDER_CHUNK16>(pl, st);

@@ -578,6 +578,11 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
     p.alone = kp.h_on && !kp.h_range && p.kpar == 0 && !p.staged &&
               (p.mix_tail > 0 ? !p.events && p.prod_mode == PM_FLUSH && kp.mix_main == 0 && kp.mix_half > 0 && total < 512
                               : p.tm == 4 && p.tn == 4 && total <= 256 && (p.events || (p.prod_mode == PM_TRUNC && !conv)));
+    if (p.alone && p.events && (total <= 192 || !p.of_only || order == LBA_ORDER_CHUNK16)) {   // smaller ones (lba_half_alone.hip)
+        p.tm = p.tn = 2;
+        p.grid_x = (int)((M + 31) / 32);
+        p.grid_y = (int)((N + 31) / 32);
+    }
     *out = p;
     return LBA_OK;
 }
