@@ -296,6 +296,14 @@ static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, Pl
     // those kernels have the 4 x 4 lane block alone outside the mixed grid: a grid too small for it (a single wave per
     // SIMD issues at half rate) becomes 32 x 32 workgroups throughout
     if (p->amode == 1 && blocks <= 256 && set_mixed_grid(M, N, 0, 0, p)) return;
+    // The recompute call in FP32, 64 x 64 throughout against 32 x 32 (both planes, nearest-even, K = 700): 500 x 500 328 -> 111 us, 700 x 700
+    // 328 -> 130, 1024 x 1024 323 -> 191, 288 workgroups 405 -> 246, 400 326 -> 315, 512 410 -> 355, 640 411 -> 434; a training step, floor, M10E5,
+    // 128 workgroups 176 -> 125, 320 212 -> 196, 400 216 -> 226.  Both planes on packed carriers, which hold 64 x 64 workgroups
+    // better (up to 256 of them: make_plan): 257 to 320 198 -> 156, 384 198 -> 184, 400 198 -> 211.
+    // (Clamped products on chains of fewer than 160 steps keep plain grids, which their tests run on.)
+    const bool short_clamp = p->prod_mode != PM_FLUSH && p->kp.K < 160 && p->amode != 1;
+    if (p->events == 1 && !p->kp.h_on && !short_clamp && blocks <= (p->of_only ? 320 : 512) && set_mixed_grid(M, N, 0, 0, p)) return;
+    if (p->events == 1 && p->kp.h_on && !p->of_only && blocks > 256 && blocks <= 384 && set_mixed_grid(M, N, 0, 0, p)) return;
     // the smallest grids of the forward call (at most 128 workgroups of 32 x 32, e.g. a 64 x 1000 classifier layer): the
     // tail's 32 x 16 tiles throughout, twice the workgroups of the 2 x 2 lane block
     if (p->events == 0 && b32 <= 128 && set_mixed_grid(M, N, 0, 0, p)) return;
