@@ -51,7 +51,8 @@ static hipError_t launch_bwd(const Plan& pl, hipStream_t st) {
     } else if (pl.kp.conv) {
         return hipErrorInvalidValue;
     }
-    return uf ? launch_bwd<PM, ORDER, true, 0>(pl, st) : aligned ? launch_bwd<PM, ORDER, false, 0>(pl, st) : launch_bwd<PM, ORDER, false, 3>(pl, st);
+    if (uf) return pl.kp.N % 4 ? launch_bwd<PM, ORDER, true, 3>(pl, st) : launch_bwd<PM, ORDER, true, 0>(pl, st);
+    return aligned ? launch_bwd<PM, ORDER, false, 0>(pl, st) : launch_bwd<PM, ORDER, false, 3>(pl, st);
 }
 // truncated products under the sequential order only (lba_half_bwd.hip)
 hipError_t launch_half_bwd_alone(const Plan& pl, hipStream_t st) {

@@ -204,12 +204,44 @@ __device__ __forceinline__ void half_bwd_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[T
 }
 
 // Stores a lane's words (one per chain, first step in bit 0) as word `word` of a plane; non-temporal, see store_event_words.
-template <int TM, int TN>
+// 16 lanes a row.  ENDS (N no multiple of 4): where the matrix ends inside a lane's columns, that lane stores the last TN words of the
+// row, some of them its neighbour's (which stores the same), so that a row still leaves by one store an instruction: word by word the end
+// of a row went to memory as partial lines of its own.  Both planes, us, before -> so: 45658 x 106 x 729 710 -> 596 (104 columns 565),
+// 30000 x 99 x 640 420 -> 364, 20000 x 250 x 500 413 -> 381.  Kernels of their own (AMODE 3): the address and masks beside the ordinary
+// stores cost these 1 % (45658 x 128 x 729 560 -> 565).
+template <int TM, int TN, bool ENDS>
 __device__ __forceinline__ void store_half_words(uint32_t* __restrict__ plane, int word, const uint32_t (&w)[TM][TN], int m0, int n0,
                                                  int tx, int ty, const KParams& p) {
+    static_assert(TN == 4 || TN == 2, "4 or 2 outputs per lane along n");
+    const int left = p.N - n0, over = p.N & (TN - 1);          // columns from n0; columns of the lane in which the matrix ends
+    const int n = n0 + tx * TN;
+    uint32_t* row = plane + ((int64_t)word * p.M + m0 + ty * TM) * p.N + n;
+    if (ENDS && p.c_vec && over != 0 && left > TN && left < 16 * TN) {   // uniform
+        const bool last = n < p.N && n + TN - 1 >= p.N;
+        row -= last ? TN - over : 0;
+        const uint32_t by1 = last && over == 1 ? ~0u : 0u, by2 = last && over == 2 ? ~0u : 0u, by3 = last && over == 3 ? ~0u : 0u;
+#pragma unroll
+        for (int i = 0; i < TM; ++i, row += p.N) {
+            uint32_t x[2 * TN];                                // the neighbour's words and the lane's
+#pragma unroll
+            for (int j = 0; j < TN; ++j) { x[j] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[i][j], 0x111, 0xF, 0xF, true); x[TN + j] = w[i][j]; }
+            uint32_t v[TN];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {                     // word j + over of the eight (masks: a choice between them went to scratch memory)
+                const uint32_t one = x[j + 1], two = x[TN == 4 ? j + 2 : j], three = x[TN == 4 ? j + 3 : j], own = x[TN + j];
+                v[j] = (one & by1) | (~by1 & ((two & by2) | (~by2 & ((three & by3) | (~by3 & own)))));
+            }
+            if (m0 + ty * TM + i < p.M && n < p.N) {
+                if (TN == 4) __builtin_nontemporal_store(u32x4_any{v[0], v[1], v[TN - 2], v[TN - 1]}, reinterpret_cast<u32x4_any*>(row));
+                else         __builtin_nontemporal_store(u32x2_any{v[0], v[1]}, reinterpret_cast<u32x2_any*>(row));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-        const int m = m0 + ty * TM + i, n = n0 + tx * TN;
+        const int m = m0 + ty * TM + i;
         if (m >= p.M) continue;
         uint32_t* dst = plane + ((int64_t)word * p.M + m) * p.N + n;
         if (TN == 4 && p.c_vec && n + 3 < p.N) {
@@ -236,7 +268,8 @@ __device__ __forceinline__ void mark_bricks_lsb(const uint32_t (&of)[TM][TN], in
     mark_bricks_of_wave<TM, TN>(any, m0, n0, w, tx, ty, p);
 }
 
-// The recompute call with an underflow plane (without one: rows_body, lba_rows.h).  TURNS: not where a wave has its SIMD to itself.
+// The recompute call with an underflow plane (without one: rows_body, lba_rows.h).  AMODE 0: rows of A, 2: im2col rows, 3: rows of A, N no
+// multiple of 4.  TURNS: not where a wave has its SIMD to itself.
 template <int TM, int TN, int PM, int ORDER, int AMODE, bool TURNS = (TM * TN > 4)>
 __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __restrict__ smem, int m0, int n0) {
     using T = HalfTile<TM, TN, 16>;
@@ -335,7 +368,7 @@ __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __rest
                 }
                 if (ORDER == LBA_ORDER_SEQ && p.map_dx) mark_bricks_lsb<TM, TN>(of, m0, n0, w, tx, ty, p);
             }
-            if (p.of_mask) store_half_words<TM, TN>(p.of_mask, w, of, m0, n0, tx, ty, p);
+            if (p.of_mask) store_half_words<TM, TN, AMODE == 3>(p.of_mask, w, of, m0, n0, tx, ty, p);
             if (p.uf_mask) {
 #pragma unroll
                 for (int i = 0; i < TM; ++i) {
@@ -343,7 +376,7 @@ __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __rest
 #pragma unroll
                     for (int j = 0; j < TN; ++j) uf[i][j] &= na & *reinterpret_cast<const uint32_t*>(&nzb[t & 1][tx * TN + j][2 * part]);
                 }
-                store_half_words<TM, TN>(p.uf_mask, w, uf, m0, n0, tx, ty, p);
+                store_half_words<TM, TN, AMODE == 3>(p.uf_mask, w, uf, m0, n0, tx, ty, p);
             }
             if (ORDER == LBA_ORDER_CHUNK16 && ((w & 15) == 15 || w == words - 1)) {
                 // two chunks per word: a second-level word is complete after 16 of them
@@ -353,8 +386,8 @@ __device__ __forceinline__ void half_bwd_body(const KParams& p, uint32_t* __rest
                 for (int i = 0; i < TM; ++i)
 #pragma unroll
                     for (int j = 0; j < TN; ++j) { of2[i][j] &= vmask; uf2[i][j] &= vmask; }
-                if (p.of_mask2) store_half_words<TM, TN>(p.of_mask2, w >> 4, of2, m0, n0, tx, ty, p);
-                if (p.uf_mask2) store_half_words<TM, TN>(p.uf_mask2, w >> 4, uf2, m0, n0, tx, ty, p);
+                if (p.of_mask2) store_half_words<TM, TN, AMODE == 3>(p.of_mask2, w >> 4, of2, m0, n0, tx, ty, p);
+                if (p.uf_mask2) store_half_words<TM, TN, AMODE == 3>(p.uf_mask2, w >> 4, uf2, m0, n0, tx, ty, p);
 #pragma unroll
                 for (int i = 0; i < TM; ++i)
 #pragma unroll

@@ -5,7 +5,7 @@
 namespace lba {
 
 // The grids of lba_fast_bwd_kernel and lba_fast_bwd_mixed_kernel.  With an underflow plane AMODE 0: a row-major matrix of any code format
-// with E <= 4, 2: im2col rows of an NHWC tensor; without one as lba_half_kernel.
+// with E <= 4, 2: im2col rows of an NHWC tensor, 3: as 0, N no multiple of 4; without one as lba_half_kernel.
 // Chunks without an underflow plane: at four waves per SIMD 33 registers are spilled, which 819 workgroups and more hide (3985 x 770 x 771,
 // training step 648 us against 662 at three, 630 with a tail) and 257 to 768 do not (24576 x 64 x 1024 114 against 109).
 template <int PM, int ORDER, bool UF, int AMODE>
@@ -59,7 +59,7 @@ static hipError_t launch_product(const Plan& pl, hipStream_t st) {
     const bool uf = pl.kp.uf_mask != nullptr || pl.kp.uf_mask2 != nullptr;
     const bool aligned = pl.kp.ld_align == 16;
     if (pl.kp.conv) return uf ? launch_one<PM, true, 2>(pl, st) : aligned && pl.kp.cv_vec ? launch_one<PM, false, 2>(pl, st) : launch_one<PM, false, 4>(pl, st);
-    return uf ? launch_one<PM, true, 0>(pl, st) : aligned ? launch_one<PM, false, 0>(pl, st) : launch_one<PM, false, 3>(pl, st);
+    return uf ? (pl.kp.N % 4 ? launch_one<PM, true, 3>(pl, st) : launch_one<PM, true, 0>(pl, st)) : aligned ? launch_one<PM, false, 0>(pl, st) : launch_one<PM, false, 3>(pl, st);
 }
 
 hipError_t launch_half_bwd(const Plan& pl, hipStream_t st) {

@@ -56,7 +56,8 @@ static void plan_kernel_name(const Plan& pl, bool uf, char* buf, size_t n) {
     } else if (pl.events == 2) {
         snprintf(buf, n, pl.mix_tail > 0 ? "lba_fast_diff_mixed_kernel<%d, %d, %d>" : "lba_fast_diff_kernel<%d, %d, %d>", pm, pl.round, ord);
     } else if (pl.events && pl.kp.h_on) {
-        const int am = (pl.kp.conv || pl.amode == 2 ? 2 : 0) + (uf || pl.kp.K % 16 == 0 ? 0 : (pl.kp.conv || pl.amode == 2 ? 2 : 3));   // (operands on a 16-byte boundary)
+        const bool im2col = pl.kp.conv || pl.amode == 2;
+        const int am = uf ? (im2col ? 2 : pl.kp.N % 4 ? 3 : 0) : pl.kp.K % 16 == 0 ? (im2col ? 2 : 0) : (im2col ? 4 : 3);   // (operands on a 16-byte boundary)
         if (pl.alone)             snprintf(buf, n, "lba_half_bwd_alone_kernel<%d, %d, %d, %s, %d>", pl.tm, pm, ord, uf ? "true" : "false", am);
         else if (pl.mix_tail > 0) snprintf(buf, n, "lba_half_bwd_mixed_kernel<%d, %d, %s, %d>", pm, ord, uf ? "true" : "false", am);
         else                      snprintf(buf, n, "lba_half_bwd_kernel<%d, %d, %s, %d>", pm, ord, uf ? "true" : "false", am);

@@ -1,0 +1,35 @@
+"""Both planes of matrices that end inside a lane's columns, on every grid of the packed recompute call, bit for bit; nothing beyond a plane is written."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2401_14110_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ref():
+    from oracle import lba_ref
+    lba_ref.build()
+    return lba_ref
+
+
+# 32 x 32 workgroups alone, 64 x 64 ones, 64 x 64 ones before 32 x 32
+@pytest.mark.parametrize("M", [35, 64 * 390, 64 * 520 + 3])
+@pytest.mark.parametrize("N", [1, 3, 5, 33, 34, 35, 61, 62, 63])
+def test_widths(ref, M, N):
+    K = 70
+    rng = np.random.default_rng([M, N, K])
+    A, B = ((rng.integers(0, 2, s) * 128 + rng.integers(0, 72, s)).astype(np.uint8) for s in ((M, K), (N, K)))
+    dA, dB = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    rows = np.unique(np.concatenate([[0, 1, M - 2, M - 1], rng.choice(M, 30, replace=False)]))
+    qp, qa = (5, 7, 12, 0), (4, 7, 9, 0)
+    for order, right in [(0, ref.gemm_bwd(np.ascontiguousarray(A[rows]), B, ref.QFmt(*qp), ref.QFmt(*qa))),
+                         (1, ref.gemm_bwd(np.ascontiguousarray(A[rows]), B, ref.QFmt(*qp), ref.QFmt(*qa), order=1, level2=True))]:
+        assert binding.lba_plan_kernel_name(M, N, K, qp, qa, order, 1).startswith("lba_half_bwd_")
+        got = binding.gemm_bwd_chunked(dA, dB, qp, qa) if order else binding.gemm_bwd(dA, dB, qp, qa)
+        torch.cuda.synchronize()
+        assert np.array_equal(got[0].cpu().numpy()[rows].view(np.uint32), np.ascontiguousarray(right[0]).view(np.uint32))
+        for g, r in zip(got[1:], right[1:]):
+            assert np.array_equal(g.cpu().numpy()[:, rows].view(np.uint32), r)
