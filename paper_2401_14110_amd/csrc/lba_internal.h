@@ -112,9 +112,13 @@ const InSpec& e4m3_spec();
 int validate_shapes(int64_t M, int64_t N, int64_t K);
 int validate_fmt(const lba_qfmt& q);
 
+// What A's rows are: a matrix's own, or im2col rows of an NHWC tensor, whose pieces of 16 codes are channels of one tap (C a multiple of 16) or
+// gathered from several taps.
+enum ARows { ROWS_MATRIX = 0, ROWS_TAPS = 1, ROWS_GATHERED = 2 };
+
 // Builds the plan (pointers in kp are left null).  Returns an lba status code.
 int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qprod, const lba_qfmt& qacc,
-              int order, int events, Plan* out, int64_t batch = 1, const InSpec* in = nullptr, bool conv = false);
+              int order, int events, Plan* out, int64_t batch = 1, const InSpec* in = nullptr, ARows rows = ROWS_MATRIX);
 
 // Gradient products: how many slices of the summation index s a launch of `blocks` workgroups (4 waves
 // of 16 rows each) is cut into so that the chip has enough waves, and the slice length (a multiple of 4).

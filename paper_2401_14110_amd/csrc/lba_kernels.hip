@@ -108,7 +108,8 @@ static int run(const uint8_t* A, const uint8_t* B, float* C, uint32_t* of_mask, 
                void* brick_ws = nullptr) {
     Plan pl;
     if (batch < 0 || batch > 65535 || stride_a < 0 || stride_b < 0 || stride_c < 0) return LBA_ERR_SHAPE;
-    int rc = make_plan(M, N, K, qprod, qacc, order, events, &pl, batch, in, conv != nullptr);
+    const ARows rows = !conv ? ROWS_MATRIX : conv->c % 16 == 0 ? ROWS_TAPS : ROWS_GATHERED;
+    int rc = make_plan(M, N, K, qprod, qacc, order, events, &pl, batch, in, rows);
     if (rc != LBA_OK) return rc;
     if (in) pl.kp.out_exp -= in->delta;                        // the operand biases' power-of-two scale
     if (M == 0 || N == 0 || batch == 0) return LBA_OK;

@@ -272,7 +272,7 @@ static bool set_mixed_grid(int64_t M, int64_t N, int64_t gx_main, int64_t gx_hal
 }
 
 // staged: waves of their own stage where the grid is 32 x 16 or 32 x 32 tiles throughout
-static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, Plan* p) {
+static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, ARows rows, Plan* p) {
     p->mix_tail = 0;
     if (p->kernel != KERNEL_FAST || p->rne_odd || batch != 1) return;
     const int64_t b32 = ((M + 31) / 32) * ((N + 31) / 32), b16 = ((M + 31) / 32) * ((N + 15) / 16);
@@ -302,7 +302,13 @@ static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, Pl
     // better (up to 256 of them: make_plan): 257 to 320 198 -> 156, 384 198 -> 184, 400 198 -> 211.
     // (Clamped products on chains of fewer than 160 steps keep plain grids, which their tests run on.)
     const bool short_clamp = p->prod_mode != PM_FLUSH && p->kp.K < 160 && p->amode != 1;
-    if (p->events == 1 && !p->kp.h_on && !short_clamp && blocks <= (p->of_only ? 320 : 512) && set_mixed_grid(M, N, 0, 0, p)) return;
+    // Rows gathered from several taps cost small tiles more, each of which gathers its own: both planes up to 384 (3 x 3 on 3, 5 x 5 on 3, 15 x 15 on 1
+    // channels, floor, M10E5, times of 32 x 32 over 64 x 64: 270 workgroups 0.93, 0.86, 0.83, 384 0.98, 0.95, 0.92, 441 1.20, 1.15, 1.15, 500 1.15, 1.14,
+    // 1.13; on 16 channels 0.71, 0.77, 0.94, 0.93), the overflow plane alone up to 320 from two k-tiles on (K = 75, 320 workgroups, 0.98, 384 1.08; K = 27 257
+    // to 320 1.05) and up to 256 where the product is truncated (270 workgroups 1.06 to 1.18).
+    const bool parts = rows == ROWS_GATHERED;
+    const int64_t most = !p->of_only ? (parts ? 384 : 512) : !parts || (p->amode == 2 && p->kp.K >= 64) ? 320 : 256;
+    if (p->events == 1 && !p->kp.h_on && !short_clamp && blocks <= most && set_mixed_grid(M, N, 0, 0, p)) return;
     if (p->events == 1 && p->kp.h_on && !p->of_only && blocks > 256 && blocks <= 384 && set_mixed_grid(M, N, 0, 0, p)) return;
     // the smallest grids of the forward call (at most 128 workgroups of 32 x 32, e.g. a 64 x 1000 classifier layer): the
     // tail's 32 x 16 tiles throughout, twice the workgroups of the 2 x 2 lane block
@@ -350,8 +356,9 @@ static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, Pl
 }
 
 int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_qfmt& qa_in,
-              int order, int events, Plan* out, int64_t batch, const InSpec* in_spec, bool conv) {
+              int order, int events, Plan* out, int64_t batch, const InSpec* in_spec, ARows rows) {
     const InSpec& in = in_spec ? *in_spec : e4m3_spec();
+    const bool conv = rows != ROWS_MATRIX;
     int rc = validate_shapes(M, N, K);
     if (rc != LBA_OK) return rc;
     if ((rc = validate_fmt(qp_in)) != LBA_OK) return rc;
@@ -578,7 +585,7 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
     const bool stages = p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH ||
                         (p.prod_mode == PM_TRUNC && !conv && (K > 512 || (K >= 224 && ((M + 31) / 32) * ((N + 31) / 32) > 64)));
     const bool staged = !p.events && (kp.h_on ? !kp.h_range && stages : rne32 && order == LBA_ORDER_SEQ && (p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH));
-    if (p.kpar == 0) plan_mixed_grid(M, N, batch, staged, &p);
+    if (p.kpar == 0) plan_mixed_grid(M, N, batch, staged, rows, &p);
     p.staged = staged && (p.mix_tail > 0 ? kp.mix_tail16 && kp.mix_main + kp.mix_half == 0 : p.tm == 2 && p.tn == 2);
     // Waves alone on their SIMDs (lba_half_alone.hip, which has the figures): at most one workgroup of 64 x 64 per CU (only the recompute call
     // and truncated products have so few: pick_tile), or one of 48 x 64 with fewer of the tail's 32 x 32 behind them than there are CUs

@@ -1,0 +1,74 @@
+"""The plans that the entry points launch (tests/launch_recorder.cpp), on the host: grids that fit the kernel's tiles, and the plan of the planes asked for."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+from paper_2401_14110_amd.binding import lba_conv2d_desc, lba_qfmt
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+FIELDS = ("grid_x", "grid_y", "tm", "tn", "mix_main", "mix_half", "mix_tail", "mix_tail16", "packed", "staged", "alone", "of_only", "kpar")
+
+
+class Launched(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in FIELDS]
+
+
+@pytest.fixture(scope="module")
+def rec(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("launches") / "launch_recorder.so")
+    csrc = os.path.join(ROOT, "paper_2401_14110_amd", "csrc")
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "-O1", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-shared",
+                    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument",
+                    "-I", os.path.join(ROOT, "include"), "-I", csrc, os.path.join(csrc, "lba_kernels.hip"), os.path.join(csrc, "lba_plan.cpp"),
+                    os.path.join(ROOT, "tests", "launch_recorder.cpp"), "-o", so], check=True)
+    lib = ctypes.CDLL(so)
+    vp, i64, i32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32
+    lib.take_launched.restype = ctypes.c_char_p
+    lib.lba_conv2d.argtypes = [vp, vp, vp, lba_conv2d_desc, i64, lba_qfmt, lba_qfmt, i32, vp]
+    lib.lba_conv2d_bwd.argtypes = [vp, vp, vp, vp, vp, lba_conv2d_desc, i64, lba_qfmt, lba_qfmt, i32, vp]
+    return lib
+
+
+def taken(lib):
+    out = Launched()
+    name = lib.take_launched(ctypes.byref(out)).decode()
+    return name, {n: getattr(out, n) for n in FIELDS}
+
+
+BUF = 1 << 20        # (never read: an address on a 16-byte boundary)
+PACKED, TRUNC = ((5, 7, 12, 0), (4, 7, 9, 0)), ((5, 4, 12, 0), (4, 7, 9, 0))
+
+
+def conv(lib, n, h, w, c, cout, k, formats, planes, order=0):
+    d = lba_conv2d_desc(n, h, w, c, k, k, 1, k // 2)
+    qp, qa = (lba_qfmt(*f) for f in formats)
+    if planes is None:
+        rc = lib.lba_conv2d(BUF, BUF, BUF, d, cout, qp, qa, order, None)
+    else:
+        rc = lib.lba_conv2d_bwd(BUF, BUF, BUF, BUF if "o" in planes else None, BUF if "u" in planes else None, d, cout, qp, qa, order, None)
+    assert rc == 0
+    o = h + 2 * (k // 2) - k + 1, w + 2 * (k // 2) - k + 1
+    return (n * o[0] * o[1], cout) + taken(lib)
+
+
+def fits(M, N, p):
+    """A plain grid of the plan's tiles, or the mixed grid's regions."""
+    up = lambda a, b: -(-a // b)  # noqa: E731
+    if p["mix_tail"] == 0:
+        return (p["grid_x"], p["grid_y"]) == (up(M, 16 * p["tm"]), up(N, 16 * p["tn"]))
+    return p["grid_x"] == p["mix_main"] + p["mix_tail"] and p["grid_y"] == 1
+
+
+WIDE, WIDE_TRUNC = ((5, 7, 12, 0), (5, 10, 9, 0)), ((5, 4, 12, 0), (5, 10, 9, 0))
+
+
+# FP32 carriers: how many workgroups of 64 x 64 are cut into 32 x 32 ones throughout; channels in multiples of 16, and pieces gathered from taps
+@pytest.mark.parametrize("c,k,formats,planes,most", [(16, 3, WIDE, "ou", 512), (16, 3, WIDE_TRUNC, "ou", 512), (3, 3, WIDE, "ou", 384), (6, 3, WIDE, "ou", 384),
+                                                     (20, 3, WIDE, "ou", 384), (3, 5, WIDE_TRUNC, "ou", 384)])
+def test_small_fp32_recompute(rec, c, k, formats, planes, most):
+    for blocks in (256, 257, 320, 321, 384, 385, 512, 513):
+        M, N, name, p = conv(rec, 1, 64, blocks, c, 64, k, formats, planes)
+        assert M == 64 * blocks and name == "launch_fast_bwd" and not p["packed"] and fits(M, N, p)
+        assert (p["mix_tail"] == 2 * blocks * 2 and p["mix_main"] == 0) == (blocks <= most), (blocks, p)
