@@ -5,7 +5,8 @@
 
 namespace lba {
 hipError_t launch_fast_bwd_conv(const Plan& pl, hipStream_t st) {
-    if (pl.amode != 2 || pl.events != 1 || pl.round != LBA_ROUND_FLOOR || pl.order != LBA_ORDER_SEQ || pl.kp.batch != 1)
+    if (pl.amode != 2 || pl.events != 1 || pl.round != LBA_ROUND_FLOOR || pl.order != LBA_ORDER_SEQ || pl.kp.batch != 1 ||
+        pl.tm != 4 || pl.tn != 4)
         return hipErrorInvalidValue;
     if (pl.prod_mode != PM_FLUSH && pl.prod_mode != PM_FLUSH_CLAMP) return hipErrorInvalidValue;
     const dim3 block(256);

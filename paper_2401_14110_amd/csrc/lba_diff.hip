@@ -12,7 +12,7 @@ static hipError_t launch_diff_rounding(const Plan& pl, hipStream_t st) {
         if (mixed) hipLaunchKernelGGL((lba_fast_diff_mixed_kernel<PM, RND, ORDER>), grid, block, 0, st, pl.kp);      \
         else       hipLaunchKernelGGL((lba_fast_diff_kernel<PM, RND, ORDER>), grid, block, 0, st, pl.kp);            \
     } while (0)
-    if (pl.amode || (pl.prod_mode != PM_FLUSH && pl.prod_mode != PM_FLUSH_CLAMP)) return hipErrorInvalidValue;
+    if (pl.amode || pl.tm != 4 || pl.tn != 4 || (pl.prod_mode != PM_FLUSH && pl.prod_mode != PM_FLUSH_CLAMP)) return hipErrorInvalidValue;
     if (pl.order == LBA_ORDER_CHUNK16) {
         if (pl.prod_mode == PM_FLUSH) LBA_DIFF(PM_FLUSH, LBA_ORDER_CHUNK16); else LBA_DIFF(PM_FLUSH_CLAMP, LBA_ORDER_CHUNK16);
     } else {

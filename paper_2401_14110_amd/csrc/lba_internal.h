@@ -113,10 +113,12 @@ int validate_shapes(int64_t M, int64_t N, int64_t K);
 int validate_fmt(const lba_qfmt& q);
 
 // What A's rows are: a matrix's own, or im2col rows of an NHWC tensor, whose pieces of 16 codes are channels of one tap (C a multiple of 16) or
-// gathered from several taps.
-enum ARows { ROWS_MATRIX = 0, ROWS_TAPS = 1, ROWS_GATHERED = 2 };
+// gathered from several taps; of those, filter rows (KW * C) of fewer than 16 codes are gathered byte by byte, and a tensor of fewer than 16 codes
+// holds no load of 16 bytes.
+enum ARows { ROWS_MATRIX = 0, ROWS_TAPS = 1, ROWS_GATHERED = 2, ROWS_NARROW = 3, ROWS_TINY = 4 };
 
-// Builds the plan (pointers in kp are left null).  Returns an lba status code.
+// Builds the plan (pointers in kp are left null).  Returns an lba status code.  A plan is launched as it is: whatever decides its carriers is
+// known here, because tiles and grid follow from them.
 int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qprod, const lba_qfmt& qacc,
               int order, int events, Plan* out, int64_t batch = 1, const InSpec* in = nullptr, ARows rows = ROWS_MATRIX);
 

@@ -108,7 +108,8 @@ static int run(const uint8_t* A, const uint8_t* B, float* C, uint32_t* of_mask, 
                void* brick_ws = nullptr) {
     Plan pl;
     if (batch < 0 || batch > 65535 || stride_a < 0 || stride_b < 0 || stride_c < 0) return LBA_ERR_SHAPE;
-    const ARows rows = !conv ? ROWS_MATRIX : conv->c % 16 == 0 ? ROWS_TAPS : ROWS_GATHERED;
+    const ARows rows = !conv ? ROWS_MATRIX : (int64_t)conv->n * conv->h * conv->w * conv->c < 16 ? ROWS_TINY
+                     : conv->kw * conv->c < 16 ? ROWS_NARROW : conv->c % 16 != 0 ? ROWS_GATHERED : ROWS_TAPS;
     int rc = make_plan(M, N, K, qprod, qacc, order, events, &pl, batch, in, rows);
     if (rc != LBA_OK) return rc;
     if (in) pl.kp.out_exp -= in->delta;                        // the operand biases' power-of-two scale
@@ -140,14 +141,7 @@ static int run(const uint8_t* A, const uint8_t* B, float* C, uint32_t* of_mask, 
         kp.conv = 1;
         kp.cv_h = conv->h; kp.cv_w = conv->w; kp.cv_c = conv->c; kp.cv_kw = conv->kw;
         kp.cv_stride = conv->stride; kp.cv_pad = conv->pad; kp.cv_oh = conv_oh; kp.cv_ow = conv_ow;
-        // Packed carriers fetch 16 bytes at a time: the tensor holds as many.  A filter row of fewer than 16 codes is gathered byte
-        // by byte when it is staged; the FP32 tile, whose byte loads are in flight over a k-tile, is faster at that (3 x 3 x 3 on 8
-        // images of 56 x 56 to 256 channels 25 us against 38, 64 images of 224 x 224 to 64 channels 524 against 686) except on
-        // the smallest grids, 32 x 16 tiles throughout (2 images of 14 x 14 to 64 channels 12.5 against 10.6).
-        const bool narrow = conv->kw * conv->c < 16 && !(pl.kp.mix_tail16 && pl.kp.mix_main + pl.kp.mix_half == 0);
-        if ((int64_t)conv->n * conv->h * conv->w * conv->c < 16 || narrow) kp.h_on = pl.staged = 0;
         kp.cv_vec = ((conv->c % 16) == 0 && ((uintptr_t)A % 16) == 0) ? 1 : 0;
-        if (!kp.cv_vec && conv->kw * conv->c < 16) pl.staged = 0;   // (gathered byte by byte)
         kp.cv_magic_c = (((uint64_t)1 << 40) + (uint64_t)conv->c - 1) / (uint64_t)conv->c;
         kp.cv_magic_kw = (((uint64_t)1 << 40) + (uint64_t)conv->kw - 1) / (uint64_t)conv->kw;
         la = lb;

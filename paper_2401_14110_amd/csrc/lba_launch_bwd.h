@@ -15,6 +15,7 @@ static hipError_t launch_fast_bwd_rounding(const Plan& pl, hipStream_t st) {
     const int uf = (pl.kp.uf_mask != nullptr || pl.kp.uf_mask2 != nullptr) ? (pl.uf_class ? 2 : 1) : 0;
 #define LBA_UF3(CALL, ...) do { if (uf == 2) CALL(__VA_ARGS__, 2); else if (uf == 1) CALL(__VA_ARGS__, 1); else CALL(__VA_ARGS__, 0); } while (0)
     if (pl.amode == 2) return hipErrorInvalidValue;        // launch_fast_bwd_conv
+    if (pl.tm != 4 || pl.tn != 4) return hipErrorInvalidValue;   // 64 x 64 workgroups, or a mixed grid
     if (pl.amode) {                                        // im2col rows / other operand formats: floor, sequential order only
         if constexpr (RND == LBA_ROUND_FLOOR) {
 #define LBA_BWD1(PM, UF) hipLaunchKernelGGL((lba_fast_bwd_kernel<PM, RND, LBA_ORDER_SEQ, UF, 1>), grid, block, 0, st, pl.kp)

@@ -220,8 +220,10 @@ static bool half_underflow_ok(const lba_qfmt& qp, const InSpec& in, int bpe, int
 // workgroups it is taken where it saves half a round of 256 and not where both need as many (8192 x 512 x 768: 136 -> 130 us, behind a
 // ReLU 117 -> 108; 5888 x 512 x 768 106 -> 101 and 93 -> 86; 560 workgroups of a batched product 37.6 us, 40.0 with 4 x 4).  Rows that do not
 // start on 16-byte boundaries keep the 2 x 4 block throughout: its parity tests run on them (1530 x 2045 x 70 18.8 us, 16.6 with 4 x 4).
+// Filter rows gathered byte by byte (ROWS_NARROW, FP32): as on packed carriers (3 x 3 x 3, 762 workgroups, 20.2 us, 17.8 with 4 x 4; 5 x 5 x 3 44.5
+// and 38.6; nearest-even 43.5 and 38.6; 1016 workgroups 55.7 and 47.8).
 // The choice never changes a result.
-static void pick_tile(int64_t M, int64_t N, int64_t batch, int kernel, int events, int prod_mode, int amode, int rne_odd, int packed, int* tm, int* tn, int* bk) {
+static void pick_tile(int64_t M, int64_t N, int64_t batch, int kernel, int events, int prod_mode, int amode, int rne_odd, bool half_rounds, int* tm, int* tn, int* bk) {
     *tm = 4; *tn = 4;
     *bk = (kernel == KERNEL_GEN || events) ? 32 : LBA_FAST_BK;
     if (kernel == KERNEL_FAST) {
@@ -232,7 +234,7 @@ static void pick_tile(int64_t M, int64_t N, int64_t batch, int kernel, int event
         // grids are cut finer until every CU has two workgroups
         if (blocks <= 128) { *tm = 2; *tn = 2; }
         else if (blocks <= 384) *tm = 2;
-        else if (blocks > 512 && blocks <= 1024 && (!packed || (blocks + 127) / 128 % 2)) *tm = 2;
+        else if (blocks > 512 && blocks <= 1024 && (!half_rounds || (blocks + 127) / 128 % 2)) *tm = 2;
     }
 }
 
@@ -306,7 +308,7 @@ static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, AR
     // channels, floor, M10E5, times of 32 x 32 over 64 x 64: 270 workgroups 0.93, 0.86, 0.83, 384 0.98, 0.95, 0.92, 441 1.20, 1.15, 1.15, 500 1.15, 1.14,
     // 1.13; on 16 channels 0.71, 0.77, 0.94, 0.93), the overflow plane alone up to 320 from two k-tiles on (K = 75, 320 workgroups, 0.98, 384 1.08; K = 27 257
     // to 320 1.05) and up to 256 where the product is truncated (270 workgroups 1.06 to 1.18).
-    const bool parts = rows == ROWS_GATHERED;
+    const bool parts = rows >= ROWS_GATHERED;
     const int64_t most = !p->of_only ? (parts ? 384 : 512) : !parts || (p->amode == 2 && p->kp.K >= 64) ? 320 : 256;
     if (p->events == 1 && !p->kp.h_on && !short_clamp && blocks <= most && set_mixed_grid(M, N, 0, 0, p)) return;
     if (p->events == 1 && p->kp.h_on && !p->of_only && blocks > 256 && blocks <= 384 && set_mixed_grid(M, N, 0, 0, p)) return;
@@ -349,7 +351,10 @@ static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, AR
     // 221 us, 767 and 175 of 32 x 32 187; 12544 x 256 x 768 -31, 10500 x 512 x 768 -24); a tail of more than one to a CU gains nothing.
     if (chunk_of && (blocks <= 512 || tail > 256)) return;
     double plain = (double)((blocks + 255) / 256);
-    if (p->tm == 2 && p->tn == 4) plain = 0.5 * (double)((2 * blocks + 255) / 256) / 0.95;   // the 32 x 64 choice
+    // the 32 x 64 choice; and filter rows gathered byte by byte of more than one k-tile, where a tail takes less time than a last round of 64 x 64
+    // that is three quarters full (914 workgroups, K = 45, 32.1 us with a tail, 34.6 without; K = 225 108 and 117; K = 27 23.3 and 19.2)
+    const bool tail_pays = rows == ROWS_NARROW && !p->events && p->kp.K > 32 && blocks > 512 && blocks <= 1024;
+    if ((p->tm == 2 && p->tn == 4) || tail_pays) plain = 0.5 * (double)((2 * blocks + 255) / 256) / 0.95;
     const double mixed = (double)(gx_main * gy) / 256.0 + (double)((tail + 255) / 256) * 0.25 / 0.8;
     if (mixed > 0.97 * plain) return;
     set_mixed_grid(M, N, gx_main, 0, p);
@@ -470,9 +475,14 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
         // chains, one v_and for both; never priced below the two slots of the FP32 multiply-add and mask
         // The recompute call for the overflow plane alone: the same, its tiles that cannot overflow are the forward call's.  With an
         // underflow plane it keeps the FP32 kernel's price, above the 8 slots of the packed step (lba_half_bwd.h): a budget.
-        // (pieces are loads of 16 bytes from inside an operand: at least 16 of them; im2col rows: checked by the caller;
-        // fetched ahead of the chain: K not at the end of its range)
-        const bool half = N * K >= 16 && K <= kPieceMaxK && (conv || M * K >= 16) && events != 2 && !rne_odd && qa.round == LBA_ROUND_FLOOR && !nouf_a &&
+        // (pieces are loads of 16 bytes from inside an operand: at least 16 of them; fetched ahead of the chain: K not at the end of its range)
+        // A filter row of fewer than 16 codes is gathered byte by byte when it is staged; the FP32 tile, whose byte loads are in flight over a
+        // k-tile, is faster at that (3 x 3 x 3 on 8 images of 56 x 56 to 256 channels 25 us against 38, 64 images of 224 x 224 to 64 channels
+        // 524 against 686) except on the smallest grids of the forward call, 32 x 16 tiles throughout (2 images of 14 x 14 to 64 channels 12.5
+        // against 10.6).
+        const bool held = rows == ROWS_MATRIX ? M * K >= 16
+                        : rows == ROWS_NARROW ? !events && ((M + 31) / 32) * ((N + 31) / 32) <= 128 : rows != ROWS_TINY;
+        const bool half = N * K >= 16 && K <= kPieceMaxK && held && events != 2 && !rne_odd && qa.round == LBA_ROUND_FLOOR && !nouf_a &&
                           (p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH || p.prod_mode == PM_TRUNC) &&
                           (!p.events || p.of_only || half_underflow_ok(qp, in, bpe, bae)) &&
                           half_carrier(qp, qa, in, p.prod_mode, bpe, bae, !p.events, &kp);
@@ -511,7 +521,7 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
         (!events || (p.events == 1 && qa.round == LBA_ROUND_FLOOR && order == LBA_ORDER_SEQ && p.prod_mode != PM_IDENT)))
         p.amode = 2;
     p.rne_odd = (fast && rne_odd) ? 1 : 0;
-    pick_tile(M, N, batch, p.kernel, p.events, p.prod_mode, p.amode == 1, p.rne_odd, kp.h_on && K % 16 == 0, &p.tm, &p.tn, &p.bk);
+    pick_tile(M, N, batch, p.kernel, p.events, p.prod_mode, p.amode == 1, p.rne_odd, (kp.h_on && K % 16 == 0) || rows == ROWS_NARROW, &p.tm, &p.tn, &p.bk);
     kp.batch = 1;
     kp.fast_thresh = -1.0f;
     kp.fast_thresh4 = -1.0f;
@@ -584,7 +594,7 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
     // workgroups still do, at 8 to 21 us where the launch is most of it)
     const bool stages = p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH ||
                         (p.prod_mode == PM_TRUNC && !conv && (K > 512 || (K >= 224 && ((M + 31) / 32) * ((N + 31) / 32) > 64)));
-    const bool staged = !p.events && (kp.h_on ? !kp.h_range && stages : rne32 && order == LBA_ORDER_SEQ && (p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH));
+    const bool staged = !p.events && (kp.h_on ? !kp.h_range && rows != ROWS_NARROW && stages : rne32 && order == LBA_ORDER_SEQ && (p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH));
     if (p.kpar == 0) plan_mixed_grid(M, N, batch, staged, rows, &p);
     p.staged = staged && (p.mix_tail > 0 ? kp.mix_tail16 && kp.mix_main + kp.mix_half == 0 : p.tm == 2 && p.tn == 2);
     // Waves alone on their SIMDs (lba_half_alone.hip, which has the figures): at most one workgroup of 64 x 64 per CU (only the recompute call

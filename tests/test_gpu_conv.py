@@ -280,3 +280,24 @@ def test_resnet50_convolutions_at_full_size(ref):
         assert np.count_nonzero(wc) > wc.size // 4, l["name"]
         del Y
     assert len(seen) >= 20 and with_planes == 3
+
+
+# Filters narrower than a piece and tensors of fewer than 16 codes, in formats that packed carriers would hold: the recompute call on few
+# workgroups and on more, the forward call on each lane block; sums that never, now and then and nearly always saturate
+@pytest.mark.parametrize("n,h,w,c,cout,k", [(1, 3, 2, 2, 40, 3), (1, 14, 14, 3, 64, 3), (8, 28, 28, 3, 130, 3), (5, 64, 64, 3, 61, 3), (15, 57, 57, 3, 64, 3), (14, 57, 57, 3, 60, 5)])
+def test_narrow_filters(ref, n, h, w, c, cout, k):
+    rng = np.random.default_rng(n + k)
+    X, W = codes(rng, (n, h, w, c)), codes(rng, (cout, k, k, c))
+    tX, tW = torch.from_numpy(X).to(DEV), torch.from_numpy(W).to(DEV)
+    A, B = ref.im2col_nhwc(X, k, k, 1, k // 2), W.reshape(cout, -1)
+    M = A.shape[0]
+    rows = np.unique(np.concatenate([[0, M - 1], rng.choice(M, min(M, 60), replace=False)]))
+    A = np.ascontiguousarray(A[rows])
+    for qp, qa in [((5, 7, 4, 0), (4, 7, -4, 0)), ((5, 7, 12, 0), (4, 7, 9, 0)), ((5, 4, 12, 0), (4, 7, 12, 0))]:
+        for order in (0, 1):
+            Y = lb.conv2d(tX, tW, qp, qa, stride=1, pad=k // 2, order=order)
+            assert np.array_equal(bits(Y.cpu().numpy().reshape(M, cout)[rows]), bits(ref.gemm(A, B, ref.QFmt(*qp), ref.QFmt(*qa), order=order))), (qp, qa, order)
+        Y, of, uf = lb.conv2d(tX, tW, qp, qa, stride=1, pad=k // 2, planes=True)
+        wc, wof, wuf = ref.gemm_bwd(A, B, ref.QFmt(*qp), ref.QFmt(*qa))
+        assert np.array_equal(bits(Y.cpu().numpy().reshape(M, cout)[rows]), bits(wc)), (qp, qa)
+        assert np.array_equal(of.cpu().numpy()[:, rows].view(np.uint32), wof) and np.array_equal(uf.cpu().numpy()[:, rows].view(np.uint32), wuf), (qp, qa)

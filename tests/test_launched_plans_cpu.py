@@ -72,3 +72,26 @@ def test_small_fp32_recompute(rec, c, k, formats, planes, most):
         M, N, name, p = conv(rec, 1, 64, blocks, c, 64, k, formats, planes)
         assert M == 64 * blocks and name == "launch_fast_bwd" and not p["packed"] and fits(M, N, p)
         assert (p["mix_tail"] == 2 * blocks * 2 and p["mix_main"] == 0) == (blocks <= most), (blocks, p)
+
+
+# Filter rows of fewer than 16 codes and tensors of fewer run on FP32 carriers: on the tiles those kernels have
+@pytest.mark.parametrize("formats", [PACKED, TRUNC])
+@pytest.mark.parametrize("shape", [(1, 14, 14, 3, 64, 3), (8, 28, 28, 3, 128, 3), (4, 64, 64, 3, 64, 3), (2, 56, 56, 4, 64, 3), (5, 56, 56, 3, 64, 4), (1, 3, 2, 2, 40, 3)])
+@pytest.mark.parametrize("planes", ["o", "ou", "u"])
+def test_recompute_of_narrow_filters(rec, shape, planes, formats):
+    M, N, name, p = conv(rec, *shape, formats, planes)
+    assert name == "launch_fast_bwd" and not p["packed"] and fits(M, N, p)
+    assert (p["tm"], p["tn"]) == (4, 4)                        # the only lane block of the FP32 recompute kernels' plain grids
+
+
+@pytest.mark.parametrize("formats", [PACKED, TRUNC])
+@pytest.mark.parametrize("order", [0, 1])
+@pytest.mark.parametrize("shape", [(1, 14, 14, 3, 64, 3), (4, 28, 28, 3, 64, 3), (3, 64, 64, 3, 64, 4), (12, 56, 56, 3, 64, 4), (8, 56, 57, 3, 128, 4), (1, 33, 33, 1, 64, 15)])
+def test_forward_of_narrow_filters(rec, shape, order, formats):
+    M, N, name, p = conv(rec, *shape, formats, None, order)
+    small = -(-M // 32) * -(-N // 32) <= 128                   # 32 x 16 tiles throughout stay on packed carriers
+    assert p["packed"] == small and not p["staged"] and fits(M, N, p)
+    if small:
+        assert p["mix_tail16"] and p["mix_main"] + p["mix_half"] == 0 and name == "launch_half_conv"
+    else:
+        assert name in ("launch_fast_conv", "launch_fast_amode", "launch_fast_in_mixed_seq", "launch_fast_in_mixed_chunk")
