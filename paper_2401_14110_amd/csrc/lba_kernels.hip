@@ -93,6 +93,11 @@ static void plan_kernel_name(const Plan& pl, bool uf, char* buf, size_t n) {
     }
 }
 
+// What a recompute call asks the planner for: 3, overflow planes alone (tiles, grids and carriers of their own), or 1
+static int plane_events(const uint32_t* of_mask, const uint32_t* uf_mask, const uint32_t* of_mask2 = nullptr, const uint32_t* uf_mask2 = nullptr) {
+    return (of_mask || of_mask2) && !uf_mask && !uf_mask2 ? 3 : 1;
+}
+
 static int gcd_align(const void* ptr, int64_t K) {
     const uintptr_t a = (uintptr_t)ptr;
     if ((a % 16) == 0 && (K % 16) == 0) return 16;
@@ -173,14 +178,13 @@ int lba_gemm_bwd(const uint8_t* A, const uint8_t* B, float* C, uint32_t* of_mask
         const int rc = lba::make_plan(M, N, K, qprod, qacc, order, 1, &pl);
         return rc != LBA_OK ? rc : LBA_ERR_UNSUPPORTED;
     }
-    // 3: the overflow plane alone (the planner may then cut the last rows finer)
-    return lba::run(A, B, C, of_mask, uf_mask, M, N, K, qprod, qacc, order, (of_mask && !uf_mask) ? 3 : 1, hip_stream);
+    return lba::run(A, B, C, of_mask, uf_mask, M, N, K, qprod, qacc, order, lba::plane_events(of_mask, uf_mask), hip_stream);
 }
 
 int lba_gemm_bwd_ws(const uint8_t* A, const uint8_t* B, float* C, uint32_t* of_mask, uint32_t* uf_mask,
                     int64_t M, int64_t N, int64_t K, lba_qfmt qprod, lba_qfmt qacc,
                     void* workspace, size_t workspace_bytes, void* hip_stream) {
-    const int events = (of_mask && !uf_mask) ? 3 : 1;
+    const int events = lba::plane_events(of_mask, uf_mask);
     lba::Plan pl;
     int rc = lba::make_plan(M, N, K, qprod, qacc, LBA_ORDER_SEQ, events, &pl);
     if (rc != LBA_OK) return rc;
@@ -232,9 +236,8 @@ int lba_gemm_bwd_diff(const uint8_t* A, const uint8_t* B, float* C, uint32_t* di
 int lba_gemm_bwd_chunked(const uint8_t* A, const uint8_t* B, float* C,
                          uint32_t* of_mask, uint32_t* uf_mask, uint32_t* of_mask2, uint32_t* uf_mask2,
                          int64_t M, int64_t N, int64_t K, lba_qfmt qprod, lba_qfmt qacc, void* hip_stream) {
-    const int events = ((of_mask || of_mask2) && !uf_mask && !uf_mask2) ? 3 : 1;
-    return lba::run(A, B, C, of_mask, uf_mask, M, N, K, qprod, qacc, LBA_ORDER_CHUNK16, events, hip_stream,
-                    1, 0, 0, 0, of_mask2, uf_mask2);
+    return lba::run(A, B, C, of_mask, uf_mask, M, N, K, qprod, qacc, LBA_ORDER_CHUNK16, lba::plane_events(of_mask, uf_mask, of_mask2, uf_mask2),
+                    hip_stream, 1, 0, 0, 0, of_mask2, uf_mask2);
 }
 
 // Operand biases are one power-of-two scale 2^-delta: C = 2^-delta * LBA(codes at canonical biases) with
@@ -261,7 +264,7 @@ int lba_gemm_bwd_in(const uint8_t* A, const uint8_t* B, float* C, uint32_t* of_m
                     int64_t M, int64_t N, int64_t K, lba_infmt fmt_a, lba_infmt fmt_b,
                     lba_qfmt qprod, lba_qfmt qacc, int32_t order, void* hip_stream) {
     if (order == LBA_ORDER_CHUNK16) return LBA_ERR_UNSUPPORTED;
-    return run_in(A, B, C, of_mask, uf_mask, M, N, K, fmt_a, fmt_b, qprod, qacc, order, 1, hip_stream);
+    return run_in(A, B, C, of_mask, uf_mask, M, N, K, fmt_a, fmt_b, qprod, qacc, order, lba::plane_events(of_mask, uf_mask), hip_stream);
 }
 
 int lba_gemm_bwd_diff_in(const uint8_t* A, const uint8_t* B, float* C, uint32_t* diff_mask,
@@ -310,7 +313,7 @@ int lba_conv2d_bwd(const uint8_t* X, const uint8_t* W, float* Y, uint32_t* of_ma
                    lba_conv2d_desc desc, int64_t cout, lba_qfmt qprod, lba_qfmt qacc, int32_t order,
                    void* hip_stream) {
     if (order == LBA_ORDER_CHUNK16) return LBA_ERR_UNSUPPORTED;
-    return run_conv(X, W, Y, of_mask, uf_mask, desc, cout, qprod, qacc, order, 1, hip_stream);
+    return run_conv(X, W, Y, of_mask, uf_mask, desc, cout, qprod, qacc, order, lba::plane_events(of_mask, uf_mask), hip_stream);
 }
 
 int lba_gemm_batched(const uint8_t* A, const uint8_t* B, float* C, int64_t batch,

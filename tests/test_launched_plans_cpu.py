@@ -5,7 +5,7 @@ import subprocess
 
 import pytest
 
-from paper_2401_14110_amd.binding import lba_conv2d_desc, lba_qfmt
+from paper_2401_14110_amd.binding import lba_conv2d_desc, lba_infmt, lba_qfmt
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 FIELDS = ("grid_x", "grid_y", "tm", "tn", "mix_main", "mix_half", "mix_tail", "mix_tail16", "packed", "staged", "alone", "of_only", "kpar")
@@ -28,6 +28,7 @@ def rec(tmp_path_factory):
     lib.take_launched.restype = ctypes.c_char_p
     lib.lba_conv2d.argtypes = [vp, vp, vp, lba_conv2d_desc, i64, lba_qfmt, lba_qfmt, i32, vp]
     lib.lba_conv2d_bwd.argtypes = [vp, vp, vp, vp, vp, lba_conv2d_desc, i64, lba_qfmt, lba_qfmt, i32, vp]
+    lib.lba_gemm_bwd_in.argtypes = [vp, vp, vp, vp, vp, i64, i64, i64, lba_infmt, lba_infmt, lba_qfmt, lba_qfmt, i32, vp]
     return lib
 
 
@@ -95,3 +96,34 @@ def test_forward_of_narrow_filters(rec, shape, order, formats):
         assert p["mix_tail16"] and p["mix_main"] + p["mix_half"] == 0 and name == "launch_half_conv"
     else:
         assert name in ("launch_fast_conv", "launch_fast_amode", "launch_fast_in_mixed_seq", "launch_fast_in_mixed_chunk")
+
+
+# One plane or both: the plan is that of the planes asked for, from every entry point
+@pytest.mark.parametrize("planes", ["o", "ou", "u"])
+def test_planes_asked_for(rec, planes):
+    of, uf = BUF if "o" in planes else None, BUF if "u" in planes else None
+    alone = planes == "o"
+    for fmt, (qp, qa), packed in [((4, 3, 7), PACKED, True), ((3, 4, 3), ((5, 7, 1, 0), (4, 7, 2, 0)), True), ((4, 3, 7), WIDE, False), ((3, 4, 3), ((5, 7, 1, 0), (5, 10, 5, 0)), False)]:
+        for blocks in (200, 300, 340, 400, 500):
+            rc = rec.lba_gemm_bwd_in(BUF, BUF, BUF, of, uf, 64 * blocks, 64, 500, lba_infmt(*fmt), lba_infmt(*fmt), lba_qfmt(*qp), lba_qfmt(*qa), 0, None)
+            name, p = taken(rec)
+            assert rc == 0 and p["of_only"] == alone and p["packed"] == packed and fits(64 * blocks, 64, p)
+            # 32 x 32 throughout: FP32 up to 384 and 512, packed from 257 to 384 (truncated products without an underflow plane to 320; fewer: truncated products
+            # as well, others have kernels of their own)
+            small = p["mix_tail"] == 4 * blocks and p["mix_main"] == 0
+            trunc = fmt == (3, 4, 3)
+            want = blocks <= (384 if alone else 512) if not packed else blocks <= (320 if alone and trunc else 384) and (trunc or blocks > 256)
+            assert small == want, (blocks, p)
+    for c, formats, packed in [(32, PACKED, True), (20, PACKED, True), (32, WIDE, False), (3, WIDE, False)]:
+        _, _, name, p = conv(rec, 1, 64, 300, c, 64, 3, formats, planes)
+        assert p["of_only"] == alone and p["packed"] == packed
+        assert (p["mix_tail"] == 1200) == (not alone or c == 32)
+
+
+# the overflow plane alone: whole taps up to 384, gathered rows up to 320 from two k-tiles on and up to 256 with truncated products
+@pytest.mark.parametrize("c,k,formats,most", [(16, 3, WIDE, 384), (16, 3, WIDE_TRUNC, 384), (3, 5, WIDE, 320), (3, 3, WIDE, 256), (3, 5, WIDE_TRUNC, 256)])
+def test_small_fp32_overflow_plane(rec, c, k, formats, most):
+    for blocks in (256, 257, 320, 321, 384, 385):
+        M, N, name, p = conv(rec, 1, 64, blocks, c, 64, k, formats, "o")
+        assert name == "launch_fast_bwd" and p["of_only"] and fits(M, N, p)
+        assert (p["mix_tail"] == 4 * blocks and p["mix_main"] == 0) == (blocks <= most), (blocks, p)
