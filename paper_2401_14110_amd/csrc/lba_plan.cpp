@@ -220,6 +220,9 @@ static bool half_underflow_ok(const lba_qfmt& qp, const InSpec& in, int bpe, int
 // workgroups it is taken where it saves half a round of 256 and not where both need as many (8192 x 512 x 768: 136 -> 130 us, behind a
 // ReLU 117 -> 108; 5888 x 512 x 768 106 -> 101 and 93 -> 86; 560 workgroups of a batched product 37.6 us, 40.0 with 4 x 4).  Rows that do not
 // start on 16-byte boundaries keep the 2 x 4 block throughout: its parity tests run on them (1530 x 2045 x 70 18.8 us, 16.6 with 4 x 4).
+// Sums beyond FP16's range (h_range) leave the packed tile now and then and gain less: from chains of 96 steps on, in chunks of 256 (2 x 4 over 4 x 4, 736
+// to 1024 workgroups, M7E5 and M10E5, K = 32 0.95 and 0.95, 64 0.98 and 0.98, 96 1.04 and 1.03, 256 1.05 and 1.03; in chunks 0.92 and 0.92, 0.95 and 0.96, 0.97 and
+// 0.97, 1.01 and 0.99, K = 2304 1.03 and 1.04), and on rows off 16-byte boundaries not at all.
 // Filter rows gathered byte by byte (ROWS_NARROW, FP32): as on packed carriers (3 x 3 x 3, 762 workgroups, 20.2 us, 17.8 with 4 x 4; 5 x 5 x 3 44.5
 // and 38.6; nearest-even 43.5 and 38.6; 1016 workgroups 55.7 and 47.8).
 // The choice never changes a result.
@@ -356,10 +359,16 @@ static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, AR
     // 221 us, 767 and 175 of 32 x 32 187; 12544 x 256 x 768 -31, 10500 x 512 x 768 -24); a tail of more than one to a CU gains nothing.
     if (chunk_of && (blocks <= 512 || tail > 256)) return;
     double plain = (double)((blocks + 255) / 256);
-    // the 32 x 64 choice; and filter rows gathered byte by byte of more than one k-tile, where a tail takes less time than a last round of 64 x 64
-    // that is three quarters full (914 workgroups, K = 45, 32.1 us with a tail, 34.6 without; K = 225 108 and 117; K = 27 23.3 and 19.2)
-    const bool tail_pays = rows == ROWS_NARROW && !p->events && p->kp.K > 32 && blocks > 512 && blocks <= 1024;
-    if ((p->tm == 2 && p->tn == 4) || tail_pays) plain = 0.5 * (double)((2 * blocks + 255) / 256) / 0.95;
+    // The estimate of 32 x 64 tiles, which favours a tail: where they are the choice, and where it is right about 64 x 64 ones whose last round is three
+    // quarters full (641 to 768 workgroups, 897 to 1024): filter rows gathered byte by byte of more than one k-tile (914 workgroups, K = 45, 32.1 us
+    // with a tail, 34.6 without; K = 225 108 and 117; K = 27 23.3 and 19.2), and M10E5 and wider from 512 steps on (700 workgroups, tail over plain, K =
+    // 64 1.09 to 1.22, 256 1.01 to 1.03, 768 0.94 to 0.99, 2304 0.93 to 0.98; narrower accumulators beyond FP16's range 1.03 to 1.23, others 1.00 to 1.16).
+    bool finer = p->tm == 2 && p->tn == 4;
+    if (!p->events && blocks > 512 && blocks <= 1024 && (blocks + 127) / 128 % 2 == 0) {
+        if (rows == ROWS_NARROW && p->amode == 2) finer = p->kp.K > 32;
+        else if (p->kp.h_on && p->kp.h_range && p->kp.K % 16 == 0) finer = p->kp.h_range == 2 && p->kp.K >= 512;
+    }
+    if (finer) plain = 0.5 * (double)((2 * blocks + 255) / 256) / 0.95;
     const double mixed = (double)(gx_main * gy) / 256.0 + (double)((tail + 255) / 256) * 0.25 / 0.8;
     if (mixed > 0.97 * plain) return;
     set_mixed_grid(M, N, gx_main, 0, p);
@@ -526,7 +535,9 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
         (!events || (p.events == 1 && qa.round == LBA_ROUND_FLOOR && order == LBA_ORDER_SEQ && p.prod_mode != PM_IDENT)))
         p.amode = 2;
     p.rne_odd = (fast && rne_odd) ? 1 : 0;
-    pick_tile(M, N, batch, p.kernel, p.events, p.prod_mode, p.amode == 1, p.rne_odd, (kp.h_on && K % 16 == 0) || rows == ROWS_NARROW, &p.tm, &p.tn, &p.bk);
+    // (pick_tile) the 2 x 4 lane block on 513 to 1024 workgroups only where it saves half a round
+    const bool half_rounds = rows == ROWS_NARROW || (kp.h_on && K % 16 == 0 && (!kp.h_range || K >= (order == LBA_ORDER_CHUNK16 ? 256 : 96)));
+    pick_tile(M, N, batch, p.kernel, p.events, p.prod_mode, p.amode == 1, p.rne_odd, half_rounds, &p.tm, &p.tn, &p.bk);
     kp.batch = 1;
     kp.fast_thresh = -1.0f;
     kp.fast_thresh4 = -1.0f;

@@ -28,6 +28,8 @@ def rec(tmp_path_factory):
     lib.take_launched.restype = ctypes.c_char_p
     lib.lba_conv2d.argtypes = [vp, vp, vp, lba_conv2d_desc, i64, lba_qfmt, lba_qfmt, i32, vp]
     lib.lba_conv2d_bwd.argtypes = [vp, vp, vp, vp, vp, lba_conv2d_desc, i64, lba_qfmt, lba_qfmt, i32, vp]
+    lib.lba_gemm.argtypes = [vp, vp, vp, i64, i64, i64, lba_qfmt, lba_qfmt, i32, vp]
+    lib.lba_gemm_batched.argtypes = [vp, vp, vp, i64, i64, i64, i64, i64, i64, i64, lba_qfmt, lba_qfmt, i32, vp]
     lib.lba_gemm_bwd_in.argtypes = [vp, vp, vp, vp, vp, i64, i64, i64, lba_infmt, lba_infmt, lba_qfmt, lba_qfmt, i32, vp]
     return lib
 
@@ -127,3 +129,29 @@ def test_small_fp32_overflow_plane(rec, c, k, formats, most):
         M, N, name, p = conv(rec, 1, 64, blocks, c, 64, k, formats, "o")
         assert name == "launch_fast_bwd" and p["of_only"] and fits(M, N, p)
         assert (p["mix_tail"] == 4 * blocks and p["mix_main"] == 0) == (blocks <= most), (blocks, p)
+
+
+WIDE7, WIDE10 = ((5, 7, 12, 0), (5, 7, -2, 0)), ((5, 7, 12, 0), (5, 10, -2, 0))     # packed, sums beyond FP16's range
+NEAREST = ((5, 7, -2, 1), (4, 7, -10, 1))
+
+
+# 513 to 1024 workgroups of 64 x 64 (a batch, which has no tail): the finer block throughout on FP32 carriers, on packed ones where it saves half a round of 256
+@pytest.mark.parametrize("batch", [512, 513, 640, 641, 768, 769, 896, 897, 1024, 1025])
+def test_half_rounds(rec, batch):
+    half_round = batch in (513, 640, 769, 896)
+    for formats, K, order, half_rounds in [(PACKED, 768, 0, True), (PACKED, 32, 1, True), (NEAREST, 768, 0, False), (WIDE, 768, 0, False),
+                                           (WIDE7, 96, 0, True), (WIDE7, 80, 0, False), (WIDE7, 256, 1, True), (WIDE7, 240, 1, False), (WIDE10, 96, 0, True), (WIDE10, 771, 0, False)]:
+        rc = rec.lba_gemm_batched(BUF, BUF, BUF, batch, 64 * K, 64 * K, 64 * 64, 64, 64, K, lba_qfmt(*formats[0]), lba_qfmt(*formats[1]), order, None)
+        name, p = taken(rec)
+        assert rc == 0 and p["mix_tail"] == 0 and p["packed"] == (formats not in (NEAREST, WIDE)) and fits(64, 64, p)
+        finer = 512 < batch <= 1024 and (half_round or not half_rounds)
+        assert (p["tm"], p["tn"]) == ((2, 4) if finer else (4, 4)), (formats, K, order)
+
+
+# a tail of 32 x 32 tiles on 700 workgroups: M10E5 from 512 steps on, narrower accumulators not
+@pytest.mark.parametrize("formats,K,tail", [(WIDE10, 512, True), (WIDE10, 496, False), (WIDE10, 64, False), (WIDE7, 2304, False), (PACKED, 2304, False), (WIDE, 768, True)])
+def test_tail_of_a_last_round(rec, formats, K, tail):
+    for order in (0, 1):
+        assert rec.lba_gemm(BUF, BUF, BUF, 64 * 700, 64, K, lba_qfmt(*formats[0]), lba_qfmt(*formats[1]), order, None) == 0
+        name, p = taken(rec)
+        assert (p["mix_main"] == 512 and p["mix_tail"] == 752) == tail and (tail or p["mix_tail"] == 0)
