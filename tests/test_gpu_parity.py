@@ -253,7 +253,7 @@ def test_every_lane_block(ref):
     # 32 x 16 tiles (2 x 1 per lane) throughout.
     rng = np.random.default_rng(70)
     small = set()
-    for (M, N, K), want_tile in (((130, 70, 70), (32, 16)), ((700, 650, 70), (32, 32)), ((1530, 2045, 70), (32, 64)),
+    for (M, N, K), want_tile in (((130, 70, 70), (32, 16)), ((700, 650, 70), (32, 32)), ((1770, 2045, 70), (32, 64)),
                                  ((2100, 2110, 70), (64, 64))):
         A = rand_codes(rng, (M, K), 3, 12)
         B = rand_codes(rng, (N, K), 3, 12)

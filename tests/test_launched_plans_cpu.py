@@ -139,7 +139,7 @@ NEAREST = ((5, 7, -2, 1), (4, 7, -10, 1))
 @pytest.mark.parametrize("batch", [512, 513, 640, 641, 768, 769, 896, 897, 1024, 1025])
 def test_half_rounds(rec, batch):
     half_round = batch in (513, 640, 769, 896)
-    for formats, K, order, half_rounds in [(PACKED, 768, 0, True), (PACKED, 32, 1, True), (NEAREST, 768, 0, False), (WIDE, 768, 0, False),
+    for formats, K, order, half_rounds in [(PACKED, 768, 0, True), (PACKED, 32, 1, True), (PACKED, 771, 0, True), (PACKED, 17, 1, True), (NEAREST, 768, 0, False), (WIDE, 768, 0, False),
                                            (WIDE7, 96, 0, True), (WIDE7, 80, 0, False), (WIDE7, 256, 1, True), (WIDE7, 240, 1, False), (WIDE10, 96, 0, True), (WIDE10, 771, 0, False)]:
         rc = rec.lba_gemm_batched(BUF, BUF, BUF, batch, 64 * K, 64 * K, 64 * 64, 64, 64, K, lba_qfmt(*formats[0]), lba_qfmt(*formats[1]), order, None)
         name, p = taken(rec)
