@@ -218,7 +218,8 @@ static bool half_underflow_ok(const lba_qfmt& qp, const InSpec& in, int bpe, int
 // which issues at half rate, so those grids take 2 x 4 (129-256) or 2 x 2 (up to 128): 1.6-3 times faster.
 // On packed carriers (rows of 8 columns a lane) the 2 x 4 block takes 1.04 to 1.08 times as long for the same outputs, so between 512 and 1024
 // workgroups it is taken where it saves half a round of 256 and not where both need as many (8192 x 512 x 768: 136 -> 130 us, behind a
-// ReLU 117 -> 108; 5888 x 512 x 768 106 -> 101 and 93 -> 86; 560 workgroups of a batched product 37.6 us, 40.0 with 4 x 4; rows off
+// ReLU 117 -> 108; 5888 x 512 x 768 106 -> 101 and 93 -> 86; 560 workgroups of a batched product 37.6 us, 40.0 with 4 x 4;
+// 64 products of 197 x 197 x 64, 1024 of 64 x 64 and 1792 of 32 x 64, 15.1 us, 15.9 with 4 x 4; rows off
 // 16-byte boundaries 1530 x 2045 x 70 25.2 -> 22.4, x 771 198 -> 184, 8192 x 500 x 147 57 -> 52, 42240 x 63 x 331, which had a tail, 1.05 times as fast).
 // Sums beyond FP16's range (h_range) leave the packed tile now and then and gain less: from chains of 96 steps on, in chunks of 256 (2 x 4 over 4 x 4, 736
 // to 1024 workgroups, M7E5 and M10E5, K = 32 0.95 and 0.95, 64 0.98 and 0.98, 96 1.04 and 1.03, 256 1.05 and 1.03; in chunks 0.92 and 0.92, 0.95 and 0.96, 0.97 and
@@ -231,13 +232,14 @@ static void pick_tile(int64_t M, int64_t N, int64_t batch, int kernel, int event
     *bk = (kernel == KERNEL_GEN || events) ? 32 : LBA_FAST_BK;
     if (kernel == KERNEL_FAST) {
         const int64_t blocks = ((M + 63) / 64) * ((N + 63) / 64) * (batch > 0 ? batch : 1);
+        const int64_t fine = ((M + 31) / 32) * ((N + 63) / 64) * (batch > 0 ? batch : 1);   // workgroups of 32 x 64
         if (events) return;                                    // the recompute kernel is 4 x 4 only
         if (prod_mode == PM_TRUNC || prod_mode == PM_TRUNC_CLAMP || amode || rne_odd) return;   // built for 4 x 4 only
         // a single wave per SIMD issues at half rate (256 workgroups of 64 x 64 take as long as 512): small
         // grids are cut finer until every CU has two workgroups
         if (blocks <= 128) { *tm = 2; *tn = 2; }
         else if (blocks <= 384) *tm = 2;
-        else if (blocks > 512 && blocks <= 1024 && (!half_rounds || (blocks + 127) / 128 % 2)) *tm = 2;
+        else if (blocks > 512 && blocks <= 1024 && (!half_rounds || (fine + 255) / 256 < (blocks + 255) / 256 * 2)) *tm = 2;
     }
 }
 
@@ -363,8 +365,9 @@ static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, AR
     // quarters full (641 to 768 workgroups, 897 to 1024): filter rows gathered byte by byte of more than one k-tile (914 workgroups, K = 45, 32.1 us
     // with a tail, 34.6 without; K = 225 108 and 117; K = 27 23.3 and 19.2), and M10E5 and wider from 512 steps on (700 workgroups, tail over plain, K =
     // 64 1.09 to 1.22, 256 1.01 to 1.03, 768 0.94 to 0.99, 2304 0.93 to 0.98; narrower accumulators beyond FP16's range 1.03 to 1.23, others 1.00 to 1.16).
+    const int64_t fine = ((M + 31) / 32) * gy;                 // workgroups of 32 x 64
     bool finer = p->tm == 2 && p->tn == 4;
-    if (!p->events && blocks > 512 && blocks <= 1024 && (blocks + 127) / 128 % 2 == 0) {
+    if (!p->events && blocks > 512 && blocks <= 1024 && (fine + 255) / 256 == (blocks + 255) / 256 * 2) {
         if (rows == ROWS_NARROW && p->amode == 2) finer = p->kp.K > 32;
         else if (p->kp.h_on && p->kp.h_range && p->kp.K % 16 == 0) finer = p->kp.h_range == 2 && p->kp.K >= 512;
     }

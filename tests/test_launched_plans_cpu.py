@@ -148,6 +148,17 @@ def test_half_rounds(rec, batch):
         assert (p["tm"], p["tn"]) == ((2, 4) if finer else (4, 4)), (formats, K, order)
 
 
+# members whose last rows fill half a tile of 64: the finer block has fewer rounds than twice the workgroups of 64 x 64
+@pytest.mark.parametrize("batch,M,finer", [(64, 197, True), (60, 197, True), (48, 197, False), (36, 197, True), (384, 70, True), (256, 128, False), (500, 96, True), (340, 100, False), (700, 32, True)])
+def test_half_tiles(rec, batch, M, finer):
+    N = 197 if M == 197 else 64
+    rc = rec.lba_gemm_batched(BUF, BUF, BUF, batch, M * 64, N * 64, M * N, M, N, 64, lba_qfmt(*PACKED[0]), lba_qfmt(*PACKED[1]), 0, None)
+    name, p = taken(rec)
+    blocks = batch * -(-M // 64) * -(-N // 64)
+    assert rc == 0 and fits(M, N, p) and 512 < blocks <= 1024 or blocks == 512
+    assert (p["tm"], p["tn"]) == ((2, 4) if finer else (4, 4)), blocks
+
+
 # a tail of 32 x 32 tiles on 700 workgroups: M10E5 from 512 steps on, narrower accumulators not
 @pytest.mark.parametrize("formats,K,tail", [(WIDE10, 512, True), (WIDE10, 496, False), (WIDE10, 64, False), (WIDE7, 2304, False), (PACKED, 2304, False), (WIDE, 768, True)])
 def test_tail_of_a_last_round(rec, formats, K, tail):
