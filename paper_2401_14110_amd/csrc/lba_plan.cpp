@@ -313,15 +313,14 @@ static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, AR
     // Rows gathered from several taps cost small tiles more, each of which gathers its own.  FP32, both planes (3 x 3 on 3, 5 x 5 on 3, 15 x 15 on 1
     // channels, floor, M10E5): 270 workgroups 0.93, 0.86, 0.83, 384 0.98, 0.95, 0.92, 441 1.20, 1.15, 1.15, 500 1.15, 1.14, 1.13 (on 16 channels 0.71, 0.77,
     // 0.94, 0.93); the overflow plane alone from two k-tiles on (K = 75) 320 0.98, 384 1.08, K = 27 1.05, truncated products 1.06 to 1.18; packed 1.05 to 1.8.
-    // (Clamped products on chains of fewer than 160 steps keep plain grids, which their tests run on.)
-    const bool short_clamp = p->prod_mode != PM_FLUSH && p->kp.K < 160 && p->amode != 1;
+    // Clamped products on short chains, both planes: 500 x 500 x 64 36 -> 17 us, 1024 x 1024 x 100 69 -> 49, 19200 x 64 x 144 113 -> 73, 32768 x 64 x 64 49 -> 46.
     const bool parts = rows >= ROWS_GATHERED, packed = p->kp.h_on != 0;
     int64_t most;
     if (!p->of_only)  most = packed ? 384 : parts ? 384 : 512;
     else if (packed)  most = parts ? 256 : p->amode == 1 || (rows == ROWS_TAPS && p->kp.K < 256) ? 320 : 384;
     else if (parts)   most = p->amode == 2 && p->kp.K >= 64 ? 320 : 256;
     else              most = p->round == LBA_ROUND_RNE || p->kp.K > 96 ? 384 : 320;
-    if (p->events == 1 && !chunk_of && !short_clamp && blocks > (packed ? 256 : 0) && blocks <= most && set_mixed_grid(M, N, 0, 0, p)) return;
+    if (p->events == 1 && !chunk_of && blocks > (packed ? 256 : 0) && blocks <= most && set_mixed_grid(M, N, 0, 0, p)) return;
     // the smallest grids of the forward call (at most 128 workgroups of 32 x 32, e.g. a 64 x 1000 classifier layer): the
     // tail's 32 x 16 tiles throughout, twice the workgroups of the 2 x 2 lane block
     if (p->events == 0 && b32 <= 128 && set_mixed_grid(M, N, 0, 0, p)) return;

@@ -407,7 +407,8 @@ def test_recompute_call_leaves_the_brick_maps(ref, gref):
     seen = set()
     cases = [((300, 200, 600), "tail", 0, True), ((130, 68, 260), "none", 0, True), ((260, 132, 515), "all", 1, True),
              ((64 * 392, 64, 72), "rows", 0, True), ((64 * 150 + 33, 132, 300), "tail", 0, False), ((257, 36, 1028), "tail", 1, False),
-             ((70, 66, 100), "tail", 0, True), ((33, 130, 65), "all", 1, True), ((1500, 64, 147), "rows", 0, True)]
+             ((70, 66, 100), "tail", 0, True), ((33, 130, 65), "all", 1, True), ((1500, 64, 147), "rows", 0, True),
+             ((64 * 330, 64, 72), "rows", 0, False), ((64 * 330 + 5, 62, 65), "rows", 0, False)]
     for (M, N, K), loud, rnd, want_uf in cases:
         need = lb.lba_grad_workspace_bytes(M, N, K)
         assert 0 < need <= ws.numel()

@@ -790,7 +790,7 @@ def test_mixed_grid(ref):
     assert small["tail_blocks"] + small["mid_blocks"] == 0 and (small["thread_m"], small["thread_n"]) == (2, 4)
     assert lb.lba_plan_query(64 * 100, 64, 64, (5, 7, 15, 0), (4, 7, 7, 0))["thread_n"] == 2
     assert lb.lba_plan_query(64 * 12544, 64, 64, (5, 7, 15, 0), (4, 7, 7, 0))["tail_blocks"] == 0
-    assert lb.lba_plan_query(64 * 300, 64, 64, (5, 7, 15, 0), (4, 7, 7, 0), 0, 1)["tail_blocks"] == 0
+    assert lb.lba_plan_query(64 * 768, 64, 64, (5, 7, 15, 0), (4, 7, 7, 0), 0, 1)["tail_blocks"] == 0
     # the recompute call has the mixed grid under the sequential order (both planes, or the overflow plane alone): quiet
     # operands (k-tiles that take the forward tile), loud ones, and a quiet start with a loud end
     for (M, N, K), lo, hi in [((64 * 420 + 17, 60, 100), 3, 8), ((64 * 392, 64, 72), 0, 15), ((64 * 150 + 33, 130, 96), 3, 9)]:

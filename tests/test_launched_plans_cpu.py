@@ -29,6 +29,7 @@ def rec(tmp_path_factory):
     lib.lba_conv2d.argtypes = [vp, vp, vp, lba_conv2d_desc, i64, lba_qfmt, lba_qfmt, i32, vp]
     lib.lba_conv2d_bwd.argtypes = [vp, vp, vp, vp, vp, lba_conv2d_desc, i64, lba_qfmt, lba_qfmt, i32, vp]
     lib.lba_gemm.argtypes = [vp, vp, vp, i64, i64, i64, lba_qfmt, lba_qfmt, i32, vp]
+    lib.lba_gemm_bwd.argtypes = [vp, vp, vp, vp, vp, i64, i64, i64, lba_qfmt, lba_qfmt, i32, vp]
     lib.lba_gemm_batched.argtypes = [vp, vp, vp, i64, i64, i64, i64, i64, i64, i64, lba_qfmt, lba_qfmt, i32, vp]
     lib.lba_gemm_bwd_in.argtypes = [vp, vp, vp, vp, vp, i64, i64, i64, lba_infmt, lba_infmt, lba_qfmt, lba_qfmt, i32, vp]
     return lib
@@ -98,6 +99,17 @@ def test_forward_of_narrow_filters(rec, shape, order, formats):
         assert p["mix_tail16"] and p["mix_main"] + p["mix_half"] == 0 and name == "launch_half_conv"
     else:
         assert name in ("launch_fast_conv", "launch_fast_amode", "launch_fast_in_mixed_seq", "launch_fast_in_mixed_chunk")
+
+
+# clamped products, chains of any length: small tiles on few workgroups
+@pytest.mark.parametrize("rnd", [0, 1])
+@pytest.mark.parametrize("K", [16, 64, 159, 160, 700])
+def test_small_clamped_recompute(rec, K, rnd):
+    for blocks, both, alone in [(1, True, True), (300, True, True), (400, True, False), (512, True, False), (768, False, False)]:
+        for uf, small in ((BUF, both), (None, alone)):
+            assert rec.lba_gemm_bwd(BUF, BUF, BUF, BUF, uf, 64 * blocks, 64, K, lba_qfmt(5, 7, 15, rnd), lba_qfmt(4, 7, 7, rnd), 0, None) == 0
+            name, p = taken(rec)
+            assert name == "launch_fast_bwd" and not p["packed"] and (p["mix_tail"] == 4 * blocks and p["mix_main"] == 0) == small, (blocks, uf)
 
 
 # One plane or both: the plan is that of the planes asked for, from every entry point
