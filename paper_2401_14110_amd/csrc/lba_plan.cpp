@@ -608,10 +608,10 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
     // 32 x 16 tiles throughout, or the 2 x 2 lane block's 32 x 32: a lone wave per SIMD gets a second one that stages for it
     // (packed carriers, or FP32 ones under nearest-even: E4M3 operands in pieces of 16 codes, fetched ahead of the chain)
     const bool rne32 = p.kernel == KERNEL_FAST && !kp.h_on && qa.round == LBA_ROUND_RNE && !p.rne_odd && p.amode == 0 && N * K >= 16 && M * K >= 16 && K <= kPieceMaxK;
-    // (truncated products ran on 256-lane workgroups of 64 x 64 or 32 x 32, up to 4.7 times as long: lba_rows.h.  Their short chains on few
-    // workgroups still do, at 8 to 21 us where the launch is most of it)
-    const bool stages = p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH ||
-                        (p.prod_mode == PM_TRUNC && !conv && (K > 512 || (K >= 224 && ((M + 31) / 32) * ((N + 31) / 32) > 64)));
+    // (truncated products ran on 256-lane workgroups of 64 x 64 or 32 x 32, up to 4.7 times as long: lba_rows.h.  On few outputs: M4E3, 64 x 1000 x 512
+    // 20.7 -> 11.5 us, x 200 11.8 -> 9.4, x 100 9.5 either way; E4M3 with 5-bit products 128 x 128 x 500 61 -> 15.6, x 200 27 -> 9.5, x 100 16.7 -> 9.4;
+    // a single k-tile has nothing to stage ahead, 64 x 1000 x 48 8.9 and 9.4)
+    const bool stages = p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH || (p.prod_mode == PM_TRUNC && !conv && K > HBK);
     const bool staged = !p.events && (kp.h_on ? !kp.h_range && rows != ROWS_NARROW && stages : rne32 && order == LBA_ORDER_SEQ && (p.prod_mode == PM_IDENT || p.prod_mode == PM_FLUSH));
     if (p.kpar == 0) plan_mixed_grid(M, N, batch, staged, rows, &p);
     p.staged = staged && (p.mix_tail > 0 ? kp.mix_tail16 && kp.mix_main + kp.mix_half == 0 : p.tm == 2 && p.tn == 2);

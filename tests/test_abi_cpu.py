@@ -311,11 +311,12 @@ def test_one_carrier_to_a_kernel():
     # kernels of other operand formats hold no second body
     name = lb.lba_plan_kernel_name_in
     m4e3, e5m2 = (3, 4, 3), (5, 2, 15)
-    for M, N, mixed in [(8192, 4096, False), (2048, 1024, False), (64, 1000, True), (3136, 512, True)]:
+    for M, N, kernel in [(8192, 4096, "lba_half_kernel<4, 4, 3"), (2048, 1024, "lba_half_kernel<4, 4, 3"), (64, 1000, "lba_half_staged_kernel<2, 3"),
+                         (3136, 512, "lba_half_mixed_kernel<3")]:
         for K, order in ((512, 0), (512, 1), (147, 0), (147, 1)):
             got = name(M, N, K, m4e3, m4e3, (5, 7, 1, 0), (4, 7, 2, 0), order)
-            assert got.startswith("lba_half_mixed_kernel<3" if mixed else "lba_half_kernel<4, 4, 3"), (M, N, K, got)
-            assert got.endswith(", 0>" if K % 16 == 0 else ", 3>"), got
+            assert got.startswith(kernel), (M, N, K, got)
+            assert got.endswith(", %d>" % order if "staged" in kernel else ", 0>" if K % 16 == 0 else ", 3>"), got
             assert name(M, N, K, m4e3, m4e3, (5, 7, 6, 0), (5, 10, 15, 0), order).startswith("lba_fast"), "a wide accumulator"
             assert name(M, N, K, e5m2, m4e3, (5, 7, 6, 0), (4, 7, 7, 0), order).startswith("lba_fast"), "E = 5"
 

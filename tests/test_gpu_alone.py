@@ -65,8 +65,8 @@ def test_recompute(ref, M, N, alone, K, zeros):
                     assert same(got[i].cpu().numpy()[:, rows], want[i]), (qp, qa, uf, i)
 
 
-# products that Q_prod truncates: forward on 64 x 64 workgroups (a batch counts all of its own), and recompute
-@pytest.mark.parametrize("batch,M,N,alone", [(1, 100, 70, True), (1, 16384, 64, True), (1, 16385, 64, False), (4, 256, 1024, True), (5, 256, 1024, False)])
+# products that Q_prod truncates: forward on 64 x 64 workgroups (a batch counts all of its own; the fewest have waves that stage), and recompute
+@pytest.mark.parametrize("batch,M,N,alone", [(1, 100, 70, False), (1, 401, 450, True), (1, 16384, 64, True), (1, 16385, 64, False), (4, 256, 1024, True), (5, 256, 1024, False)])
 @pytest.mark.parametrize("K", [48, 83, 160])
 def test_truncated_products(ref, batch, M, N, alone, K):
     rng = np.random.default_rng([batch, M, K])
@@ -75,7 +75,7 @@ def test_truncated_products(ref, batch, M, N, alone, K):
     rows = some(rng, M)
     for qp, qa in [((5, 4, 4, 0), (4, 7, -4, 0)), ((5, 4, 4, 0), (4, 7, 0, 0))]:
         if batch == 1:
-            assert ("alone" in binding.lba_plan_kernel_name(M, N, K, qp, qa, 0)) == alone
+            assert ("alone" in binding.lba_plan_kernel_name(M, N, K, qp, qa, 0)) == (alone or (M == 100 and K <= 64))
         for order in (0, 1):
             got = binding.gemm_batched(dA, dB, qp, qa, order=order).cpu().numpy()
             for b in range(batch):
