@@ -307,17 +307,17 @@ static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, AR
     // 328 -> 130, 1024 x 1024 323 -> 191, 288 workgroups 405 -> 246, 400 326 -> 315, 512 410 -> 355, 640 411 -> 434.  Both planes on packed carriers, which
     // hold 64 x 64 workgroups better (up to 256 of them: make_plan): 257 to 320 198 -> 156, 384 198 -> 184, 400 198 -> 211.
     // The overflow plane alone, times of 32 x 32 over 64 x 64.  FP32, K = 300, floor with M10E5 and nearest-even: 270 workgroups 0.94 and 0.62, 384 1.00
-    // and 0.71, 390 to 512 1.20 and 0.91 to 1.01; chains of up to three k-tiles under floor: 320 0.97 to 1.02, 384 1.04.  Packed, sums that never and often
-    // reach R_OF: K = 700, 320 workgroups 0.81 and 0.80, 384 0.93 and 0.93, 400 1.15 and 1.07; M4E3 with truncated products 320 0.89, 340 1.03;
-    // whole taps, K = 144, 320 0.92, 384 1.02 to 1.09, K = 576 0.80, 0.93.
+    // and 0.71, 390 to 512 1.20 and 0.91 to 1.01; chains of up to three k-tiles under floor: 320 0.97 to 1.02, 384 1.04.  Packed carriers keep 64 x 64,
+    // whose lists leave out zero codes that small tiles run (behind a ReLU, sums that stay below R_OF: 320 workgroups 0.88 to 1.08, 384 1.02 to 1.24, 7371 x 159
+    // x 1502 1.42; where sums often reach it 0.74 to 0.96).
     // Rows gathered from several taps cost small tiles more, each of which gathers its own.  FP32, both planes (3 x 3 on 3, 5 x 5 on 3, 15 x 15 on 1
     // channels, floor, M10E5): 270 workgroups 0.93, 0.86, 0.83, 384 0.98, 0.95, 0.92, 441 1.20, 1.15, 1.15, 500 1.15, 1.14, 1.13 (on 16 channels 0.71, 0.77,
-    // 0.94, 0.93); the overflow plane alone from two k-tiles on (K = 75) 320 0.98, 384 1.08, K = 27 1.05, truncated products 1.06 to 1.18; packed 1.05 to 1.8.
+    // 0.94, 0.93); the overflow plane alone from two k-tiles on (K = 75) 320 0.98, 384 1.08, K = 27 1.05, truncated products 1.06 to 1.18.
     // Clamped products on short chains, both planes: 500 x 500 x 64 36 -> 17 us, 1024 x 1024 x 100 69 -> 49, 19200 x 64 x 144 113 -> 73, 32768 x 64 x 64 49 -> 46.
     const bool parts = rows >= ROWS_GATHERED, packed = p->kp.h_on != 0;
     int64_t most;
     if (!p->of_only)  most = packed ? 384 : parts ? 384 : 512;
-    else if (packed)  most = parts ? 256 : p->amode == 1 || (rows == ROWS_TAPS && p->kp.K < 256) ? 320 : 384;
+    else if (packed)  most = 256;
     else if (parts)   most = p->amode == 2 && p->kp.K >= 64 ? 320 : 256;
     else              most = p->round == LBA_ROUND_RNE || p->kp.K > 96 ? 384 : 320;
     if (p->events == 1 && !chunk_of && blocks > (packed ? 256 : 0) && blocks <= most && set_mixed_grid(M, N, 0, 0, p)) return;

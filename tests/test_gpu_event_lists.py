@@ -46,7 +46,7 @@ def some(rng, M):
 
 
 # 64 x 64 workgroups, and those with 32 x 32 behind them; 16-byte rows and not; K of one tile and of many
-@pytest.mark.parametrize("M,N,kernel", [(30000, 60, "lba_half_bwd_kernel"), (17000, 72, "lba_half_bwd_mixed_kernel"), (27000, 64, "lba_half_bwd_mixed_kernel")])
+@pytest.mark.parametrize("M,N,kernel", [(20000, 60, "lba_half_bwd_kernel"), (17000, 72, "lba_half_bwd_mixed_kernel"), (27000, 64, "lba_half_bwd_mixed_kernel")])
 @pytest.mark.parametrize("K", [64, 400, 403, 640])
 def test_rows(ref, M, N, kernel, K):
     rng = np.random.default_rng([M, K])

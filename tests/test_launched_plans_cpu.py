@@ -122,16 +122,15 @@ def test_planes_asked_for(rec, planes):
             rc = rec.lba_gemm_bwd_in(BUF, BUF, BUF, of, uf, 64 * blocks, 64, 500, lba_infmt(*fmt), lba_infmt(*fmt), lba_qfmt(*qp), lba_qfmt(*qa), 0, None)
             name, p = taken(rec)
             assert rc == 0 and p["of_only"] == alone and p["packed"] == packed and fits(64 * blocks, 64, p)
-            # 32 x 32 throughout: FP32 up to 384 and 512, packed from 257 to 384 (truncated products without an underflow plane to 320; fewer: truncated products
-            # as well, others have kernels of their own)
+            # 32 x 32 throughout: FP32 up to 384 and 512, packed with both planes from 257 to 384 (fewer: truncated products, others have kernels of their own)
             small = p["mix_tail"] == 4 * blocks and p["mix_main"] == 0
             trunc = fmt == (3, 4, 3)
-            want = blocks <= (384 if alone else 512) if not packed else blocks <= (320 if alone and trunc else 384) and (trunc or blocks > 256)
+            want = blocks <= (384 if alone else 512) if not packed else blocks <= (256 if alone else 384) and (trunc or blocks > 256)
             assert small == want, (blocks, p)
     for c, formats, packed in [(32, PACKED, True), (20, PACKED, True), (32, WIDE, False), (3, WIDE, False)]:
         _, _, name, p = conv(rec, 1, 64, 300, c, 64, 3, formats, planes)
         assert p["of_only"] == alone and p["packed"] == packed
-        assert (p["mix_tail"] == 1200) == (not alone or c == 32)
+        assert (p["mix_tail"] == 1200) == (not alone or (c == 32 and not packed))
 
 
 # the overflow plane alone: whole taps up to 384, gathered rows up to 320 from two k-tiles on and up to 256 with truncated products
