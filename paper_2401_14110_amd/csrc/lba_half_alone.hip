@@ -17,7 +17,10 @@ namespace lba {
 
 // The recompute call on at most 256 workgroups of 64 x 64.  T 2: workgroups of 32 x 32, a CU's share of which is the smaller the fewer
 // there are, and whose chains are a fourth of a wave's work.  T 4: 64 x 64, for the overflow plane under the sequential order on more than 192
-// of them, where a wave alone on its SIMD issues as much as the four of the small ones (900 x 900 x 700, training step, 151 us, 152).
+// of them, where a wave alone on its SIMD issues as much as the four of the small ones (900 x 900 x 700, training step, 151 us, 152), and for
+// widths that are no multiple of 32, whose small tiles write parts of cache lines (partial_lines, lba_plan.cpp; 64 x 64 and 32 x 32, 256 workgroups, both planes,
+// N = 190, K = 1000 1.24 times as long, K = 300 0.84 to 1.09, 192 workgroups 0.68 to 0.93; the overflow plane in chunks, N = 159, K = 1501 124.6 and 192 us, 200
+// workgroups 123.7 and 140, K = 300, 256 workgroups 31.5 and 34.7; in order, N = 702, K = 1501, 192 workgroups 119 and 136).
 // 64 x 64 -> 32 x 32, both planes: 500 x 500 x 700 143 -> 60 us, 700 x 700 145 -> 78, 1024 x 1024 142 -> 122; training steps, K = 700:
 // 500 x 500 115 -> 84, 700 x 700 125 -> 103, 1024 x 700 145 -> 133, in chunks 149 -> 108, 179 -> 131, 194 -> 180, 1024 x 1024 210 -> 207.
 template <int T, int PM, int ORDER, bool UF, int AMODE>
@@ -37,9 +40,8 @@ __global__ void __launch_bounds__(256, 2) lba_half_alone_mixed_kernel(const KPar
 template <int PM, int ORDER, bool UF, int AMODE>
 static hipError_t launch_bwd(const Plan& pl, hipStream_t st) {
     const dim3 grid(pl.grid_x, pl.grid_y, 1), block(256);
-    if (pl.tm == 2)                                        hipLaunchKernelGGL((lba_half_bwd_alone_kernel<2, PM, ORDER, UF, AMODE>), grid, block, 0, st, pl.kp);
-    else if constexpr (!UF && ORDER == LBA_ORDER_SEQ) hipLaunchKernelGGL((lba_half_bwd_alone_kernel<4, PM, ORDER, UF, AMODE>), grid, block, 0, st, pl.kp);
-    else                                                   return hipErrorInvalidValue;
+    if (pl.tm == 2) hipLaunchKernelGGL((lba_half_bwd_alone_kernel<2, PM, ORDER, UF, AMODE>), grid, block, 0, st, pl.kp);
+    else            hipLaunchKernelGGL((lba_half_bwd_alone_kernel<4, PM, ORDER, UF, AMODE>), grid, block, 0, st, pl.kp);
     return hipGetLastError();
 }
 template <int PM, int ORDER>

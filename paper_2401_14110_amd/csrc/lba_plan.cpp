@@ -278,6 +278,11 @@ static bool set_mixed_grid(int64_t M, int64_t N, int64_t gx_main, int64_t gx_hal
     return true;
 }
 
+// Event planes whose rows of 32 columns do not start and end with cache lines: the non-temporal words of a 32 x 32 tile leave as two parts of lines a
+// row, which a tile of 64 columns has beside a whole one.  Where the planes are larger than what the caches hold back, that costs more
+// than small tiles gain.
+static bool partial_lines(int64_t N) { return N % 32 != 0; }
+
 // staged: waves of their own stage where the grid is 32 x 16 or 32 x 32 tiles throughout
 static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, ARows rows, Plan* p) {
     p->mix_tail = 0;
@@ -303,7 +308,7 @@ static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, AR
     // those kernels have the 4 x 4 lane block alone outside the mixed grid: a grid too small for it (a single wave per
     // SIMD issues at half rate) becomes 32 x 32 workgroups throughout
     if (p->amode == 1 && blocks <= 256 && set_mixed_grid(M, N, 0, 0, p)) return;
-    // The recompute call, 64 x 64 throughout against 32 x 32, on FP32 carriers (both planes, nearest-even, K = 700): 500 x 500 328 -> 111 us, 700 x 700
+    // The recompute call, 64 x 64 throughout against 32 x 32 (lines in four workgroups of 32 x 32, so that empty halves of 64 x 64 ones do not count), on FP32 carriers (both planes, nearest-even, K = 700): 500 x 500 328 -> 111 us, 700 x 700
     // 328 -> 130, 1024 x 1024 323 -> 191, 288 workgroups 405 -> 246, 400 326 -> 315, 512 410 -> 355, 640 411 -> 434.  Both planes on packed carriers, which
     // hold 64 x 64 workgroups better (up to 256 of them: make_plan): 257 to 320 198 -> 156, 384 198 -> 184, 400 198 -> 211.
     // The overflow plane alone, times of 32 x 32 over 64 x 64.  FP32, K = 300, floor with M10E5 and nearest-even: 270 workgroups 0.94 and 0.62, 384 1.00
@@ -314,13 +319,16 @@ static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, AR
     // channels, floor, M10E5): 270 workgroups 0.93, 0.86, 0.83, 384 0.98, 0.95, 0.92, 441 1.20, 1.15, 1.15, 500 1.15, 1.14, 1.13 (on 16 channels 0.71, 0.77,
     // 0.94, 0.93); the overflow plane alone from two k-tiles on (K = 75) 320 0.98, 384 1.08, K = 27 1.05, truncated products 1.06 to 1.18.
     // Clamped products on short chains, both planes: 500 x 500 x 64 36 -> 17 us, 1024 x 1024 x 100 69 -> 49, 19200 x 64 x 144 113 -> 73, 32768 x 64 x 64 49 -> 46.
-    const bool parts = rows >= ROWS_GATHERED, packed = p->kp.h_on != 0;
+    // Widths that are no multiple of 32 (partial_lines): packed, both planes, N = 122 to 1230, K = 300, 300 workgroups 0.70 to 1.00, 384 0.83 to 1.25, K = 1000
+    // 0.84 to 1.10, 1.02 to 1.36; FP32 under floor K = 300, 512 workgroups 0.73 to 1.03, K = 1000 0.77 to 1.12, 2000 and more 0.88 to 1.21, 384 0.71 to 0.90; the
+    // overflow plane alone 384 1.05 to 1.09, N = 159, 384 workgroups (320 by what they hold), K = 1501 1.05.
+    const bool parts = rows >= ROWS_GATHERED, packed = p->kp.h_on != 0, floor = p->round == LBA_ROUND_FLOOR, partial = partial_lines(N), deep = p->kp.K > 512;
     int64_t most;
-    if (!p->of_only)  most = packed ? 384 : parts ? 384 : 512;
-    else if (packed)  most = 256;
+    if (!p->of_only)  most = packed ? (partial ? (deep ? 256 : 320) : 384) : parts || (partial && deep && floor) ? 384 : 512;
+    else if (packed)  most = 192;
     else if (parts)   most = p->amode == 2 && p->kp.K >= 64 ? 320 : 256;
-    else              most = p->round == LBA_ROUND_RNE || p->kp.K > 96 ? 384 : 320;
-    if (p->events == 1 && !chunk_of && blocks > (packed ? 256 : 0) && blocks <= most && set_mixed_grid(M, N, 0, 0, p)) return;
+    else              most = !floor || (p->kp.K > 96 && !partial) ? 384 : partial && deep ? 300 : 320;
+    if (p->events == 1 && !chunk_of && blocks > (packed ? 256 : 0) && (b32 + 3) / 4 <= most && set_mixed_grid(M, N, 0, 0, p)) return;
     // the smallest grids of the forward call (at most 128 workgroups of 32 x 32, e.g. a 64 x 1000 classifier layer): the
     // tail's 32 x 16 tiles throughout, twice the workgroups of the 2 x 2 lane block
     if (p->events == 0 && b32 <= 128 && set_mixed_grid(M, N, 0, 0, p)) return;
@@ -621,7 +629,10 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
     p.alone = kp.h_on && !kp.h_range && p.kpar == 0 && !p.staged &&
               (p.mix_tail > 0 ? !p.events && p.prod_mode == PM_FLUSH && kp.mix_main == 0 && kp.mix_half > 0 && total < 512
                               : p.tm == 4 && p.tn == 4 && total <= 256 && (p.events || (p.prod_mode == PM_TRUNC && !conv)));
-    if (p.alone && p.events && (total <= 192 || !p.of_only || order == LBA_ORDER_CHUNK16)) {   // smaller ones (lba_half_alone.hip)
+    // smaller ones (lba_half_alone.hip has the figures of both lines)
+    int64_t most_small = p.of_only && order == LBA_ORDER_SEQ ? 192 : 256;
+    if (partial_lines(N)) most_small = std::min<int64_t>(most_small, !p.of_only ? (K > 512 ? 192 : 256) : K > 512 ? 160 : K > 160 ? 192 : 256);
+    if (p.alone && p.events && (((M + 31) / 32) * ((N + 31) / 32) + 3) / 4 <= most_small) {
         p.tm = p.tn = 2;
         p.grid_x = (int)((M + 31) / 32);
         p.grid_y = (int)((N + 31) / 32);

@@ -33,3 +33,23 @@ def test_widths(ref, M, N):
         assert np.array_equal(got[0].cpu().numpy()[rows].view(np.uint32), np.ascontiguousarray(right[0]).view(np.uint32))
         for g, r in zip(got[1:], right[1:]):
             assert np.array_equal(g.cpu().numpy()[:, rows].view(np.uint32), r)
+
+
+# chains of more than 512 steps: 32 x 32 workgroups on the smallest grids, 64 x 64 ones alone on their CUs and more of them
+@pytest.mark.parametrize("M", [64 * 160, 64 * 200 + 3, 64 * 256, 64 * 300])
+@pytest.mark.parametrize("N", [34, 61])
+def test_deep_chains(ref, M, N):
+    K = 515
+    rng = np.random.default_rng([M, N, K])
+    A, B = ((rng.integers(0, 2, s) * 128 + rng.integers(0, 72, s)).astype(np.uint8) for s in ((M, K), (N, K)))
+    dA, dB = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    rows = np.unique(np.concatenate([[0, 1, M - 2, M - 1], rng.choice(M, 30, replace=False)]))
+    qp, qa = (5, 7, 12, 0), (4, 7, 9, 0)
+    for order in (0, 1):
+        right = ref.gemm_bwd(np.ascontiguousarray(A[rows]), B, ref.QFmt(*qp), ref.QFmt(*qa), **({"order": 1, "level2": True} if order else {}))
+        for uf in (True, False):
+            got = binding.gemm_bwd_chunked(dA, dB, qp, qa, want_uf=uf) if order else binding.gemm_bwd(dA, dB, qp, qa, want_uf=uf)
+            torch.cuda.synchronize()
+            assert np.array_equal(got[0].cpu().numpy()[rows].view(np.uint32), np.ascontiguousarray(right[0]).view(np.uint32))
+            for g, r in zip(got[1:], right[1:]):
+                assert g is None or np.array_equal(g.cpu().numpy()[:, rows].view(np.uint32), r)

@@ -30,6 +30,7 @@ def rec(tmp_path_factory):
     lib.lba_conv2d_bwd.argtypes = [vp, vp, vp, vp, vp, lba_conv2d_desc, i64, lba_qfmt, lba_qfmt, i32, vp]
     lib.lba_gemm.argtypes = [vp, vp, vp, i64, i64, i64, lba_qfmt, lba_qfmt, i32, vp]
     lib.lba_gemm_bwd.argtypes = [vp, vp, vp, vp, vp, i64, i64, i64, lba_qfmt, lba_qfmt, i32, vp]
+    lib.lba_gemm_bwd_chunked.argtypes = [vp, vp, vp, vp, vp, vp, vp, i64, i64, i64, lba_qfmt, lba_qfmt, vp]
     lib.lba_gemm_batched.argtypes = [vp, vp, vp, i64, i64, i64, i64, i64, i64, i64, lba_qfmt, lba_qfmt, i32, vp]
     lib.lba_gemm_bwd_in.argtypes = [vp, vp, vp, vp, vp, i64, i64, i64, lba_infmt, lba_infmt, lba_qfmt, lba_qfmt, i32, vp]
     return lib
@@ -65,6 +66,7 @@ def fits(M, N, p):
     return p["grid_x"] == p["mix_main"] + p["mix_tail"] and p["grid_y"] == 1
 
 
+NEAREST = ((5, 7, -2, 1), (4, 7, -10, 1))
 WIDE, WIDE_TRUNC = ((5, 7, 12, 0), (5, 10, 9, 0)), ((5, 4, 12, 0), (5, 10, 9, 0))
 
 
@@ -99,6 +101,35 @@ def test_forward_of_narrow_filters(rec, shape, order, formats):
         assert p["mix_tail16"] and p["mix_main"] + p["mix_half"] == 0 and name == "launch_half_conv"
     else:
         assert name in ("launch_fast_conv", "launch_fast_amode", "launch_fast_in_mixed_seq", "launch_fast_in_mixed_chunk")
+
+
+# widths that are no multiple of 32, whose small tiles write parts of cache lines: the blocks up to which tiles are 32 x 32, alone on their CUs or throughout
+@pytest.mark.parametrize("N", [60, 64])
+@pytest.mark.parametrize("formats,K,planes,order,most", [
+    (PACKED, 160, "ou", 0, (320, 384)), (PACKED, 512, "ou", 0, (320, 384)), (PACKED, 513, "ou", 0, (192, 384)), (PACKED, 513, "ou", 1, (192, 256)), (PACKED, 512, "ou", 1, (256, 256)),
+    (PACKED, 160, "o", 0, (192, 192)), (PACKED, 512, "o", 0, (192, 192)), (PACKED, 513, "o", 0, (160, 192)), (PACKED, 160, "o", 1, (256, 256)), (PACKED, 161, "o", 1, (192, 256)),
+    (PACKED, 513, "o", 1, (160, 256)), (WIDE, 512, "ou", 0, (512, 512)), (WIDE, 513, "ou", 0, (384, 512)), (WIDE, 513, "o", 0, (300, 384)), (WIDE, 512, "o", 0, (320, 384)), (WIDE, 96, "o", 0, (320, 320)),
+    (NEAREST, 513, "ou", 0, (512, 512)), (NEAREST, 513, "o", 0, (384, 384))])
+def test_partial_lines(rec, N, formats, K, planes, order, most):
+    most = most[N == 64]
+    for blocks in (1, 160, 161, 192, 193, 256, 257, 300, 301, 320, 321, 384, 385, 512, 513):
+        M, qp, qa = 64 * blocks, lba_qfmt(*formats[0]), lba_qfmt(*formats[1])
+        of, uf = BUF, BUF if "u" in planes else None
+        rc = rec.lba_gemm_bwd_chunked(BUF, BUF, BUF, of, uf, of, uf, M, N, K, qp, qa, None) if order else rec.lba_gemm_bwd(BUF, BUF, BUF, of, uf, M, N, K, qp, qa, 0, None)
+        name, p = taken(rec)
+        assert rc == 0 and fits(M, N, p)
+        small = p["tm"] == 2 if p["alone"] else p["mix_tail"] == 4 * blocks and p["mix_main"] == 0
+        assert small == (blocks <= most), (blocks, name, p)
+
+
+# tiles whose halves are empty count for what they hold
+@pytest.mark.parametrize("N,formats,planes,blocks,small", [(32, WIDE, "o", 512, True), (32, WIDE, "ou", 1024, True), (32, WIDE, "ou", 1026, False), (32, PACKED, "o", 256, True),
+                                                           (160, PACKED, "o", 228, True), (160, PACKED, "o", 300, False), (32, PACKED, "o", 384, True), (160, PACKED, "o", 234, False), (32, PACKED, "ou", 700, True), (64, PACKED, "o", 300, False)])
+def test_empty_halves(rec, N, formats, planes, blocks, small):
+    M = 64 * (blocks // -(-N // 64))
+    assert rec.lba_gemm_bwd(BUF, BUF, BUF, BUF, BUF if "u" in planes else None, M, N, 700, lba_qfmt(*formats[0]), lba_qfmt(*formats[1]), 0, None) == 0
+    name, p = taken(rec)
+    assert (p["tm"] == 2 if p["alone"] else p["mix_tail"] > 0 and p["mix_main"] == 0) == small, (name, p)
 
 
 # clamped products, chains of any length: small tiles on few workgroups
@@ -143,7 +174,6 @@ def test_small_fp32_overflow_plane(rec, c, k, formats, most):
 
 
 WIDE7, WIDE10 = ((5, 7, 12, 0), (5, 7, -2, 0)), ((5, 7, 12, 0), (5, 10, -2, 0))     # packed, sums beyond FP16's range
-NEAREST = ((5, 7, -2, 1), (4, 7, -10, 1))
 
 
 # 513 to 1024 workgroups of 64 x 64 (a batch, which has no tail): the finer block throughout on FP32 carriers, on packed ones where it saves half a round of 256
