@@ -328,7 +328,9 @@ static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, AR
     else if (packed)  most = 192;
     else if (parts)   most = p->amode == 2 && p->kp.K >= 64 ? 320 : 256;
     else              most = !floor || (p->kp.K > 96 && !partial) ? 384 : partial && deep ? 300 : 320;
-    if (p->events == 1 && !chunk_of && blocks > (packed ? 256 : 0) && (b32 + 3) / 4 <= most && set_mixed_grid(M, N, 0, 0, p)) return;
+    // (beyond 384 workgroups, 512 on FP32 carriers, only where half of each is empty: there a tail is the other choice, 8352 x 160 x 208, 393, 66 us with one, 72)
+    if (p->events == 1 && !chunk_of && blocks > (packed ? 256 : 0) && (b32 + 3) / 4 <= most && (blocks <= (packed ? 384 : 512) || b32 <= 2 * blocks) &&
+        set_mixed_grid(M, N, 0, 0, p)) return;
     // the smallest grids of the forward call (at most 128 workgroups of 32 x 32, e.g. a 64 x 1000 classifier layer): the
     // tail's 32 x 16 tiles throughout, twice the workgroups of the 2 x 2 lane block
     if (p->events == 0 && b32 <= 128 && set_mixed_grid(M, N, 0, 0, p)) return;
