@@ -223,7 +223,8 @@ static bool half_underflow_ok(const lba_qfmt& qp, const InSpec& in, int bpe, int
 // 16-byte boundaries 1530 x 2045 x 70 25.2 -> 22.4, x 771 198 -> 184, 8192 x 500 x 147 57 -> 52, 42240 x 63 x 331, which had a tail, 1.05 times as fast).
 // Sums beyond FP16's range (h_range) leave the packed tile now and then and gain less: from chains of 96 steps on, in chunks of 256 (2 x 4 over 4 x 4, 736
 // to 1024 workgroups, M7E5 and M10E5, K = 32 0.95 and 0.95, 64 0.98 and 0.98, 96 1.04 and 1.03, 256 1.05 and 1.03; in chunks 0.92 and 0.92, 0.95 and 0.96, 0.97 and
-// 0.97, 1.01 and 0.99, K = 2304 1.03 and 1.04), and on rows off 16-byte boundaries not at all.
+// 0.97, 1.01 and 0.99, K = 2304 1.03 and 1.04), and on rows off 16-byte boundaries not at all; on rows gathered from
+// several taps always (2 x 2 on 20 channels, 768 workgroups, 1.17 and 1.19, in chunks 1.16 and 1.12): the finer block gathers them twice as often.
 // Filter rows gathered byte by byte (ROWS_NARROW, FP32): as on packed carriers (3 x 3 x 3, 762 workgroups, 20.2 us, 17.8 with 4 x 4; 5 x 5 x 3 44.5
 // and 38.6; nearest-even 43.5 and 38.6; 1016 workgroups 55.7 and 47.8).
 // The choice never changes a result.
@@ -548,7 +549,7 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
         p.amode = 2;
     p.rne_odd = (fast && rne_odd) ? 1 : 0;
     // (pick_tile) the 2 x 4 lane block on 513 to 1024 workgroups only where it saves half a round
-    const bool half_rounds = rows == ROWS_NARROW || (kp.h_on && (!kp.h_range || (K % 16 == 0 && K >= (order == LBA_ORDER_CHUNK16 ? 256 : 96))));
+    const bool half_rounds = rows == ROWS_NARROW || (kp.h_on && (!kp.h_range || (K % 16 == 0 && (rows == ROWS_GATHERED || K >= (order == LBA_ORDER_CHUNK16 ? 256 : 96)))));
     pick_tile(M, N, batch, p.kernel, p.events, p.prod_mode, p.amode == 1, p.rne_odd, half_rounds, &p.tm, &p.tn, &p.bk);
     kp.batch = 1;
     kp.fast_thresh = -1.0f;

@@ -189,6 +189,14 @@ def test_half_rounds(rec, batch):
         assert (p["tm"], p["tn"]) == ((2, 4) if finer else (4, 4)), (formats, K, order)
 
 
+# im2col rows beyond FP16's range: gathered from several taps, and whole taps
+@pytest.mark.parametrize("c,k,order,half_rounds", [(20, 2, 0, True), (20, 2, 1, True), (12, 2, 0, True), (16, 2, 0, False), (16, 3, 0, True), (16, 3, 1, False), (32, 3, 1, True)])
+def test_wide_convolutions(rec, c, k, order, half_rounds):
+    M, N, name, p = conv(rec, 1, 64 + (k == 2) * -1, 768 + (k == 2) * -1, c, 64, k, WIDE7, None, order)
+    assert M == 64 * 768 and name == "launch_wide_conv" and p["mix_tail"] == 0 and fits(M, N, p)
+    assert (p["tm"], p["tn"]) == ((4, 4) if half_rounds else (2, 4))
+
+
 # members whose last rows fill half a tile of 64: the finer block has fewer rounds than twice the workgroups of 64 x 64
 @pytest.mark.parametrize("batch,M,finer", [(64, 197, True), (60, 197, True), (48, 197, False), (36, 197, True), (384, 70, True), (256, 128, False), (500, 96, True), (340, 100, False), (700, 32, True)])
 def test_half_tiles(rec, batch, M, finer):
