@@ -215,3 +215,13 @@ def test_tail_of_a_last_round(rec, formats, K, tail):
         assert rec.lba_gemm(BUF, BUF, BUF, 64 * 700, 64, K, lba_qfmt(*formats[0]), lba_qfmt(*formats[1]), order, None) == 0
         name, p = taken(rec)
         assert (p["mix_main"] == 512 and p["mix_tail"] == 752) == tail and (tail or p["mix_tail"] == 0)
+
+
+# chunks of few outputs: side by side up to 96 workgroups of 32 x 32 (128 on short chains), one after the other with waves that stage beyond
+@pytest.mark.parametrize("K,most", [(1712, 96), (224, 96), (208, 128)])
+def test_chunks_side_by_side(rec, K, most):
+    for b32 in (1, 64, 65, 96, 97, 128, 129, 300):
+        assert rec.lba_gemm(BUF, BUF, BUF, 32 * b32, 32, K, lba_qfmt(*PACKED[0]), lba_qfmt(*PACKED[1]), 1, None) == 0
+        name, p = taken(rec)
+        assert (p["kpar"] > 0) == (b32 <= most or (K == 208 and b32 > 256)), b32
+        assert name == ("launch_kpar" if p["kpar"] else "launch_half") and (p["kpar"] > 0 or p["staged"])
