@@ -322,15 +322,16 @@ static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, AR
     // Clamped products on short chains, both planes: 500 x 500 x 64 36 -> 17 us, 1024 x 1024 x 100 69 -> 49, 19200 x 64 x 144 113 -> 73, 32768 x 64 x 64 49 -> 46.
     // Widths that are no multiple of 32 (partial_lines): packed, both planes, N = 122 to 1230, K = 300, 300 workgroups 0.70 to 1.00, 384 0.83 to 1.25, K = 1000
     // 0.84 to 1.10, 1.02 to 1.36; FP32 under floor K = 300, 512 workgroups 0.73 to 1.03, K = 1000 0.77 to 1.12, 2000 and more 0.88 to 1.21, 384 0.71 to 0.90; the
-    // overflow plane alone 384 1.05 to 1.09, N = 159, 384 workgroups (320 by what they hold), K = 1501 1.05.
-    const bool parts = rows >= ROWS_GATHERED, packed = p->kp.h_on != 0, floor = p->round == LBA_ROUND_FLOOR, partial = partial_lines(N), deep = p->kp.K > 512;
+    // overflow plane alone (half the words per step: deep beyond K = 1024) clamped K = 300 to 668, 384 0.77 to 1.00, N = 55, K = 1482, 607 of full tiles and
+    // 337 us, N = 159, 384 workgroups (320 by what they hold), K = 1501 1.05.
+    const bool parts = rows >= ROWS_GATHERED, packed = p->kp.h_on != 0, floor = p->round == LBA_ROUND_FLOOR, partial = partial_lines(N), deep = p->kp.K > (p->of_only ? 1024 : 512);
     int64_t most;
     if (!p->of_only)  most = packed ? (partial ? (deep ? 256 : 320) : 384) : parts || (partial && deep && floor) ? 384 : 512;
     else if (packed)  most = 192;
     else if (parts)   most = p->amode == 2 && p->kp.K >= 64 ? 320 : 256;
-    else              most = !floor || (p->kp.K > 96 && !partial) ? 384 : partial && deep ? 300 : 320;
+    else              most = !floor || (p->kp.K > 96 && !(partial && deep)) ? 384 : 320;
     // (beyond 384 workgroups, 512 on FP32 carriers, only where half of each is empty: there a tail is the other choice, 8352 x 160 x 208, 393, 66 us with one, 72)
-    if (p->events == 1 && !chunk_of && blocks > (packed ? 256 : 0) && (b32 + 3) / 4 <= most && (blocks <= (packed ? 384 : 512) || b32 <= 2 * blocks) &&
+    if (p->events == 1 && !chunk_of && blocks > (packed ? 256 : 0) && (b32 + 3) / 4 <= most && (blocks <= (packed ? 384 : p->of_only && partial && deep ? 320 : 512) || b32 <= 2 * blocks) &&
         set_mixed_grid(M, N, 0, 0, p)) return;
     // the smallest grids of the forward call (at most 128 workgroups of 32 x 32, e.g. a 64 x 1000 classifier layer): the
     // tail's 32 x 16 tiles throughout, twice the workgroups of the 2 x 2 lane block
@@ -636,7 +637,7 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
                               : p.tm == 4 && p.tn == 4 && total <= 256 && (p.events || (p.prod_mode == PM_TRUNC && !conv)));
     // smaller ones (lba_half_alone.hip has the figures of both lines)
     int64_t most_small = p.of_only && order == LBA_ORDER_SEQ ? 192 : 256;
-    if (partial_lines(N)) most_small = std::min<int64_t>(most_small, !p.of_only ? (K > 512 ? 192 : 256) : K > 512 ? 160 : K > 160 ? 192 : 256);
+    if (partial_lines(N)) most_small = std::min<int64_t>(most_small, !p.of_only ? (K > 512 ? 192 : 256) : K > 1024 ? 160 : K > 160 ? 192 : 256);
     if (p.alone && p.events && (((M + 31) / 32) * ((N + 31) / 32) + 3) / 4 <= most_small) {
         p.tm = p.tn = 2;
         p.grid_x = (int)((M + 31) / 32);

@@ -107,8 +107,8 @@ def test_forward_of_narrow_filters(rec, shape, order, formats):
 @pytest.mark.parametrize("N", [60, 64])
 @pytest.mark.parametrize("formats,K,planes,order,most", [
     (PACKED, 160, "ou", 0, (320, 384)), (PACKED, 512, "ou", 0, (320, 384)), (PACKED, 513, "ou", 0, (192, 384)), (PACKED, 513, "ou", 1, (192, 256)), (PACKED, 512, "ou", 1, (256, 256)),
-    (PACKED, 160, "o", 0, (192, 192)), (PACKED, 512, "o", 0, (192, 192)), (PACKED, 513, "o", 0, (160, 192)), (PACKED, 160, "o", 1, (256, 256)), (PACKED, 161, "o", 1, (192, 256)),
-    (PACKED, 513, "o", 1, (160, 256)), (WIDE, 512, "ou", 0, (512, 512)), (WIDE, 513, "ou", 0, (384, 512)), (WIDE, 513, "o", 0, (300, 384)), (WIDE, 512, "o", 0, (320, 384)), (WIDE, 96, "o", 0, (320, 320)),
+    (PACKED, 160, "o", 0, (192, 192)), (PACKED, 1024, "o", 0, (192, 192)), (PACKED, 1025, "o", 0, (160, 192)), (PACKED, 160, "o", 1, (256, 256)), (PACKED, 161, "o", 1, (192, 256)),
+    (PACKED, 1024, "o", 1, (192, 256)), (PACKED, 1025, "o", 1, (160, 256)), (WIDE, 512, "ou", 0, (512, 512)), (WIDE, 513, "ou", 0, (384, 512)), (WIDE, 1025, "o", 0, (320, 384)), (WIDE, 1024, "o", 0, (384, 384)), (WIDE, 96, "o", 0, (320, 320)),
     (NEAREST, 513, "ou", 0, (512, 512)), (NEAREST, 513, "o", 0, (384, 384))])
 def test_partial_lines(rec, N, formats, K, planes, order, most):
     most = most[N == 64]
