@@ -33,3 +33,23 @@ def test_overflow_planes(ref, M, N, tail, K):
         assert uf is None and uf2 is None
         assert np.array_equal(c.cpu().numpy()[rows].view(np.uint32), np.ascontiguousarray(want[0]).view(np.uint32))
         assert np.array_equal(of.cpu().numpy()[:, rows].view(np.uint32), want[1]) and np.array_equal(of2.cpu().numpy()[:, rows].view(np.uint32), want[3])
+
+
+# a format that packed carriers hold without an underflow plane only: both levels of the overflow planes, on few workgroups, a plain grid and one with a tail
+@pytest.mark.parametrize("M,N", [(33, 37), (64 * 200 + 1, 60), (64 * 300, 64), (64 * 530 + 45, 60)])
+@pytest.mark.parametrize("K", [15, 100, 1050])
+def test_products_far_below_the_sums(ref, M, N, K):
+    if K > 1000 and M > 64 * 200 + 1:
+        K = 550                                                # (more than 32 chunks: a second word of the second level, on the smaller ones)
+    rng = np.random.default_rng([M, N, K])
+    A, B = ((rng.integers(0, 2, s) * 128 + rng.integers(0, 110, s)).astype(np.uint8) for s in ((M, K), (N, K)))
+    A[::3] = rng.integers(124, 127, A[::3].shape)             # rows whose sums reach R_OF on the longest chains, at the second level
+    B[::2] = rng.integers(124, 127, B[::2].shape)
+    qp, qa = (5, 7, 1, 0), (4, 7, -10, 0)
+    assert "half" in binding.lba_plan_kernel_name(M, N, K, qp, qa, 1, 3) and "half" not in binding.lba_plan_kernel_name(M, N, K, qp, qa, 1, 1)
+    rows = np.unique(np.concatenate([[0, M - 1], rng.choice(M, min(M, 30), replace=False)]))
+    c, of, _, of2, _ = binding.gemm_bwd_chunked(torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda(), qp, qa, want_uf=False)
+    want = ref.gemm_bwd(np.ascontiguousarray(A[rows]), B, ref.QFmt(*qp), ref.QFmt(*qa), order=1, level2=True)
+    assert np.array_equal(c.cpu().numpy()[rows].view(np.uint32), np.ascontiguousarray(want[0]).view(np.uint32))
+    assert np.array_equal(of.cpu().numpy()[:, rows].view(np.uint32), want[1]) and np.array_equal(of2.cpu().numpy()[:, rows].view(np.uint32), want[3])
+    assert want[3].any() == (K > 500)
