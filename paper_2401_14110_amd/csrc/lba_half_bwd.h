@@ -208,7 +208,10 @@ __device__ __forceinline__ void half_bwd_tile(h2 (&acc)[TM][TN / 2], h2 (&top)[T
 // row, some of them its neighbour's (which stores the same), so that a row still leaves by one store an instruction: word by word the end
 // of a row went to memory as partial lines of its own.  Both planes, us, before -> so: 45658 x 106 x 729 710 -> 596 (104 columns 565),
 // 30000 x 99 x 640 420 -> 364, 20000 x 250 x 500 413 -> 381.  Kernels of their own (AMODE 3): the address and masks beside the ordinary
-// stores cost these 1 % (45658 x 128 x 729 560 -> 565).
+// stores cost these 1 % (45658 x 128 x 729 560 -> 565).  Not the whole of it: a tile that holds no more than one lane's columns (width 64 n + 1 to
+// 64 n + 3, 32 n + 1 in small tiles) has no neighbour to take words from and stores them one by one, and so do im2col rows (AMODE 2)
+// and the overflow plane alone (lba_rows.h).  With truncated products, chains of 33 to 64 steps and one round and a third of workgroups,
+// it loses where C is stored too (2328 x 2243 x 46 63 -> 69; without C 60 -> 59, 1164 rows 42 -> 41, 160 steps 139 -> 135).
 template <int TM, int TN, bool ENDS>
 __device__ __forceinline__ void store_half_words(uint32_t* __restrict__ plane, int word, const uint32_t (&w)[TM][TN], int m0, int n0,
                                                  int tx, int ty, const KParams& p) {

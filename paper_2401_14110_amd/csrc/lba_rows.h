@@ -777,7 +777,7 @@ __device__ __forceinline__ void rows_body(const KParams& p, uint32_t* __restrict
 // 16-byte read for four or two of them, 8 cycles each among other instructions), and branches: a taken one costs a lone wave 40 to 130
 // cycles (measured with loops of 16 to 256 steps).  So a tile of 64 steps is run straight through, its operands read ahead across its
 // end, and a loop has one branch a tile.  Lists of non-zero codes do not pay here: a step then needs a read and an address of its own.
-// Four waves that do both -> parts of 32 steps that start anew -> here, us: 64 x 1000 x 2048 44 -> 27 -> 21, 300 x 300 x 1500 36 -> 20.2 ->
+// Four waves that do both -> parts of 32 steps that start anew -> here, us: 64 x 1000 x 2048 44 -> 26.9 -> 22.4, 300 x 300 x 1500 36 -> 20.2 ->
 // 16.7, 512 x 512 x 512 16 -> 12.6 -> 11.4, 416 x 480 x 3312 64.6 -> 57.2 for the last two, with R_OF near the sums (clamped) 300 x 300 x 1500
 // 29 -> 22.
 template <int TN>
