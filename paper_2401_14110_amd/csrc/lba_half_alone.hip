@@ -19,8 +19,9 @@ namespace lba {
 // there are, and whose chains are a fourth of a wave's work.  T 4: 64 x 64, for the overflow plane under the sequential order on more than 192
 // of them, where a wave alone on its SIMD issues as much as the four of the small ones (900 x 900 x 700, training step, 151 us, 152), and for
 // widths that are no multiple of 32, whose small tiles write parts of cache lines (partial_lines, lba_plan.cpp; 64 x 64 and 32 x 32, 256 workgroups, both planes,
-// N = 190, K = 1000 1.24 times as long, K = 300 0.84 to 1.09, 192 workgroups 0.68 to 0.93; the overflow plane in chunks, N = 159, K = 1501 124.6 and 192 us, 200
-// workgroups 123.7 and 140, K = 300, 256 workgroups 31.5 and 34.7; in order, N = 702, K = 1501, 192 workgroups 119 and 136).
+// N = 190, K = 1000 1.24 times as long, 193 to 256, K = 513 to 768 0.88 to 1.09, mean 0.95, to 2500 0.93 to 1.24, in chunks from 513 0.97 to 1.19, K = 300 0.84 to 1.09, 192 workgroups 0.68 to 0.93; the overflow plane in chunks,
+// N = 159, K = 1501 124.6 and 192 us, 200 to 224 workgroups, K > 1024, 1.04 to 1.35 times as long, K = 300, 256 workgroups 31.5 and 34.7; 161 to 192, K > 1024, in
+// either order 0.77 to 1.00).
 // 64 x 64 -> 32 x 32, both planes: 500 x 500 x 700 143 -> 60 us, 700 x 700 145 -> 78, 1024 x 1024 142 -> 122; training steps, K = 700:
 // 500 x 500 115 -> 84, 700 x 700 125 -> 103, 1024 x 700 145 -> 133, in chunks 149 -> 108, 179 -> 131, 194 -> 180, 1024 x 1024 210 -> 207.
 template <int T, int PM, int ORDER, bool UF, int AMODE>

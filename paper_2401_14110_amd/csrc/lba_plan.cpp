@@ -320,18 +320,21 @@ static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, AR
     // channels, floor, M10E5): 270 workgroups 0.93, 0.86, 0.83, 384 0.98, 0.95, 0.92, 441 1.20, 1.15, 1.15, 500 1.15, 1.14, 1.13 (on 16 channels 0.71, 0.77,
     // 0.94, 0.93); the overflow plane alone from two k-tiles on (K = 75) 320 0.98, 384 1.08, K = 27 1.05, truncated products 1.06 to 1.18.
     // Clamped products on short chains, both planes: 500 x 500 x 64 36 -> 17 us, 1024 x 1024 x 100 69 -> 49, 19200 x 64 x 144 113 -> 73, 32768 x 64 x 64 49 -> 46.
-    // Widths that are no multiple of 32 (partial_lines): packed, both planes, N = 122 to 1230, K = 300, 300 workgroups 0.70 to 1.00, 384 0.83 to 1.25, K = 1000
-    // 0.84 to 1.10, 1.02 to 1.36; FP32 under floor K = 300, 512 workgroups 0.73 to 1.03, K = 1000 0.77 to 1.12, 2000 and more 0.88 to 1.21, 384 0.71 to 0.90; the
-    // overflow plane alone (half the words per step: deep beyond K = 1024) clamped K = 300 to 668, 384 0.77 to 1.00, N = 55, K = 1482, 607 of full tiles and
-    // 337 us, N = 159, 384 workgroups (320 by what they hold), K = 1501 1.05.
-    const bool parts = rows >= ROWS_GATHERED, packed = p->kp.h_on != 0, floor = p->round == LBA_ROUND_FLOOR, partial = partial_lines(N), deep = p->kp.K > (p->of_only ? 1024 : 512);
+    // Widths that are no multiple of 32 (partial_lines), N = 33 to 2036, times of 32 x 32 over 64 x 64, sums below R_OF (and sums that often reach it).  Packed, both
+    // planes: 257 to 320 K = 300 0.70 to 1.00, 513 to 2500 0.84 to 1.15, mean 0.97 (0.77 to 0.79); 321 to 384 K <= 512 1.00 to 1.19 (0.91 to 0.94), above
+    // 0.87 to 1.20 (0.90); truncated products 257 to 320 0.81 to 1.00 (0.77), 321 to 384 K <= 256 0.96 to 1.04 (0.90 to 0.94), above 0.94 to 1.20 (0.90).  FP32 under
+    // floor, both planes, 385 to 512, K = 300 0.73 to 1.03, above 0.85 to 1.12, mean 0.97.  The overflow plane alone: clamped K = 300 to 668, 384 0.77 to 1.00,
+    // N = 159, 384 workgroups (320 by what they hold), K = 1501 1.05.
+    const bool parts = rows >= ROWS_GATHERED, packed = p->kp.h_on != 0, floor = p->round == LBA_ROUND_FLOOR, partial = partial_lines(N);
+    const bool trunc = p->prod_mode == PM_TRUNC, deep = partial && p->kp.K > 1024;
     int64_t most;
-    if (!p->of_only)  most = packed ? (partial ? (deep ? 256 : 320) : 384) : parts || (partial && deep && floor) ? 384 : 512;
+    if (!p->of_only)  most = packed ? (partial && !(trunc && p->kp.K <= 256) ? 320 : 384) : parts ? 384 : 512;
     else if (packed)  most = 192;
     else if (parts)   most = p->amode == 2 && p->kp.K >= 64 ? 320 : 256;
-    else              most = !floor || (p->kp.K > 96 && !(partial && deep)) ? 384 : 320;
-    // (beyond 384 workgroups, 512 on FP32 carriers, only where half of each is empty: there a tail is the other choice, 8352 x 160 x 208, 393, 66 us with one, 72)
-    if (p->events == 1 && !chunk_of && blocks > (packed ? 256 : 0) && (b32 + 3) / 4 <= most && (blocks <= (packed ? 384 : p->of_only && partial && deep ? 320 : 512) || b32 <= 2 * blocks) &&
+    else              most = !floor || (p->kp.K > 96 && !deep) ? 384 : 320;
+    const int64_t large = packed ? 384 : !p->of_only ? 512 : deep ? 320 : 512;
+    // (beyond that many workgroups only where half of each is empty: there a tail is the other choice, 8352 x 160 x 208, 393, 66 us with one, 72)
+    if (p->events == 1 && !chunk_of && blocks > (packed ? 256 : 0) && (b32 + 3) / 4 <= most && (blocks <= large || b32 <= 2 * blocks) &&
         set_mixed_grid(M, N, 0, 0, p)) return;
     // the smallest grids of the forward call (at most 128 workgroups of 32 x 32, e.g. a 64 x 1000 classifier layer): the
     // tail's 32 x 16 tiles throughout, twice the workgroups of the 2 x 2 lane block
@@ -637,7 +640,7 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
                               : p.tm == 4 && p.tn == 4 && total <= 256 && (p.events || (p.prod_mode == PM_TRUNC && !conv)));
     // smaller ones (lba_half_alone.hip has the figures of both lines)
     int64_t most_small = p.of_only && order == LBA_ORDER_SEQ ? 192 : 256;
-    if (partial_lines(N)) most_small = std::min<int64_t>(most_small, !p.of_only ? (K > 512 ? 192 : 256) : K > 1024 ? 160 : K > 160 ? 192 : 256);
+    if (partial_lines(N)) most_small = std::min<int64_t>(most_small, K > (p.of_only ? 160 : order == LBA_ORDER_SEQ ? 768 : 512) ? 192 : 256);
     if (p.alone && p.events && (((M + 31) / 32) * ((N + 31) / 32) + 3) / 4 <= most_small) {
         p.tm = p.tn = 2;
         p.grid_x = (int)((M + 31) / 32);

@@ -106,10 +106,10 @@ def test_forward_of_narrow_filters(rec, shape, order, formats):
 # widths that are no multiple of 32, whose small tiles write parts of cache lines: the blocks up to which tiles are 32 x 32, alone on their CUs or throughout
 @pytest.mark.parametrize("N", [60, 64])
 @pytest.mark.parametrize("formats,K,planes,order,most", [
-    (PACKED, 160, "ou", 0, (320, 384)), (PACKED, 512, "ou", 0, (320, 384)), (PACKED, 513, "ou", 0, (192, 384)), (PACKED, 513, "ou", 1, (192, 256)), (PACKED, 512, "ou", 1, (256, 256)),
-    (PACKED, 160, "o", 0, (192, 192)), (PACKED, 1024, "o", 0, (192, 192)), (PACKED, 1025, "o", 0, (160, 192)), (PACKED, 160, "o", 1, (256, 256)), (PACKED, 161, "o", 1, (192, 256)),
-    (PACKED, 1024, "o", 1, (192, 256)), (PACKED, 1025, "o", 1, (160, 256)), (WIDE, 512, "ou", 0, (512, 512)), (WIDE, 513, "ou", 0, (384, 512)), (WIDE, 1025, "o", 0, (320, 384)), (WIDE, 1024, "o", 0, (384, 384)), (WIDE, 96, "o", 0, (320, 320)),
-    (NEAREST, 513, "ou", 0, (512, 512)), (NEAREST, 513, "o", 0, (384, 384))])
+    (PACKED, 160, "ou", 0, (320, 384)), (PACKED, 512, "ou", 0, (320, 384)), (PACKED, 768, "ou", 0, (320, 384)), (PACKED, 769, "ou", 0, (320, 384)), (PACKED, 513, "ou", 1, (192, 256)), (PACKED, 512, "ou", 1, (256, 256)),
+    (PACKED, 160, "o", 0, (192, 192)), (PACKED, 1024, "o", 0, (192, 192)), (PACKED, 1025, "o", 0, (192, 192)), (PACKED, 160, "o", 1, (256, 256)), (PACKED, 161, "o", 1, (192, 256)),
+    (PACKED, 1024, "o", 1, (192, 256)), (PACKED, 1025, "o", 1, (192, 256)), (WIDE, 512, "ou", 0, (512, 512)), (WIDE, 513, "ou", 0, (512, 512)), (WIDE, 1025, "o", 0, (320, 384)), (WIDE, 1024, "o", 0, (384, 384)), (WIDE, 96, "o", 0, (320, 320)),
+    (TRUNC, 256, "ou", 0, (384, 384)), (TRUNC, 257, "ou", 0, (320, 384)), (NEAREST, 513, "ou", 0, (512, 512)), (NEAREST, 513, "o", 0, (384, 384))])
 def test_partial_lines(rec, N, formats, K, planes, order, most):
     most = most[N == 64]
     for blocks in (1, 160, 161, 192, 193, 256, 257, 300, 301, 320, 321, 384, 385, 512, 513):
@@ -119,7 +119,8 @@ def test_partial_lines(rec, N, formats, K, planes, order, most):
         name, p = taken(rec)
         assert rc == 0 and fits(M, N, p)
         small = p["tm"] == 2 if p["alone"] else p["mix_tail"] == 4 * blocks and p["mix_main"] == 0
-        assert small == (blocks <= most), (blocks, name, p)
+        alone = (formats, K, planes, order, N) == (PACKED, 769, "ou", 0, 60) and 192 < blocks <= 256   # 64 x 64 ones alone on their CUs
+        assert small == (blocks <= most and not alone), (blocks, name, p)
 
 
 # tiles whose halves are empty count for what they hold
