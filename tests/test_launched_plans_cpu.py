@@ -125,7 +125,7 @@ def test_partial_lines(rec, N, formats, K, planes, order, most):
 
 # tiles whose halves are empty count for what they hold
 @pytest.mark.parametrize("N,formats,planes,blocks,small", [(32, WIDE, "o", 512, True), (32, WIDE, "ou", 1024, True), (32, WIDE, "ou", 1026, False), (32, PACKED, "o", 256, True),
-                                                           (160, PACKED, "o", 228, True), (160, PACKED, "o", 300, False), (32, PACKED, "o", 384, True), (160, PACKED, "o", 234, False), (32, PACKED, "ou", 700, True), (160, PACKED, "ou", 384, True), (160, PACKED, "ou", 393, False), (160, WIDE, "ou", 510, True), (160, WIDE, "ou", 516, False), (64, PACKED, "o", 300, False)])
+                                                           (160, PACKED, "o", 228, True), (160, PACKED, "o", 300, False), (32, PACKED, "o", 384, True), (160, PACKED, "o", 234, False), (32, PACKED, "ou", 700, True), (160, PACKED, "ou", 384, True), (160, PACKED, "ou", 393, False), (160, WIDE, "ou", 510, True), (160, WIDE, "ou", 516, False), (64, PACKED, "o", 300, False), (70, WIDE, "o", 384, True), (70, WIDE, "o", 386, False), (70, WIDE_TRUNC, "o", 386, True), (32, WIDE, "o", 514, True)])
 def test_empty_halves(rec, N, formats, planes, blocks, small):
     M = 64 * (blocks // -(-N // 64))
     assert rec.lba_gemm_bwd(BUF, BUF, BUF, BUF, BUF if "u" in planes else None, M, N, 700, lba_qfmt(*formats[0]), lba_qfmt(*formats[1]), 0, None) == 0
