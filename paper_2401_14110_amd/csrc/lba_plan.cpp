@@ -608,11 +608,12 @@ int make_plan(int64_t M, int64_t N, int64_t K, const lba_qfmt& qp_in, const lba_
         const int64_t b32 = ((M + 31) / 32) * ((N + 31) / 32);
         // Packed carriers whose k-tiles other waves stage hold a wave on every SIMD from half of that, and its chains are the cheaper
         // ones (one chunk after the other): 350 x 350 x 700 here 16.1 us, there 10.7, 700 x 700 x 1000 60 and 30; 1000 x 500 x 64 7.7 and 7.9, 400 x 1000 x
-        // 100 9.0 and 7.8.  Where most sums saturate the staged chains need a clamp and take longer, which chunks side by side do not: there over here,
-        // K = 512 to 4608, sums below R_OF and sums that mostly reach it, 72 workgroups 0.93 to 0.99 and 1.43 to 1.80, 121 0.78 to 0.84 and 1.22 to 1.50, 240
-        // 0.66 and 0.97 to 1.08; the line lies where the one outweighs the other for sums that seldom saturate.
+        // 100 9.0 and 7.8.  Chunks side by side pay for a k-tile of 256 steps where K ends inside one, and are not held up by sums that saturate, for which the
+        // staged chains need a clamp: there over here, 65 to 96 workgroups, sums below R_OF K = 300 0.64 to 0.72, 575 to 700 0.69 to 0.77, 1033 to 3300 0.68
+        // to 0.95, K a multiple of 256 0.93 to 1.24; sums that mostly saturate 0.91, 1.19, 1.19 to 1.80.  121 workgroups 0.78 to 0.84 and 1.22 to 1.50, 240 0.66
+        // and 0.97 to 1.08.
         const int64_t b64 = ((M + 63) / 64) * ((N + 63) / 64);
-        const bool chains = kp.h_on && !kp.h_range && p.prod_mode != PM_FLUSH_CLAMP && ((K >= 224 && b32 > 96 && b32 <= 384) || (K > 64 && b32 > 128 && b64 <= 128));
+        const bool chains = kp.h_on && !kp.h_range && p.prod_mode != PM_FLUSH_CLAMP && ((K >= 224 && b32 > 64 && b32 <= 384) || (K > 64 && b32 > 128 && b64 <= 128));
         if (!chains && b32 < 512 && (N + 15) / 16 <= 65535) {
             p.kpar = K < 128 ? 1 : 3;
             const int64_t tm = p.kpar == 1 ? 32 : 8, tn = p.kpar == 1 ? 32 : 16;

@@ -218,8 +218,8 @@ def test_tail_of_a_last_round(rec, formats, K, tail):
         assert (p["mix_main"] == 512 and p["mix_tail"] == 752) == tail and (tail or p["mix_tail"] == 0)
 
 
-# chunks of few outputs: side by side up to 96 workgroups of 32 x 32 (128 on short chains), one after the other with waves that stage beyond
-@pytest.mark.parametrize("K,most", [(1712, 96), (224, 96), (208, 128)])
+# chunks of few outputs: side by side up to 64 workgroups of 32 x 32 (128 on short chains), one after the other with waves that stage beyond
+@pytest.mark.parametrize("K,most", [(1712, 64), (224, 64), (208, 128)])
 def test_chunks_side_by_side(rec, K, most):
     for b32 in (1, 64, 65, 96, 97, 128, 129, 300):
         assert rec.lba_gemm(BUF, BUF, BUF, 32 * b32, 32, K, lba_qfmt(*PACKED[0]), lba_qfmt(*PACKED[1]), 1, None) == 0
