@@ -324,16 +324,16 @@ static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, AR
     // planes: 257 to 320 K = 300 0.70 to 1.00, 513 to 2500 0.84 to 1.15, mean 0.97 (0.77 to 0.79); 321 to 384 K <= 512 1.00 to 1.19 (0.91 to 0.94), above
     // 0.87 to 1.20 (0.90); truncated products 257 to 320 0.81 to 1.00 (0.77), 321 to 384 K <= 256 0.96 to 1.04 (0.90 to 0.94), above 0.94 to 1.20 (0.90).  FP32 under
     // floor, both planes, 385 to 512, K = 300 0.73 to 1.03, above 0.85 to 1.12, mean 0.97.  The overflow plane alone: clamped K = 300 to 668, 384 0.77 to 1.00,
-    // N = 159, 384 workgroups (320 by what they hold), K = 1501 1.05; beyond 384 workgroups, whose number empty halves keep below the line, products flushed
-    // 0.97 to 1.10, clamped 0.95 to 1.02, truncated 0.89 to 0.95, nearest-even 0.85 to 0.97.
+    // N = 159, 384 workgroups (320 by what they hold), K = 1501 1.05, truncated, 335 to 377, K = 1152 0.83 to 0.84; beyond 384 workgroups, whose number empty halves keep below the line, products flushed
+    // 0.97 to 1.10, clamped 0.95 to 1.12, truncated 0.89 to 0.95, nearest-even 0.85 to 0.97.
     const bool parts = rows >= ROWS_GATHERED, packed = p->kp.h_on != 0, floor = p->round == LBA_ROUND_FLOOR, partial = partial_lines(N);
-    const bool trunc = p->prod_mode == PM_TRUNC, deep = partial && p->kp.K > 1024;
+    const bool trunc = p->prod_mode == PM_TRUNC, deep = partial && !trunc && p->kp.K > 1024;
     int64_t most;
     if (!p->of_only)  most = packed ? (partial && !(trunc && p->kp.K <= 256) ? 320 : 384) : parts ? 384 : 512;
     else if (packed)  most = 192;
     else if (parts)   most = p->amode == 2 && p->kp.K >= 64 ? 320 : 256;
     else              most = !floor || (p->kp.K > 96 && !deep) ? 384 : 320;
-    const int64_t large = packed ? 384 : !p->of_only ? 512 : deep ? 320 : floor && p->prod_mode == PM_FLUSH ? 384 : 512;
+    const int64_t large = packed ? 384 : !p->of_only ? 512 : deep ? 320 : floor && !trunc ? 384 : 512;
     // (beyond that many workgroups only where half of each is empty: there a tail is the other choice, 8352 x 160 x 208, 393, 66 us with one, 72)
     if (p->events == 1 && !chunk_of && blocks > (packed ? 256 : 0) && (b32 + 3) / 4 <= most && (blocks <= large || b32 <= 2 * blocks) &&
         set_mixed_grid(M, N, 0, 0, p)) return;

@@ -67,7 +67,7 @@ def fits(M, N, p):
 
 
 NEAREST = ((5, 7, -2, 1), (4, 7, -10, 1))
-WIDE, WIDE_TRUNC = ((5, 7, 12, 0), (5, 10, 9, 0)), ((5, 4, 12, 0), (5, 10, 9, 0))
+WIDE, WIDE_TRUNC, WIDE_CLAMP = ((5, 7, 12, 0), (5, 10, 9, 0)), ((5, 4, 12, 0), (5, 10, 9, 0)), ((5, 7, 17, 0), (5, 10, 15, 0))
 
 
 # FP32 carriers: how many workgroups of 64 x 64 are cut into 32 x 32 ones throughout; channels in multiples of 16, and pieces gathered from taps
@@ -108,7 +108,7 @@ def test_forward_of_narrow_filters(rec, shape, order, formats):
 @pytest.mark.parametrize("formats,K,planes,order,most", [
     (PACKED, 160, "ou", 0, (320, 384)), (PACKED, 512, "ou", 0, (320, 384)), (PACKED, 768, "ou", 0, (320, 384)), (PACKED, 769, "ou", 0, (320, 384)), (PACKED, 513, "ou", 1, (192, 256)), (PACKED, 512, "ou", 1, (256, 256)),
     (PACKED, 160, "o", 0, (192, 192)), (PACKED, 1024, "o", 0, (192, 192)), (PACKED, 1025, "o", 0, (192, 192)), (PACKED, 160, "o", 1, (256, 256)), (PACKED, 161, "o", 1, (192, 256)),
-    (PACKED, 1024, "o", 1, (192, 256)), (PACKED, 1025, "o", 1, (192, 256)), (WIDE, 512, "ou", 0, (512, 512)), (WIDE, 513, "ou", 0, (512, 512)), (WIDE, 1025, "o", 0, (320, 384)), (WIDE, 1024, "o", 0, (384, 384)), (WIDE, 96, "o", 0, (320, 320)),
+    (PACKED, 1024, "o", 1, (192, 256)), (PACKED, 1025, "o", 1, (192, 256)), (WIDE, 512, "ou", 0, (512, 512)), (WIDE, 513, "ou", 0, (512, 512)), (WIDE, 1025, "o", 0, (320, 384)), (WIDE, 1024, "o", 0, (384, 384)), (WIDE_TRUNC, 1025, "o", 0, (384, 384)), (WIDE, 96, "o", 0, (320, 320)),
     (TRUNC, 256, "ou", 0, (384, 384)), (TRUNC, 257, "ou", 0, (320, 384)), (NEAREST, 513, "ou", 0, (512, 512)), (NEAREST, 513, "o", 0, (384, 384))])
 def test_partial_lines(rec, N, formats, K, planes, order, most):
     most = most[N == 64]
@@ -125,7 +125,7 @@ def test_partial_lines(rec, N, formats, K, planes, order, most):
 
 # tiles whose halves are empty count for what they hold
 @pytest.mark.parametrize("N,formats,planes,blocks,small", [(32, WIDE, "o", 512, True), (32, WIDE, "ou", 1024, True), (32, WIDE, "ou", 1026, False), (32, PACKED, "o", 256, True),
-                                                           (160, PACKED, "o", 228, True), (160, PACKED, "o", 300, False), (32, PACKED, "o", 384, True), (160, PACKED, "o", 234, False), (32, PACKED, "ou", 700, True), (160, PACKED, "ou", 384, True), (160, PACKED, "ou", 393, False), (160, WIDE, "ou", 510, True), (160, WIDE, "ou", 516, False), (64, PACKED, "o", 300, False), (70, WIDE, "o", 384, True), (70, WIDE, "o", 386, False), (70, WIDE_TRUNC, "o", 386, True), (32, WIDE, "o", 514, True)])
+                                                           (160, PACKED, "o", 228, True), (160, PACKED, "o", 300, False), (32, PACKED, "o", 384, True), (160, PACKED, "o", 234, False), (32, PACKED, "ou", 700, True), (160, PACKED, "ou", 384, True), (160, PACKED, "ou", 393, False), (160, WIDE, "ou", 510, True), (160, WIDE, "ou", 516, False), (64, PACKED, "o", 300, False), (70, WIDE, "o", 384, True), (70, WIDE, "o", 386, False), (70, WIDE_TRUNC, "o", 386, True), (70, WIDE_CLAMP, "o", 386, False), (32, WIDE, "o", 514, True)])
 def test_empty_halves(rec, N, formats, planes, blocks, small):
     M = 64 * (blocks // -(-N // 64))
     assert rec.lba_gemm_bwd(BUF, BUF, BUF, BUF, BUF if "u" in planes else None, M, N, 700, lba_qfmt(*formats[0]), lba_qfmt(*formats[1]), 0, None) == 0
