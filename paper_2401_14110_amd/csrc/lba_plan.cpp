@@ -313,9 +313,10 @@ static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, AR
     // 328 -> 130, 1024 x 1024 323 -> 191, 288 workgroups 405 -> 246, 400 326 -> 315, 512 410 -> 355, 640 411 -> 434.  Both planes on packed carriers, which
     // hold 64 x 64 workgroups better (up to 256 of them: make_plan): 257 to 320 198 -> 156, 384 198 -> 184, 400 198 -> 211.
     // The overflow plane alone, times of 32 x 32 over 64 x 64.  FP32, K = 300, floor with M10E5 and nearest-even: 270 workgroups 0.94 and 0.62, 384 1.00
-    // and 0.71, 390 to 512 1.20 and 0.91 to 1.01; chains of up to three k-tiles under floor: 320 0.97 to 1.02, 384 1.04.  Packed carriers keep 64 x 64,
-    // whose lists leave out zero codes that small tiles run (behind a ReLU, sums that stay below R_OF: 320 workgroups 0.88 to 1.08, 384 1.02 to 1.24, 7371 x 159
-    // x 1502 1.42; where sums often reach it 0.74 to 0.96).
+    // and 0.71, 390 to 512 1.20 and 0.91 to 1.01; chains of up to three k-tiles under floor: 320 0.97 to 1.02, 384 1.04.  Packed: 257 to 320 from
+    // K = 256 on 0.94 to 0.99 dense, 0.90 to 0.98 with half of the codes zero, 0.79 to 0.83 where sums often reach R_OF, but 1.02 to 1.16 with 0.65 of them zero and 1.12
+    // to 1.15 with 0.7, since 64 x 64 tiles have lists that leave zeros out; K = 16 to 144 1.01 to 1.12 (0.86 to 0.89 often at R_OF); 321 to 384 1.07 to 1.21 (0.94); widths that
+    // are no multiple of 32 lose more to zeros (7371 x 159 x 1502, half zero, 1.42) and keep 64 x 64, rows gathered from several taps too.
     // Rows gathered from several taps cost small tiles more, each of which gathers its own.  FP32, both planes (3 x 3 on 3, 5 x 5 on 3, 15 x 15 on 1
     // channels, floor, M10E5): 270 workgroups 0.93, 0.86, 0.83, 384 0.98, 0.95, 0.92, 441 1.20, 1.15, 1.15, 500 1.15, 1.14, 1.13 (on 16 channels 0.71, 0.77,
     // 0.94, 0.93); the overflow plane alone from two k-tiles on (K = 75) 320 0.98, 384 1.08, K = 27 1.05, truncated products 1.06 to 1.18.
@@ -330,7 +331,7 @@ static void plan_mixed_grid(int64_t M, int64_t N, int64_t batch, bool staged, AR
     const bool trunc = p->prod_mode == PM_TRUNC, deep = partial && !trunc && p->kp.K > 1024;
     int64_t most;
     if (!p->of_only)  most = packed ? (partial && !(trunc && p->kp.K <= 256) ? 320 : 384) : parts ? 384 : 512;
-    else if (packed)  most = 192;
+    else if (packed)  most = rows <= ROWS_TAPS && !partial && p->kp.K >= 256 ? 320 : 192;
     else if (parts)   most = p->amode == 2 && p->kp.K >= 64 ? 320 : 256;
     else              most = !floor || (p->kp.K > 96 && !deep) ? 384 : 320;
     const int64_t large = packed ? 384 : !p->of_only ? 512 : deep ? 320 : floor && !trunc ? 384 : 512;

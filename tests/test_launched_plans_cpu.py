@@ -107,7 +107,7 @@ def test_forward_of_narrow_filters(rec, shape, order, formats):
 @pytest.mark.parametrize("N", [60, 64])
 @pytest.mark.parametrize("formats,K,planes,order,most", [
     (PACKED, 160, "ou", 0, (320, 384)), (PACKED, 512, "ou", 0, (320, 384)), (PACKED, 768, "ou", 0, (320, 384)), (PACKED, 769, "ou", 0, (320, 384)), (PACKED, 513, "ou", 1, (192, 256)), (PACKED, 512, "ou", 1, (256, 256)),
-    (PACKED, 160, "o", 0, (192, 192)), (PACKED, 1024, "o", 0, (192, 192)), (PACKED, 1025, "o", 0, (192, 192)), (PACKED, 160, "o", 1, (256, 256)), (PACKED, 161, "o", 1, (192, 256)),
+    (PACKED, 255, "o", 0, (192, 192)), (PACKED, 256, "o", 0, (192, 320)), (PACKED, 1025, "o", 0, (192, 320)), (PACKED, 160, "o", 1, (256, 256)), (PACKED, 161, "o", 1, (192, 256)),
     (PACKED, 1024, "o", 1, (192, 256)), (PACKED, 1025, "o", 1, (192, 256)), (WIDE, 512, "ou", 0, (512, 512)), (WIDE, 513, "ou", 0, (512, 512)), (WIDE, 1025, "o", 0, (320, 384)), (WIDE, 1024, "o", 0, (384, 384)), (WIDE_TRUNC, 1025, "o", 0, (384, 384)), (WIDE, 96, "o", 0, (320, 320)),
     (TRUNC, 256, "ou", 0, (384, 384)), (TRUNC, 257, "ou", 0, (320, 384)), (NEAREST, 513, "ou", 0, (512, 512)), (NEAREST, 513, "o", 0, (384, 384))])
 def test_partial_lines(rec, N, formats, K, planes, order, most):
@@ -119,13 +119,13 @@ def test_partial_lines(rec, N, formats, K, planes, order, most):
         name, p = taken(rec)
         assert rc == 0 and fits(M, N, p)
         small = p["tm"] == 2 if p["alone"] else p["mix_tail"] == 4 * blocks and p["mix_main"] == 0
-        alone = (formats, K, planes, order, N) == (PACKED, 769, "ou", 0, 60) and 192 < blocks <= 256   # 64 x 64 ones alone on their CUs
+        alone = 192 < blocks <= 256 and formats == PACKED and order == 0 and (planes == "o" or (K, N) == (769, 60))   # 64 x 64 ones alone on their CUs
         assert small == (blocks <= most and not alone), (blocks, name, p)
 
 
 # tiles whose halves are empty count for what they hold
 @pytest.mark.parametrize("N,formats,planes,blocks,small", [(32, WIDE, "o", 512, True), (32, WIDE, "ou", 1024, True), (32, WIDE, "ou", 1026, False), (32, PACKED, "o", 256, True),
-                                                           (160, PACKED, "o", 228, True), (160, PACKED, "o", 300, False), (32, PACKED, "o", 384, True), (160, PACKED, "o", 234, False), (32, PACKED, "ou", 700, True), (160, PACKED, "ou", 384, True), (160, PACKED, "ou", 393, False), (160, WIDE, "ou", 510, True), (160, WIDE, "ou", 516, False), (64, PACKED, "o", 300, False), (70, WIDE, "o", 384, True), (70, WIDE, "o", 386, False), (70, WIDE_TRUNC, "o", 386, True), (70, WIDE_CLAMP, "o", 386, False), (32, WIDE, "o", 514, True)])
+                                                           (160, PACKED, "o", 228, True), (160, PACKED, "o", 300, True), (32, PACKED, "o", 384, True), (160, PACKED, "o", 234, False), (32, PACKED, "ou", 700, True), (160, PACKED, "ou", 384, True), (160, PACKED, "ou", 393, False), (160, WIDE, "ou", 510, True), (160, WIDE, "ou", 516, False), (64, PACKED, "o", 320, True), (64, PACKED, "o", 321, False), (70, WIDE, "o", 384, True), (70, WIDE, "o", 386, False), (70, WIDE_TRUNC, "o", 386, True), (70, WIDE_CLAMP, "o", 386, False), (32, WIDE, "o", 514, True)])
 def test_empty_halves(rec, N, formats, planes, blocks, small):
     M = 64 * (blocks // -(-N // 64))
     assert rec.lba_gemm_bwd(BUF, BUF, BUF, BUF, BUF if "u" in planes else None, M, N, 700, lba_qfmt(*formats[0]), lba_qfmt(*formats[1]), 0, None) == 0
@@ -154,15 +154,15 @@ def test_planes_asked_for(rec, planes):
             rc = rec.lba_gemm_bwd_in(BUF, BUF, BUF, of, uf, 64 * blocks, 64, 500, lba_infmt(*fmt), lba_infmt(*fmt), lba_qfmt(*qp), lba_qfmt(*qa), 0, None)
             name, p = taken(rec)
             assert rc == 0 and p["of_only"] == alone and p["packed"] == packed and fits(64 * blocks, 64, p)
-            # 32 x 32 throughout: FP32 up to 384 and 512, packed with both planes from 257 to 384 (fewer: truncated products, others have kernels of their own)
+            # 32 x 32 throughout: FP32 up to 384 and 512, packed from 257 to 320 and with both planes to 384 (fewer: truncated products, others have kernels of their own)
             small = p["mix_tail"] == 4 * blocks and p["mix_main"] == 0
             trunc = fmt == (3, 4, 3)
-            want = blocks <= (384 if alone else 512) if not packed else blocks <= (256 if alone else 384) and (trunc or blocks > 256)
+            want = blocks <= (384 if alone else 512) if not packed else blocks <= (320 if alone else 384) and (trunc or blocks > 256)
             assert small == want, (blocks, p)
     for c, formats, packed in [(32, PACKED, True), (20, PACKED, True), (32, WIDE, False), (3, WIDE, False)]:
         _, _, name, p = conv(rec, 1, 64, 300, c, 64, 3, formats, planes)
         assert p["of_only"] == alone and p["packed"] == packed
-        assert (p["mix_tail"] == 1200) == (not alone or (c == 32 and not packed))
+        assert (p["mix_tail"] == 1200) == (not alone or c == 32)
 
 
 # the overflow plane alone: whole taps up to 384, gathered rows up to 320 from two k-tiles on and up to 256 with truncated products
